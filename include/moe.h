@@ -513,7 +513,7 @@ moe_status_t moe_probe_mfma_fp8(const void* image, int iters, int workgroups, fl
  * Clock sample of the grouped bf16 GEMMs (measurement aid, like the probes
  * above).  ticks: DEVICE memory, 2 x uint64, or NULL to switch the sampling off
  * (the default).  While set, workgroup 0 of every grouped bf16 GEMM launch that
- * runs on the persistent kernel (forward, backward) writes ticks[0] = shader
+ * runs on the persistent or the streaming kernel (forward, backward) writes ticks[0] = shader
  * clocks and ticks[1] = 100 MHz reference clocks it spent in the kernel, so
  * ticks[0] / ticks[1] * 100 is the shader clock in MHz the launch ran at.  The
  * pointer is process-wide host state read at launch time (not thread-safe); the
@@ -528,9 +528,11 @@ moe_status_t moe_gemm_clock_sample(uint64_t* ticks);
  * kernel for layers whose H or F is below 128; 40 / 41 = persistent kernel with
  * three LDS stages for the activation tile, 4 / 8 waves; 42 / 43 = three stages
  * for the weight tile, 4 / 8 waves; 30 / 31 = one workgroup per tile, 4 / 8
- * waves; 99 = the plain LDS-tiled kernel of the fp32 and odd-shape layers;
+ * waves; 99 = a plain LDS-tiled FMA kernel for any shape and type;
  * any other value makes the expert calls return MOE_ERR_UNSUPPORTED);
- * "fp8_deep_weights" (FP8 expert GEMMs: 1, the default = three LDS stages for
+ * "gemm_stream" (the weight-streaming expert kernel for few rows per expert: -1 =
+ * chosen by size, the default; 0 = only for the shapes no other kernel takes; 1 =
+ * always, under "gemm_variant" 0 and in FP8); "fp8_deep_weights" (FP8 expert GEMMs: 1, the default = three LDS stages for
  * the weight tile, 0 = for the activation tile); "gemm_workgroups" (workgroups launched by the
  * persistent grouped-GEMM kernels; 0 = one per compute unit, values below 8
  * are raised to 8); "router_tile" (16-token blocks per router workgroup: 1, 2

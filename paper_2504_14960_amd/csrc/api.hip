@@ -7,6 +7,7 @@
 #include <cmath>
 
 #include "common.h"
+#include "gemm_stream.h"
 
 namespace moe {
 
@@ -904,6 +905,10 @@ moe_status_t moe_gemm_clock_sample(uint64_t* ticks) {
 moe_status_t moe_set_option(const char* name, int value) {
     if (name && strcmp(name, "gemm_idle_skip") == 0) {
         moe::set_persist_idle_skip(value < 0 ? -1 : (value != 0));
+        return MOE_OK;
+    }
+    if (name && strcmp(name, "gemm_stream") == 0) {
+        moe::set_gemm_stream(value < 0 ? -1 : (value != 0));
         return MOE_OK;
     }
     if (name && strcmp(name, "fp8_deep_weights") == 0) {

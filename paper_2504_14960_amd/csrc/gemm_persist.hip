@@ -22,6 +22,7 @@
 #include <type_traits>
 
 #include "gemm_persist.h"
+#include "gemm_stream.h"
 
 
 namespace moe {
@@ -29,6 +30,8 @@ namespace moe {
 static int g_persist_workgroups = 0;  // 0: one per compute unit
 static int g_persist_idle_skip = -1;  // -1: chosen from the expert count; 0 / 1: forced
 static unsigned long long* g_persist_ticks = nullptr;  // device cell pair of the clock sample, or none
+
+bool persist_grid_overridden() { return g_persist_workgroups > 0; }
 
 int persist_grid() {
     // every one of the 8 tile shares needs a workgroup with its residue mod 8
@@ -725,6 +728,7 @@ void run_persist_pair(const void* x_perm, const int32_t* offsets, int r_max, int
 void set_persist_workgroups(int n) { g_persist_workgroups = n; }
 void set_persist_idle_skip(int v) { g_persist_idle_skip = v; }
 void set_persist_clock_sample(unsigned long long* ticks) { g_persist_ticks = ticks; }
+unsigned long long* persist_clock_sample() { return g_persist_ticks; }
 bool persist_idle_skip(int E) { return g_persist_idle_skip < 0 ? E >= 16 : g_persist_idle_skip != 0; }
 
 // C [rows, N] = A [rows, K] . B[e]^T with B [E, N, K], rows grouped by expert (bf16): the
@@ -732,6 +736,10 @@ bool persist_idle_skip(int E) { return g_persist_idle_skip < 0 ? E >= 16 : g_per
 bool launch_grouped_nt(const void* A, const int32_t* offsets, int r_max, int E, int N, int K, const void* B,
                        void* C, hipStream_t s) {
     if (K < 128 || K % 64 || N % 8) return false;
+    if (stream_covers(K * 2ll) && stream_preferred(r_max, E, N, false)) {
+        launch_stream(kStreamBf16, A, offsets, r_max, E, N, K, B, nullptr, C, nullptr, 0.f, 0.f, 0.f, nullptr, s);
+        return true;
+    }
     launch_persist<256, 256, 2, 4, 0, true>(A, offsets, r_max, E, N, K, B, nullptr, C, nullptr, s);
     return true;
 }
@@ -761,6 +769,10 @@ bool launch_grouped_nt_swiglu_bwd(const void* A, const int32_t* offsets, int r_m
 bool launch_gate_up_saving(const void* x_perm, const int32_t* offsets, int r_max, int H, int F, int E,
                            const void* w_gate, const void* w_up, void* h, void* gu, hipStream_t s) {
     if (H < 128 || H % 64 || F % 8) return false;
+    if (stream_covers(H * 2ll) && stream_preferred(r_max, E, F, true)) {   // the same choice as the plain forward's
+        launch_stream(kStreamBf16, x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, gu, 0.f, 0.f, 0.f, nullptr, s);
+        return true;
+    }
     launch_persist<256, 256, 2, 4, 2, true>(x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, gu, s);
     return true;
 }

@@ -17,6 +17,7 @@
 // step's (delayed) scale; the down GEMM dequantises into bf16.
 #include "fp8_convert.h"
 #include "gemm_persist.h"
+#include "gemm_stream.h"
 
 namespace moe {
 
@@ -463,10 +464,18 @@ void launch_expert_ffn_fp8(const void* x_perm, const int32_t* offsets, int r_max
                            const void* w_gate, const void* w_up, const void* w_down, float dq_gate, float dq_up,
                            float scale_h, float dq_down, void* h, float* amax_h, void* y_perm, int phase,
                            hipStream_t s) {
-    if (phase & 1)
-        launch_fp8<true>(x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, dq_gate, dq_up, scale_h, amax_h, s);
-    if (phase & 2)
-        launch_fp8<false>(h, offsets, r_max, E, H, F, w_down, nullptr, y_perm, dq_down, 0.f, 0.f, nullptr, s);
+    if (phase & 1) {
+        if (stream_covers(H) && stream_preferred(r_max, E, F, true))
+            launch_stream(kStreamFp8, x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, nullptr, dq_gate, dq_up, scale_h, amax_h, s);
+        else
+            launch_fp8<true>(x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, dq_gate, dq_up, scale_h, amax_h, s);
+    }
+    if (phase & 2) {
+        if (stream_covers(F) && stream_preferred(r_max, E, H, false))
+            launch_stream(kStreamFp8, h, offsets, r_max, E, H, F, w_down, nullptr, y_perm, nullptr, dq_down, 0.f, 0.f, nullptr, s);
+        else
+            launch_fp8<false>(h, offsets, r_max, E, H, F, w_down, nullptr, y_perm, dq_down, 0.f, 0.f, nullptr, s);
+    }
 }
 
 }  // namespace moe

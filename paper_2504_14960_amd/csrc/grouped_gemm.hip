@@ -6,17 +6,18 @@
 // both contiguous along the contraction index), which is exactly the operand
 // order the gfx950 bf16 MFMA wants: each lane feeds 8 consecutive-K values.
 //
-// This file holds the dispatch and the plain kernel for fp32 layers and odd
-// shapes.  The MFMA kernels live in gemm_persist.hip (default: one persistent
-// workgroup per compute unit walking a device-side tile list) and
-// gemm_pipe3.hip (one workgroup per tile; taken when the contraction is too
-// shallow for the persistent kernel's k stream).  For the first GEMM a weight
+// This file holds the dispatch and a plain FMA kernel.  The MFMA kernels live in
+// gemm_persist.hip (one persistent workgroup per compute unit walking a
+// device-side tile list), gemm_stream.hip (few rows per expert, fp32 layers, odd
+// shapes) and gemm_pipe3.hip (one workgroup per tile; taken when the contraction
+// is too shallow for the persistent kernel's k stream).  For the first GEMM a weight
 // tile holds 128 gate rows and the 128 matching up rows and every wave owns the
 // same feature range of both, so silu(g)*u happens in registers and only h is
 // written.
 //
 // Ragged scheduling: the per-expert row offsets live in device memory; the
 // kernels derive the real tile list from them, no host round trip.
+#include "gemm_stream.h"
 #include "gemm_tile.h"
 
 namespace moe {
@@ -24,8 +25,7 @@ namespace moe {
 namespace {
 
 // ---------------------------------------------------------------------------
-// Plain tiled kernel for fp32 layers and for bf16 shapes the MFMA kernel does
-// not take (K not a multiple of 64).  64x64 outputs per workgroup, 16-wide K
+// Plain tiled kernel: "gemm_variant" 99, and rows too long for the others' 32-bit offsets.  64x64 outputs per workgroup, 16-wide K
 // slices in LDS, 4x4 outputs per thread, fp32 FMA.  Every access is guarded.
 template <typename TIn, bool SWIGLU>
 __global__ __launch_bounds__(256) void gemm_simple_kernel(
@@ -126,26 +126,42 @@ void launch_simple_gemm(const void* A, const int32_t* offsets, int r_max, int E,
 bool launch_expert_ffn(const void* x_perm, const int32_t* offsets, int r_max, int H, int F, int E,
                        const void* w_gate, const void* w_up, const void* w_down, moe_dtype_t dt,
                        void* h, void* y_perm, int variant, int phase, hipStream_t s) {
-    if (dt == MOE_F32) {
-        if (phase & 1) launch_simple_gemm<float, true>(x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, s);
-        if (phase & 2) launch_simple_gemm<float, false>(h, offsets, r_max, E, H, F, w_down, nullptr, y_perm, s);
+    const bool f32 = dt == MOE_F32;
+    // shapes without a large-tile kernel go to the weight-streaming one, whatever their size
+    const bool fast = !f32 && (H % 64 == 0) && (F % 64 == 0);
+    const int elt = f32 ? kStreamF32 : kStreamBf16;
+    auto stream = [&](int ph) {
+        if (ph & 1) launch_stream(elt, x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, nullptr, 0.f, 0.f, 0.f, nullptr, s);
+        if (ph & 2) launch_stream(elt, h, offsets, r_max, E, H, F, w_down, nullptr, y_perm, nullptr, 0.f, 0.f, 0.f, nullptr, s);
+    };
+    if (variant == 99 || (!fast && !stream_covers((H > F ? H : F) * (f32 ? 4ll : 2ll)))) {
+        if (f32) {
+            if (phase & 1) launch_simple_gemm<float, true>(x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, s);
+            if (phase & 2) launch_simple_gemm<float, false>(h, offsets, r_max, E, H, F, w_down, nullptr, y_perm, s);
+        } else {
+            if (phase & 1) launch_simple_gemm<bf16_t, true>(x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, s);
+            if (phase & 2) launch_simple_gemm<bf16_t, false>(h, offsets, r_max, E, H, F, w_down, nullptr, y_perm, s);
+        }
         return true;
     }
-    const bool fast = (H % 64 == 0) && (F % 64 == 0);
-    if (!fast || variant == 99) {
-        if (phase & 1) launch_simple_gemm<bf16_t, true>(x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, s);
-        if (phase & 2) launch_simple_gemm<bf16_t, false>(h, offsets, r_max, E, H, F, w_down, nullptr, y_perm, s);
+    if (!fast) {
+        stream(phase);
         return true;
     }
     if (variant == 0) {
-        // tuned default (measured on MI355X at the benchmark shapes): the persistent 8-wave kernel with three LDS
-        // stages for the weight tile; layers too shallow for its k stream fall back to the
-        // one-workgroup-per-tile kernels (8 waves gate/up, 4 waves down)
-        if (launch_persist_ffn(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, 43, phase, s))
-            return true;
+        // Tuned default, phase by phase (the second product reads what the first wrote): few rows per expert go to the
+        // streaming kernel, the rest to the persistent 8-wave kernel with three LDS stages for the weight tile, and
+        // layers too shallow for its k stream to the one-workgroup-per-tile kernels (8 waves gate/up, 4 waves down).
         bool ok = true;
-        if (phase & 1) ok = ok && launch_pipe3_ffn(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, 31, 1, s);
-        if (phase & 2) ok = ok && launch_pipe3_ffn(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, 30, 2, s);
+        for (int ph = 1; ph <= 2; ph <<= 1) {
+            if (!(phase & ph)) continue;
+            const int N = ph == 1 ? F : H, K = ph == 1 ? H : F;
+            if (stream_covers(K * 2ll) && stream_preferred(r_max, E, N, ph == 1))
+                stream(ph);
+            else if (!launch_persist_ffn(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, 43, ph, s))
+                ok = ok && launch_pipe3_ffn(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm,
+                                            ph == 1 ? 31 : 30, ph, s);
+        }
         return ok;
     }
     if (variant >= 40 && launch_persist_ffn(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, variant, phase, s))

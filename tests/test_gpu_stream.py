@@ -1,0 +1,84 @@
+"""The weight-streaming expert kernel at the sizes where it can go wrong: the row counts at which a tile changes its
+form (16, 32, 64, 128), contractions that end inside a 128-byte block or hold none at all, output columns that end
+inside a block of 16, and sizes that select every width of workgroup."""
+import numpy as np
+import pytest
+
+import oracle
+from helpers import assert_close
+from test_gpu_experts import _case as bf16_case, _run as bf16_run
+from test_gpu_fp8 import _case as fp8_case, _check_h_codes, _run as fp8_run
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [1, 16, 17, 32, 33, 0, 64, 65, 128, 129, 2, 260]
+
+
+@pytest.fixture(autouse=True)
+def _always_stream():
+    import paper_2504_14960_amd as moe
+    moe.set_option("gemm_stream", 1)
+    yield
+    moe.set_option("gemm_stream", -1)
+
+
+@pytest.mark.parametrize("H,F,counts,bf16", [
+    (64, 64, EDGES, True),             # one whole block of the contraction
+    (8, 16, EDGES, True),              # less than one block, fewer columns than a block of 16 twice over
+    (136, 1416, EDGES, True),          # wide first product, narrow second one; remainders on both axes
+    (3000, 72, EDGES, True),           # the other way round
+    (1000, 200, EDGES, True),
+    (1048, 640, [40, 3], True),        # few workgroups: the waves share the contraction
+    (2048, 520, [64], True),
+    (1536, 512, [1, 0, 3, 12], True),  # at most 16 rows in all
+    (72, 16384, [5, 9], True),         # the same, with the wide form
+    (4, 8, EDGES, False),              # fp32: 16 bytes per row
+    (100, 260, EDGES, False),
+    (1028, 36, [7, 2], False),
+])
+def test_stream_against_the_oracle(H, F, counts, bf16):
+    inp, x_perm, offsets, h_ref, y_ref = bf16_case(H=H, F=F, E=len(counts), counts=counts, bf16=bf16, seed=6300 + H, r_pad=5)
+    R = int(offsets[-1])
+    h, y = bf16_run(x_perm, offsets, inp, 0, r_max=R + 5)
+    if not bf16 and H > 256:
+        # fp32 sums of 1028 terms: sqrt(1028) * 6e-8 = 2e-6 relative, within the bar's 1e-5
+        assert H <= 1028
+    assert_close(h[:R], h_ref, bf16, "h")
+    assert_close(y[:R], y_ref, bf16, "y_perm")
+    assert not h[R:].any() and not y[R:].any()     # rows past the last expert stay untouched
+
+
+@pytest.mark.parametrize("H,F,counts", [(256, 1408, EDGES), (1536, 256, EDGES), (2304, 256, [40, 3]), (512, 768, [1, 0, 3, 12])])
+def test_stream_fp8_against_the_oracle(H, F, counts):
+    c = fp8_case(seed=6500 + H, H=H, F=F, E=len(counts), counts=counts)
+    h, y, amax = fp8_run(c, r_pad=5)
+    R = c["R"]
+    _check_h_codes(h[:R], c["ref"].hq, "h codes")
+    assert abs(amax - c["ref"].amax_h) <= 1e-5 * c["ref"].amax_h
+    assert_close(y[:R], c["ref"].y, True, "y_perm")
+    assert not h[R:].any() and not y[R:].any()
+
+
+def test_saving_form_and_both_kernels_agree():
+    """The pre-activations are those behind h, and the large-tile kernel's results differ by rounding only."""
+    import torch
+    import paper_2504_14960_amd as moe
+    from helpers import to_dev, to_host, values
+    inp, x_perm, offsets, h_ref, _ = bf16_case(H=256, F=384, E=len(EDGES), counts=EDGES, seed=6600)
+    R = int(offsets[-1])
+    x, off = to_dev(x_perm), to_dev(offsets)
+    wg, wu, wd = (to_dev(inp[k]) for k in ("w_gate", "w_up", "w_down"))
+    out = {}
+    for stream in (1, 0):
+        moe.set_option("gemm_stream", stream)
+        gu = torch.zeros((R, 768), dtype=torch.bfloat16, device="cuda")
+        h, h2 = (torch.zeros((R, 384), dtype=torch.bfloat16, device="cuda") for _ in range(2))
+        moe.expert_gate_up_saving(x, off, wg, wu, h, gu)
+        moe.expert_gate_up(x, off, wg, wu, h2)
+        torch.cuda.synchronize()
+        assert torch.equal(h, h2)
+        assert_close(to_host(h), h_ref, True, f"h (stream {stream})")
+        out[stream] = values(to_host(gu))
+    # one rounding each: at most a unit in the last place (2^-8 relative) where the sums straddle a boundary
+    assert np.abs(out[0] - out[1]).max() <= np.abs(out[0]).max() * 2.0 ** -7
+    assert np.linalg.norm(out[0] - out[1]) <= 1e-3 * np.linalg.norm(out[0])
