@@ -536,7 +536,7 @@ moe_status_t moe_gemm_clock_sample(uint64_t* ticks);
  * the weight tile, 0 = for the activation tile); "gemm_workgroups" (workgroups launched by the
  * persistent grouped-GEMM kernels; 0 = one per compute unit, values below 8
  * are raised to 8); "router_tile" (16-token blocks per router workgroup: 1, 2
- * or 4; 0 = chosen from T and E); "wgrad_rowmajor" (1 = the expert FFN's backward
+ * or 4; 8 = experts spread over workgroups, the selection a launch of its own; 0 = chosen by size); "wgrad_rowmajor" (1 = the expert FFN's backward
  * forms the weight gradients straight from the row-major activations with
  * transposing LDS loads instead of from transposed copies: about 1.8x slower
  * weight-gradient GEMMs, no ragged transposes; default 0); "permute_fused" (1, the default: layers with at most 8 experts and at most

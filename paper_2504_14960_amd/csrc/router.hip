@@ -9,6 +9,7 @@
 // from global memory.  Partial sums are folded in a fixed wave order, so the
 // logits are bit-reproducible.  Selection is done by groups of lanes, one
 // group per token, with butterfly reductions on (value desc, index asc) keys.
+// With few tokens the same work is spread over more waves (router_split_kernel).
 #include "common.h"
 
 namespace moe {
@@ -366,34 +367,188 @@ __global__ __launch_bounds__(256) void router_bf16_kernel(
     select_tokens(&red[0][0], EP + 1, TOK, t0, T, E, K, renorm, topk_idx, topk_gate);
 }
 
+// ------------------------------------------------------------------ bf16 / MFMA, many experts and few tokens
+// A compute unit reads about 40 bytes per nanosecond here, whatever is in flight, and the kernel above has one workgroup
+// read the whole router weight: 64 experts x 3584 is 460 KB, 11 us for a single token.  So with few tokens the experts
+// are spread over workgroups too (blockIdx.y): a workgroup forms the logits of at most 16 MB tokens (tb of them used)
+// and 16 experts (eg used), and the selection, which needs all experts of a token, is a launch of its own
+// (topk_rank_kernel).  The 16 waves split the hidden dimension, U steps of 64 elements in flight each; operands go
+// straight from memory to the matrix instruction's registers (lane group j holds bytes 32 j .. 32 j + 31 of a 128-byte
+// step of both, so whole lines are asked for; the order inside a step plays no part in a dot product).  The partial
+// sums are added in wave order (fixed => reproducible).
+constexpr int kSplitWaves = 16;
+
+template <int MB>
+__global__ __launch_bounds__(kSplitWaves * 64) void router_logits_kernel(
+    const bf16_t* __restrict__ x, const bf16_t* __restrict__ w, const float* __restrict__ bias,
+    float* __restrict__ logits, int T, int H, int E, int tb, int eg) {
+    constexpr int LD = 20;                     // row of a partial tile: the four lane groups of a store hit different banks
+    constexpr int U = MB == 1 ? 4 : 3;         // steps in flight
+    __shared__ float part[kSplitWaves][16 * MB][LD];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int t0 = blockIdx.x * tb, e0 = blockIdx.y * eg;
+    const int fr = lane & 15, fg = lane >> 4;
+    const int nsteps = (H + 63) / 64;
+    // rows and experts past the workgroup's repeat its last one (the same lines) and are never stored
+    const bf16_t* xrow[MB];
+#pragma unroll
+    for (int a = 0; a < MB; ++a) xrow[a] = x + (size_t)min(t0 + min(a * 16 + fr, tb - 1), T - 1) * H;
+    const bf16_t* const wrow = w + (size_t)min(e0 + min(fr, eg - 1), E - 1) * H;
+    f32x4 acc[MB];
+#pragma unroll
+    for (int a = 0; a < MB; ++a) acc[a] = f32x4{0.f, 0.f, 0.f, 0.f};
+    for (int s0 = wave; s0 < nsteps; s0 += U * kSplitWaves) {
+        u32x4 xa[U][MB][2], wa[U][2];
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int p = 0; p < 2; ++p) {
+                const int k = (s0 + u * kSplitWaves) * 64 + fg * 16 + p * 8;
+                const bool in = k < H;         // H is a multiple of 8: a piece is in or out as a whole
+                wa[u][p] = u32x4{0u, 0u, 0u, 0u};
+                if (in) wa[u][p] = *reinterpret_cast<const u32x4*>(wrow + k);
+#pragma unroll
+                for (int a = 0; a < MB; ++a) {
+                    xa[u][a][p] = u32x4{0u, 0u, 0u, 0u};
+                    if (in) xa[u][a][p] = *reinterpret_cast<const u32x4*>(xrow[a] + k);
+                }
+            }
+#pragma unroll
+        for (int u = 0; u < U; ++u)
+#pragma unroll
+            for (int p = 0; p < 2; ++p)
+#pragma unroll
+                for (int a = 0; a < MB; ++a)
+                    acc[a] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, xa[u][a][p]),
+                                                                     __builtin_bit_cast(bf16x8, wa[u][p]), acc[a], 0, 0, 0);
+    }
+#pragma unroll
+    for (int a = 0; a < MB; ++a)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) part[wave][a * 16 + fg * 4 + r][fr] = acc[a][r];
+    __syncthreads();
+    for (int i = threadIdx.x; i < 16 * MB * 16; i += kSplitWaves * 64) {
+        const int lt = i >> 4, le = i & 15;
+        if (lt >= tb || le >= eg || t0 + lt >= T || e0 + le >= E) continue;
+        float v = part[0][lt][le];
+#pragma unroll
+        for (int ww = 1; ww < kSplitWaves; ++ww) v += part[ww][lt][le];
+        if (bias) v += bias[e0 + le];
+        logits[(size_t)(t0 + lt) * E + e0 + le] = v;
+    }
+}
+
+// Selection by rank, one wave per token: lane l holds the logits of experts l, l + 64, ..; the rank of an expert is the
+// number of experts in front of it (value descending, index ascending), counted against every logit in turn, and the
+// experts of rank < K write the slots.  No sorted lists, so the chain of dependent instructions is short: what counts
+// when there are too few tokens to fill the chip (7 us of the list form's time at 64 experts was that chain).
+// E <= 64 VPL.
+template <int VPL>
+__global__ __launch_bounds__(256) void topk_rank_kernel(const float* __restrict__ logits, int T, int E, int K,
+                                                        int renorm, int32_t* __restrict__ topk_idx,
+                                                        float* __restrict__ topk_gate) {
+    const int lane = threadIdx.x & 63;
+    const int t = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+    if (t >= T) return;
+    float v[VPL];
+    float m = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < VPL; ++j) {
+        const int e = lane + 64 * j;
+        const float l = e < E ? logits[(size_t)t * E + e] : -INFINITY;
+        v[j] = (l != l) ? -INFINITY : l;   // NaN ranks last
+        m = fmaxf(m, v[j]);
+    }
+    int rank[VPL];
+#pragma unroll
+    for (int j = 0; j < VPL; ++j) rank[j] = 0;
+#pragma unroll
+    for (int q = 0; q < VPL; ++q)
+#pragma unroll
+        for (int i0 = 0; i0 < 64; i0 += 16) {
+            if (64 * q + i0 >= E) break;   // uniform; the padding up to the next multiple of 16 ranks behind everything
+#pragma unroll
+            for (int i = i0; i < i0 + 16; ++i) {
+                const float s = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, v[q]), i));
+#pragma unroll
+                for (int j = 0; j < VPL; ++j) {
+                    const bool lower = j > q || (j == q && lane > i);   // expert 64 q + i has the lower index
+                    rank[j] += lower ? s >= v[j] : s > v[j];
+                }
+            }
+        }
+    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+    float p[VPL], z = 0.f;
+#pragma unroll
+    for (int j = 0; j < VPL; ++j) {
+        p[j] = lane + 64 * j < E ? expf(v[j] - m) : 0.f;
+        z += p[j];
+    }
+    for (int off = 32; off > 0; off >>= 1) z += __shfl_xor(z, off, 64);
+    float gsum = 0.f;
+#pragma unroll
+    for (int j = 0; j < VPL; ++j) {
+        p[j] = p[j] / z;
+        if (lane + 64 * j < E && rank[j] < K) gsum += p[j];
+    }
+    if (renorm)
+        for (int off = 32; off > 0; off >>= 1) gsum += __shfl_xor(gsum, off, 64);
+#pragma unroll
+    for (int j = 0; j < VPL; ++j) {
+        const int e = lane + 64 * j;
+        if (e < E && rank[j] < K) {
+            topk_idx[(size_t)t * K + rank[j]] = e;
+            topk_gate[(size_t)t * K + rank[j]] = renorm ? p[j] / gsum : p[j];
+        }
+    }
+}
+
 // ------------------------------------------------------------------ fp32 / VALU
-// One wave per token; lanes stride the hidden dimension, one expert at a time.
+// One wave per token; lanes stride the hidden dimension, eight experts at a time: their weight loads are in flight
+// together, and the eight sums are folded across the wave in ten shuffles (three halving steps that leave lane l with
+// the sum of expert l mod 8 over an eighth of the wave, then three ordinary ones).
 __global__ __launch_bounds__(256) void router_f32_kernel(
     const float* __restrict__ x, const float* __restrict__ w, const float* __restrict__ bias,
     float* __restrict__ logits, int T, int H, int E, int K, int renorm,
     int32_t* __restrict__ topk_idx, float* __restrict__ topk_gate) {
+    constexpr int EB = 8;
     __shared__ float red[4][kMaxExperts + 1];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int t0 = blockIdx.x * 4;
     const int t = t0 + wave;
     if (t < T) {
         const float* xr = x + (size_t)t * H;
-        for (int e = 0; e < E; ++e) {
-            const float* wr = w + (size_t)e * H;
-            float s = 0.f;
+        for (int e0 = 0; e0 < E; e0 += EB) {
+            float s[EB];
+#pragma unroll
+            for (int j = 0; j < EB; ++j) s[j] = 0.f;
             for (int h = lane * 4; h < H; h += 256) {
                 const f32x4 a = *reinterpret_cast<const f32x4*>(xr + h);
-                const f32x4 b = *reinterpret_cast<const f32x4*>(wr + h);
-                s = fmaf(a[0], b[0], s);
-                s = fmaf(a[1], b[1], s);
-                s = fmaf(a[2], b[2], s);
-                s = fmaf(a[3], b[3], s);
+                f32x4 b[EB];
+#pragma unroll
+                for (int j = 0; j < EB; ++j) b[j] = *reinterpret_cast<const f32x4*>(w + (size_t)min(e0 + j, E - 1) * H + h);
+#pragma unroll
+                for (int j = 0; j < EB; ++j)
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) s[j] = fmaf(a[q], b[j][q], s[j]);
             }
-            for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-            if (bias) s += bias[e];
-            if (lane == 0) {
-                red[wave][e] = s;
-                logits[(size_t)t * E + e] = s;
+#pragma unroll
+            for (int n = EB / 2; n > 0; n >>= 1) {
+                const bool up = lane & n;   // this lane keeps the upper half of the values it still holds
+#pragma unroll
+                for (int j = 0; j < n; ++j) {
+                    const float keep = up ? s[j + n] : s[j], give = up ? s[j] : s[j + n];
+                    s[j] = keep + __shfl_xor(give, n, 64);
+                }
+            }
+            float v = s[0];
+#pragma unroll
+            for (int off = EB; off < 64; off <<= 1) v += __shfl_xor(v, off, 64);
+            const int e = e0 + lane;
+            if (lane < EB && e < E) {
+                if (bias) v += bias[e];
+                red[wave][e] = v;
+                logits[(size_t)t * E + e] = v;
             }
         }
     }
@@ -444,17 +599,39 @@ void launch_bf16(const void* x, const void* w, const float* bias, float* logits,
 
 }  // namespace
 
-static int g_router_tile = 0;  // 16-token blocks per workgroup; 0 = chosen from T and E
+// Where the experts are spread over workgroups (one launch before / logits + selection after, us, H = 3584):
+// (inside the layer, 64 tokens of the Qwen2 shape: 33 / 10)
+//   64 experts:  1 token 23.1 / 7.2, 64 tokens 24.4 / 9.0, 500 tokens 24.7 / 11.6, 2048 tokens 26.9 / 18.7, 4096 27.8 / 31.6
+//   128 experts x 2048:  1 token 31.3 / 8.6, 2048 tokens 37.1 / 24.8, 4096 tokens 36.6 / 41.5
+// and below 64 KB of router weight the second launch costs what the first saves: 8 experts x 4096, one token 8.6 / 6.4
+// alone and 10.6 / 9.5 inside the layer, 12 experts x 1000 7.9 / 9.7 inside the layer.
+constexpr int kSplitMaxTokens = 2048, kSplitMinWeights = 32768;
+// Selection alone, lists of eight lanes / by rank (us, 64 experts, K = 8): 1024 tokens 10.2 / 4.1, 4096 tokens 10.3 / 6.7,
+// 16384 tokens 13.3 / 13.1; 128 experts 17.1 / 13.1 at 4096.
+constexpr int kRankMaxTokens = 4096;
+
+// selection from logits alone
+static void launch_topk(const float* logits, int T, int E, int K, int renorm, int32_t* idx, float* gate, hipStream_t s) {
+    if (E <= 128 && T <= kRankMaxTokens) {
+        const dim3 grid((T + 3) / 4);
+        if (E <= 64) hipLaunchKernelGGL((topk_rank_kernel<1>), grid, dim3(256), 0, s, logits, T, E, K, renorm, idx, gate);
+        else hipLaunchKernelGGL((topk_rank_kernel<2>), grid, dim3(256), 0, s, logits, T, E, K, renorm, idx, gate);
+        return;
+    }
+    const int per_block = topk_tile_tokens(E, K);
+    int grid = (T + per_block - 1) / per_block;
+    if (grid > 4096) grid = 4096;
+    hipLaunchKernelGGL(topk_only_kernel, dim3(grid), dim3(256), 0, s, logits, T, E, K, renorm, idx, gate);
+}
+
+static int g_router_tile = 0;  // 16-token blocks per workgroup; 0 = chosen by size, 8 = experts spread over workgroups
 void set_router_tile(int mb) { g_router_tile = mb; }
 
 void launch_router(const void* x, const void* w, const float* bias, float* logits, int T, int H,
                    int E, int K, int renorm, moe_dtype_t dt, int32_t* idx, float* gate,
                    hipStream_t s) {
     if (x == nullptr) {
-        const int per_block = topk_tile_tokens(E, K);
-        int grid = (T + per_block - 1) / per_block;
-        if (grid > 4096) grid = 4096;
-        hipLaunchKernelGGL(topk_only_kernel, dim3(grid), dim3(256), 0, s, logits, T, E, K, renorm, idx, gate);
+        launch_topk(logits, T, E, K, renorm, idx, gate, s);
         return;
     }
     if (dt == MOE_F32) {
@@ -464,6 +641,27 @@ void launch_router(const void* x, const void* w, const float* bias, float* logit
         return;
     }
     const int nb = (E + 15) / 16;
+    if (nb <= 8 && (g_router_tile == 8 || (g_router_tile == 0 && T <= kSplitMaxTokens && (long long)E * H >= kSplitMinWeights))) {
+        // Tokens and experts per workgroup: halve the larger side while that still gives every workgroup a compute unit
+        const bool wide = T >= 1024;
+        int tb = wide ? 32 : 16, eg = 16;
+        auto groups = [&](int a, int b) { return (long long)((T + a - 1) / a) * ((E + b - 1) / b); };
+        while (eg > 2) {
+            const int a = min(tb, T), ntb = a > eg ? tb / 2 : tb, neg = a > eg ? eg : eg / 2;
+            if (groups(ntb, neg) > 256) break;
+            tb = ntb;
+            eg = neg;
+        }
+        const dim3 grid((T + tb - 1) / tb, (E + eg - 1) / eg);
+        if (tb > 16)
+            hipLaunchKernelGGL((router_logits_kernel<2>), grid, dim3(kSplitWaves * 64), 0, s, static_cast<const bf16_t*>(x),
+                               static_cast<const bf16_t*>(w), bias, logits, T, H, E, tb, eg);
+        else
+            hipLaunchKernelGGL((router_logits_kernel<1>), grid, dim3(kSplitWaves * 64), 0, s, static_cast<const bf16_t*>(x),
+                               static_cast<const bf16_t*>(w), bias, logits, T, H, E, tb, eg);
+        launch_topk(logits, T, E, K, renorm, idx, gate, s);
+        return;
+    }
     // tokens per workgroup: enough workgroups to fill 256 CUs, but from 16
     // experts on a taller tile so the router weight is re-read less often
     int mb = (T >= 32768) ? 4 : (T >= 16384 ? 2 : 1);
