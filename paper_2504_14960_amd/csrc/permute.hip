@@ -12,8 +12,8 @@
 //                           with wave ballots and writes both maps.
 //   3. permute_copy_kernel  one wave per token: the row is read once with
 //                           16-byte lanes and stored to each kept destination.
-// Layers with few experts and a small index array (the Mixtral shapes) take
-// permute_fused_kernel instead: the same maps from ONE launch, the counting
+// Small index arrays take one launch: permute_small_kernel for decode and short
+// prompts, permute_fused_kernel for few experts (the Mixtral shapes): the same maps from ONE launch, the counting
 // hidden under the latency of the row loads.
 #include <mutex>
 
@@ -607,6 +607,165 @@ __global__ __launch_bounds__(kFusedWaves * 64) void permute_fused_kernel(
     }
 }
 
+// ---- all of a2 in one launch, any number of experts, few assignments (decode, short prompts) ----
+// The three launches above cost more than their work then: 64 tokens of a 64-expert layer took 4.4 + 5.7 + 5.4 us for
+// 4 MB of rows.  As in permute_fused_kernel every workgroup counts the whole index array itself, here into LDS
+// histograms (assignments before the workgroup's own, and the rest), so E is not limited to the packed counters; the
+// row loads are requested first and land under the counting.  A workgroup of 16 waves owns TB tokens, and 16 / TB
+// waves share a row (piece i of wave w: the KiB i * 16 / TB + w / TB), so that a handful of tokens still occupies many
+// compute units.  FP8: the row is quantised on the way, its maximum goes to *amax.  Same maps, bit for bit, as the
+// three-kernel path: rank = assignments of the same expert with a lower index.
+constexpr int kSmallWaves = 16, kSmallThreads = kSmallWaves * 64;
+constexpr int kSmallMaxOwn = 1024;   // assignments of a workgroup's own tokens
+
+template <int NV, int TB, bool FP8>
+__global__ __launch_bounds__(kSmallThreads) void permute_small_kernel(
+    const uint8_t* __restrict__ x, const int32_t* __restrict__ idx, int T, int K, int E, int capacity, int row_bytes,
+    int r_max, uint8_t* __restrict__ x_perm, int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
+    int32_t* __restrict__ row_of_assign, int32_t* __restrict__ assign_of_row, float scale, float* __restrict__ amax) {
+    constexpr int P = kSmallWaves / TB;
+    __shared__ int base[kMaxExperts];       // assignments of the expert before this workgroup's own, then the next rank
+    __shared__ int rest[kMaxExperts];       // the others
+    __shared__ int off[kMaxExperts + 1];
+    __shared__ int rows[kSmallMaxOwn];
+    __shared__ float wave_max[kSmallWaves];
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int A = T * K;
+    const int t0 = blockIdx.x * TB;
+    const int a0 = t0 * K, na = min(TB, T - t0) * K;
+    const int t = t0 + wave % TB, piece0 = wave / TB;
+
+    const bool copy = x != nullptr;
+    u32x4 v[NV];
+    if (copy) {
+#pragma unroll
+        for (int i = 0; i < NV; ++i) {
+            const int o = (i * P + piece0) * 1024 + lane * 16;
+            if (t < T && o < row_bytes) v[i] = *reinterpret_cast<const u32x4*>(x + (size_t)t * row_bytes + o);
+        }
+    }
+    if (tid < kMaxExperts) {
+        base[tid] = 0;
+        rest[tid] = 0;
+    }
+    __syncthreads();
+#pragma unroll 4
+    for (int a = tid; a < A; a += kSmallThreads) {
+        const int e = idx[a];
+        if ((unsigned)e < (unsigned)E) atomicAdd(a < a0 ? &base[e] : &rest[e], 1);
+    }
+    __syncthreads();
+    if (wave == 0) {   // lane l: experts 4 l .. 4 l + 3
+        int cnt[4], s = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int tot = base[4 * lane + j] + rest[4 * lane + j];
+            cnt[j] = (capacity > 0 && tot > capacity) ? capacity : tot;
+            s += cnt[j];
+        }
+        int incl = s;
+        for (int d = 1; d < 64; d <<= 1) {
+            const int o = __shfl_up(incl, d, 64);
+            if (lane >= d) incl += o;
+        }
+        int run = incl - s;
+        if (lane == 0) off[0] = 0;
+        if (blockIdx.x == 0 && lane == 0) offsets[0] = 0;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int e = 4 * lane + j;
+            run += cnt[j];
+            off[e + 1] = run;
+            if (blockIdx.x == 0 && e < E) {
+                counts[e] = cnt[j];
+                offsets[e + 1] = run;
+            }
+        }
+        // this workgroup's own assignments, 64 at a time in ascending order
+        int nbits = 0;
+        while ((1 << nbits) < E) ++nbits;
+        const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
+        for (int u0 = 0; u0 < na; u0 += 64) {
+            const int a = a0 + u0 + lane;
+            const int e = (u0 + lane < na) ? idx[a] : -1;
+            const bool valid = (unsigned)e < (unsigned)E;
+            uint64_t peers = __ballot(valid);
+            for (int b = 0; b < nbits; ++b) {   // uniform trip count
+                const bool bit = (e >> b) & 1;
+                const uint64_t m = __ballot(valid && bit);
+                peers &= bit ? m : ~m;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // the writes of the unit before, and the offsets
+            int row = -1;
+            if (valid) {
+                const int before = base[e];
+                const int rank = before + __popcll(peers & lt_mask);
+                if (capacity <= 0 || rank < capacity) row = off[e] + rank;
+                if (row >= r_max) row = -1;  // cannot happen for a consistent r_max; never an address
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // every lane has read base[e]
+                if ((peers & lt_mask) == 0) base[e] = before + __popcll(peers);
+            }
+            if (u0 + lane < na) {
+                rows[u0 + lane] = row;
+                row_of_assign[a] = row;
+                if (row >= 0) assign_of_row[row] = a;
+            }
+        }
+    }
+    __syncthreads();
+    // rows past the kept total are marked unused
+    for (int r = off[E] + blockIdx.x * kSmallThreads + tid; r < r_max; r += gridDim.x * kSmallThreads) assign_of_row[r] = -1;
+
+    float m = 0.f;
+    if (copy && t < T) {
+        const int* const mine = rows + (wave % TB) * K;
+        u32x2 q[NV];
+        if constexpr (FP8) {
+            bool any = false;
+            for (int k = 0; k < K; ++k) any |= mine[k] >= 0;
+            if (any) {
+#pragma unroll
+                for (int i = 0; i < NV; ++i) {
+                    if ((i * P + piece0) * 1024 + lane * 16 >= row_bytes) continue;
+                    float f[8];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        f[2 * j] = __uint_as_float(v[i][j] << 16);
+                        f[2 * j + 1] = __uint_as_float(v[i][j] & 0xffff0000u);
+                    }
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) m = fmaxf(m, fabsf(f[j]));
+                    q[i][0] = f32x4_to_e4m3(f[0] * scale, f[1] * scale, f[2] * scale, f[3] * scale);
+                    q[i][1] = f32x4_to_e4m3(f[4] * scale, f[5] * scale, f[6] * scale, f[7] * scale);
+                }
+            }
+        }
+        for (int k = 0; k < K; ++k) {
+            const int row = mine[k];   // wave-uniform
+            if (row < 0) continue;
+            uint8_t* const dst = x_perm + (size_t)row * (FP8 ? row_bytes / 2 : row_bytes);
+#pragma unroll
+            for (int i = 0; i < NV; ++i) {
+                const int o = (i * P + piece0) * 1024 + lane * 16;
+                if (o >= row_bytes) continue;
+                if constexpr (FP8) *reinterpret_cast<u32x2*>(dst + o / 2) = q[i];
+                else *reinterpret_cast<u32x4*>(dst + o) = v[i];
+            }
+        }
+    }
+    if (FP8 && amax) {
+        // one atomic per workgroup at most, and none if the value read is already as large (*amax only grows)
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) m = fmaxf(m, __shfl_xor(m, o, 64));
+        if (lane == 0) wave_max[wave] = m;
+        __syncthreads();
+        if (tid == 0) {
+            for (int w = 1; w < kSmallWaves; ++w) m = fmaxf(m, wave_max[w]);
+            if (m > __builtin_nontemporal_load(amax)) atomicMax(reinterpret_cast<int*>(amax), __float_as_int(m));
+        }
+    }
+}
+
 __global__ void fill_i32_kernel(int32_t* p, int n, int32_t v0, int32_t step) {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = v0 + i * step;
@@ -615,7 +774,38 @@ __global__ void fill_i32_kernel(int32_t* p, int n, int32_t v0, int32_t step) {
 }  // namespace
 
 static int g_permute_fused = 1;   // 0: always the three-kernel path
-void set_permute_fused(int v) { g_permute_fused = v; }   // 2 / 3: force one / two tokens per wave (experiments)
+void set_permute_fused(int v) { g_permute_fused = v; }   // 2 / 3: the packed form with one / two tokens per wave, 4: the histogram form
+
+// Where the histogram form of the one-launch dispatch takes over (us, the three launches or the packed form / this one):
+//   64 experts x 3584, K = 8: 64 tokens 11.5 / 5.7, 500 tokens 18.5 / 10.6, 2048 tokens 38.1 / 29.8, 4096 tokens 34.8 / 37.6
+//   8 experts x 4096, K = 2: 1 token 6.2 / 3.4, 500 tokens 9.9 / 5.8, 2048 tokens 15.1 / 10.8, 4096 tokens 16.4 / 26.4
+//   the same in FP8: 1 token 9.4 / 5.1, 1024 tokens 13.1 / 9.3, 2048 tokens 11.2 / 14.5
+constexpr int kSmallMaxAssign = 16384;
+
+// The one-launch dispatch of few assignments; false if the call is none of its own.  `x` may be null (maps only).
+template <bool FP8>
+static bool launch_permute_small(const void* x, const int32_t* idx, int T, int K, int E, int capacity, int row_bytes,
+                                 int r_max, void* x_perm, int32_t* counts, int32_t* offsets, int32_t* row_of_assign,
+                                 int32_t* assign_of_row, float scale, float* amax, hipStream_t s) {
+    if (row_bytes > 16384 || row_bytes % 16) return false;
+    const bool few = E <= kFusedMaxExperts ? T <= (FP8 ? 1024 : 2048) : (long long)T * K <= kSmallMaxAssign;
+    if (g_permute_fused != 4 && (g_permute_fused != 1 || !few)) return false;
+    const bool narrow = T <= 1024 || 16 * K > kSmallMaxOwn;   // 4 tokens per workgroup, else 16
+    const int tb = narrow ? 4 : 16;
+    if (tb * K > kSmallMaxOwn) return false;
+    const int nv = (row_bytes + 1024 * (16 / tb) - 1) / (1024 * (16 / tb));   // pieces of a wave
+#define SMALL_CASE(NVV, TBB)                                                                                            \
+    hipLaunchKernelGGL((permute_small_kernel<NVV, TBB, FP8>), dim3((T + TBB - 1) / TBB), dim3(kSmallThreads), 0, s,      \
+                       static_cast<const uint8_t*>(x), idx, T, K, E, capacity, row_bytes, r_max,                         \
+                       static_cast<uint8_t*>(x_perm), counts, offsets, row_of_assign, assign_of_row, scale, amax)
+    if (narrow) {
+        if (nv <= 2) SMALL_CASE(2, 4); else SMALL_CASE(4, 4);
+    } else {
+        if (nv <= 4) SMALL_CASE(4, 16); else if (nv <= 8) SMALL_CASE(8, 16); else SMALL_CASE(16, 16);
+    }
+#undef SMALL_CASE
+    return true;
+}
 
 size_t permute_workspace_bytes(int T, int K, int E) {
     const long long A = (long long)T * K;
@@ -628,7 +818,10 @@ void launch_permute(const void* x, const int32_t* idx, int T, int H, int E, int 
                     int32_t* row_of_assign, int32_t* assign_of_row, void* ws, hipStream_t s) {
     const int A = T * K;
     const int row_bytes_all = H * (dt == MOE_BF16 ? 2 : 4);
-    if (g_permute_fused && E <= kFusedMaxExperts && A <= kFusedMaxAssign && row_bytes_all <= kFusedMaxRowVecs * 1024 &&
+    if (launch_permute_small<false>((x != nullptr && x_perm != nullptr) ? x : nullptr, idx, T, K, E, capacity, row_bytes_all,
+                                    r_max, x_perm, counts, offsets, row_of_assign, assign_of_row, 0.f, nullptr, s))
+        return;
+    if (g_permute_fused && g_permute_fused != 4 && E <= kFusedMaxExperts && A <= kFusedMaxAssign && row_bytes_all <= kFusedMaxRowVecs * 1024 &&
         row_bytes_all % 16 == 0) {
         // few experts, small index array: one launch (the workspace is not used)
         const uint8_t* xs = (x != nullptr && x_perm != nullptr) ? static_cast<const uint8_t*>(x) : nullptr;
@@ -742,6 +935,9 @@ void launch_permute_zero_rows(const int32_t* assign_of_row, void* x_perm, int ro
 void launch_permute_fp8(const void* x, const int32_t* idx, int T, int H, int E, int K, int capacity, int r_max,
                         float scale, void* x_perm_fp8, int32_t* counts, int32_t* offsets, int32_t* row_of_assign,
                         int32_t* assign_of_row, float* amax, void* ws, hipStream_t s) {
+    if (launch_permute_small<true>(x, idx, T, K, E, capacity, H * 2, r_max, x_perm_fp8, counts, offsets, row_of_assign,
+                                   assign_of_row, scale, amax, s))
+        return;
     // maps as in launch_permute, then the quantising copy
     launch_permute(nullptr, idx, T, H, E, K, capacity, r_max, MOE_BF16, nullptr, counts, offsets, row_of_assign,
                    assign_of_row, ws, s);

@@ -3,8 +3,9 @@ import numpy as np
 import pytest
 
 import oracle
-from moe_inputs import get_config, make_layer_inputs
-from helpers import GATE_RTOL, LOGIT_ATOL, guard_margins
+from moe_inputs import get_config, make_layer_inputs, make_tokens
+from helpers import GATE_RTOL, LOGIT_ATOL, assert_close, guard_margins, to_dev, values
+from test_gpu_permute import _gpu_combine, _gpu_permute, _idx
 from test_gpu_router import _gpu_topk
 
 pytestmark = pytest.mark.gpu
@@ -51,3 +52,76 @@ def test_selection_by_rank(kind, T, E, K):
     _, idx, gate = _gpu_topk(logits, K, False)
     np.testing.assert_array_equal(idx, want_idx)
     np.testing.assert_allclose(gate, want_gate, rtol=GATE_RTOL, atol=1e-6)
+
+
+@pytest.mark.parametrize("T,H,E,K,capacity,kind,bf16", [
+    (1, 4096, 8, 2, 0, "normal", True),           # one workgroup, three of its four tokens missing
+    (1023, 24, 64, 8, 0, "normal", True),         # rows of 48 bytes: most waves hold no piece
+    (1024, 2056, 12, 3, 100, "onehot", True),     # five pieces of a KiB over four waves; drops
+    (1025, 1544, 256, 2, 0, "normal", False),     # 16 tokens per workgroup, 6 KiB rows, every lane of the scan
+    (2000, 2560, 100, 4, 64, "normal", False),    # 10 KiB rows
+    (1100, 8192, 9, 1, 0, "normal", True),        # 16 KiB rows, the largest
+    (90, 8, 64, 64, 0, "normal", True),           # 4 workgroups' worth of 64-assignment units per token group
+])
+def test_one_launch_dispatch_with_histograms(T, H, E, K, capacity, kind, bf16):
+    import paper_2504_14960_amd as moe
+    idx = _idx(4100 + T, T, E, K, kind)[0].copy()
+    idx[T // 2, 0] = E           # an index outside [0, E): a dropped assignment
+    x = make_tokens(4101, T, H, bf16=bf16)
+    want = oracle.permute(x, idx, E, capacity)
+    moe.set_option("permute_fused", 4)
+    try:
+        x_perm, counts, offsets, roa, aor = _gpu_permute(x, idx, E, capacity)
+        maps_only = _gpu_permute(None, idx, E, capacity)
+    finally:
+        moe.set_option("permute_fused", 1)
+    for got in ((counts, offsets, roa, aor), maps_only[1:]):
+        for a, b in zip(got, (want.counts, want.offsets, want.row_of_assign, want.assign_of_row)):
+            np.testing.assert_array_equal(a, b)
+    np.testing.assert_array_equal(x_perm[:want.R], want.x_perm[:want.R])
+    assert (x_perm[want.R:] == 0).all(), "rows past the kept total must be left untouched"
+
+
+@pytest.mark.parametrize("T,H,E,K,capacity", [(1, 4096, 8, 2, 0), (37, 1032, 64, 8, 0), (1024, 520, 20, 2, 60), (1500, 2048, 60, 4, 0)])
+def test_one_launch_fp8_dispatch_with_histograms(T, H, E, K, capacity):
+    import torch
+    import paper_2504_14960_amd as moe
+    idx = _idx(4300 + T, T, E, K, "onehot" if capacity else "normal")[0]
+    x = make_tokens(4301, T, H, bf16=True)
+    r_max = moe.max_rows(T, K, E, capacity)
+    i32 = dict(dtype=torch.int32, device="cuda")
+    out = []
+    for fused in (0, 4):
+        xq = torch.full((r_max + 2, H), 0xAA, dtype=torch.uint8, device="cuda")
+        maps = [torch.empty((n,), **i32) for n in (E, E + 1, T * K, r_max)]
+        ws = torch.empty((moe.permute_workspace_bytes(T, K, E) + 256,), dtype=torch.uint8, device="cuda")
+        amax = torch.zeros(1, dtype=torch.float32, device="cuda")
+        moe.set_option("permute_fused", fused)
+        try:
+            moe.permute_fp8(to_dev(x), to_dev(idx), E, capacity, 23.7, xq[:r_max], *maps, amax, ws)
+            torch.cuda.synchronize()
+        finally:
+            moe.set_option("permute_fused", 1)
+        out.append([xq, *maps, amax])
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+
+
+@pytest.mark.parametrize("T,H,K,bf16,with_addend", [
+    (1, 4104, 2, True, True),          # three slices of a row, the last of 16 bytes
+    (3, 3584, 8, True, True),
+    (64, 1028, 4, False, True),
+    (2047, 1032, 1, True, False),      # the last token count that is split, two slices
+    (5, 2056, 20, True, True),         # more than eight slots: the general kernel
+])
+def test_combine_of_few_tokens(T, H, K, bf16, with_addend):
+    rng = np.random.default_rng(T + H)
+    rows = T * K + 3
+    y_perm = make_tokens(4400, rows, H, bf16=bf16)
+    addend = make_tokens(4401, T, H, bf16=bf16) if with_addend else None
+    roa = rng.permutation(rows)[:T * K].astype(np.int32)
+    roa[::5] = -1
+    gate = rng.random((T, K)).astype(np.float32)
+    want = oracle.combine(values(y_perm), roa, gate.astype(np.float64), None if addend is None else values(addend))
+    got = _gpu_combine(y_perm, roa, gate, addend, T, K)
+    assert_close(got, want, bf16, "y")
