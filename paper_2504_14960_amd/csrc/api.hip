@@ -52,7 +52,7 @@ static moe_status_t check_dims(const char* fn, int T, int H, int E, int K, moe_d
 
 struct LayerLayout {
     size_t logits, idx, gate, counts, offsets, roa, aor, perm_ws, x_perm, h, y_perm;
-    size_t s_offsets, s_h, s_y, total;
+    size_t s_offsets, s_h, s_y, total, part_bytes;
     int r_max;
 };
 
@@ -80,6 +80,10 @@ static LayerLayout layer_layout(int T, int H, int E, int K, int F, int Fs, int c
     L.s_h = take(Fs > 0 ? (size_t)T * Fs * es : 0);
     L.s_y = take(Fs > 0 ? (size_t)T * H * es : 0);
     L.total = o;
+    // at the end, and not required: partial sums of the expert products
+    const size_t routed = expert_ffn_part_bytes(L.r_max, H, F, E, dt);
+    const size_t shared = Fs > 0 ? expert_ffn_part_bytes(T, H, Fs, 1, dt) : 0;
+    L.part_bytes = routed > shared ? routed : shared;
     return L;
 }
 
@@ -282,7 +286,8 @@ moe_status_t moe_sort_chunks(const void* src, int R_src, const int32_t* chunk_ro
 static moe_status_t expert_ffn(const char* fn, int phase, const void* x_perm,
                                const int32_t* expert_offsets, int R_max, int H, int F, int E,
                                const void* w_gate, const void* w_up, const void* w_down,
-                               moe_dtype_t dt, void* h, void* y_perm, moe_stream_t stream) {
+                               moe_dtype_t dt, void* h, void* y_perm, moe_stream_t stream,
+                               void* part = nullptr, size_t part_bytes = 0) {
     if (dt != MOE_F32 && dt != MOE_BF16) return fail(MOE_ERR_INVALID_ARG, "%s: unknown dtype %d", fn, (int)dt);
     if (R_max < 0 || H <= 0 || F <= 0 || E <= 0)
         return fail(MOE_ERR_INVALID_ARG, "%s: need R_max >= 0 and H, F, E > 0", fn);
@@ -303,7 +308,7 @@ static moe_status_t expert_ffn(const char* fn, int phase, const void* x_perm,
         REQUIRE_PTR(fn, y_perm);
     }
     if (!launch_expert_ffn(x_perm, expert_offsets, R_max, H, F, E, w_gate, w_up, w_down, dt, h, y_perm,
-                           g_gemm_variant, phase, static_cast<hipStream_t>(stream)))
+                           g_gemm_variant, phase, part, part_bytes, static_cast<hipStream_t>(stream)))
         return fail(MOE_ERR_UNSUPPORTED, "%s: no kernel for H=%d F=%d", fn, H, F);
     return check_launch(fn);
 }
@@ -589,7 +594,8 @@ moe_status_t moe_grouped_gemm_swiglu_backward(const void* x_perm, const void* h,
 size_t moe_layer_workspace_bytes(int T, int H, int E, int K, int F, int Fs, int capacity,
                                  moe_dtype_t dt) {
     if (T < 0 || H <= 0 || E <= 0 || K <= 0 || F <= 0 || Fs < 0) return 0;
-    return layer_layout(T, H, E, K, F, Fs, capacity, dt).total;
+    const LayerLayout L = layer_layout(T, H, E, K, F, Fs, capacity, dt);
+    return L.total + L.part_bytes;
 }
 
 size_t moe_workspace_bytes(int T, int H, int E, int K, int F, int capacity, moe_dtype_t dt) {
@@ -639,16 +645,18 @@ moe_status_t moe_layer_forward(const void* x, const void* w_router, const float*
     st = moe_permute(x, idx, T, H, E, K, capacity, dt, ws + L.x_perm, counts, offsets, roa, aor,
                      ws + L.perm_ws, permute_workspace_bytes(T, K, E), stream);
     if (st) return st;
-    st = moe_grouped_gemm_swiglu(ws + L.x_perm, offsets, L.r_max, H, F, E, w_gate, w_up, w_down, dt,
-                                 ws + L.h, ws + L.y_perm, stream);
+    void* const part = ws + L.total;
+    const size_t part_bytes = workspace_bytes - L.total;
+    st = expert_ffn("moe_grouped_gemm_swiglu", 3, ws + L.x_perm, offsets, L.r_max, H, F, E, w_gate, w_up, w_down, dt,
+                    ws + L.h, ws + L.y_perm, stream, part, part_bytes);
     if (st) return st;
     const void* addend = nullptr;
     if (shared) {
         // the shared expert sees every token: one "expert" owning rows [0, T)
         int32_t* so = reinterpret_cast<int32_t*>(ws + L.s_offsets);
         launch_fill_i32(so, 2, 0, T, static_cast<hipStream_t>(stream));
-        st = moe_grouped_gemm_swiglu(x, so, T, H, Fs, 1, ws_gate, ws_up, ws_down, dt, ws + L.s_h,
-                                     ws + L.s_y, stream);
+        st = expert_ffn("moe_grouped_gemm_swiglu", 3, x, so, T, H, Fs, 1, ws_gate, ws_up, ws_down, dt, ws + L.s_h,
+                        ws + L.s_y, stream, part, part_bytes);
         if (st) return st;
         addend = ws + L.s_y;
     }
@@ -908,7 +916,7 @@ moe_status_t moe_set_option(const char* name, int value) {
         return MOE_OK;
     }
     if (name && strcmp(name, "gemm_stream") == 0) {
-        moe::set_gemm_stream(value < 0 ? -1 : (value != 0));
+        moe::set_gemm_stream(value < 0 ? -1 : value > 2 ? 1 : value);
         return MOE_OK;
     }
     if (name && strcmp(name, "fp8_deep_weights") == 0) {

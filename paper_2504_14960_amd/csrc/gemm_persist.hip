@@ -736,8 +736,9 @@ bool persist_idle_skip(int E) { return g_persist_idle_skip < 0 ? E >= 16 : g_per
 bool launch_grouped_nt(const void* A, const int32_t* offsets, int r_max, int E, int N, int K, const void* B,
                        void* C, hipStream_t s) {
     if (K < 128 || K % 64 || N % 8) return false;
-    if (stream_covers(K * 2ll) && stream_preferred(r_max, E, N, false)) {
-        launch_stream(kStreamBf16, A, offsets, r_max, E, N, K, B, nullptr, C, nullptr, 0.f, 0.f, 0.f, nullptr, s);
+    const StreamPlan plan = plan_stream(kStreamBf16, r_max, E, N, K, false, true, 0);
+    if (plan.kind != kPlanLarge) {
+        launch_stream(plan, kStreamBf16, A, offsets, r_max, E, N, K, B, nullptr, C, nullptr, 0.f, 0.f, 0.f, nullptr, nullptr, s);
         return true;
     }
     launch_persist<256, 256, 2, 4, 0, true>(A, offsets, r_max, E, N, K, B, nullptr, C, nullptr, s);
@@ -769,8 +770,9 @@ bool launch_grouped_nt_swiglu_bwd(const void* A, const int32_t* offsets, int r_m
 bool launch_gate_up_saving(const void* x_perm, const int32_t* offsets, int r_max, int H, int F, int E,
                            const void* w_gate, const void* w_up, void* h, void* gu, hipStream_t s) {
     if (H < 128 || H % 64 || F % 8) return false;
-    if (stream_covers(H * 2ll) && stream_preferred(r_max, E, F, true)) {   // the same choice as the plain forward's
-        launch_stream(kStreamBf16, x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, gu, 0.f, 0.f, 0.f, nullptr, s);
+    const StreamPlan plan = plan_stream(kStreamBf16, r_max, E, F, H, true, true, 0);   // the same choice as the plain forward's
+    if (plan.kind != kPlanLarge) {
+        launch_stream(plan, kStreamBf16, x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, gu, 0.f, 0.f, 0.f, nullptr, nullptr, s);
         return true;
     }
     launch_persist<256, 256, 2, 4, 2, true>(x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, gu, s);

@@ -465,14 +465,18 @@ void launch_expert_ffn_fp8(const void* x_perm, const int32_t* offsets, int r_max
                            float scale_h, float dq_down, void* h, float* amax_h, void* y_perm, int phase,
                            hipStream_t s) {
     if (phase & 1) {
-        if (stream_covers(H) && stream_preferred(r_max, E, F, true))
-            launch_stream(kStreamFp8, x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, nullptr, dq_gate, dq_up, scale_h, amax_h, s);
+        const StreamPlan plan = plan_stream(kStreamFp8, r_max, E, F, H, true, true, 0);
+        if (plan.kind != kPlanLarge)
+            launch_stream(plan, kStreamFp8, x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, nullptr, dq_gate, dq_up, scale_h,
+                          amax_h, nullptr, s);
         else
             launch_fp8<true>(x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, dq_gate, dq_up, scale_h, amax_h, s);
     }
     if (phase & 2) {
-        if (stream_covers(F) && stream_preferred(r_max, E, H, false))
-            launch_stream(kStreamFp8, h, offsets, r_max, E, H, F, w_down, nullptr, y_perm, nullptr, dq_down, 0.f, 0.f, nullptr, s);
+        const StreamPlan plan = plan_stream(kStreamFp8, r_max, E, H, F, false, true, 0);
+        if (plan.kind != kPlanLarge)
+            launch_stream(plan, kStreamFp8, h, offsets, r_max, E, H, F, w_down, nullptr, y_perm, nullptr, dq_down, 0.f, 0.f,
+                          nullptr, nullptr, s);
         else
             launch_fp8<false>(h, offsets, r_max, E, H, F, w_down, nullptr, y_perm, dq_down, 0.f, 0.f, nullptr, s);
     }

@@ -5,19 +5,30 @@
 
 namespace moe {
 
-enum { kStreamF32 = 0, kStreamBf16 = 1, kStreamFp8 = 2 };   // operand type of launch_stream
+enum { kStreamF32 = 0, kStreamBf16 = 1, kStreamFp8 = 2 };   // operand type
+enum { kPlanLarge = 0, kPlanNarrow = 1, kPlanWide = 2 };    // 256-row tiles (another kernel), four waves, eight waves
+
+struct StreamPlan {
+    int kind;
+    int units;    // wide: blocks of 32 weight rows per workgroup
+    int splits;   // wide: parts of the contraction
+};
 
 // rows of at most 16 MiB (32-bit offsets inside a tile)
 bool stream_covers(long long K_bytes);
-// whether this product is better off here than on the 256-row-tile kernels (see the definition)
-bool stream_preferred(int r_max, int E, int N, bool swiglu);
-// -1 (default): by size; 0: only the shapes no other kernel takes; 1: always
+// The kernel for one product of r_max rows on E experts, [N, K] weights each; large_ok: the 256-row tiles cover the shape;
+// part_bytes: room for partial sums (0: the contraction is not split).  Depends on nothing but its arguments and options.
+StreamPlan plan_stream(int elt, int r_max, int E, int N, int K, bool swiglu, bool large_ok, size_t part_bytes);
+// room for partial sums that the plan wants, at most 64 MiB
+size_t stream_part_bytes(int elt, int r_max, int E, int N, int K, bool swiglu, bool large_ok);
+// -1 (default): by size; 0: only the shapes no other kernel takes; 1: always the narrow, 2: always the wide form
 void set_gemm_stream(int v);
 
 // C [rows, N] = A [rows, K] . B0[e]^T; with B1 the SwiGLU pair silu(A B0^T) * (A B1^T), and with GU (bf16) also its two
 // pre-activations, [rows, 2N].  FP8: s0, s1 dequantise the two products, s2 is the scale of the stored codes, amax
-// (may be null) receives max |h|; without B1 the output is bf16.
-void launch_stream(int elt, const void* A, const int32_t* offsets, int r_max, int E, int N, int K, const void* B0,
-                   const void* B1, void* C, void* GU, float s0, float s1, float s2, float* amax, hipStream_t s);
+// (may be null) receives max |h|; without B1 the output is bf16.  part: the room the plan was made with.
+void launch_stream(const StreamPlan& plan, int elt, const void* A, const int32_t* offsets, int r_max, int E, int N, int K,
+                   const void* B0, const void* B1, void* C, void* GU, float s0, float s1, float s2, float* amax,
+                   float* part, hipStream_t s);
 
 }  // namespace moe

@@ -10,8 +10,9 @@
 //
 //   up to 16 rows    registers as well (direct_tile): no barrier and no LDS in the loop, the waves take the blocks of
 //                    the contraction in turn;
-//   17 to 128 rows   through LDS, shared by the waves (shared_tile); with more rows than that per expert the read of
-//                    the rows outweighs the weights and the large tiles are the better kernel.
+//   17 to 128 rows   through LDS, shared by the waves (shared_tile, narrow workgroups of four waves; wide_tile, eight
+//                    waves and up to 256 weight rows); with more rows than that per expert the read of the rows
+//                    outweighs the weights and the large tiles are mostly the better kernel.
 //
 // Measured (bf16, weights of several launches so that no cache holds them; before: the large-tile kernel):
 //   down, 2 experts x 1 row, 4096 x 14336     231 us -> 36 us   (6.6 TB/s of weights)
@@ -80,6 +81,8 @@ struct StreamArgs {
     unsigned long long* ticks;   // clock sample of workgroup 0, or null
     float s0, s1, s2;
     int E, N, kbytes, ntn;
+    int units, S, r_max;   // wide kernel: 32-row units per tile, splits of the contraction; rows of a partial plane
+    float* part;           // split partial sums [S][r_max][N, or 2 N with SwiGLU], or null
 };
 
 // Where a workgroup's tile lies: FB blocks of 16 weight rows (with SwiGLU half of them gate rows and half the matching
@@ -182,6 +185,15 @@ __device__ __forceinline__ float finish_tile(const StreamArgs& p, const Tile& t,
         amax = fmaxf(amax, store_block<ELT, MODE>(p, t, n0, i, f, v, up));
     }
     return amax;
+}
+
+// one atomic per wave; h >= 0 as a float compares like its bit pattern, and *amax only grows
+__device__ __forceinline__ void fold_amax(const StreamArgs& p, float amax) {
+    if (!p.amax) return;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
+    if ((threadIdx.x & 63) == 0 && amax > __builtin_nontemporal_load(p.amax))
+        atomicMax(reinterpret_cast<int*>(p.amax), __float_as_int(amax));
 }
 
 // At most 16 rows: both operands go straight from memory to registers, the waves take the 128-byte blocks of the
@@ -393,6 +405,202 @@ __device__ __forceinline__ float shared_tile(const StreamArgs& p, const Tile& t,
     return finish_tile<ELT, MODE, FB, MF, KS>(p, t, at.n0, red);
 }
 
+// ---- wide tiles: 17 rows per expert and more ----
+// A compute unit takes in some 25 bytes per nanosecond of a stream from HBM, and the rows that pass through LDS count
+// like the weights (loads return in order), so what a workgroup reads per weight byte is what matters: eight waves and
+// up to 256 weight rows on one ring of row stages, one workgroup per compute unit.  The number of weight rows is
+// chosen per launch (units x 32) so that the tiles fill whole rounds of the compute units, and where that leaves too
+// few of them the contraction is split: the splits leave fp32 partial sums that stream_reduce_kernel adds in split
+// order.  Measured (us, the better of the narrow and the large-tile kernel / here):
+//   one expert, gate/up 20480 x 3584: 64 rows 82 / 61 (160 weight rows each on 256 workgroups), 125 rows 84 / 73
+//   the same, down: 64 rows 69 / 42 (16 splits), 250 rows 124 / 68, 500 rows 161 / 110 (4 splits)
+//   2 experts, 4096 x 14336: gate/up 64 rows 100 / 87, down 74 / 55;  8 experts, down 125 rows 240 / 216
+//   16 experts, gate/up 1408 x 2048: 64 rows 49 / 40
+constexpr int kWideWaves = 8, kWideRing = 128 * 1024;
+
+template <int ELT, int MODE, int MF>
+__device__ __forceinline__ float wide_tile(const StreamArgs& p, const Tile& t, int n, int ks, uint8_t* smem) {
+    constexpr int STAGE = MF * 16 * 128;                // bytes of one 128-byte block of the rows
+    constexpr int D = kWideRing / STAGE < 8 ? kWideRing / STAGE : 8;
+    constexpr int PA = STAGE / (kWideWaves * 1024);     // direct loads per thread and stage
+    constexpr int PER = PA + 4;                         // vector loads per thread and stage
+    static_assert(PA >= 1 && (D - 2) * PER < 64, "vmcnt holds 6 bits");
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int r = lane & 15, j = lane >> 4;
+    const uint32_t kb = (uint32_t)p.kbytes;
+    // a unit is 32 weight rows: with SwiGLU 16 gate rows and the matching up rows, else 32 rows; one unit per wave
+    const int n0 = n * p.units * (MODE != 0 ? 16 : 32);
+    const int col0 = n0 + wave * (MODE != 0 ? 16 : 32);
+    const bool idle = wave >= p.units || col0 >= p.N;
+    const uint8_t* const a0 = p.A + (size_t)t.row0 * kb;
+    const uint8_t* b_base[2];
+    uint32_t boff[2];
+    {
+        const size_t wrow = ((size_t)t.expert * p.N + (idle ? 0 : col0)) * kb;
+        b_base[0] = p.B0 + wrow;
+        b_base[1] = (MODE != 0 ? p.B1 : p.B0) + wrow;
+#pragma unroll
+        for (int f = 0; f < 2; ++f)
+            boff[f] = idle ? 0u : (uint32_t)min((MODE != 0 ? 0 : 16 * f) + r, p.N - 1 - col0) * kb + 32u * j;
+    }
+    // direct load q of a stage: unit u = q waves + wave covers rows 8 u .. + 7
+    uint32_t aoff[PA];
+#pragma unroll
+    for (int q = 0; q < PA; ++q) {
+        const int row = 8 * (q * kWideWaves + wave) + (lane >> 3);
+        aoff[q] = (uint32_t)min(row, t.rows - 1) * kb + 16u * ((lane & 7) ^ lds_swizzle(row));
+    }
+    f32x4 acc[MF][2];
+#pragma unroll
+    for (int i = 0; i < MF; ++i)
+#pragma unroll
+        for (int f = 0; f < 2; ++f) acc[i][f] = f32x4{0.f, 0.f, 0.f, 0.f};
+    Piece fb[D][2];
+    const int nfull = p.kbytes / 128;
+    const int st0 = (int)((long long)nfull * ks / p.S), nst = (int)((long long)nfull * (ks + 1) / p.S) - st0;
+    Tile tn = t;
+    tn.ntile = n;
+    const int rot = rotation(tn, nst);
+    auto issue = [&](int slot, int s) {
+        // past the last stage: one line again and again, never used (the waits count loads)
+        const bool over = s >= nst;
+        const int sr = s + rot >= nst ? s + rot - nst : s + rot;
+        const uint32_t k = over ? 0u : (uint32_t)(st0 + sr) * 128u;
+        const uint32_t mask = over ? 0u : ~0u;
+#pragma unroll
+        for (int q = 0; q < PA; ++q)
+            __builtin_amdgcn_global_load_lds(
+                (const __attribute__((address_space(1))) void*)(a0 + k + (aoff[q] & mask)),
+                (__attribute__((address_space(3))) void*)(smem + slot * STAGE + (q * kWideWaves + wave) * 1024), 16, 0, 0);
+        const bool none = over || idle;
+        const uint32_t bmask = none ? 0u : ~0u;
+#pragma unroll
+        for (int f = 0; f < 2; ++f) {
+            const uint8_t* b = (none ? a0 : b_base[f] + k) + (boff[f] & bmask);
+            fb[slot][f].lo = ld16(b);
+            fb[slot][f].hi = ld16(b + 16);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    const int sw = lds_swizzle(r);   // blocks of 16 rows: the swizzle of row 16 i + r
+    const uint8_t* const arow = smem + r * 128;
+    const int c_lo = ((2 * j) ^ sw) * 16, c_hi = ((2 * j + 1) ^ sw) * 16;
+    auto use = [&](int slot) {
+#pragma unroll
+        for (int i = 0; i < MF; ++i) {
+            Piece a;
+            a.lo = *reinterpret_cast<const u32x4*>(arow + slot * STAGE + i * 2048 + c_lo);
+            a.hi = *reinterpret_cast<const u32x4*>(arow + slot * STAGE + i * 2048 + c_hi);
+#pragma unroll
+            for (int f = 0; f < 2; ++f) acc[i][f] = mul_step<ELT>(fb[slot][f], a, acc[i][f]);
+        }
+    };
+    if (nst > 0) {
+#pragma unroll
+        for (int d = 0; d < D - 1; ++d) issue(d, d);
+        for (int s0 = 0; s0 < nst; s0 += D) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                // this wave's loads of the stage have landed and its reads of the stage before are in registers
+                constexpr int W = (D - 2) * PER;
+                __builtin_amdgcn_s_waitcnt((W & 0xF) | ((W >> 4) << 14) | 0x70);
+                __builtin_amdgcn_s_barrier();
+                __builtin_amdgcn_sched_barrier(0);
+                issue((d + D - 1) % D, s0 + d + D - 1);
+                if (s0 + d < nst && !idle) use(d);
+                __builtin_amdgcn_sched_barrier(0);
+            }
+        }
+    }
+    // the partial block at the end of the rows: straight from memory, by the last split
+    const int rem = p.kbytes & 127;
+    if (rem && ks == p.S - 1 && !idle) {
+#pragma unroll
+        for (int f = 0; f < 2; ++f) fb[0][f] = tail_piece(b_base[f] + 128 * nfull + (boff[f] - 32u * j), j, rem);
+#pragma unroll
+        for (int i = 0; i < MF; ++i) {
+            const Piece a = tail_piece(a0 + 128 * nfull + (size_t)((uint32_t)min(16 * i + r, t.rows - 1) * kb), j, rem);
+#pragma unroll
+            for (int f = 0; f < 2; ++f) acc[i][f] = mul_step<ELT>(fb[0][f], a, acc[i][f]);
+        }
+    }
+    __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0), lgkmcnt(0): nothing lands in the ring any more
+    if (idle) return 0.f;
+    if (p.part) {
+        const int cols = MODE != 0 ? 2 * p.N : p.N;
+        float* const plane = p.part + (size_t)ks * p.r_max * cols;
+#pragma unroll
+        for (int i = 0; i < MF; ++i) {
+            const int m = 16 * i + r;
+            if (m >= t.rows) break;
+#pragma unroll
+            for (int f = 0; f < 2; ++f) {
+                const int c = col0 + (MODE != 0 ? 0 : 16 * f) + 4 * j;
+                if (c < p.N) *reinterpret_cast<f32x4*>(plane + (size_t)(t.row0 + m) * cols + (MODE != 0 ? f * p.N : 0) + c) = acc[i][f];
+            }
+        }
+        return 0.f;
+    }
+    float amax = 0.f;
+#pragma unroll
+    for (int i = 0; i < MF; ++i) {
+        if (16 * i >= t.rows) break;
+        if constexpr (MODE != 0)
+            amax = fmaxf(amax, store_block<ELT, MODE>(p, t, col0, i, 0, acc[i][0], acc[i][1]));
+        else
+#pragma unroll
+            for (int f = 0; f < 2; ++f) store_block<ELT, MODE>(p, t, col0, i, f, acc[i][f], acc[i][f]);
+    }
+    return amax;
+}
+
+template <int ELT, int MODE>
+__global__ __launch_bounds__(kWideWaves * 64, 2) void gemm_wide_kernel(const StreamArgs p) {
+    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+    const Tile t = find_tile<128>(p.offsets, p.E, p.ntn * p.S, reinterpret_cast<int*>(smem + kWideRing));
+    if (!t.valid) return;
+    const int n = t.ntile / p.S, ks = t.ntile - n * p.S;
+    const bool sample = ELT == kEltBf16 && p.ticks != nullptr && blockIdx.x == 0;
+    unsigned long long tk_entry = 0, rt_entry = 0;
+    if (sample) {
+        tk_entry = __builtin_amdgcn_s_memtime();
+        rt_entry = __builtin_amdgcn_s_memrealtime();
+    }
+    const float amax = t.rows <= 64 ? wide_tile<ELT, MODE, 4>(p, t, n, ks, smem) : wide_tile<ELT, MODE, 8>(p, t, n, ks, smem);
+    if (sample && threadIdx.x == 0) {
+        p.ticks[0] = __builtin_amdgcn_s_memtime() - tk_entry;
+        p.ticks[1] = __builtin_amdgcn_s_memrealtime() - rt_entry;
+    }
+    if constexpr (ELT == kEltFp8 && MODE == 1) fold_amax(p, amax);
+}
+
+// The sums of the S partial planes, in split order, through the epilogue.  One thread per four columns of a row.
+template <int MODE>
+__global__ __launch_bounds__(256) void stream_reduce_kernel(const float* __restrict__ part, const int32_t* __restrict__ offsets,
+                                                            int E, int S, int r_max, int N, bf16_t* __restrict__ C) {
+    const int q = N / 4, cols = MODE != 0 ? 2 * N : N;
+    const long long total = (long long)offsets[E] * q;
+    for (long long i = blockIdx.x * 256ll + threadIdx.x; i < total; i += gridDim.x * 256ll) {
+        const int row = (int)(i / q), c = (int)(i - (long long)row * q) * 4;
+        const float* src = part + (size_t)row * cols + c;
+        f32x4 v = *reinterpret_cast<const f32x4*>(src);
+        f32x4 up = v;
+        if (MODE != 0) up = *reinterpret_cast<const f32x4*>(src + N);
+#pragma unroll 4
+        for (int s = 1; s < S; ++s) {
+            src += (size_t)r_max * cols;
+            v += *reinterpret_cast<const f32x4*>(src);
+            if (MODE != 0) up += *reinterpret_cast<const f32x4*>(src + N);
+        }
+        if (MODE != 0)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) v[k] = v[k] * __builtin_amdgcn_rcpf(1.f + __expf(-v[k])) * up[k];
+        const u32x2 o = {pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3])};
+        *reinterpret_cast<u32x2*>(C + (size_t)row * N + c) = o;
+    }
+}
+
 template <int FB> constexpr int tile_rows() { return FB == 1 ? 64 : 128; }
 template <int FB> constexpr int blocks_per_wave() { return FB == 8 ? 2 : 1; }
 // LDS of a workgroup: the ring of shared_tile (two workgroups per compute unit; one where the waves share the
@@ -430,15 +638,7 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(const StreamArgs p)
         p.ticks[0] = __builtin_amdgcn_s_memtime() - tk_entry;
         p.ticks[1] = __builtin_amdgcn_s_memrealtime() - rt_entry;
     }
-    if constexpr (ELT == kEltFp8 && MODE == 1) {
-        // one atomic per wave; h >= 0 as a float compares like its bit pattern, and *amax only grows
-        if (p.amax) {
-#pragma unroll
-            for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
-            if ((threadIdx.x & 63) == 0 && amax > __builtin_nontemporal_load(p.amax))
-                atomicMax(reinterpret_cast<int*>(p.amax), __float_as_int(amax));
-        }
-    }
+    if constexpr (ELT == kEltFp8 && MODE == 1) fold_amax(p, amax);
 }
 
 template <int ELT, int MODE, int FB, bool DIRECT>
@@ -455,39 +655,142 @@ void launch(StreamArgs p, int r_max, hipStream_t s) {
     hipLaunchKernelGGL(kern, dim3(grid_for(r_max, p.E, tile_rows<FB>(), p.ntn)), dim3(256), smem, s, p);
 }
 
-// Weight blocks per workgroup: as many as leave enough workgroups.  A wider workgroup reads the rows less often and
-// keeps more weight bytes in flight, but 256 compute units want work.  Measured (us, blocks 8 / 4 / 2 / 1):
+// Weight blocks of a narrow workgroup: as many as leave enough workgroups.  A wider workgroup reads the rows less often
+// and keeps more weight bytes in flight, but 256 compute units want work.  Measured (us, blocks 8 / 4 / 2 / 1):
 //   down 4096 x 14336, 8 experts x 8 rows    182 / 166 / 172 / 209   (256 / 512 / 1024 / 2048 workgroups)
 //   the same, 2 experts x 1 row                - /  57 /  36 /  39   ( 64 / 128 /  256 /  512)
 //   the same, 8 experts x 64 rows            206 / 242 / 328 / 538
 //   down 3584 x 20480, one expert x 64 rows  207 / 116 /  83 /  66   ( 28 /  56 /  112 /  224)
 //   the same, 500 rows                       237 / 159 / 230 / 408   (112 / 224 /  448 / 1792)
 //   gate/up 2560 x 3584, 64 experts x 8 rows 385 / 392 / 537 /  -
-template <int ELT, int MODE>
-void launch_any(const StreamArgs& p, int r_max, hipStream_t s) {
-    const int experts = p.E < r_max ? p.E : r_max;
+int narrow_blocks(int r_max, int E, int N, bool swiglu) {
+    const int experts = E < r_max ? E : r_max;
     const bool few = (long long)r_max <= 16ll * experts;   // up to 16 rows per expert on average
     const long long mt = r_max / 128 + experts;            // M-tiles, at most
-    auto groups = [&](int fb) { const int bn = 16 * (MODE != 0 ? fb / 2 : fb); return mt * ((p.N + bn - 1) / bn); };
-    if (r_max <= 16) {
-        if (groups(4) >= 400)
-            launch<ELT, MODE, 4, true>(p, r_max, s);
-        else
-            launch<ELT, MODE, 2, true>(p, r_max, s);
-        return;
-    }
+    auto groups = [&](int fb) { const int bn = 16 * (swiglu ? fb / 2 : fb); return mt * ((N + bn - 1) / bn); };
+    if (r_max <= 16) return groups(4) >= 400 ? 4 : 2;
     const long long want = few ? 400 : 200;
-    if (groups(8) >= want)
-        launch<ELT, MODE, 8, false>(p, r_max, s);
-    else if (groups(4) >= want)
-        launch<ELT, MODE, 4, false>(p, r_max, s);
-    else if (MODE != 0 || groups(2) >= want)
-        launch<ELT, MODE, 2, false>(p, r_max, s);
-    else
-        launch<ELT, MODE, MODE != 0 ? 2 : 1, false>(p, r_max, s);
+    return groups(8) >= want ? 8 : groups(4) >= want ? 4 : swiglu || groups(2) >= want ? 2 : 1;
 }
 
-int g_stream = -1;   // -1: by size; 0: only where no other kernel takes the shape; 1: always
+template <int ELT, int MODE>
+void launch_narrow(const StreamArgs& p, int r_max, hipStream_t s) {
+    const int fb = narrow_blocks(r_max, p.E, p.N, MODE != 0);
+    if (r_max <= 16) {
+        if (fb == 4) launch<ELT, MODE, 4, true>(p, r_max, s);
+        else launch<ELT, MODE, 2, true>(p, r_max, s);
+    } else if (fb == 8) {
+        launch<ELT, MODE, 8, false>(p, r_max, s);
+    } else if (fb == 4) {
+        launch<ELT, MODE, 4, false>(p, r_max, s);
+    } else {
+        if (MODE != 0 || fb == 2) launch<ELT, MODE, 2, false>(p, r_max, s);
+        else launch<ELT, MODE, MODE != 0 ? 2 : 1, false>(p, r_max, s);
+    }
+}
+
+template <int ELT, int MODE>
+void launch_wide(StreamArgs p, int r_max, const StreamPlan& plan, float* part, hipStream_t s) {
+    constexpr int smem = kWideRing + (kMaxExperts + 2) * 4;
+    const int bn = plan.units * (MODE != 0 ? 16 : 32);
+    p.units = plan.units;
+    p.S = plan.splits;
+    p.part = plan.splits > 1 ? part : nullptr;
+    p.ntn = (p.N + bn - 1) / bn;
+    auto kern = gemm_wide_kernel<ELT, MODE>;
+    static bool attr_set = false;
+    if (!attr_set) {
+        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
+        attr_set = true;
+    }
+    hipLaunchKernelGGL(kern, dim3(grid_for(r_max, p.E, 128, p.ntn * p.S)), dim3(kWideWaves * 64), smem, s, p);
+    if constexpr (ELT == kEltBf16 && MODE != 2) {
+        if (p.S > 1) {
+            const long long groups = ((long long)r_max * p.N / 4 + 255) / 256;
+            hipLaunchKernelGGL((stream_reduce_kernel<MODE>), dim3((int)(groups < 2048 ? groups : 2048)), dim3(256), 0, s, part,
+                               p.offsets, p.E, p.S, r_max, p.N, static_cast<bf16_t*>(p.C));
+        }
+    }
+}
+
+template <int ELT, int MODE>
+void launch_any(const StreamArgs& p, int r_max, const StreamPlan& plan, float* part, hipStream_t s) {
+    if constexpr (ELT != kEltF32) {
+        if (plan.kind == kPlanWide) {
+            launch_wide<ELT, MODE>(p, r_max, plan, part, s);
+            return;
+        }
+    }
+    launch_narrow<ELT, MODE>(p, r_max, s);
+}
+
+int g_stream = -1;   // -1: by size; 0: large tiles where they cover the shape; 1: narrow; 2: wide
+
+// ---- which kernel: estimated times (us) of the three ----
+// Fitted to measurements of gate/up and down at (E, H, F) = (1, 3584, 20480), (1, 2 and 8, 4096, 14336), (64, 3584, 2560),
+// (16, 2048, 1408) and (8, 2048, 4096) with 1 to 2000 rows per expert; the kernel they pick is within 6 % of the
+// best of the three at all but a few of those 130 points.
+//   A round of workgroups takes (bytes of its weight rows) x 43 us/MB (36 where several M-tiles share them), plus its
+//   rows at a smaller rate, plus its start and end, which the narrow workgroups, two to a compute unit, mostly hide.
+//   A k-tile of the large tiles takes 1.1 us alone, 1.5 us with all compute units at work (1.9 where the rows lie a
+//   multiple of 4096 bytes apart), 2 us where 256 rows per expert make it both a stream and a full product.
+struct Work {
+    int experts, rows, N, kbytes, r_max;
+    bool swiglu;
+};
+constexpr int kUnitsCU = 256;   // compute units the estimates are made for
+
+int blocks_of(int a, int b) { return (a + b - 1) / b; }
+
+// M-tiles of all experts.  With equal experts that would be ceil(rows / height) each; a skewed router makes up to
+// r_max / height more.  Half of those are counted where an expert with three times the average rows would need a second
+// tile (less down to a third): a plan must not spill into another round for a tile or two (8 experts x 3264 x 1984, 618
+// rows of a Zipf-1.2 router: the layer took 148 us with equal experts assumed and takes 125).
+double skew_share(const Work& w, int height) {
+    const double near = 3.0 * w.rows / height - 1.0;
+    return w.experts == 1 || w.rows <= 16 || near < 0.0 ? 0.0 : near > 1.0 ? 1.0 : near;
+}
+double m_tiles(const Work& w, int height) {
+    const double even = (double)w.experts * blocks_of(w.rows, height), most = w.experts + (double)w.r_max / height;
+    return most > even ? even + 0.5 * skew_share(w, height) * (most - even) : even;
+}
+double rounds_of(double tiles) { return (double)(long long)((tiles + kUnitsCU - 1) / kUnitsCU); }
+
+double large_us(const Work& w) {
+    const int mt = blocks_of(w.rows, 256);
+    const double tiles = m_tiles(w, 256) * blocks_of(w.N, w.swiglu ? 128 : 256);
+    const double rounds = rounds_of(tiles), fill = tiles / (rounds * kUnitsCU);
+    const double part = (w.rows < 256 ? w.rows : 256) / 256.0;
+    const double stream = w.kbytes % 4096 == 0 ? 0.8 : 0.42;
+    const double per = mt > 1 ? 1.05 + 0.5 * fill : 1.08 + fill * (stream + 0.55 * part * part);
+    return 4.0 + rounds * (w.kbytes / 128) * per;
+}
+
+double narrow_us(const Work& w, int fb) {
+    const int tr = fb == 1 ? 64 : 128, mt = blocks_of(w.rows, tr);
+    const int nt = blocks_of(w.N, 16 * (w.swiglu ? fb / 2 : fb));
+    const double tiles = m_tiles(w, tr) * nt, even_tiles = (double)mt * w.experts * nt;
+    // a second workgroup on a compute unit adds less than a round while the weights are what is waited for
+    const double whole = rounds_of(tiles), over = tiles / kUnitsCU - (whole - 1.0);
+    const double q = whole <= 1.0 || mt > 1 || over > 0.6 ? whole : whole - 0.6;
+    const bool direct = w.rows <= 16;
+    const int rows = w.rows < tr ? w.rows : tr;
+    const double weight = direct ? 41e-6 : mt > 1 ? 36e-6 : 43e-6;
+    const double risk = whole > 1.0 && even_tiles <= kUnitsCU ? 1.1 : 1.0;   // a skewed router would cost a round
+    return risk * q * w.kbytes * (16 * fb * weight + rows * (direct ? 8e-6 : 18e-6)) + (direct ? 2.0 : 3.0) * (long long)((whole + 1) / 2);
+}
+
+double wide_us(const Work& w, int units, int S) {
+    const int mt = blocks_of(w.rows, 128);
+    const double tiles = m_tiles(w, 128) * blocks_of(w.N, units * (w.swiglu ? 16 : 32)) * S;
+    const int rows = w.rows < 128 ? w.rows : 128;
+    const double round = w.kbytes / (double)S * (32 * units * (mt > 1 ? 36e-6 : 43e-6) + rows * (rows <= 64 ? 5e-6 : 12e-6)) + 10.0;
+    const double reduce = S > 1 ? 4.0 + (double)S * w.r_max * w.N * (w.swiglu ? 16.0 : 8.0) / 4.5e6 : 0.0;
+    // one workgroup to a compute unit: a tile too many costs a round, so a plan for skewed experts keeps some slack
+    return rounds_of(tiles * (1.0 + 0.12 * skew_share(w, 128))) * round + reduce;
+}
+
+constexpr size_t kMaxPartBytes = 64u << 20;   // partial planes of one product, at most
 
 }  // namespace
 
@@ -495,21 +798,52 @@ void set_gemm_stream(int v) { g_stream = v; }
 
 bool stream_covers(long long K_bytes) { return K_bytes <= (1 << 24); }
 
-// Against the 256-row tiles (us, large tiles / here): gate/up 2560 x 3584 on 64 experts with 8 rows each 420 / 385, with
-// 16 rows 438 / 410, with 31 rows 427 / 433, with 62 rows 440 / 490; down there 234 / 206, 238 / 231, 239 / 255, 252 /
-// 284: the line lies at 24 rows per expert.  With more rows than that the large tiles lose only where they are too few
-// to occupy the compute units (down 3584 x 20480 for one expert's 500 rows, 28 tiles: 356 / 159).
-bool stream_preferred(int r_max, int E, int N, bool swiglu) {
-    if (g_stream >= 0) return g_stream != 0;
-    if (persist_grid_overridden()) return false;
-    const int experts = E < r_max ? E : r_max;
-    if ((long long)r_max <= 24ll * experts) return true;
-    const int outn = swiglu ? 128 : 256;
-    return (long long)(r_max / 256 + experts) * ((N + outn - 1) / outn) <= 128;
+StreamPlan plan_stream(int elt, int r_max, int E, int N, int K, bool swiglu, bool large_ok, size_t part_bytes) {
+    StreamPlan plan = {kPlanNarrow, 0, 1};
+    if (r_max <= 0) return plan;
+    Work w;
+    w.experts = E < r_max ? E : r_max;
+    w.rows = (r_max + w.experts - 1) / w.experts;
+    w.N = N;
+    const long long kbytes = (long long)K * (elt == kEltF32 ? 4 : elt == kEltBf16 ? 2 : 1);
+    if (large_ok && (g_stream == 0 || (g_stream < 0 && persist_grid_overridden()) || !stream_covers(kbytes))) {
+        plan.kind = kPlanLarge;
+        return plan;
+    }
+    if (elt == kEltF32 || g_stream == 1 || !stream_covers(kbytes)) return plan;
+    w.kbytes = (int)kbytes;
+    w.r_max = r_max;
+    w.swiglu = swiglu;
+    double best = g_stream == 2 ? 1e30 : narrow_us(w, narrow_blocks(r_max, E, N, swiglu));
+    if (g_stream < 0 && large_ok && large_us(w) < best) {
+        best = large_us(w);
+        plan.kind = kPlanLarge;
+    }
+    for (int units = 8; units >= 3; --units)
+        for (int S = 1; S <= 16; S *= 2) {
+            // a split leaves at least 16 blocks of the contraction to a workgroup
+            if (S > 1 && (elt != kEltBf16 || w.kbytes / 128 < 16 * S ||
+                          (size_t)S * r_max * N * (swiglu ? 8 : 4) > part_bytes))
+                break;
+            const double t = wide_us(w, units, S);
+            if (t < best) {
+                best = t;
+                plan.kind = kPlanWide;
+                plan.units = units;
+                plan.splits = S;
+            }
+        }
+    return plan;
 }
 
-void launch_stream(int elt, const void* A, const int32_t* offsets, int r_max, int E, int N, int K, const void* B0,
-                   const void* B1, void* C, void* GU, float s0, float s1, float s2, float* amax, hipStream_t s) {
+size_t stream_part_bytes(int elt, int r_max, int E, int N, int K, bool swiglu, bool large_ok) {
+    const StreamPlan plan = plan_stream(elt, r_max, E, N, K, swiglu, large_ok, kMaxPartBytes);
+    return plan.splits > 1 ? (size_t)plan.splits * r_max * N * (swiglu ? 8 : 4) : 0;
+}
+
+void launch_stream(const StreamPlan& plan, int elt, const void* A, const int32_t* offsets, int r_max, int E, int N, int K,
+                   const void* B0, const void* B1, void* C, void* GU, float s0, float s1, float s2, float* amax,
+                   float* part, hipStream_t s) {
     StreamArgs p;
     p.A = static_cast<const uint8_t*>(A);
     p.offsets = offsets;
@@ -521,15 +855,16 @@ void launch_stream(int elt, const void* A, const int32_t* offsets, int r_max, in
     p.ticks = persist_clock_sample();
     p.s0 = s0; p.s1 = s1; p.s2 = s2;
     p.E = E; p.N = N; p.ntn = 0;
+    p.units = 0; p.S = 1; p.r_max = r_max; p.part = nullptr;
     p.kbytes = K * (elt == kEltF32 ? 4 : elt == kEltBf16 ? 2 : 1);
     if (elt == kEltF32) {
-        if (B1) launch_any<kEltF32, 1>(p, r_max, s); else launch_any<kEltF32, 0>(p, r_max, s);
+        if (B1) launch_any<kEltF32, 1>(p, r_max, plan, part, s); else launch_any<kEltF32, 0>(p, r_max, plan, part, s);
     } else if (elt == kEltBf16) {
-        if (GU) launch_any<kEltBf16, 2>(p, r_max, s);
-        else if (B1) launch_any<kEltBf16, 1>(p, r_max, s);
-        else launch_any<kEltBf16, 0>(p, r_max, s);
+        if (GU) launch_any<kEltBf16, 2>(p, r_max, plan, part, s);
+        else if (B1) launch_any<kEltBf16, 1>(p, r_max, plan, part, s);
+        else launch_any<kEltBf16, 0>(p, r_max, plan, part, s);
     } else {
-        if (B1) launch_any<kEltFp8, 1>(p, r_max, s); else launch_any<kEltFp8, 0>(p, r_max, s);
+        if (B1) launch_any<kEltFp8, 1>(p, r_max, plan, part, s); else launch_any<kEltFp8, 0>(p, r_max, plan, part, s);
     }
 }
 

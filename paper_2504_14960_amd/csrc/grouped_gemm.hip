@@ -123,18 +123,24 @@ void launch_simple_gemm(const void* A, const int32_t* offsets, int r_max, int E,
 
 }  // namespace
 
+// whether the MFMA kernels with 256-row tiles take the layer
+static bool large_covers(moe_dtype_t dt, int H, int F) { return dt == MOE_BF16 && H % 64 == 0 && F % 64 == 0; }
+
+size_t expert_ffn_part_bytes(int r_max, int H, int F, int E, moe_dtype_t dt) {
+    if (dt == MOE_F32) return 0;
+    const bool large = large_covers(dt, H, F);
+    const size_t a = stream_part_bytes(kStreamBf16, r_max, E, F, H, true, large);
+    const size_t b = stream_part_bytes(kStreamBf16, r_max, E, H, F, false, large);
+    return a > b ? a : b;
+}
+
 bool launch_expert_ffn(const void* x_perm, const int32_t* offsets, int r_max, int H, int F, int E,
                        const void* w_gate, const void* w_up, const void* w_down, moe_dtype_t dt,
-                       void* h, void* y_perm, int variant, int phase, hipStream_t s) {
+                       void* h, void* y_perm, int variant, int phase, void* part, size_t part_bytes, hipStream_t s) {
     const bool f32 = dt == MOE_F32;
-    // shapes without a large-tile kernel go to the weight-streaming one, whatever their size
-    const bool fast = !f32 && (H % 64 == 0) && (F % 64 == 0);
+    const bool large = large_covers(dt, H, F);
     const int elt = f32 ? kStreamF32 : kStreamBf16;
-    auto stream = [&](int ph) {
-        if (ph & 1) launch_stream(elt, x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, nullptr, 0.f, 0.f, 0.f, nullptr, s);
-        if (ph & 2) launch_stream(elt, h, offsets, r_max, E, H, F, w_down, nullptr, y_perm, nullptr, 0.f, 0.f, 0.f, nullptr, s);
-    };
-    if (variant == 99 || (!fast && !stream_covers((H > F ? H : F) * (f32 ? 4ll : 2ll)))) {
+    if (variant == 99 || (!large && !stream_covers((H > F ? H : F) * (f32 ? 4ll : 2ll)))) {
         if (f32) {
             if (phase & 1) launch_simple_gemm<float, true>(x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, s);
             if (phase & 2) launch_simple_gemm<float, false>(h, offsets, r_max, E, H, F, w_down, nullptr, y_perm, s);
@@ -144,20 +150,20 @@ bool launch_expert_ffn(const void* x_perm, const int32_t* offsets, int r_max, in
         }
         return true;
     }
-    if (!fast) {
-        stream(phase);
-        return true;
-    }
-    if (variant == 0) {
-        // Tuned default, phase by phase (the second product reads what the first wrote): few rows per expert go to the
-        // streaming kernel, the rest to the persistent 8-wave kernel with three LDS stages for the weight tile, and
-        // layers too shallow for its k stream to the one-workgroup-per-tile kernels (8 waves gate/up, 4 waves down).
+    if (variant == 0 || !large) {
+        // Tuned default, phase by phase (the second product reads what the first wrote): few rows per expert, and shapes
+        // without a large-tile kernel, go to the streaming kernel, the rest to the persistent 8-wave kernel with three
+        // LDS stages for the weight tile, and layers too shallow for its k stream to the one-workgroup-per-tile kernels
+        // (8 waves gate/up, 4 waves down).
         bool ok = true;
         for (int ph = 1; ph <= 2; ph <<= 1) {
             if (!(phase & ph)) continue;
             const int N = ph == 1 ? F : H, K = ph == 1 ? H : F;
-            if (stream_covers(K * 2ll) && stream_preferred(r_max, E, N, ph == 1))
-                stream(ph);
+            const StreamPlan plan = plan_stream(elt, r_max, E, N, K, ph == 1, large, part_bytes);
+            if (plan.kind != kPlanLarge)
+                launch_stream(plan, elt, ph == 1 ? x_perm : h, offsets, r_max, E, N, K, ph == 1 ? w_gate : w_down,
+                              ph == 1 ? w_up : nullptr, ph == 1 ? h : y_perm, nullptr, 0.f, 0.f, 0.f, nullptr,
+                              static_cast<float*>(part), s);
             else if (!launch_persist_ffn(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, 43, ph, s))
                 ok = ok && launch_pipe3_ffn(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm,
                                             ph == 1 ? 31 : 30, ph, s);

@@ -1,0 +1,82 @@
+"""The wide form of the weight-streaming expert kernel: row counts on both sides of its tile forms, partial blocks of the
+contraction, every number of weight rows per workgroup, and the contraction split over workgroups."""
+import numpy as np
+import pytest
+
+from moe_inputs import get_config, make_layer_inputs
+from helpers import assert_close, guard_margins, to_dev, to_host, values
+from test_gpu_experts import _case as bf16_case, _run as bf16_run
+from test_gpu_fp8 import _case as fp8_case, _check_h_codes, _run as fp8_run
+from test_gpu_layer import oracle_layer
+from test_gpu_stream import EDGES
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(autouse=True)
+def _always_wide():
+    import paper_2504_14960_amd as moe
+    moe.set_option("gemm_stream", 2)
+    yield
+    moe.set_option("gemm_stream", -1)
+
+
+@pytest.mark.parametrize("H,F,counts", [
+    (64, 64, EDGES),               # one whole block of the contraction; fewer columns than a workgroup's
+    (8, 16, EDGES),                # no whole block at all
+    (136, 1416, EDGES),            # remainders on both axes
+    (3000, 72, EDGES),             # the other way round
+    (1088, 640, [40, 3]),          # a contraction that is not a multiple of the ring's stages
+    (256, 20480, [65]),            # one round of workgroups of 160 weight rows
+    (14336, 256, [5, 90, 7]),
+])
+def test_wide_against_the_oracle(H, F, counts):
+    inp, x_perm, offsets, h_ref, y_ref = bf16_case(H=H, F=F, E=len(counts), counts=counts, bf16=True, seed=7300 + H, r_pad=5)
+    R = int(offsets[-1])
+    h, y = bf16_run(x_perm, offsets, inp, 0, r_max=R + 5)
+    assert_close(h[:R], h_ref, True, "h")
+    assert_close(y[:R], y_ref, True, "y_perm")
+    assert not h[R:].any() and not y[R:].any()     # rows past the last expert stay untouched
+
+
+@pytest.mark.parametrize("H,F,counts", [(256, 1408, EDGES), (1536, 256, EDGES), (512, 768, [1, 0, 3, 12])])
+def test_wide_fp8_against_the_oracle(H, F, counts):
+    c = fp8_case(seed=7500 + H, H=H, F=F, E=len(counts), counts=counts)
+    h, y, amax = fp8_run(c, r_pad=5)
+    R = c["R"]
+    _check_h_codes(h[:R], c["ref"].hq, "h codes")
+    assert abs(amax - c["ref"].amax_h) <= 1e-5 * c["ref"].amax_h
+    assert_close(y[:R], c["ref"].y, True, "y_perm")
+    assert not h[R:].any() and not y[R:].any()
+
+
+@pytest.mark.parametrize("T,H,F,Fs,E,K", [
+    (40, 512, 128, 4096, 4, 2),        # the shared expert's down projection is split
+    (150, 2560, 64, 1024, 6, 2),       # both of its products; two M-tiles
+    (20, 2048, 2048, 0, 2, 1),         # the routed experts'
+])
+def test_split_contraction_in_the_layer(T, H, F, Fs, E, K):
+    """With the workspace that is asked for, and with one too small for the partial sums: both are the oracle's layer."""
+    import torch
+    import paper_2504_14960_amd as moe
+    cfg = get_config("qwen2_57b_a14b").scaled(T=T, H=H, F=F, E=E, K=K, shared_F=Fs, seed=7700 + T)
+    inp = make_layer_inputs(cfg)
+    guard_margins(inp, K)
+    want = oracle_layer(inp, 0)
+    d = {k: to_dev(v) for k, v in inp.tensors.items()}
+    bias = None if inp.bias is None else to_dev(inp.bias)
+    nbytes = moe.layer_workspace_bytes(T, H, E, K, F, Fs, 0, moe.MOE_BF16)
+    lay = moe.layer_workspace_layout(T, H, E, K, F, Fs, 0, moe.MOE_BF16)
+    end = (max(lay.values()) + (T * H * 2 if Fs else 0) + 255) // 256 * 256
+    assert nbytes > end, "the shape is meant to want partial sums"
+    out = []
+    for size in (nbytes, end):
+        ws = torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda")      # NaN patterns: nothing unwritten is added
+        y = torch.empty_like(d["x"])
+        moe.layer_forward(d["x"], d["w_router"], bias, d["w_gate"], d["w_up"], d["w_down"], d.get("ws_gate"),
+                          d.get("ws_up"), d.get("ws_down"), K, cfg.renormalize, 0, y, ws)
+        torch.cuda.synchronize()
+        out.append(values(to_host(y)))
+        assert_close(to_host(y), want.y, True, f"y ({size} bytes)")
+    # the same products with their sums in another order: half a unit in the last place of bf16 here and there
+    assert np.linalg.norm(out[0] - out[1]) <= 2e-3 * np.linalg.norm(out[0])
