@@ -14,61 +14,77 @@
 //                              weight-gradient GEMMs contract over whole k-tiles
 //   swiglu_backward_kernel     (dh, g, u) -> dg | du side by side
 //
-// All bf16, 64 x 64 tiles through LDS for the transposes.
+// All bf16, 128 x 128 tiles through LDS for the transposes.
 #include "common.h"
 
 namespace moe {
 
 namespace {
 
-constexpr int TT = 64;  // transpose tile
+// ---- 128 x 128 transposes ----
+// Bound by HBM: every byte is read once and written once.  Rows of 256 bytes on both sides (64 x 64 tiles, 128 bytes,
+// ran at 5.0 TB/s, these at 5.2, the rate of a plain copy), all eight loads of a thread in flight, and 32-bit LDS traffic: a thread takes the same eight
+// columns of two adjacent rows, so that a dword of the transposed tile is one of its element pairs, and the tile
+// [column][row pair] is read back 16 bytes at a time.  Group g of four dwords of column c lies at g ^ (c / 8): the 64
+// dwords a wave writes at a time then fall into 64 different banks, and a read covers whole 256-byte rows.
+constexpr int TT = 128, TP = TT / 2;   // tile; row pairs
 
-// Load a TT x TT tile of 16-bit elements (rows r0.., cols c0..) into LDS, rows
-// beyond `rows` / cols beyond `cols` as zero.  256 threads: 8 lanes x 16 bytes
-// per row, 32 rows per pass.
-__device__ __forceinline__ void load_tile(const uint16_t* __restrict__ src, size_t ld, int r0, int c0, int rows,
-                                          int cols, uint16_t (*tile)[TT + 2]) {
-    const int tid = threadIdx.x;
+struct TransposeRows {   // where a half of the tile's rows (64 positions) comes from
+    int first, valid;    // first source row; how many of the 64 exist, the rest count as zeros
+};
+
+// The transposed tile of columns c0 .. c0 + 127 (below `cols`) of two times 64 rows of `src`.
+__device__ __forceinline__ void load_tile(const uint16_t* __restrict__ src, size_t ld, int c0, int cols,
+                                          const TransposeRows (&half)[2], uint32_t (*tile)[TP]) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int cv = lane & 15, c = cv * 8;
+    u32x4 v[4][2];
 #pragma unroll
-    for (int p = 0; p < 2; ++p) {
-        const int r = p * 32 + tid / 8, c = (tid % 8) * 8;
-        u32x4 v = u32x4{0u, 0u, 0u, 0u};
-        if (r0 + r < rows && c0 + c < cols)   // cols is a multiple of 8
-            v = *reinterpret_cast<const u32x4*>(src + (size_t)(r0 + r) * ld + c0 + c);
+    for (int p = 0; p < 4; ++p) {
+        const int r = 2 * (4 * (4 * p + wave) + (lane >> 4));   // even row of the pair
+        const TransposeRows h = half[p / 2];
+#pragma unroll
+        for (int k = 0; k < 2; ++k) {
+            const int rr = (r & 63) + k;
+            v[p][k] = u32x4{0u, 0u, 0u, 0u};
+            if (rr < h.valid && c0 + c < cols)   // cols is a multiple of 8
+                v[p][k] = *reinterpret_cast<const u32x4*>(src + (size_t)(h.first + rr) * ld + c0 + c);
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < 4; ++p) {
+        const int at = (4 * ((4 * p + wave) ^ cv)) + (lane >> 4);
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            tile[r][c + 2 * j] = (uint16_t)(v[j] & 0xffffu);
-            tile[r][c + 2 * j + 1] = (uint16_t)(v[j] >> 16);
+            tile[c + 2 * j][at] = (v[p][0][j] & 0xffffu) | (v[p][1][j] << 16);
+            tile[c + 2 * j + 1][at] = (v[p][0][j] >> 16) | (v[p][1][j] & 0xffff0000u);
         }
     }
 }
 
-// Store the transpose of the tile: output row c0 + c gets 8 consecutive source
-// rows per lane (16 bytes), i.e. dst[(c0 + c) * ldo + o0 + r .. + 7].
+// Output row c0 + c gets the tile's column c at dst[(c0 + c) * ldo + o0 ..], n_out elements of it (a multiple of 8).
 __device__ __forceinline__ void store_tile_t(uint16_t* __restrict__ dst, size_t ldo, int c0, int cols, size_t o0,
-                                             int n_out, const uint16_t (*tile)[TT + 2]) {
-    const int tid = threadIdx.x;
+                                             int n_out, const uint32_t (*tile)[TP]) {
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    const int g = lane & 15;
 #pragma unroll
-    for (int p = 0; p < 2; ++p) {
-        const int c = p * 32 + tid / 8, r = (tid % 8) * 8;
-        if (c0 + c >= cols || r >= n_out) continue;   // n_out is a multiple of 8
-        u32x4 v;
-#pragma unroll
-        for (int j = 0; j < 4; ++j)
-            v[j] = (uint32_t)tile[r + 2 * j][c] | ((uint32_t)tile[r + 2 * j + 1][c] << 16);
-        *reinterpret_cast<u32x4*>(dst + (size_t)(c0 + c) * ldo + o0 + r) = v;
+    for (int p = 0; p < 8; ++p) {
+        const int c = 4 * (4 * p + wave) + (lane >> 4);
+        if (c0 + c >= cols || g * 8 >= n_out) continue;
+        const u32x4 v = *reinterpret_cast<const u32x4*>(&tile[c][4 * (g ^ (c >> 3))]);
+        *reinterpret_cast<u32x4*>(dst + (size_t)(c0 + c) * ldo + o0 + g * 8) = v;
     }
 }
 
 // dst[b][c][col0 + r] = src[b][r][c];  R, C multiples of 8.
 __global__ __launch_bounds__(256) void transpose_batched_kernel(const uint16_t* __restrict__ src, int R, int C,
                                                                 uint16_t* __restrict__ dst, size_t ldo, int col0) {
-    __shared__ uint16_t tile[TT][TT + 2];
+    __shared__ __attribute__((aligned(16))) uint32_t tile[TT][TP];
     const int b = blockIdx.z, r0 = blockIdx.y * TT, c0 = blockIdx.x * TT;
-    load_tile(src + (size_t)b * R * C, (size_t)C, r0, c0, R, C, tile);
+    const TransposeRows half[2] = {{r0, min(64, R - r0)}, {r0 + 64, min(64, R - r0 - 64)}};
+    load_tile(src + (size_t)b * R * C, (size_t)C, c0, C, half, tile);
     __syncthreads();
-    const int n_out = min(TT, R - r0);
-    store_tile_t(dst + (size_t)b * C * ldo, ldo, c0, C, (size_t)col0 + r0, n_out, tile);
+    store_tile_t(dst + (size_t)b * C * ldo, ldo, c0, C, (size_t)col0 + r0, min(TT, R - r0), tile);
 }
 
 // padded length of an expert's column segment in the transposed activations
@@ -94,35 +110,37 @@ __global__ __launch_bounds__(256) void ragged_offsets_kernel(const int32_t* __re
 }
 
 // dst[c][poff_e + (r - lo_e)] = src[r][c] for the rows r of expert e; the pad up to
-// padded_rows(n_e) is zero.  One workgroup per (64-column block, 64-row block of the
+// padded_rows(n_e) is zero.  One workgroup per (128-column block, 128-row block of the
 // padded axis); the expert of a padded position is the one whose segment [poff_e,
-// poff_e+1) holds it (segments are multiples of 64, so a block never straddles two).
+// poff_e+1) holds it (segments are multiples of 64, so a half block never straddles two).
 __global__ __launch_bounds__(256) void ragged_transpose_kernel(const uint16_t* __restrict__ src,
                                                                const int32_t* __restrict__ offsets,
                                                                const int32_t* __restrict__ poff, int E, int C,
                                                                uint16_t* __restrict__ dst, size_t ldo) {
-    __shared__ uint16_t tile[TT][TT + 2];
-    __shared__ int seg[3];   // first source row of this block, valid rows from there on, found flag
+    __shared__ __attribute__((aligned(16))) uint32_t tile[TT][TP];
+    __shared__ int seg[2][2];   // of each half: first source row, valid rows from there on (-1: past the last segment)
     const int p0 = blockIdx.y * TT, c0 = blockIdx.x * TT;
-    if (threadIdx.x == 0) seg[2] = 0;
+    if (threadIdx.x < 2) seg[threadIdx.x][1] = -1;
     __syncthreads();
     for (int e = threadIdx.x; e < E; e += 256) {
         const int lo_p = poff[e], hi_p = poff[e + 1];
-        if (lo_p <= p0 && p0 < hi_p) {   // at most one expert
-            const int lo = offsets[e], n = offsets[e + 1] - lo;
-            seg[0] = lo + (p0 - lo_p);
-            seg[1] = n - (p0 - lo_p);   // may be <= 0: a block of pure padding
-            seg[2] = 1;
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int p = p0 + 64 * h;
+            if (lo_p <= p && p < hi_p) {   // at most one expert
+                const int lo = offsets[e], n = offsets[e + 1] - lo;
+                seg[h][0] = lo + (p - lo_p);
+                seg[h][1] = max(0, n - (p - lo_p));   // 0: 64 positions of pure padding
+            }
         }
     }
     __syncthreads();
-    if (!seg[2]) return;   // past the last expert's padding: nothing to write
-    const int r_first = seg[0];
-    const int n_valid = max(0, min(TT, seg[1]));
-    // rows r_first .. r_first + n_valid of src; the rest of the 64 positions are padding (zeros)
-    load_tile(src, (size_t)C, r_first, c0, r_first + n_valid, C, tile);
+    if (seg[0][1] < 0) return;   // past the last expert's padding: nothing to write
+    const TransposeRows half[2] = {{seg[0][0], min(64, seg[0][1])}, {seg[1][0], min(64, seg[1][1])}};
+    const int n_out = seg[1][1] < 0 ? 64 : TT;
+    load_tile(src, (size_t)C, c0, C, half, tile);
     __syncthreads();
-    store_tile_t(dst, ldo, c0, C, (size_t)p0, TT, tile);
+    store_tile_t(dst, ldo, c0, C, (size_t)p0, n_out, tile);
 }
 
 // dg | du from dh [rows, F] and g, u (bf16, rows ld_gu elements apart; out [rows, 2F]): with s = 1/(1+e^-g),
@@ -180,7 +198,7 @@ void launch_ragged_offsets(const int32_t* offsets, int E, int32_t* poff, hipStre
 void launch_ragged_transpose(const void* src, const int32_t* offsets, const int32_t* poff, int E, int C, int rp_max,
                              void* dst, hipStream_t s) {
     if (rp_max <= 0 || C <= 0) return;
-    hipLaunchKernelGGL(ragged_transpose_kernel, dim3((C + TT - 1) / TT, rp_max / TT), dim3(256), 0, s,
+    hipLaunchKernelGGL(ragged_transpose_kernel, dim3((C + TT - 1) / TT, (rp_max + TT - 1) / TT), dim3(256), 0, s,
                        static_cast<const uint16_t*>(src), offsets, poff, E, C, static_cast<uint16_t*>(dst),
                        (size_t)rp_max);
 }
