@@ -187,13 +187,19 @@ __device__ __forceinline__ float finish_tile(const StreamArgs& p, const Tile& t,
     return amax;
 }
 
-// one atomic per wave; h >= 0 as a float compares like its bit pattern, and *amax only grows
-__device__ __forceinline__ void fold_amax(const StreamArgs& p, float amax) {
+// max |h| of the workgroup into *amax: one atomic per workgroup at most, and none if the value read is already as large
+// (*amax only grows; as floats >= 0 compare like their bit patterns).  One per wave put thousands of them on one address
+// at the end of the first round: gate/up of 32 tokens, 8 experts, 14336 x 4096, 200 us against 162 with *amax preset.
+__device__ __forceinline__ void fold_amax(const StreamArgs& p, float amax, float* scratch) {
     if (!p.amax) return;
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
-    if ((threadIdx.x & 63) == 0 && amax > __builtin_nontemporal_load(p.amax))
-        atomicMax(reinterpret_cast<int*>(p.amax), __float_as_int(amax));
+    __syncthreads();   // the scheduler's reads of the scratch are over
+    if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = amax;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (unsigned w = 1; w < blockDim.x / 64; ++w) amax = fmaxf(amax, scratch[w]);
+    if (amax > __builtin_nontemporal_load(p.amax)) atomicMax(reinterpret_cast<int*>(p.amax), __float_as_int(amax));
 }
 
 // At most 16 rows: both operands go straight from memory to registers, the waves take the 128-byte blocks of the
@@ -572,7 +578,7 @@ __global__ __launch_bounds__(kWideWaves * 64, 2) void gemm_wide_kernel(const Str
         p.ticks[0] = __builtin_amdgcn_s_memtime() - tk_entry;
         p.ticks[1] = __builtin_amdgcn_s_memrealtime() - rt_entry;
     }
-    if constexpr (ELT == kEltFp8 && MODE == 1) fold_amax(p, amax);
+    if constexpr (ELT == kEltFp8 && MODE == 1) fold_amax(p, amax, reinterpret_cast<float*>(smem + kWideRing));
 }
 
 // The sums of the S partial planes, in split order, through the epilogue.  One thread per four columns of a row.
@@ -638,7 +644,7 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(const StreamArgs p)
         p.ticks[0] = __builtin_amdgcn_s_memtime() - tk_entry;
         p.ticks[1] = __builtin_amdgcn_s_memrealtime() - rt_entry;
     }
-    if constexpr (ELT == kEltFp8 && MODE == 1) fold_amax(p, amax);
+    if constexpr (ELT == kEltFp8 && MODE == 1) fold_amax(p, amax, reinterpret_cast<float*>(smem + RING));
 }
 
 template <int ELT, int MODE, int FB, bool DIRECT>
