@@ -562,6 +562,7 @@ moe_status_t moe_grouped_gemm_swiglu_backward(const void* x_perm, const void* h,
             return fail(MOE_ERR_UNSUPPORTED, "%s: no kernel for H=%d F=%d", fn, H, F);
     }
     const bool pipe3 = g_gemm_variant == 30 || g_gemm_variant == 31;
+    if (!pipe3) launch_wgrad_zero_empty(expert_offsets, E, (size_t)H * F, dw_down, dw_gate, dw_up, s);
     if (g_wgrad_rowmajor && !pipe3) {
         // weight gradients straight from the row-major activations; rows past an expert's end read a zero row
         if (R_max > 0) {

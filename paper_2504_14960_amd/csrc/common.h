@@ -139,6 +139,9 @@ bool launch_grouped_nt_swiglu_bwd(const void* A, const int32_t* offsets, int r_m
 // the forward's gate/up GEMM that also stores the pre-activations g | u to gu [rows, 2F]; false if not covered
 bool launch_gate_up_saving(const void* x_perm, const int32_t* offsets, int r_max, int H, int F, int E,
                            const void* w_gate, const void* w_up, void* h, void* gu, hipStream_t s);
+// zeros the gradients of experts without rows, which the persistent weight-gradient launches leave alone
+void launch_wgrad_zero_empty(const int32_t* offsets, int E, size_t per_expert, void* dw0, void* dw1, void* dw2,
+                             hipStream_t s);
 // dw [E, M, N] = per expert a_t[:, seg_e] . b_t[:, seg_e]^T over the expert's padded column segment
 // persistent: one workgroup per compute unit; pipe3: one workgroup per output tile
 void launch_persist_wgrad(const void* a_t, const void* b_t, const int32_t* offsets, int E, int M, int N, int ld,

@@ -821,9 +821,12 @@ StreamPlan plan_stream(int elt, int r_max, int E, int N, int K, bool swiglu, boo
     w.r_max = r_max;
     w.swiglu = swiglu;
     double best = g_stream == 2 ? 1e30 : narrow_us(w, narrow_blocks(r_max, E, N, swiglu));
-    if (g_stream < 0 && large_ok && large_us(w) < best) {
-        best = large_us(w);
-        plan.kind = kPlanLarge;
+    if (g_stream < 0 && large_ok) {
+        const double t = 0.96 * large_us(w);   // in a tie the kernel that a skewed router disturbs least
+        if (t < best) {
+            best = t;
+            plan.kind = kPlanLarge;
+        }
     }
     for (int units = 8; units >= 3; --units)
         for (int S = 1; S <= 16; S *= 2) {

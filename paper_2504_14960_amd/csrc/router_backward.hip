@@ -2,8 +2,9 @@
 // backward workflow mirrors the forward one).
 //
 //   router_dlogits_kernel   dgate [T,K] -> dlogits [T,E] through the (optional)
-//                           renormalisation and the softmax Jacobian; one lane
-//                           per token, a few passes over its E fp32 logits
+//                           renormalisation and the softmax Jacobian; one wave
+//                           per token (one lane where there are many tokens of
+//                           few experts)
 //   router_dx_kernel        dx[t,:]  = sum_e dlogits[t,e] W_g[e,:]   (32 tokens x
 //                           512 columns per workgroup on the fp32 matrix
 //                           instruction, dlogits tile in LDS)
@@ -63,6 +64,74 @@ __global__ __launch_bounds__(64) void router_dlogits_kernel(const float* __restr
         const float q = renorm ? (dg[k] - a) / S : dg[k];
         dl[e] += q * (expf(l[e] - m) * rz);
     }
+}
+
+// One wave per token: lane l holds the logits of experts l, l + 64, .. and slot l.  The lane form above is a chain of 4 E
+// dependent loads and exponentials, 40 us for any number of tokens of a 64-expert layer up to 16384; this one reads the
+// logits once, coalesced, and takes 4 us.  E <= 64 VPL.
+template <int VPL>
+__global__ __launch_bounds__(256) void router_dlogits_wave_kernel(const float* __restrict__ logits,
+                                                                  const int32_t* __restrict__ idx,
+                                                                  const float* __restrict__ dgate, int T, int E, int K,
+                                                                  int renorm, float* __restrict__ dlogits) {
+    const int lane = threadIdx.x & 63;
+    const int t = __builtin_amdgcn_readfirstlane(blockIdx.x * 4 + (threadIdx.x >> 6));
+    if (t >= T) return;
+    auto wave_sum = [](float v) {
+#pragma unroll
+        for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off, 64);
+        return v;
+    };
+    int e = -1;
+    float dg = 0.f;
+    if (lane < K) {
+        e = idx[(size_t)t * K + lane];
+        dg = dgate[(size_t)t * K + lane];
+        if ((unsigned)e >= (unsigned)E) e = -1;
+    }
+    float p[VPL], m = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < VPL; ++j) {
+        p[j] = lane + 64 * j < E ? logits[(size_t)t * E + lane + 64 * j] : -INFINITY;
+        m = fmaxf(m, p[j]);
+    }
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
+    float z = 0.f;
+#pragma unroll
+    for (int j = 0; j < VPL; ++j) {
+        p[j] = lane + 64 * j < E ? expf(p[j] - m) : 0.f;
+        z += p[j];
+    }
+    const float rz = 1.f / wave_sum(z);
+#pragma unroll
+    for (int j = 0; j < VPL; ++j) p[j] *= rz;
+    float pk = 0.f;   // the probability of this lane's slot; slots outside [0, E) count for nothing
+#pragma unroll
+    for (int j = 0; j < VPL; ++j) {
+        const float v = __shfl(p[j], e & 63, 64);
+        if (e >= 0 && (e >> 6) == j) pk = v;
+    }
+    float q = dg;
+    if (renorm) {
+        const float S = wave_sum(pk);
+        const float a = wave_sum(e >= 0 ? dg * (pk / S) : 0.f);
+        q = (dg - a) / S;
+    }
+    const float c = e >= 0 ? q * pk : 0.f;
+    const float sum_qp = wave_sum(c);
+#pragma unroll
+    for (int j = 0; j < VPL; ++j) p[j] = -p[j] * sum_qp;
+    for (int k = 0; k < K; ++k) {   // slots in ascending order; a repeated expert adds up
+        const int ek = __builtin_amdgcn_readlane(e, k);
+        const float ck = __builtin_bit_cast(float, __builtin_amdgcn_readlane(__builtin_bit_cast(int, c), k));
+#pragma unroll
+        for (int j = 0; j < VPL; ++j)
+            if (ek == lane + 64 * j) p[j] += ck;
+    }
+#pragma unroll
+    for (int j = 0; j < VPL; ++j)
+        if (lane + 64 * j < E) dlogits[(size_t)t * E + lane + 64 * j] = p[j];
 }
 
 // Both products of the router's backward run on the fp32 matrix instruction
@@ -338,8 +407,21 @@ size_t router_backward_workspace_bytes(int T, int H, int E) {
 void launch_router_backward(const void* x, const void* w, const float* logits, const int32_t* idx, const float* dgate,
                             int T, int H, int E, int K, int renorm, moe_dtype_t dt, float* dlogits, void* dx,
                             float* dw, float* dbias, void* ws, hipStream_t s) {
-    hipLaunchKernelGGL(router_dlogits_kernel, dim3((T + 63) / 64), dim3(64), 0, s, logits, idx, dgate, T, E, K,
-                       renorm, dlogits);
+    // One lane per token only where few experts leave most of a wave idle (us, lane / wave): 8 experts, 8192 tokens 7.8 /
+    // 5.7, 16384 tokens 7.8 / 8.5, 65536 tokens 9.1 / 24.7; 16 experts, 16384 tokens 11.7 / 8.6, 32768 tokens 12.4 / 13.9;
+    // 64 experts, 1024 tokens 41.0 / 4.2, 65536 tokens 72.9 / 27.2; 256 experts, 4096 tokens 125 / 5.9.
+    if (E < 32 && T > 1024 * E)
+        hipLaunchKernelGGL(router_dlogits_kernel, dim3((T + 63) / 64), dim3(64), 0, s, logits, idx, dgate, T, E, K,
+                           renorm, dlogits);
+    else if (E <= 64)
+        hipLaunchKernelGGL(router_dlogits_wave_kernel<1>, dim3((T + 3) / 4), dim3(256), 0, s, logits, idx, dgate, T, E, K,
+                           renorm, dlogits);
+    else if (E <= 128)
+        hipLaunchKernelGGL(router_dlogits_wave_kernel<2>, dim3((T + 3) / 4), dim3(256), 0, s, logits, idx, dgate, T, E, K,
+                           renorm, dlogits);
+    else
+        hipLaunchKernelGGL(router_dlogits_wave_kernel<4>, dim3((T + 3) / 4), dim3(256), 0, s, logits, idx, dgate, T, E, K,
+                           renorm, dlogits);
     const bool bf16 = dt == MOE_BF16;
     if (dx) {
         const dim3 grid((H + 4 * RB_WCOLS - 1) / (4 * RB_WCOLS), (T + DX_TOK - 1) / DX_TOK);
