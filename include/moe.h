@@ -355,8 +355,11 @@ moe_status_t moe_grouped_gemm_swiglu_backward(const void* x_perm, const void* h,
                                               void* workspace, size_t workspace_bytes,
                                               moe_stream_t stream);
 
-/* Bytes of workspace moe_layer_forward needs.  Fs = FFN size of the shared
- * expert (0 = none).  Host only. */
+/* Bytes of workspace moe_layer_forward asks for: its intermediates, and at most
+ * 64 MiB for partial sums of expert products whose contraction is split over
+ * workgroups (few rows on few experts).  A workspace without room for the
+ * partial sums is taken too; the contraction is then not split.  Fs = FFN size
+ * of the shared expert (0 = none).  Host only. */
 size_t moe_layer_workspace_bytes(int T, int H, int E, int K, int F, int Fs, int capacity,
                                  moe_dtype_t dt);
 /* The same for a layer without a shared expert (Fs = 0): the forward workflow of

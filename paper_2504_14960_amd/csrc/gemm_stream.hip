@@ -822,7 +822,7 @@ StreamPlan plan_stream(int elt, int r_max, int E, int N, int K, bool swiglu, boo
     w.swiglu = swiglu;
     double best = g_stream == 2 ? 1e30 : narrow_us(w, narrow_blocks(r_max, E, N, swiglu));
     if (g_stream < 0 && large_ok) {
-        const double t = 0.96 * large_us(w);   // in a tie the kernel that a skewed router disturbs least
+        const double t = 0.93 * large_us(w);   // in a tie the kernel that a skewed router disturbs least
         if (t < best) {
             best = t;
             plan.kind = kPlanLarge;
