@@ -776,9 +776,10 @@ double narrow_us(const Work& w, int fb) {
     const int tr = fb == 1 ? 64 : 128, mt = blocks_of(w.rows, tr);
     const int nt = blocks_of(w.N, 16 * (w.swiglu ? fb / 2 : fb));
     const double tiles = m_tiles(w, tr) * nt, even_tiles = (double)mt * w.experts * nt;
-    // a second workgroup on a compute unit adds less than a round while the weights are what is waited for
+    // a second workgroup on a compute unit adds less than a round while the weights are what is waited for, a third waits
+    // for one of the two
     const double whole = rounds_of(tiles), over = tiles / kUnitsCU - (whole - 1.0);
-    const double q = whole <= 1.0 || mt > 1 || over > 0.6 ? whole : whole - 0.6;
+    const double q = whole <= 1.0 || mt > 1 || over > 0.6 ? whole : whole - (whole <= 2.0 ? 0.6 : 0.3);
     const bool direct = w.rows <= 16;
     const int rows = w.rows < tr ? w.rows : tr;
     const double weight = direct ? 41e-6 : mt > 1 ? 36e-6 : 43e-6;
@@ -822,7 +823,8 @@ StreamPlan plan_stream(int elt, int r_max, int E, int N, int K, bool swiglu, boo
     w.swiglu = swiglu;
     double best = g_stream == 2 ? 1e30 : narrow_us(w, narrow_blocks(r_max, E, N, swiglu));
     if (g_stream < 0 && large_ok) {
-        const double t = 0.93 * large_us(w);   // in a tie the kernel that a skewed router disturbs least
+        // in a tie the kernel that a skewed router disturbs least; a handful of rows per expert is the narrow kernel's own
+        const double t = (w.rows > 16 ? 0.93 : 1.0) * large_us(w);
         if (t < best) {
             best = t;
             plan.kind = kPlanLarge;
