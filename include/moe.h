@@ -35,8 +35,10 @@
  *     treated as a dropped assignment, never as an address.
  *   - T == 0 is legal (MOE_OK, nothing launched).  Experts with no rows are
  *     legal everywhere.
- *   - Same inputs give bit-identical outputs on every call (no floating-point
- *     atomics, no slot-claiming atomics).
+ *   - Same inputs and sizes give bit-identical outputs on every call (no
+ *     floating-point atomics, no slot-claiming atomics).  The order of a sum
+ *     depends on the sizes of the call (tokens, R_max, rows of the expert), so a
+ *     token's result may differ by rounding from batch to batch.
  *   - Limits: 1 <= K <= min(E, 64), E <= 256, T*K < 2^31, H % 8 == 0 and
  *     F % 8 == 0 for MOE_BF16 (H % 4, F % 4 for MOE_F32).
  */
@@ -355,11 +357,13 @@ moe_status_t moe_grouped_gemm_swiglu_backward(const void* x_perm, const void* h,
                                               void* workspace, size_t workspace_bytes,
                                               moe_stream_t stream);
 
-/* Bytes of workspace moe_layer_forward asks for: its intermediates, and at most
- * 64 MiB for partial sums of expert products whose contraction is split over
- * workgroups (few rows on few experts).  A workspace without room for the
- * partial sums is taken too; the contraction is then not split.  Fs = FFN size
- * of the shared expert (0 = none).  Host only. */
+/* Bytes of workspace moe_layer_forward asks for: its intermediates and, for a
+ * layer with a shared expert and few tokens, at most 64 MiB for the partial sums
+ * of the shared expert's products, whose contraction is then split over
+ * workgroups.  A workspace that holds the intermediates but not all of the
+ * partial sums is taken too; the contraction is then not split, and y may differ
+ * by rounding.  Room beyond what is asked for changes nothing.  Fs = FFN size of
+ * the shared expert (0 = none).  Host only. */
 size_t moe_layer_workspace_bytes(int T, int H, int E, int K, int F, int Fs, int capacity,
                                  moe_dtype_t dt);
 /* The same for a layer without a shared expert (Fs = 0): the forward workflow of
@@ -414,7 +418,11 @@ moe_status_t moe_layer_workspace_layout(int T, int H, int E, int K, int F, int F
  * optional always-on shared expert (ws_* non-NULL and Fs > 0) that is evaluated
  * on x directly and added, ungated, in a4.  The throughput metric times this
  * call.  y [T,H] (dt) is the only user-visible output; intermediates live in
- * `workspace` (layout private, see moe_layer_workspace_bytes).
+ * `workspace` (layout private, see moe_layer_workspace_bytes).  Without a shared
+ * expert y is, bit for bit, what the four stage calls give with R_max =
+ * moe_max_rows(T, K, E, capacity), and what moe_layer_forward_train gives; the
+ * shared expert's part may differ by rounding from moe_grouped_gemm_swiglu on x
+ * (see moe_layer_workspace_bytes).
  */
 moe_status_t moe_layer_forward(const void* x, const void* w_router, const float* logit_bias,
                                const void* w_gate, const void* w_up, const void* w_down,

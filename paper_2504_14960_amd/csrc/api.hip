@@ -80,10 +80,9 @@ static LayerLayout layer_layout(int T, int H, int E, int K, int F, int Fs, int c
     L.s_h = take(Fs > 0 ? (size_t)T * Fs * es : 0);
     L.s_y = take(Fs > 0 ? (size_t)T * H * es : 0);
     L.total = o;
-    // at the end, and not required: partial sums of the expert products
-    const size_t routed = expert_ffn_part_bytes(L.r_max, H, F, E, dt);
-    const size_t shared = Fs > 0 ? expert_ffn_part_bytes(T, H, Fs, 1, dt) : 0;
-    L.part_bytes = routed > shared ? routed : shared;
+    // at the end, and not required: partial sums of the shared expert's products.  The routed experts have none: their
+    // products stay those of the stage calls and of the training forward, bit for bit.
+    L.part_bytes = Fs > 0 ? expert_ffn_part_bytes(T, H, Fs, 1, dt) : 0;
     return L;
 }
 
@@ -646,18 +645,18 @@ moe_status_t moe_layer_forward(const void* x, const void* w_router, const float*
     st = moe_permute(x, idx, T, H, E, K, capacity, dt, ws + L.x_perm, counts, offsets, roa, aor,
                      ws + L.perm_ws, permute_workspace_bytes(T, K, E), stream);
     if (st) return st;
-    void* const part = ws + L.total;
-    const size_t part_bytes = workspace_bytes - L.total;
-    st = expert_ffn("moe_grouped_gemm_swiglu", 3, ws + L.x_perm, offsets, L.r_max, H, F, E, w_gate, w_up, w_down, dt,
-                    ws + L.h, ws + L.y_perm, stream, part, part_bytes);
+    st = moe_grouped_gemm_swiglu(ws + L.x_perm, offsets, L.r_max, H, F, E, w_gate, w_up, w_down, dt,
+                                 ws + L.h, ws + L.y_perm, stream);
     if (st) return st;
     const void* addend = nullptr;
     if (shared) {
         // the shared expert sees every token: one "expert" owning rows [0, T)
         int32_t* so = reinterpret_cast<int32_t*>(ws + L.s_offsets);
         launch_fill_i32(so, 2, 0, T, static_cast<hipStream_t>(stream));
+        // all the room that is asked for or none: the order of the sums takes no other form for sizes in between or above
+        const size_t part_bytes = workspace_bytes - L.total >= L.part_bytes ? L.part_bytes : 0;
         st = expert_ffn("moe_grouped_gemm_swiglu", 3, x, so, T, H, Fs, 1, ws_gate, ws_up, ws_down, dt, ws + L.s_h,
-                        ws + L.s_y, stream, part, part_bytes);
+                        ws + L.s_y, stream, ws + L.total, part_bytes);
         if (st) return st;
         addend = ws + L.s_y;
     }

@@ -97,7 +97,7 @@ unsigned long long* persist_clock_sample();
 bool launch_expert_ffn(const void* x_perm, const int32_t* offsets, int r_max, int H, int F, int E,
                        const void* w_gate, const void* w_up, const void* w_down, moe_dtype_t dt,
                        void* h, void* y_perm, int variant, int phase, void* part, size_t part_bytes, hipStream_t s);
-// room for partial sums (part, part_bytes above) that the layer makes use of; with less its contractions are not split
+// room for partial sums (part, part_bytes above) that the two products make use of; with less they are not split
 size_t expert_ffn_part_bytes(int r_max, int H, int F, int E, moe_dtype_t dt);
 
 inline size_t up256(size_t v) { return (v + 255) & ~size_t(255); }
