@@ -31,6 +31,9 @@ namespace {
 
 constexpr int NW = 4;   // waves per workgroup
 
+// MODE of the kernels: 0 one product, 1 the SwiGLU pair, 2 the pair with its pre-activations stored too, 3 as 1 for the shapes
+// that no large tile covers (see silu_mul)
+
 constexpr int kEltF32 = kStreamF32, kEltBf16 = kStreamBf16, kEltFp8 = kStreamFp8;
 
 // What a lane holds of a 128-byte k-step of one operand row: lane group j = lane / 16 of row lane % 16 holds bytes
@@ -122,6 +125,16 @@ __device__ __forceinline__ Piece tail_piece(const uint8_t* row, int j, int rem) 
     return v;
 }
 
+// silu(g) * u as the other kernel that takes the shape forms it: shapes of the large tiles with the fast exponential and
+// reciprocal, the rest (fp32, MODE 3) with the full expf and divide of the plain FMA kernel: the fast exponential's error
+// grows with |g|, some 40 units in the last place at g = -60.  (gate/up of 2331 rows on 12 experts, 1000 x 1416: 50.4 us
+// with the fast form, 51.6 with the full one.)
+template <int ELT, int MODE>
+__device__ __forceinline__ float silu_mul(float g, float u) {
+    if constexpr (ELT == kEltF32 || MODE == 3) return (g / (1.f + expf(-g))) * u;
+    else return g * __builtin_amdgcn_rcpf(1.f + __expf(-g)) * u;
+}
+
 // Stores the 16 x 16 output block (row block i, column block f) from its sums: v (with SwiGLU the gate's) and up.  A
 // lane holds row 16 i + lane % 16 and four consecutive columns.  Returns the largest |h| stored (FP8).
 template <int ELT, int MODE>
@@ -142,12 +155,7 @@ __device__ __forceinline__ float store_block(const StreamArgs& p, const Tile& t,
             *reinterpret_cast<u32x2*>(gu + p.N) = u2;
         }
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            if constexpr (ELT == kEltF32)
-                v[q] = (v[q] / (1.f + expf(-v[q]))) * up[q];
-            else
-                v[q] = v[q] * __builtin_amdgcn_rcpf(1.f + __expf(-v[q])) * up[q];
-        }
+        for (int q = 0; q < 4; ++q) v[q] = silu_mul<ELT, MODE>(v[q], up[q]);
     } else if constexpr (ELT == kEltFp8) {
         v *= p.s0;
     }
@@ -601,7 +609,7 @@ __global__ __launch_bounds__(256) void stream_reduce_kernel(const float* __restr
         }
         if (MODE != 0)
 #pragma unroll
-            for (int k = 0; k < 4; ++k) v[k] = v[k] * __builtin_amdgcn_rcpf(1.f + __expf(-v[k])) * up[k];
+            for (int k = 0; k < 4; ++k) v[k] = silu_mul<kEltBf16, MODE>(v[k], up[k]);
         const u32x2 o = {pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3])};
         *reinterpret_cast<u32x2*>(C + (size_t)row * N + c) = o;
     }
@@ -872,6 +880,7 @@ void launch_stream(const StreamPlan& plan, int elt, const void* A, const int32_t
         if (B1) launch_any<kEltF32, 1>(p, r_max, plan, part, s); else launch_any<kEltF32, 0>(p, r_max, plan, part, s);
     } else if (elt == kEltBf16) {
         if (GU) launch_any<kEltBf16, 2>(p, r_max, plan, part, s);
+        else if (B1 && (N % 64 || K % 64)) launch_any<kEltBf16, 3>(p, r_max, plan, part, s);   // no large tile covers it
         else if (B1) launch_any<kEltBf16, 1>(p, r_max, plan, part, s);
         else launch_any<kEltBf16, 0>(p, r_max, plan, part, s);
     } else {

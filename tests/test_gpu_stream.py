@@ -5,7 +5,7 @@ import numpy as np
 import pytest
 
 import oracle
-from helpers import assert_close
+from helpers import assert_close, to_dev, to_host, values
 from test_gpu_experts import _case as bf16_case, _run as bf16_run
 from test_gpu_fp8 import _case as fp8_case, _check_h_codes, _run as fp8_run
 
@@ -63,7 +63,6 @@ def test_saving_form_and_both_kernels_agree():
     """The pre-activations are those behind h, and the large-tile kernel's results differ by rounding only."""
     import torch
     import paper_2504_14960_amd as moe
-    from helpers import to_dev, to_host, values
     inp, x_perm, offsets, h_ref, _ = bf16_case(H=256, F=384, E=len(EDGES), counts=EDGES, seed=6600)
     R = int(offsets[-1])
     x, off = to_dev(x_perm), to_dev(offsets)
@@ -82,3 +81,29 @@ def test_saving_form_and_both_kernels_agree():
     # one rounding each: at most a unit in the last place (2^-8 relative) where the sums straddle a boundary
     assert np.abs(out[0] - out[1]).max() <= np.abs(out[0]).max() * 2.0 ** -7
     assert np.linalg.norm(out[0] - out[1]) <= 1e-3 * np.linalg.norm(out[0])
+
+
+@pytest.mark.parametrize("H,F,rows", [(8, 16, 30000), (72, 64, 60), (64, 72, 9)])
+def test_silu_is_the_plain_kernels(H, F, rows):
+    """silu over the bf16 numbers of [-100, 100], with g and u formed without rounding: the bits of the plain FMA kernel,
+    which took the shapes that no large tile covers before (many rows, some sixty, at most sixteen)."""
+    import torch
+    import paper_2504_14960_amd as moe
+    g = np.arange(0x10000, dtype=np.uint32).astype(np.uint16)
+    g = g[(g & 0x7FFF) <= 0x42C8]                      # |g| <= 100
+    g = g[np.linspace(0, g.size - 1, rows).astype(int)]
+    x = np.zeros((rows, H), np.uint16)
+    x[:, 0], x[:, 1] = g, 0x3F80                       # g and 1
+    w = np.zeros((2, F, H), np.uint16)
+    w[0, :, 0] = w[1, :, 1] = 0x3F80
+    out = []
+    for variant in (0, 99):
+        h = torch.zeros((rows, F), dtype=torch.bfloat16, device="cuda")
+        moe.set_option("gemm_variant", variant)
+        try:
+            moe.expert_gate_up(to_dev(x), to_dev(np.array([0, rows], np.int32)), to_dev(w[:1]), to_dev(w[1:]), h)
+            torch.cuda.synchronize()
+        finally:
+            moe.set_option("gemm_variant", 0)
+        out.append(to_host(h))
+    np.testing.assert_array_equal(out[0], out[1])
