@@ -24,6 +24,7 @@
 #include "fp8_convert.h"
 #include "gemm_stream.h"
 #include "gemm_tile.h"
+#include "once_per_device.h"
 
 namespace moe {
 
@@ -615,6 +616,13 @@ __global__ __launch_bounds__(256) void stream_reduce_kernel(const float* __restr
     }
 }
 
+// The LDS limit of a kernel on the current device (`lds`: the kernel's own)
+void allow_lds(OncePerDevice& lds, const void* kern, int bytes) {
+    int device = -1;   // unknown: set it every time
+    (void)hipGetDevice(&device);
+    lds.run(device, [&] { (void)hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); });
+}
+
 template <int FB> constexpr int tile_rows() { return FB == 1 ? 64 : 128; }
 template <int FB> constexpr int blocks_per_wave() { return FB == 8 ? 2 : 1; }
 // LDS of a workgroup: the ring of shared_tile (two workgroups per compute unit; one where the waves share the
@@ -661,11 +669,8 @@ void launch(StreamArgs p, int r_max, hipStream_t s) {
     constexpr int smem = lds_bytes<FB, DIRECT>() + (kMaxExperts + 2) * 4;
     p.ntn = (p.N + BN - 1) / BN;
     auto kern = gemm_stream_kernel<ELT, MODE, FB, DIRECT>;
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-        attr_set = true;
-    }
+    static OncePerDevice lds;
+    allow_lds(lds, reinterpret_cast<const void*>(kern), smem);
     hipLaunchKernelGGL(kern, dim3(grid_for(r_max, p.E, tile_rows<FB>(), p.ntn)), dim3(256), smem, s, p);
 }
 
@@ -712,11 +717,8 @@ void launch_wide(StreamArgs p, int r_max, const StreamPlan& plan, float* part, h
     p.part = plan.splits > 1 ? part : nullptr;
     p.ntn = (p.N + bn - 1) / bn;
     auto kern = gemm_wide_kernel<ELT, MODE>;
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem);
-        attr_set = true;
-    }
+    static OncePerDevice lds;
+    allow_lds(lds, reinterpret_cast<const void*>(kern), smem);
     hipLaunchKernelGGL(kern, dim3(grid_for(r_max, p.E, 128, p.ntn * p.S)), dim3(kWideWaves * 64), smem, s, p);
     if constexpr (ELT == kEltBf16 && MODE != 2) {
         if (p.S > 1) {
