@@ -552,7 +552,8 @@ moe_status_t moe_gemm_clock_sample(uint64_t* ticks);
  * forms the weight gradients straight from the row-major activations with
  * transposing LDS loads instead of from transposed copies: about 1.8x slower
  * weight-gradient GEMMs, no ragged transposes; default 0); "permute_fused" (1, the default: layers with at most 8 experts and at most
- * 65532 assignments, and any layer with at most 16384, run moe_permute as ONE
+ * 65532 assignments, and any layer with at most 16384 of at most 8192 tokens
+ * (4096 in moe_permute_fp8), run moe_permute as ONE
  * kernel in which every workgroup counts the whole index array itself while its
  * rows are on their way; 0: always the three-kernel form; 2 / 3 force one / two
  * tokens per wave where there are at most 8 experts, 4 the form for any number); "gemm_idle_skip" (the

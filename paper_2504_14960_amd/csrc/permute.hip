@@ -780,6 +780,10 @@ void set_permute_fused(int v) { g_permute_fused = v; }   // 2 / 3: the packed fo
 //   64 experts x 3584, K = 8: 64 tokens 11.5 / 5.7, 500 tokens 18.5 / 10.6, 2048 tokens 38.1 / 29.8, 4096 tokens 34.8 / 37.6
 //   8 experts x 4096, K = 2: 1 token 6.2 / 3.4, 500 tokens 9.9 / 5.8, 2048 tokens 15.1 / 10.8, 4096 tokens 16.4 / 26.4
 //   the same in FP8: 1 token 9.4 / 5.1, 1024 tokens 13.1 / 9.3, 2048 tokens 11.2 / 14.5
+//   8 experts x 4096, K = 8: 1024 tokens 21.1 / 20.9, 1536 tokens 26.0 / 27.1
+// Every workgroup counts every assignment, so with few experts per token it is the number of workgroups that ends it:
+//   16 experts x 7168, K = 1: 4096 tokens 33.9 / 28.4, 8192 tokens 56.2 / 56.1, 16384 tokens 100.6 / 111.7
+//   the same in FP8: 2048 tokens 23.9 / 22.0, 4096 tokens 29.6 / 29.8, 8192 tokens 47.2 / 57.6
 constexpr int kSmallMaxAssign = 16384;
 
 // The one-launch dispatch of few assignments; false if the call is none of its own.  `x` may be null (maps only).
@@ -788,7 +792,8 @@ static bool launch_permute_small(const void* x, const int32_t* idx, int T, int K
                                  int r_max, void* x_perm, int32_t* counts, int32_t* offsets, int32_t* row_of_assign,
                                  int32_t* assign_of_row, float scale, float* amax, hipStream_t s) {
     if (row_bytes > 16384 || row_bytes % 16) return false;
-    const bool few = E <= kFusedMaxExperts ? T <= (FP8 ? 1024 : 2048) : (long long)T * K <= kSmallMaxAssign;
+    const bool few = E <= kFusedMaxExperts ? T <= (FP8 ? 1024 : 2048) && (FP8 || (long long)T * K <= kSmallMaxAssign / 2)
+                                           : T <= (FP8 ? 4096 : 8192) && (long long)T * K <= kSmallMaxAssign;
     if (g_permute_fused != 4 && (g_permute_fused != 1 || !few)) return false;
     const bool narrow = T <= 1024 || 16 * K > kSmallMaxOwn;   // 4 tokens per workgroup, else 16
     const int tb = narrow ? 4 : 16;

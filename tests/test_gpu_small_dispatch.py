@@ -107,6 +107,24 @@ def test_one_launch_fp8_dispatch_with_histograms(T, H, E, K, capacity):
         assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("T,one_launch", [(8192, True), (8193, False)])
+def test_many_tokens_of_one_expert_each_leave_the_one_launch_form(T, one_launch):
+    """The three-launch form keeps its histograms in the workspace, the one-launch form does not touch it."""
+    import torch
+    import paper_2504_14960_amd as moe
+    H, E, K = 64, 16, 1
+    idx = _idx(4500 + T, T, E, K, "normal")[0]
+    x = make_tokens(4501, T, H, bf16=True)
+    want = oracle.permute(x, idx, E, 0)
+    maps = [torch.empty((n,), dtype=torch.int32, device="cuda") for n in (E, E + 1, T, T)]
+    ws = torch.full((moe.permute_workspace_bytes(T, K, E) + 256,), 0xAA, dtype=torch.uint8, device="cuda")
+    moe.permute(to_dev(x), to_dev(idx), E, 0, torch.empty((T, H), dtype=torch.bfloat16, device="cuda"), *maps, ws)
+    torch.cuda.synchronize()
+    for got, ref in zip(maps, (want.counts, want.offsets, want.row_of_assign, want.assign_of_row)):
+        np.testing.assert_array_equal(got.cpu().numpy(), ref)
+    assert bool((ws == 0xAA).all()) == one_launch
+
+
 @pytest.mark.parametrize("T,H,K,bf16,with_addend", [
     (1, 4104, 2, True, True),          # three slices of a row, the last of 16 bytes
     (3, 3584, 8, True, True),
