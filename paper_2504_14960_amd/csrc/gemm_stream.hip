@@ -33,7 +33,7 @@ namespace {
 constexpr int NW = 4;   // waves per workgroup
 
 // MODE of the kernels: 0 one product, 1 the SwiGLU pair, 2 the pair with its pre-activations stored too, 3 as 1 for the shapes
-// that no large tile covers (see silu_mul)
+// that the persistent large tiles do not take (see silu_mul)
 
 constexpr int kEltF32 = kStreamF32, kEltBf16 = kStreamBf16, kEltFp8 = kStreamFp8;
 
@@ -126,10 +126,10 @@ __device__ __forceinline__ Piece tail_piece(const uint8_t* row, int j, int rem) 
     return v;
 }
 
-// silu(g) * u as the other kernel that takes the shape forms it: shapes of the large tiles with the fast exponential and
-// reciprocal, the rest (fp32, MODE 3) with the full expf and divide of the plain FMA kernel: the fast exponential's error
-// grows with |g|, some 40 units in the last place at g = -60.  (gate/up of 2331 rows on 12 experts, 1000 x 1416: 50.4 us
-// with the fast form, 51.6 with the full one.)
+// silu(g) * u as the persistent large tiles form it for the shapes they take, with the fast exponential and reciprocal; for
+// the rest (fp32; MODE 3: H or F not a multiple of 64, or H = 64) with the full expf and divide of the plain FMA kernel:
+// the fast exponential's error grows with |g|, some 40 units in the last place at g = -60.  (gate/up of 2331 rows on 12
+// experts, 1000 x 1416: 50.4 us with the fast form, 51.6 with the full one.)
 template <int ELT, int MODE>
 __device__ __forceinline__ float silu_mul(float g, float u) {
     if constexpr (ELT == kEltF32 || MODE == 3) return (g / (1.f + expf(-g))) * u;
@@ -882,7 +882,7 @@ void launch_stream(const StreamPlan& plan, int elt, const void* A, const int32_t
         if (B1) launch_any<kEltF32, 1>(p, r_max, plan, part, s); else launch_any<kEltF32, 0>(p, r_max, plan, part, s);
     } else if (elt == kEltBf16) {
         if (GU) launch_any<kEltBf16, 2>(p, r_max, plan, part, s);
-        else if (B1 && (N % 64 || K % 64)) launch_any<kEltBf16, 3>(p, r_max, plan, part, s);   // no large tile covers it
+        else if (B1 && (N % 64 || K % 64 || K < 128)) launch_any<kEltBf16, 3>(p, r_max, plan, part, s);
         else if (B1) launch_any<kEltBf16, 1>(p, r_max, plan, part, s);
         else launch_any<kEltBf16, 0>(p, r_max, plan, part, s);
     } else {

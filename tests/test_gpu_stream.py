@@ -83,10 +83,10 @@ def test_saving_form_and_both_kernels_agree():
     assert np.linalg.norm(out[0] - out[1]) <= 1e-3 * np.linalg.norm(out[0])
 
 
-@pytest.mark.parametrize("H,F,rows", [(8, 16, 30000), (72, 64, 60), (64, 72, 9)])
+@pytest.mark.parametrize("H,F,rows", [(8, 16, 30000), (72, 64, 60), (64, 72, 9), (64, 64, 30000)])
 def test_silu_is_the_plain_kernels(H, F, rows):
     """silu over the bf16 numbers of [-100, 100], with g and u formed without rounding: the bits of the plain FMA kernel,
-    which took the shapes that no large tile covers before (many rows, some sixty, at most sixteen)."""
+    for the shapes that the persistent large tiles do not take (many rows, some sixty, at most sixteen; H = 64)."""
     import torch
     import paper_2504_14960_amd as moe
     g = np.arange(0x10000, dtype=np.uint32).astype(np.uint16)
