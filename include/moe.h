@@ -544,7 +544,10 @@ moe_status_t moe_gemm_clock_sample(uint64_t* ticks);
  * "gemm_stream" (the weight-streaming expert kernel for few rows per expert: -1 =
  * chosen by size, the default; 0 = only for the shapes no other kernel takes; 1 =
  * always, under "gemm_variant" 0 and in FP8; 2 = always, with wide workgroups
- * where the type has them); "fp8_deep_weights" (FP8 expert GEMMs: 1, the default = three LDS stages for
+ * where the type has them; 11, 12, 14, 18 = as 1 with 16, 32, 64, 128 weight rows
+ * per workgroup; 100 S + U = as 2 with U = 3 to 8 times 32 weight rows per
+ * workgroup and, where there is room for partial sums, the contraction in S = 1,
+ * 2, 4, 8 or 16 parts); "fp8_deep_weights" (FP8 expert GEMMs: 1, the default = three LDS stages for
  * the weight tile, 0 = for the activation tile); "gemm_workgroups" (workgroups launched by the
  * persistent grouped-GEMM kernels; 0 = one per compute unit, values below 8
  * are raised to 8); "router_tile" (16-token blocks per router workgroup: 1, 2

@@ -21,7 +21,9 @@ bool stream_covers(long long K_bytes);
 StreamPlan plan_stream(int elt, int r_max, int E, int N, int K, bool swiglu, bool large_ok, size_t part_bytes);
 // room for partial sums that the plan wants, at most 64 MiB
 size_t stream_part_bytes(int elt, int r_max, int E, int N, int K, bool swiglu, bool large_ok);
-// -1 (default): by size; 0: only the shapes no other kernel takes; 1: always the narrow, 2: always the wide form
+// -1 (default): by size; 0: only the shapes no other kernel takes; 1: always the narrow, 2: always the wide form.  10 + FB:
+// narrow with FB (1, 2, 4, 8) blocks of 16 weight rows per workgroup (2 for 1 with SwiGLU; 2 or 4 for at most 16 rows in
+// all); 100 S + U: wide with U (3 .. 8) units and S (1, 2, 4, 8, 16) splits, halved until they fit the contraction and the room
 void set_gemm_stream(int v);
 
 // C [rows, N] = A [rows, K] . B0[e]^T; with B1 the SwiGLU pair silu(A B0^T) * (A B1^T), and with GU (bf16) also its two

@@ -674,6 +674,10 @@ void launch(StreamArgs p, int r_max, hipStream_t s) {
     hipLaunchKernelGGL(kern, dim3(grid_for(r_max, p.E, tile_rows<FB>(), p.ntn)), dim3(256), smem, s, p);
 }
 
+int g_stream = -1;   // see set_gemm_stream
+int forced_blocks() { return g_stream > 10 && g_stream < 20 ? g_stream - 10 : 0; }
+bool forced_wide() { return g_stream >= 100; }
+
 // Weight blocks of a narrow workgroup: as many as leave enough workgroups.  A wider workgroup reads the rows less often
 // and keeps more weight bytes in flight, but 256 compute units want work.  Measured (us, blocks 8 / 4 / 2 / 1):
 //   down 4096 x 14336, 8 experts x 8 rows    182 / 166 / 172 / 209   (256 / 512 / 1024 / 2048 workgroups)
@@ -683,6 +687,7 @@ void launch(StreamArgs p, int r_max, hipStream_t s) {
 //   the same, 500 rows                       237 / 159 / 230 / 408   (112 / 224 /  448 / 1792)
 //   gate/up 2560 x 3584, 64 experts x 8 rows 385 / 392 / 537 /  -
 int narrow_blocks(int r_max, int E, int N, bool swiglu) {
+    if (const int fb = forced_blocks()) return r_max <= 16 ? (fb >= 4 ? 4 : 2) : swiglu && fb == 1 ? 2 : fb;
     const int experts = E < r_max ? E : r_max;
     const bool few = (long long)r_max <= 16ll * experts;   // up to 16 rows per expert on average
     const long long mt = r_max / 128 + experts;            // M-tiles, at most
@@ -740,7 +745,6 @@ void launch_any(const StreamArgs& p, int r_max, const StreamPlan& plan, float* p
     launch_narrow<ELT, MODE>(p, r_max, s);
 }
 
-int g_stream = -1;   // -1: by size; 0: large tiles where they cover the shape; 1: narrow; 2: wide
 
 // ---- which kernel: estimated times (us) of the three ----
 // Fitted to measurements of gate/up and down at (E, H, F) = (1, 3584, 20480), (1, 2 and 8, 4096, 14336), (64, 3584, 2560),
@@ -827,7 +831,18 @@ StreamPlan plan_stream(int elt, int r_max, int E, int N, int K, bool swiglu, boo
         plan.kind = kPlanLarge;
         return plan;
     }
-    if (elt == kEltF32 || g_stream == 1 || !stream_covers(kbytes)) return plan;
+    if (elt == kEltF32 || g_stream == 1 || forced_blocks() || !stream_covers(kbytes)) return plan;
+    // a split leaves at least 16 blocks of the contraction to a workgroup
+    auto splits_fit = [&](int S) {
+        return S == 1 || (elt == kEltBf16 && kbytes / 128 >= 16 * S && (size_t)S * r_max * N * (swiglu ? 8 : 4) <= part_bytes);
+    };
+    if (forced_wide()) {
+        plan.kind = kPlanWide;
+        plan.units = g_stream % 100;
+        plan.splits = g_stream / 100;
+        while (!splits_fit(plan.splits)) plan.splits /= 2;
+        return plan;
+    }
     w.kbytes = (int)kbytes;
     w.r_max = r_max;
     w.swiglu = swiglu;
@@ -842,10 +857,7 @@ StreamPlan plan_stream(int elt, int r_max, int E, int N, int K, bool swiglu, boo
     }
     for (int units = 8; units >= 3; --units)
         for (int S = 1; S <= 16; S *= 2) {
-            // a split leaves at least 16 blocks of the contraction to a workgroup
-            if (S > 1 && (elt != kEltBf16 || w.kbytes / 128 < 16 * S ||
-                          (size_t)S * r_max * N * (swiglu ? 8 : 4) > part_bytes))
-                break;
+            if (!splits_fit(S)) break;
             const double t = wide_us(w, units, S);
             if (t < best) {
                 best = t;

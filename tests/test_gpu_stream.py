@@ -31,18 +31,17 @@ def _always_stream():
     (1048, 640, [40, 3], True),        # few workgroups: the waves share the contraction
     (2048, 520, [64], True),
     (1536, 512, [1, 0, 3, 12], True),  # at most 16 rows in all
-    (72, 16384, [5, 9], True),         # the same, with the wide form
+    (72, 16384, [5, 9], True),         # the same, many columns
     (4, 8, EDGES, False),              # fp32: 16 bytes per row
     (100, 260, EDGES, False),
     (1028, 36, [7, 2], False),
 ])
 def test_stream_against_the_oracle(H, F, counts, bf16):
-    inp, x_perm, offsets, h_ref, y_ref = bf16_case(H=H, F=F, E=len(counts), counts=counts, bf16=bf16, seed=6300 + H, r_pad=5)
+    pad = 0 if sum(counts) <= 16 else 5
+    inp, x_perm, offsets, h_ref, y_ref = bf16_case(H=H, F=F, E=len(counts), counts=counts, bf16=bf16, seed=6300 + H, r_pad=pad)
     R = int(offsets[-1])
-    h, y = bf16_run(x_perm, offsets, inp, 0, r_max=R + 5)
-    if not bf16 and H > 256:
-        # fp32 sums of 1028 terms: sqrt(1028) * 6e-8 = 2e-6 relative, within the bar's 1e-5
-        assert H <= 1028
+    h, y = bf16_run(x_perm, offsets, inp, 0, r_max=R + pad)
+    # fp32: sums of at most 1028 terms, sqrt(1028) * 6e-8 = 2e-6 relative, within the bar's 1e-5
     assert_close(h[:R], h_ref, bf16, "h")
     assert_close(y[:R], y_ref, bf16, "y_perm")
     assert not h[R:].any() and not y[R:].any()     # rows past the last expert stay untouched
@@ -51,12 +50,74 @@ def test_stream_against_the_oracle(H, F, counts, bf16):
 @pytest.mark.parametrize("H,F,counts", [(256, 1408, EDGES), (1536, 256, EDGES), (2304, 256, [40, 3]), (512, 768, [1, 0, 3, 12])])
 def test_stream_fp8_against_the_oracle(H, F, counts):
     c = fp8_case(seed=6500 + H, H=H, F=F, E=len(counts), counts=counts)
-    h, y, amax = fp8_run(c, r_pad=5)
+    h, y, amax = fp8_run(c, r_pad=0 if sum(counts) <= 16 else 5)
     R = c["R"]
     _check_h_codes(h[:R], c["ref"].hq, "h codes")
     assert abs(amax - c["ref"].amax_h) <= 1e-5 * c["ref"].amax_h
     assert_close(y[:R], c["ref"].y, True, "y_perm")
     assert not h[R:].any() and not y[R:].any()
+
+
+# Contractions that go round every ring of stages at least twice: up to eight stages of KS = 8 / FB blocks of 128 bytes (one
+# from 64 weight rows on), and 2 x 4 blocks per wave in the form without a ring.  69 blocks and 48 bytes in bf16.
+LONG = [5, 16, 17, 30, 33, 0, 64, 65, 128, 129]
+
+
+@pytest.fixture(scope="module", params=["gate_up", "down"])
+def long_contraction(request):
+    H, F = (4440, 200) if request.param == "gate_up" else (200, 4440)
+    return {len(c): bf16_case(H=H, F=F, E=len(c), counts=c, seed=6700 + H) for c in (LONG, [1, 0, 3, 12])}
+
+
+@pytest.mark.parametrize("blocks", [1, 2, 4, 8])
+@pytest.mark.parametrize("experts", [len(LONG), 4])      # 4: at most 16 rows in all
+def test_every_width_goes_round_its_ring(long_contraction, experts, blocks):
+    import paper_2504_14960_amd as moe
+    inp, x_perm, offsets, h_ref, y_ref = long_contraction[experts]
+    moe.set_option("gemm_stream", 10 + blocks)
+    h, y = bf16_run(x_perm, offsets, inp, 0)
+    assert_close(h, h_ref, True, "h")
+    assert_close(y, y_ref, True, "y_perm")
+
+
+def check_fp8(c, option):
+    """The kernel form `option` on an FP8 case of many sums: y against the oracle, h against the large tiles' h.
+
+    The matrix instruction's own sums of E4M3 products are some 1e-5 off in every kernel: more than a step of the codes for one
+    small h in a million.  Between two kernels the order of at most 66 additions remains, sqrt(66) * 6e-8 = 5e-7 relative in
+    each of g and u."""
+    import paper_2504_14960_amd as moe
+    moe.set_option("gemm_stream", 0)
+    h_large, _, amax_large = fp8_run(c)
+    moe.set_option("gemm_stream", option)
+    h, y, amax = fp8_run(c)
+    _check_h_codes(h, h_large, "h codes")
+    assert abs(amax - amax_large) <= 1e-6 * amax_large
+    assert_close(y, c["ref"].y, True, "y_perm")
+
+
+@pytest.fixture(scope="module", params=["gate_up", "down"])
+def long_contraction_fp8(request):
+    H, F = (8448, 256) if request.param == "gate_up" else (256, 8448)      # 66 blocks
+    return {len(c): fp8_case(seed=6800 + H, H=H, F=F, E=len(c), counts=c) for c in (LONG, [1, 0, 3, 12])}
+
+
+@pytest.mark.parametrize("blocks", [1, 2, 4, 8])
+@pytest.mark.parametrize("experts", [len(LONG), 4])
+def test_every_width_goes_round_its_ring_in_fp8(long_contraction_fp8, experts, blocks):
+    check_fp8(long_contraction_fp8[experts], 10 + blocks)
+
+
+@pytest.mark.parametrize("blocks", [1, 2, 4, 8])
+@pytest.mark.parametrize("H,F", [(1100, 68), (68, 1100)])      # 34 blocks and 48 bytes
+def test_every_width_goes_round_its_ring_in_fp32(H, F, blocks):
+    import paper_2504_14960_amd as moe
+    inp, x_perm, offsets, h_ref, y_ref = bf16_case(H=H, F=F, E=len(LONG), counts=LONG, bf16=False, seed=6900 + H)
+    moe.set_option("gemm_stream", 10 + blocks)
+    h, y = bf16_run(x_perm, offsets, inp, 0)
+    # sums of 1100 terms: sqrt(1100) * 6e-8 = 2e-6 relative, within the bar's 1e-5
+    assert_close(h, h_ref, False, "h")
+    assert_close(y, y_ref, False, "y_perm")
 
 
 def test_saving_form_and_both_kernels_agree():
