@@ -1,5 +1,5 @@
 """The wide form of the weight-streaming expert kernel: row counts on both sides of its tile forms, partial blocks of the
-contraction, every number of weight rows per workgroup, and the contraction split over workgroups."""
+contraction, every number of weight rows per workgroup, and the contraction in every number of parts."""
 import numpy as np
 import pytest
 
@@ -8,7 +8,7 @@ from helpers import assert_close, guard_margins, to_dev, to_host, values
 from test_gpu_experts import _case as bf16_case, _run as bf16_run
 from test_gpu_fp8 import _case as fp8_case, _check_h_codes, _run as fp8_run
 from test_gpu_layer import oracle_layer
-from test_gpu_stream import EDGES
+from test_gpu_stream import EDGES, check_fp8
 
 pytestmark = pytest.mark.gpu
 
@@ -50,32 +50,87 @@ def test_wide_fp8_against_the_oracle(H, F, counts):
     assert not h[R:].any() and not y[R:].any()
 
 
-@pytest.mark.parametrize("T,H,F,Fs,E,K", [
-    (40, 512, 128, 4096, 4, 2),        # the shared expert's down projection is split
-    (150, 2560, 64, 1024, 6, 2),       # both of its products; two M-tiles
-])
-def test_split_contraction_in_the_layer(T, H, F, Fs, E, K):
-    """With the workspace that is asked for, and with one too small for the partial sums: both are the oracle's layer."""
-    import torch
+UNITS = [3, 4, 5, 6, 7, 8]      # blocks of 32 weight rows per workgroup; the last has no idle wave
+
+
+@pytest.fixture(scope="module", params=[(2184, 1416), (1416, 2184)])
+def ragged(request):
+    """34 blocks of 128 bytes and 16 bytes, 22 and 16: each ring of eight stages is gone round twice; the columns end inside a
+    workgroup's and inside a block of 16."""
+    H, F = request.param
+    return bf16_case(H=H, F=F, E=len(EDGES), counts=EDGES, seed=7600 + H, r_pad=5)
+
+
+@pytest.mark.parametrize("units", UNITS)
+def test_every_number_of_weight_rows(ragged, units):
     import paper_2504_14960_amd as moe
+    inp, x_perm, offsets, h_ref, y_ref = ragged
+    R = int(offsets[-1])
+    moe.set_option("gemm_stream", 100 + units)
+    h, y = bf16_run(x_perm, offsets, inp, 0, r_max=R + 5)
+    assert_close(h[:R], h_ref, True, "h")
+    assert_close(y[:R], y_ref, True, "y_perm")
+    assert not h[R:].any() and not y[R:].any()
+
+
+@pytest.mark.parametrize("units", UNITS)
+def test_every_number_of_weight_rows_in_fp8(units):
+    check_fp8(fp8_case(seed=7650, H=2304, F=640, E=len(EDGES), counts=EDGES), 100 + units)
+
+
+def _layer_case(T, H, F, Fs, E, K):
     cfg = get_config("qwen2_57b_a14b").scaled(T=T, H=H, F=F, E=E, K=K, shared_F=Fs, seed=7700 + T)
     inp = make_layer_inputs(cfg)
     guard_margins(inp, K)
-    want = oracle_layer(inp, 0)
+    return inp, oracle_layer(inp, 0)
+
+
+def _check_split_layer(case, parts):
+    """With the workspace that is asked for, `parts` bytes beyond the intermediates, and with one too small for the partial
+    sums: both are the oracle's layer."""
+    import torch
+    import paper_2504_14960_amd as moe
+    inp, want = case
+    c = inp.cfg
     d = {k: to_dev(v) for k, v in inp.tensors.items()}
     bias = None if inp.bias is None else to_dev(inp.bias)
-    nbytes = moe.layer_workspace_bytes(T, H, E, K, F, Fs, 0, moe.MOE_BF16)
-    lay = moe.layer_workspace_layout(T, H, E, K, F, Fs, 0, moe.MOE_BF16)
-    end = (max(lay.values()) + T * H * 2 + 255) // 256 * 256
-    assert nbytes > end, "the shape is meant to want partial sums"
+    nbytes = moe.layer_workspace_bytes(c.T, c.H, c.E, c.K, c.F, c.shared_F, 0, moe.MOE_BF16)
+    lay = moe.layer_workspace_layout(c.T, c.H, c.E, c.K, c.F, c.shared_F, 0, moe.MOE_BF16)
+    end = (lay["shared_y"] + c.T * c.H * 2 + 255) // 256 * 256
+    assert nbytes - end == parts, "the shape is meant to want these partial sums"
     out = []
     for size in (nbytes, end):
         ws = torch.full((size,), 0xFF, dtype=torch.uint8, device="cuda")      # NaN patterns: nothing unwritten is added
         y = torch.empty_like(d["x"])
-        moe.layer_forward(d["x"], d["w_router"], bias, d["w_gate"], d["w_up"], d["w_down"], d.get("ws_gate"),
-                          d.get("ws_up"), d.get("ws_down"), K, cfg.renormalize, 0, y, ws)
+        moe.layer_forward(d["x"], d["w_router"], bias, d["w_gate"], d["w_up"], d["w_down"], d["ws_gate"], d["ws_up"],
+                          d["ws_down"], c.K, c.renormalize, 0, y, ws)
         torch.cuda.synchronize()
         out.append(values(to_host(y)))
         assert_close(to_host(y), want.y, True, f"y ({size} bytes)")
     # the same products with their sums in another order: half a unit in the last place of bf16 here and there
     assert np.linalg.norm(out[0] - out[1]) <= 2e-3 * np.linalg.norm(out[0])
+
+
+@pytest.mark.parametrize("T,H,F,Fs,E,K,parts", [
+    (40, 512, 128, 4096, 4, 2, 4 * 40 * 512 * 4),          # the down projection in four parts
+    (150, 2560, 64, 1024, 6, 2, 2 * 150 * 1024 * 8),       # gate/up in two; two M-tiles
+])
+def test_split_contraction_in_the_layer(T, H, F, Fs, E, K, parts):
+    _check_split_layer(_layer_case(T, H, F, Fs, E, K), parts)
+
+
+# 260 blocks of 128 bytes and 16 bytes: no whole number of blocks to a part, and the partial block goes to the last one; the
+# other axis ends inside a workgroup's columns
+@pytest.fixture(scope="module", params=[(40, 16648, 328), (40, 328, 16648), (100, 16648, 328), (130, 328, 16648)])
+def long_shared(request):
+    T, H, Fs = request.param
+    return _layer_case(T, H, 64, Fs, 4, 2)
+
+
+@pytest.mark.parametrize("units,splits", [(3, 16), (4, 8), (5, 4), (6, 2), (7, 16), (8, 16), (8, 1)])
+def test_every_number_of_parts(long_shared, units, splits):
+    import paper_2504_14960_amd as moe
+    moe.set_option("gemm_stream", 100 * splits + units)
+    c = long_shared[0].cfg
+    per = c.shared_F * 8 if c.H > c.shared_F else c.H * 4         # gate/up with its two sums, or down; the other stays whole
+    _check_split_layer(long_shared, splits * c.T * per if splits > 1 else 0)
