@@ -178,9 +178,10 @@ def test_ffn_fp8_is_reproducible_and_handles_empty_input():
                                     None, torch.zeros((8, 192), dtype=torch.bfloat16, device="cuda"))
 
 
-# fused: the "permute_fused" option (0 = the maps from the three-kernel path, 1 = default dispatch, 2 / 3 = the maps from
-# the one-launch kernel with one / two tokens per wave); the quantising copy follows in either case.  Shapes with at
-# most 8 experts take the one-launch kernel: rows of 272 bytes up to 16 KiB, drops that leave whole tokens without a row
+# fused: the "permute_fused" option (0 = the maps from the three-kernel path; 1 = the default, all of it in one launch at
+# these sizes; 2 / 3 = the maps from the one-launch kernel of at most 8 experts with one / two tokens per wave, beyond 8
+# experts from the three kernels; the quantising copy follows).  Rows of 272 bytes up to 16 KiB, drops that leave whole
+# tokens without a row
 @pytest.mark.parametrize("fused", [0, 1, 2, 3])
 @pytest.mark.parametrize("T,H,E,K,capacity", [(300, 256, 8, 2, 0), (1000, 136, 16, 4, 150), (257, 1032, 64, 8, 0),
                                               (64, 64, 4, 1, 3), (700, 6144, 8, 2, 0), (513, 4096, 8, 2, 40),
@@ -188,8 +189,6 @@ def test_ffn_fp8_is_reproducible_and_handles_empty_input():
 def test_permute_fp8_writes_the_codes_of_the_permuted_rows(T, H, E, K, capacity, fused):
     import torch
     import paper_2504_14960_amd as moe
-    if fused and E > 8:
-        pytest.skip("more than 8 experts: the dispatch is the three-kernel path whatever the option says")
     rng = np.random.default_rng(T + H)
     x = make_tokens(6000 + T, T, H, bf16=True)
     idx = np.stack([rng.permutation(E)[:K] for _ in range(T)]).astype(np.int32)
