@@ -758,8 +758,11 @@ void launch_wgrad_zero_empty(const int32_t* offsets, int E, size_t per_expert, v
 // dw [E, M, N] = per expert a_t[:, seg_e] . b_t[:, seg_e]^T (see WgradSched); M, N multiples of 8, ld of 64
 void launch_persist_wgrad(const void* a_t, const void* b_t, const int32_t* offsets, int E, int M, int N, int ld,
                           void* dw, hipStream_t s) {
-    // Gradients streamed past the L2 (us, three products): 64 experts x 256 rows, 6144 x 2048 1828 / 1722; with 8 experts x
-    // 2048 rows, 6144 x 16384, the layer's forward and backward are 0.4 % slower for it.
+    // Gradients streamed past the L2 (us, the expert FFN's backward, stored as usual / so):
+    //   64 experts, 6144 x 2048: 256 rows 3364 / 3155, 512 rows 5260 / 5180, 768 rows 7368 / 7306, 1024 rows 9350 / 9314
+    //   8 experts, 4096 x 4096:  256 rows 703 / 625, 512 rows 900 / 832, 1024 rows 1539 / 1505, 1536 rows 2178 / 2169
+    // With 8 experts x 2048 rows, 6144 x 16384, the layer's forward and backward are 0.4 % slower for it: the line lies below
+    // where the two meet.
     if (ld <= 640ll * E)   // up to some 512 rows per expert, the padding included
         launch_persist_groupk<256, 256, 2, 4, true>(a_t, b_t, offsets, E, M, N, ld, dw, s);
     else

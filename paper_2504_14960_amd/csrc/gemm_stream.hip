@@ -4,7 +4,7 @@
 // With few rows per expert the product is a read of the weights: what bounds it is how many bytes of them are on
 // their way from HBM at a time.  The large-tile kernel has one workgroup per 256 weight rows, so the down projection of
 // two experts (4096 outputs, one decoded token) is 32 workgroups on 256 compute units, and a 256-row tile is multiplied
-// whatever it holds.  Here a workgroup owns 16 to 128 weight rows, the weights go straight from memory into the
+// whatever it holds.  Here a workgroup owns 16 to 256 weight rows, the weights go straight from memory into the
 // matrix instruction's operand registers (each byte is wanted by one wave only; two 16-byte loads per lane cover
 // whole 128-byte lines of 16 rows), and the rows of the tile decide how the other operand travels:
 //
@@ -14,13 +14,14 @@
 //                    waves and up to 256 weight rows); with more rows than that per expert the read of the rows
 //                    outweighs the weights and the large tiles are mostly the better kernel.
 //
-// Measured (bf16, weights of several launches so that no cache holds them; before: the large-tile kernel):
-//   down, 2 experts x 1 row, 4096 x 14336     231 us -> 36 us   (6.6 TB/s of weights)
-//   gate/up, 64 experts x 8 rows, 2560 x 3584  420 us -> 385 us  (6.1 TB/s);  down 234 us -> 206 us
-//   gate/up, 8 experts x 8 rows, 14336 x 4096  470 us -> 325 us  (5.8 TB/s);  down 292 us -> 166 us
-//   the same in FP8                            230 us -> 161 us  (5.8 TB/s);  down 148 us ->  86 us
-//   12 experts, 2331 rows, H = 1000, F = 1416  330 us ->  47 us  (plain FMA kernel before);  down 293 us -> 25 us
-//   fp32, 8 experts, 512 rows, H = 128, F = 256  27 us ->  9 us;  down 31 us -> 8 us
+// Measured (us, the large tiles / here; weights of several launches, so that no cache holds them):
+//   2 experts x 1 row, H x F = 4096 x 14336    gate/up 102 /  89 (5.3 TB/s of weights), down 251 /  46
+//   64 experts x 8 rows, 3584 x 2560           gate/up 417 / 400 (5.9 TB/s),            down 236 / 213
+//   8 experts x 8 rows, 4096 x 14336           gate/up 458 / 314 (6.0 TB/s),            down 289 / 161
+//   the same in FP8                            gate/up 211 / 166 (5.7 TB/s),            down 148 /  88
+// and against the plain FMA kernel, which took these shapes before:
+//   12 experts, 2331 rows, 1000 x 1416         gate/up 310 /  50,                       down 271 /  30
+//   fp32, 8 experts x 64 rows, 128 x 256       gate/up  29 /   8,                       down  36 /   7
 #include "fp8_convert.h"
 #include "gemm_stream.h"
 #include "gemm_tile.h"
@@ -37,9 +38,9 @@ constexpr int NW = 4;   // waves per workgroup
 
 constexpr int kEltF32 = kStreamF32, kEltBf16 = kStreamBf16, kEltFp8 = kStreamFp8;
 
-// What a lane holds of a 128-byte k-step of one operand row: lane group j = lane / 16 of row lane % 16 holds bytes
-// 16 j .. 16 j + 15 of both 64-byte halves (a load instruction then asks for whole 64-byte sectors).  The contraction order inside a step is the same for both operands, so any
-// assignment of bytes to contraction slots is right.
+// What a lane holds of a 128-byte k-step of one operand row: lane group j = lane / 16 of row lane % 16 holds the 32 bytes
+// from 32 j (two 16-byte loads; the four groups together ask for the row's whole line).  The contraction order inside a step
+// is the same for both operands, so any assignment of bytes to contraction slots is right.
 struct Piece {
     u32x4 lo, hi;
 };
@@ -107,9 +108,10 @@ struct TileAt {
 };
 
 // Where a workgroup starts in its n steps of the contraction.  Operand rows lie a whole row apart, so workgroups that
-// walk the contraction in step ask the same few memory channels at a time.  Depends on the weight tile only, so a row's
-// result does not depend on which rows it is computed with.  Measured (us, all from step 0 / so): down 4096 x 14336, 2
-// experts x 8 rows 51.0 / 44.6, 8 experts x 32 rows 187.7 / 175.1; gate/up 1408 x 2048, 16 experts x 8 rows 43.2 / 38.7.
+// walk the contraction in step ask the same few memory channels at a time.  The order of a row's sum is thus that of its
+// weight tile and expert, and beyond that of the form: the number of rows in its tile, and the plan, which follows r_max.  The
+// same call gives the same bits; another batch around a row may not.  Measured (us, all from step 0 / so): down 4096 x 14336,
+// 2 experts x 8 rows 51.0 / 44.6, 8 experts x 32 rows 187.7 / 175.1; gate/up 1408 x 2048, 16 experts x 8 rows 43.2 / 38.7.
 __device__ __forceinline__ int rotation(const Tile& t, int n) {
     return n > 0 ? __builtin_amdgcn_readfirstlane((int)((unsigned)(t.ntile * 3 + t.expert * 5) % (unsigned)n)) : 0;
 }
@@ -425,12 +427,11 @@ __device__ __forceinline__ float shared_tile(const StreamArgs& p, const Tile& t,
 // like the weights (loads return in order), so what a workgroup reads per weight byte is what matters: eight waves and
 // up to 256 weight rows on one ring of row stages, one workgroup per compute unit.  The number of weight rows is
 // chosen per launch (units x 32) so that the tiles fill whole rounds of the compute units, and where that leaves too
-// few of them the contraction is split: the splits leave fp32 partial sums that stream_reduce_kernel adds in split
-// order.  Measured (us, the better of the narrow and the large-tile kernel / here):
-//   one expert, gate/up 20480 x 3584: 64 rows 82 / 61 (160 weight rows each on 256 workgroups), 125 rows 84 / 73
-//   the same, down: 64 rows 69 / 42 (16 splits), 250 rows 124 / 68, 500 rows 161 / 110 (4 splits)
-//   2 experts, 4096 x 14336: gate/up 64 rows 100 / 87, down 74 / 55;  8 experts, down 125 rows 240 / 216
-//   16 experts, gate/up 1408 x 2048: 64 rows 49 / 40
+// few of them and there is room (the layer's shared expert) the contraction is split: the splits leave fp32 partial sums
+// that stream_reduce_kernel adds in split order.  Measured (us, the better of the narrow and the large-tile kernel / here):
+//   one expert, gate/up 20480 x 3584: 64 rows 84 / 61 (160 weight rows each on 256 workgroups), 125 rows 86 / 74
+//   the same, down: 64 rows 70 / 185 whole, 42 in 16 parts; 250 rows 126 / 68 and 500 rows 162 / 110 in parts
+//   8 experts, gate/up 14336 x 4096, 125 rows 421 / 404;  16 experts, gate/up 1408 x 2048, 64 rows 51 / 44
 constexpr int kWideWaves = 8, kWideRing = 128 * 1024;
 
 template <int ELT, int MODE, int MF>
@@ -748,8 +749,11 @@ void launch_any(const StreamArgs& p, int r_max, const StreamPlan& plan, float* p
 
 // ---- which kernel: estimated times (us) of the three ----
 // Fitted to measurements of gate/up and down at (E, H, F) = (1, 3584, 20480), (1, 2 and 8, 4096, 14336), (64, 3584, 2560),
-// (16, 2048, 1408) and (8, 2048, 4096) with 1 to 2000 rows per expert; the kernel they pick is within 6 % of the
-// best of the three at all but a few of those 130 points.
+// (16, 2048, 1408) and (8, 2048, 4096) with 1 to 2000 rows per expert.  With equal experts the kernel they pick is behind the
+// best of the three by up to 17 %, the price of the slack for skewed ones (m_tiles, wide_us): 8 experts x 125 rows, 4096 x
+// 14336, gate/up 457 instead of 404 and down 281 instead of 242; 16 experts x 64 rows, 2048 x 1408, 51 instead of 44 and 30
+// instead of 26.  A router more skewed than that slack costs the other way: 64 tokens of a Zipf-1.2 router, K = 4 of 60
+// experts, 2048 x 1408, down 38 instead of 33; K = 8 of 64, 3584 x 2560, both products 510 instead of 494.
 //   A round of workgroups takes (bytes of its weight rows) x 43 us/MB (36 where several M-tiles share them), plus its
 //   rows at a smaller rate, plus its start and end, which the narrow workgroups, two to a compute unit, mostly hide.
 //   A k-tile of the large tiles takes 1.1 us alone, 1.5 us with all compute units at work (1.9 where the rows lie a
@@ -758,14 +762,15 @@ struct Work {
     int experts, rows, N, kbytes, r_max;
     bool swiglu;
 };
-constexpr int kUnitsCU = 256;   // compute units the estimates are made for
+constexpr int kUnitsCU = 256;   // compute units the estimates are made for (gfx950, not partitioned)
 
 int blocks_of(int a, int b) { return (a + b - 1) / b; }
 
 // M-tiles of all experts.  With equal experts that would be ceil(rows / height) each; a skewed router makes up to
 // r_max / height more.  Half of those are counted where an expert with three times the average rows would need a second
 // tile (less down to a third): a plan must not spill into another round for a tile or two (8 experts x 3264 x 1984, 618
-// rows of a Zipf-1.2 router: the layer took 148 us with equal experts assumed and takes 125).
+// rows of a Zipf-1.2 router: the layer took 148 us with equal experts assumed and takes 125).  A capacity that rules the
+// skew out is not known here: r_max is all that is.
 double skew_share(const Work& w, int height) {
     const double near = 3.0 * w.rows / height - 1.0;
     return w.experts == 1 || w.rows <= 16 || near < 0.0 ? 0.0 : near > 1.0 ? 1.0 : near;

@@ -9,7 +9,7 @@
 // from global memory.  Partial sums are folded in a fixed wave order, so the
 // logits are bit-reproducible.  Selection is done by groups of lanes, one
 // group per token, with butterfly reductions on (value desc, index asc) keys.
-// With few tokens the same work is spread over more waves (router_split_kernel).
+// With few tokens the same work is spread over more workgroups (router_logits_kernel), the selection a launch of its own.
 #include "common.h"
 
 namespace moe {
@@ -603,8 +603,11 @@ void launch_bf16(const void* x, const void* w, const float* bias, float* logits,
 // (inside the layer, 64 tokens of the Qwen2 shape: 33 / 10)
 //   64 experts:  1 token 23.1 / 7.2, 64 tokens 24.4 / 9.0, 500 tokens 24.7 / 11.6, 2048 tokens 26.9 / 18.7, 4096 27.8 / 31.6
 //   128 experts x 2048:  1 token 31.3 / 8.6, 2048 tokens 37.1 / 24.8, 4096 tokens 36.6 / 41.5
-// and below 64 KB of router weight the second launch costs what the first saves: 8 experts x 4096, one token 8.6 / 6.4
-// alone and 10.6 / 9.5 inside the layer, 12 experts x 1000 7.9 / 9.7 inside the layer.
+// Inside a layer with a small expert FFN (us of the layer; 64 and 2048 tokens):
+//   8 experts x 1024  26.1 / 26.4, 45.2 / 46.3     12 x 1000  27.7 / 26.4, 49.5 / 48.4     8 x 3072  35.1 / 33.7, 74.0 / 73.5
+//   8 x 3584          38.4 / 36.3, 90.5 / 91.2      8 x 4096  40.9 / 38.3, 98.0 / 96.6    64 x 512   33.5 / 27.4, 64.2 / 58.6
+// The line lies at 64 KB of router weight, from where on the two launches are ahead for every number of tokens; below, down to
+// some 24 KB, they are by up to 3 us for most.
 constexpr int kSplitMaxTokens = 2048, kSplitMinWeights = 32768;
 // Selection alone, lists of eight lanes / by rank (us, 64 experts, K = 8): 1024 tokens 10.2 / 4.1, 4096 tokens 10.3 / 6.7,
 // 16384 tokens 13.3 / 13.1; 128 experts 17.1 / 13.1 at 4096.
