@@ -124,17 +124,20 @@ def test_rows_past_the_last_expert_are_untouched_and_result_is_reproducible():
     assert_close(y1[:R], y_ref, True, "y_perm")
 
 
-def test_shapes_outside_the_mfma_fast_path_use_the_plain_kernel():
+# by size on the streaming kernel; 99: the plain kernel
+@pytest.mark.parametrize("variant", [0, 99])
+def test_shapes_outside_the_mfma_fast_path(variant):
     inp, x_perm, offsets, h_ref, y_ref = _case(H=72, F=40, E=3, counts=[65, 3, 130], seed=4400)
-    h, y = _run(x_perm, offsets, inp, 0)
+    h, y = _run(x_perm, offsets, inp, variant)
     assert_close(h, h_ref, True, "h odd shape")
     assert_close(y, y_ref, True, "y odd shape")
 
 
-def test_fp32_experts():
+@pytest.mark.parametrize("variant", [0, 99])
+def test_fp32_experts(variant):
     inp, x_perm, offsets, h_ref, y_ref = _case(H=128, F=256, E=8, counts=[64, 70, 1, 0, 129, 33, 90, 125],
                                                bf16=False, seed=4500)
-    h, y = _run(x_perm, offsets, inp, 0)
+    h, y = _run(x_perm, offsets, inp, variant)
     assert_close(h, h_ref, False, "h fp32")
     assert_close(y, y_ref, False, "y fp32")
 
