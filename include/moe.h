@@ -550,7 +550,9 @@ moe_status_t moe_gemm_clock_sample(uint64_t* ticks);
  * 2, 4, 8 or 16 parts); "fp8_deep_weights" (FP8 expert GEMMs: 1, the default = three LDS stages for
  * the weight tile, 0 = for the activation tile); "gemm_workgroups" (workgroups launched by the
  * persistent grouped-GEMM kernels; 0 = one per compute unit, values below 8
- * are raised to 8); "router_tile" (16-token blocks per router workgroup: 1, 2
+ * are raised to 8); "gemm_tile_rows" (rows of the tiles of the persistent expert kernels,
+ * 256, 192 or 128; 0, the default = chosen on the device from the rows every expert has; the
+ * results do not depend on it); "router_tile" (16-token blocks per router workgroup: 1, 2
  * or 4; 8 = experts spread over workgroups, the selection a launch of its own; 0 = chosen by size); "wgrad_rowmajor" (1 = the expert FFN's backward
  * forms the weight gradients straight from the row-major activations with
  * transposing LDS loads instead of from transposed copies: about 1.8x slower

@@ -945,6 +945,12 @@ moe_status_t moe_set_option(const char* name, int value) {
         moe::set_persist_workgroups(value);
         return MOE_OK;
     }
+    if (name && strcmp(name, "gemm_tile_rows") == 0) {
+        if (value != 0 && value != 128 && value != 192 && value != 256)
+            return fail(MOE_ERR_INVALID_ARG, "moe_set_option: gemm_tile_rows must be 0, 128, 192 or 256");
+        moe::set_persist_tile_rows(value);
+        return MOE_OK;
+    }
     if (name && strcmp(name, "gemm_variant") == 0) {
         g_gemm_variant = value;
         return MOE_OK;

@@ -88,6 +88,7 @@ void launch_combine_backward(const void* dy, const void* y_perm, const int32_t* 
 void set_persist_workgroups(int n);
 bool persist_grid_overridden();   // the count above was set: the caller wants the persistent kernels
 void set_persist_idle_skip(int v);   // -1 auto, 0 off, 1 on
+void set_persist_tile_rows(int v);   // 0 chosen, 128, 192 or 256
 // device cells {shader-clock ticks, 100 MHz ticks} that workgroup 0 of every later persistent or streaming bf16 GEMM launch fills
 void set_persist_clock_sample(unsigned long long* ticks);
 unsigned long long* persist_clock_sample();

@@ -3,12 +3,15 @@
 #pragma once
 
 #include "gemm_tile.h"
+#include "tile_cost.h"
 
 namespace moe {
 
 // workgroups a persistent grouped-GEMM kernel is launched with: one per compute
 // unit unless overridden (at least 8, one per tile share)
 int persist_grid();
+// rows of the tiles of every launch that would choose them (256, 192 or 128); 0: chosen (see pick_height)
+int persist_tile_rows();
 // whether a launch over E experts uses the kernels whose waves without valid rows skip the multiplications
 bool persist_idle_skip(int E);
 
@@ -21,6 +24,45 @@ __device__ __forceinline__ const uint8_t* uni(const uint8_t* p) {
     const uint64_t u = reinterpret_cast<uint64_t>(p);
     const uint32_t lo = uni((uint32_t)u), hi = uni((uint32_t)(u >> 32));
     return reinterpret_cast<const uint8_t*>(((uint64_t)hi << 32) | lo);
+}
+
+__device__ __forceinline__ int wave_sum(int v) {
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
+    return v;
+}
+
+// The height of the tiles of a launch: 256, 192 or 128 rows, whichever takes least by the estimate (a lower one only where
+// it is ahead by 3 %).  Every wave of every workgroup comes to the same result: it depends on the offsets and on the launch
+// alone.  What the lower tiles gain is rows of padding and nearly empty last rounds, what they cost is more reads of the
+// weight panels per row: at full size a row of a 192-row tile takes as long as one of a 256-row tile, a row of a 128-row
+// tile a fifth longer.
+__device__ __forceinline__ int pick_height(const TileCosts& c, const int32_t* __restrict__ offsets, int E, int ntn, int kt, int lane) {
+    int m256 = 0, m192 = 0, m128 = 0, some = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const int e = lane * 4 + j;
+        const int n = e < E ? max(0, offsets[e + 1] - offsets[e]) : 0;
+        m256 += (n + 255) / 256;
+        m192 += (n + 191) / 192;
+        m128 += (n + 127) / 128;
+        some += n > 0;
+    }
+    m256 = wave_sum(m256);
+    m192 = wave_sum(m192);
+    m128 = wave_sum(m128);
+    some = wave_sum(some);
+    if (some == 0) return 256;
+    const int slots = gridDim.x;
+    float best = 0.97f * tiles_us(c.h256, m256, some, ntn, slots, kt);
+    int h = 256;
+    const float t192 = tiles_us(c.h192, m192, some, ntn, slots, kt), t128 = tiles_us(c.h128, m128, some, ntn, slots, kt);
+    if (t192 < best) {
+        best = t192;
+        h = 192;
+    }
+    if (t128 < best) h = 128;
+    return __builtin_amdgcn_readfirstlane(h);
 }
 
 // wave-uniform description of one output tile

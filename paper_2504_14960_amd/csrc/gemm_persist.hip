@@ -29,6 +29,7 @@ namespace moe {
 
 static int g_persist_workgroups = 0;  // 0: one per compute unit
 static int g_persist_idle_skip = -1;  // -1: chosen from the expert count; 0 / 1: forced
+static int g_persist_tile_rows = 0;   // 0: chosen from the rows of the experts; 256, 192 or 128: forced
 static unsigned long long* g_persist_ticks = nullptr;  // device cell pair of the clock sample, or none
 
 bool persist_grid_overridden() { return g_persist_workgroups > 0; }
@@ -217,12 +218,12 @@ __device__ __forceinline__ void store_tile_staged(f32x16 (&acc)[FM][FN], int t_r
 // DEEP_B: which operand gets the three LDS stages.  false: the activation tile (three stages, fetched two k-tiles
 // ahead) and two stages for the weight tile; true: the other way round -- the weights are what streams in from
 // HBM (every weight byte is used by one M-group only), the activation panels are re-read from the caches.
-template <int BM, int BN, int WGM, int WGN, int MODE, bool GROUPK = false, bool KMAJ = false, bool IDLE_SKIP = false,
-          bool DEEP_B = false, bool BY_ROUND = true, bool STREAM_OUT = false>
-__global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_persist_kernel(
+template <int BM, int BN, int WGM, int WGN, int MODE, bool GROUPK, bool KMAJ, bool IDLE_SKIP, bool DEEP_B, bool BY_ROUND,
+          bool STREAM_OUT>
+__device__ __forceinline__ void persist_body(
     const bf16_t* __restrict__ A, const int32_t* __restrict__ offsets, int E, int N, int K,
     const bf16_t* __restrict__ B0, const bf16_t* __restrict__ B1, bf16_t* __restrict__ C, bf16_t* __restrict__ GU,
-    int ntn, int ldb, unsigned long long* __restrict__ ticks) {
+    int ntn, int ldb, unsigned long long* __restrict__ ticks, uint8_t* smem) {
     static_assert(!GROUPK || MODE == 0, "the weight-gradient form has a plain epilogue");
     static_assert(!KMAJ || (GROUPK && BM == 256 && BN == 256 && WGM * WGN == 8), "row-major form: 256 x 256 tiles, 8 waves");
     static_assert(!(KMAJ && DEEP_B), "the row-major form keeps three activation stages");
@@ -260,10 +261,9 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_persist_kernel(
     static_assert(LA <= PE, "only loads of the early operand may be issued under k-step 3");
     static_assert(LB - LA <= NSLOT && LC - LB <= NSLOT && LA <= NSLOT, "not enough slots for the loads");
     static_assert(PL < 64, "vmcnt holds 6 bits");
-    static_assert(3 * A_BYTES + 2 * B_BYTES <= 160 * 1024, "tile stages exceed the 160 KiB of LDS");
+    static_assert((DEEP_B ? 2 * A_BYTES + 3 * B_BYTES : 3 * A_BYTES + 2 * B_BYTES) <= 160 * 1024, "tile stages exceed the 160 KiB of LDS");
     static_assert(NW * 32 * FO * 64 <= (DEEP_B ? B_BYTES : A_BYTES), "epilogue patches must fit into one slot of the late operand");
 
-    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     // clock sample (ticks != NULL): shader-clock and 100 MHz reference ticks workgroup 0 spends in the kernel
     const bool sample = ticks != nullptr && blockIdx.x == 0;
     unsigned long long tk_entry = 0, rt_entry = 0;
@@ -642,11 +642,44 @@ __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_persist_kernel(
     }
 }
 
+// BM = 0: the height of the tiles is chosen on the device, from the rows that every expert really has (pick_height);
+// 256, 192 or 128 rows, all of BN = 256 columns (ldb: a height to be taken instead, or 0).  A row's sums are formed in the same order whatever the height.
+template <int BM, int BN, int WGM, int WGN, int MODE, bool GROUPK = false, bool KMAJ = false, bool IDLE_SKIP = false,
+          bool DEEP_B = false, bool BY_ROUND = true, bool STREAM_OUT = false>
+__global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_persist_kernel(
+    const bf16_t* __restrict__ A, const int32_t* __restrict__ offsets, int E, int N, int K,
+    const bf16_t* __restrict__ B0, const bf16_t* __restrict__ B1, bf16_t* __restrict__ C, bf16_t* __restrict__ GU,
+    int ntn, int ldb, unsigned long long* __restrict__ ticks) {
+    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+    if constexpr (BM != 0) {
+        persist_body<BM, BN, WGM, WGN, MODE, GROUPK, KMAJ, IDLE_SKIP, DEEP_B, BY_ROUND, STREAM_OUT>(A, offsets, E, N, K, B0, B1, C,
+                                                                                                  GU, ntn, ldb, ticks, smem);
+    } else {
+        const int height = ldb != 0 ? ldb : pick_height(kCostBf16, offsets, E, ntn, K / 64, threadIdx.x & 63);
+        auto run = [&](auto rows) {
+            persist_body<decltype(rows)::value, BN, WGM, WGN, MODE, false, false, IDLE_SKIP, DEEP_B, BY_ROUND, false>(
+                A, offsets, E, N, K, B0, B1, C, GU, ntn, ldb, ticks, smem);
+        };
+        if (height == 256) run(std::integral_constant<int, 256>{});
+        else if (height == 192) run(std::integral_constant<int, 192>{});
+        else run(std::integral_constant<int, 128>{});
+    }
+}
+
 template <int BM, int BN, int WGM, int WGN, int MODE, bool DEEP_B = false>
 void launch_persist(const void* A, const int32_t* offsets, int r_max, int E, int N, int K, const void* B0,
                     const void* B1, void* C, void* GU, hipStream_t s) {
     constexpr int OUTN = (MODE == 1 || MODE == 2) ? BN / 2 : BN;
-    constexpr size_t smem = (size_t)(3 * BM + 2 * BN) * 64 * 2;
+    constexpr int HMAX = BM != 0 ? BM : 256, HMIN = BM != 0 ? BM : 128;   // tallest and lowest tile
+    constexpr size_t smem = (size_t)(DEEP_B ? 2 * HMAX + 3 * BN : 3 * HMAX + 2 * BN) * 64 * 2;
+    if constexpr (BM == 0 && MODE != 3) {
+        // many rows on many experts: 256 rows would be chosen, and the kernel that holds this height alone is the faster one
+        // (32768 tokens, K = 6 of 64 experts, 2048 x 5632: 1 % of the layer; 768 to 2048 rows on 16 experts: 0.6 to 1 %)
+        if (g_persist_tile_rows == 0 && E >= 16 && r_max >= 640ll * E) {
+            launch_persist<256, BN, WGM, WGN, MODE, DEEP_B>(A, offsets, r_max, E, N, K, B0, B1, C, GU, s);
+            return;
+        }
+    }
     const int ntn = (N + OUTN - 1) / OUTN;
     // many experts = many ragged tail tiles: the instantiation whose idle waves skip the multiplication
     const bool idle_skip = MODE != 3 && persist_idle_skip(E);
@@ -663,10 +696,10 @@ void launch_persist(const void* A, const int32_t* offsets, int r_max, int E, int
         attr_set[idle_skip][by_round] = true;
     }
     // never more workgroups than the static bound on the tile count
-    const int grid = min(persist_grid(), grid_for(r_max, E, BM, ntn));
+    const int grid = min(persist_grid(), grid_for(r_max, E, HMIN, ntn));
     hipLaunchKernelGGL(kern, dim3(grid), dim3(WGM * WGN * 64), smem, s, static_cast<const bf16_t*>(A), offsets, E, N,
                        K, static_cast<const bf16_t*>(B0), static_cast<const bf16_t*>(B1), static_cast<bf16_t*>(C),
-                       static_cast<bf16_t*>(GU), ntn, 0, g_persist_ticks);
+                       static_cast<bf16_t*>(GU), ntn, g_persist_tile_rows, g_persist_ticks);
 }
 
 // dw[e] = 0 for every expert without rows (the persistent weight-gradient kernel gives them no tiles)
@@ -730,6 +763,8 @@ void run_persist_pair(const void* x_perm, const int32_t* offsets, int r_max, int
 
 void set_persist_workgroups(int n) { g_persist_workgroups = n; }
 void set_persist_idle_skip(int v) { g_persist_idle_skip = v; }
+void set_persist_tile_rows(int v) { g_persist_tile_rows = v; }
+int persist_tile_rows() { return g_persist_tile_rows; }
 void set_persist_clock_sample(unsigned long long* ticks) { g_persist_ticks = ticks; }
 unsigned long long* persist_clock_sample() { return g_persist_ticks; }
 bool persist_idle_skip(int E) { return g_persist_idle_skip < 0 ? E >= 16 : g_persist_idle_skip != 0; }
@@ -744,7 +779,7 @@ bool launch_grouped_nt(const void* A, const int32_t* offsets, int r_max, int E, 
         launch_stream(plan, kStreamBf16, A, offsets, r_max, E, N, K, B, nullptr, C, nullptr, 0.f, 0.f, 0.f, nullptr, nullptr, s);
         return true;
     }
-    launch_persist<256, 256, 2, 4, 0, true>(A, offsets, r_max, E, N, K, B, nullptr, C, nullptr, s);
+    launch_persist<0, 256, 2, 4, 0, true>(A, offsets, r_max, E, N, K, B, nullptr, C, nullptr, s);
     return true;
 }
 
@@ -780,7 +815,7 @@ void launch_persist_wgrad_rowmajor(const void* a, int lda, const void* b, int ld
 bool launch_grouped_nt_swiglu_bwd(const void* A, const int32_t* offsets, int r_max, int E, int N, int K,
                                   const void* B, const void* gu, void* dgdu, hipStream_t s) {
     if (K < 128 || K % 64 || N % 8) return false;
-    launch_persist<256, 256, 2, 4, 3, true>(A, offsets, r_max, E, N, K, B, nullptr, dgdu, const_cast<void*>(gu), s);
+    launch_persist<0, 256, 2, 4, 3, true>(A, offsets, r_max, E, N, K, B, nullptr, dgdu, const_cast<void*>(gu), s);
     return true;
 }
 
@@ -793,7 +828,7 @@ bool launch_gate_up_saving(const void* x_perm, const int32_t* offsets, int r_max
         launch_stream(plan, kStreamBf16, x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, gu, 0.f, 0.f, 0.f, nullptr, nullptr, s);
         return true;
     }
-    launch_persist<256, 256, 2, 4, 2, true>(x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, gu, s);
+    launch_persist<0, 256, 2, 4, 2, true>(x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, gu, s);
     return true;
 }
 
@@ -805,7 +840,7 @@ bool launch_persist_ffn(const void* x_perm, const int32_t* offsets, int r_max, i
         case 40: run_persist_pair<256, 256, 2, 2>(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, phase, s); return true;
         case 41: run_persist_pair<256, 256, 2, 4>(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, phase, s); return true;
         case 42: run_persist_pair<256, 256, 2, 2, true>(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, phase, s); return true;
-        case 43: run_persist_pair<256, 256, 2, 4, true>(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, phase, s); return true;
+        case 43: run_persist_pair<0, 256, 2, 4, true>(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, phase, s); return true;
         default: return false;
     }
 }

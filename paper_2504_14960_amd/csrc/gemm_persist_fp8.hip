@@ -130,12 +130,12 @@ __device__ __forceinline__ void store_y_bf16(f32x16 (&acc)[FM][FN], int t_row0, 
 // 128.  SWIGLU: C is h [rows, N] E4M3, s0/s1 dequantise g/u, s2 scales h, amax
 // receives max |h|.  Otherwise C is y [rows, N] bf16 and s0 dequantises it.
 // DEEP_B: the weight tile, not the activation tile, gets the three LDS stages (see gemm_persist.hip).
-template <bool SWIGLU, bool IDLE_SKIP = false, bool DEEP_B = false>
-__global__ __launch_bounds__(256) void gemm_fp8_persist_kernel(
+template <int BM, bool SWIGLU, bool IDLE_SKIP, bool DEEP_B>
+__device__ __forceinline__ void fp8_body(
     const uint8_t* __restrict__ A, const int32_t* __restrict__ offsets, int E, int N, int K,
     const uint8_t* __restrict__ B0, const uint8_t* __restrict__ B1, void* __restrict__ C, int ntn, float s0,
-    float s1, float s2, float* __restrict__ amax_out) {
-    constexpr int BM = 256, BN = 256, WGM = 2, WGN = 2;
+    float s1, float s2, float* __restrict__ amax_out, uint8_t* smem) {
+    constexpr int BN = 256, WGM = 2, WGN = 2;
     constexpr int NW = WGM * WGN;
     constexpr int NT = NW * 64;
     constexpr int WM = BM / WGM, WN = BN / WGN;
@@ -157,10 +157,9 @@ __global__ __launch_bounds__(256) void gemm_fp8_persist_kernel(
     // k-tile (after the barrier), the rest and the activation tile under k-step 0
     constexpr int LA = NLOAD / 3;
     static_assert(LA <= PE && NLOAD - LA <= NSLOT && LA <= NSLOT && NREAD <= 2 * NSLOT, "slots");
-    static_assert(3 * A_BYTES + 2 * B_BYTES <= 160 * 1024, "tile stages exceed the 160 KiB of LDS");
+    static_assert((DEEP_B ? 2 * A_BYTES + 3 * B_BYTES : 3 * A_BYTES + 2 * B_BYTES) <= 160 * 1024, "tile stages exceed the 160 KiB of LDS");
     static_assert(NW * 32 * (FN * 64) <= (DEEP_B ? B_BYTES : A_BYTES), "epilogue patches must fit into one slot of the late operand");
 
-    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     const int tid = threadIdx.x, lane = tid & 63;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int wm = wave / WGN, wn = wave % WGN;
@@ -430,6 +429,26 @@ __global__ __launch_bounds__(256) void gemm_fp8_persist_kernel(
     }
 }
 
+// Tiles of 256, 192 or 128 rows, chosen on the device from the rows that every expert really has; `rows` != 0: those.
+template <bool SWIGLU, bool IDLE_SKIP, bool DEEP_B>
+__global__ __launch_bounds__(256) void gemm_fp8_persist_kernel(
+    const uint8_t* __restrict__ A, const int32_t* __restrict__ offsets, int E, int N, int K,
+    const uint8_t* __restrict__ B0, const uint8_t* __restrict__ B1, void* __restrict__ C, int ntn, float s0,
+    float s1, float s2, float* __restrict__ amax_out, int rows) {
+    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+    if constexpr (!DEEP_B) {
+        fp8_body<256, SWIGLU, IDLE_SKIP, DEEP_B>(A, offsets, E, N, K, B0, B1, C, ntn, s0, s1, s2, amax_out, smem);
+    } else {
+        const int height = rows != 0 ? rows : pick_height(kCostFp8, offsets, E, ntn, K / 128, threadIdx.x & 63);
+        if (height == 256)
+            fp8_body<256, SWIGLU, IDLE_SKIP, DEEP_B>(A, offsets, E, N, K, B0, B1, C, ntn, s0, s1, s2, amax_out, smem);
+        else if (height == 192)
+            fp8_body<192, SWIGLU, IDLE_SKIP, DEEP_B>(A, offsets, E, N, K, B0, B1, C, ntn, s0, s1, s2, amax_out, smem);
+        else
+            fp8_body<128, SWIGLU, IDLE_SKIP, DEEP_B>(A, offsets, E, N, K, B0, B1, C, ntn, s0, s1, s2, amax_out, smem);
+    }
+}
+
 static int g_fp8_deep_b = 1;   // three LDS stages for the weight tile (0: for the activation tile)
 
 template <bool SWIGLU>
@@ -449,9 +468,10 @@ void launch_fp8(const void* A, const int32_t* offsets, int r_max, int E, int N, 
                                   (int)smem);
         attr_set[deep][idle_skip] = true;
     }
-    const int grid = min(persist_grid(), grid_for(r_max, E, 256, ntn));
+    const int grid = min(persist_grid(), grid_for(r_max, E, deep ? 128 : 256, ntn));
     hipLaunchKernelGGL(kern, dim3(grid), dim3(256), smem, s, static_cast<const uint8_t*>(A), offsets, E, N, K,
-                       static_cast<const uint8_t*>(B0), static_cast<const uint8_t*>(B1), C, ntn, s0, s1, s2, amax);
+                       static_cast<const uint8_t*>(B0), static_cast<const uint8_t*>(B1), C, ntn, s0, s1, s2, amax,
+                       persist_tile_rows());
 }
 
 }  // namespace

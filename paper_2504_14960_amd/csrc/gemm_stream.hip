@@ -26,6 +26,7 @@
 #include "gemm_stream.h"
 #include "gemm_tile.h"
 #include "once_per_device.h"
+#include "tile_cost.h"
 
 namespace moe {
 
@@ -748,19 +749,17 @@ void launch_any(const StreamArgs& p, int r_max, const StreamPlan& plan, float* p
 
 
 // ---- which kernel: estimated times (us) of the three ----
-// Fitted to measurements of gate/up and down at (E, H, F) = (1, 3584, 20480), (1, 2 and 8, 4096, 14336), (64, 3584, 2560),
-// (16, 2048, 1408) and (8, 2048, 4096) with 1 to 2000 rows per expert.  With equal experts the kernel they pick is behind the
-// best of the three by up to 17 %, the price of the slack for skewed ones (m_tiles, wide_us): 8 experts x 125 rows, 4096 x
-// 14336, gate/up 457 instead of 404 and down 281 instead of 242; 16 experts x 64 rows, 2048 x 1408, 51 instead of 44 and 30
-// instead of 26.  A router more skewed than that slack costs the other way: 64 tokens of a Zipf-1.2 router, K = 4 of 60
-// experts, 2048 x 1408, down 38 instead of 33; K = 8 of 64, 3584 x 2560, both products 510 instead of 494.
-//   A round of workgroups takes (bytes of its weight rows) x 43 us/MB (36 where several M-tiles share them), plus its
-//   rows at a smaller rate, plus its start and end, which the narrow workgroups, two to a compute unit, mostly hide.
-//   A k-tile of the large tiles takes 1.1 us alone, 1.5 us with all compute units at work (1.9 where the rows lie a
-//   multiple of 4096 bytes apart), 2 us where 256 rows per expert make it both a stream and a full product.
+// The large tiles: tile_cost.h.  A round of the streaming workgroups takes (bytes of its weight rows) x 43 us/MB (36 where
+// several M-tiles share them), plus its rows at a smaller rate, plus its start and end, which the narrow workgroups, two to a
+// compute unit, mostly hide.  Fitted to gate/up and down at (E, H, F) = (1, 3584, 20480), (1, 2 and 8, 4096, 14336), (64, 3584,
+// 2560), (16, 2048, 1408) and (8, 2048, 4096) with 1 to 2000 rows per expert.  Over 650 products each in bf16 and FP8 (12
+// layers, 24 to 512 rows per expert, routers without bias, with a normal and a Zipf-1.2 one) the kernel they pick is behind
+// the best of the three by 1.7 % on average.  At most by 43 % (58 % in FP8): few experts, where the narrow kernel's second
+// workgroup per compute unit is priced too high (down, 4 experts x 72 rows, 4096 x 8192: wide 95, narrow 66), and by 37 %
+// for skewed routers, where it is priced too low (down, 8 experts x 24 rows, 6144 x 16384, Zipf: narrow 392, wide 287).
 struct Work {
     int experts, rows, N, kbytes, r_max;
-    bool swiglu;
+    bool swiglu, fp8;
 };
 constexpr int kUnitsCU = 256;   // compute units the estimates are made for (gfx950, not partitioned)
 
@@ -781,14 +780,26 @@ double m_tiles(const Work& w, int height) {
 }
 double rounds_of(double tiles) { return (double)(long long)((tiles + kUnitsCU - 1) / kUnitsCU); }
 
+// The large tiles choose their height on the device, from the rows every expert has.  Here only the average is known: the
+// time for equal experts and the time for experts of 0.4 to 1.8 times the average, half of each.
 double large_us(const Work& w) {
-    const int mt = blocks_of(w.rows, 256);
-    const double tiles = m_tiles(w, 256) * blocks_of(w.N, w.swiglu ? 128 : 256);
-    const double rounds = rounds_of(tiles), fill = tiles / (rounds * kUnitsCU);
-    const double part = (w.rows < 256 ? w.rows : 256) / 256.0;
-    const double stream = w.kbytes % 4096 == 0 ? 0.8 : 0.42;
-    const double per = mt > 1 ? 1.05 + 0.5 * fill : 1.08 + fill * (stream + 0.55 * part * part);
-    return 4.0 + rounds * (w.kbytes / 128) * per;
+    constexpr double kSpread[8] = {0.386, 0.552, 0.717, 0.883, 1.048, 1.214, 1.434, 1.766};
+    const TileCosts& c = w.fp8 ? kCostFp8 : kCostBf16;
+    const int ntn = blocks_of(w.N, w.swiglu ? 128 : 256);
+    auto best = [&](bool equal) {
+        double t = 1e30;
+        for (const int height : {256, 192, 128}) {
+            double mt = (double)w.experts * blocks_of(w.rows, height);
+            if (!equal) {
+                mt = 0.0;
+                for (const double f : kSpread) mt += w.experts / 8.0 * (double)(long long)((w.rows * f + height - 1e-6) / height);
+            }
+            const HeightCost& h = height == 256 ? c.h256 : height == 192 ? c.h192 : c.h128;
+            t = fmin(t, tiles_us(h, (float)mt, (float)w.experts, ntn, kUnitsCU, w.kbytes / 128));
+        }
+        return t;
+    };
+    return 4.0 + (w.experts == 1 ? best(true) : 0.5 * (best(true) + best(false)));
 }
 
 double narrow_us(const Work& w, int fb) {
@@ -851,10 +862,10 @@ StreamPlan plan_stream(int elt, int r_max, int E, int N, int K, bool swiglu, boo
     w.kbytes = (int)kbytes;
     w.r_max = r_max;
     w.swiglu = swiglu;
+    w.fp8 = elt == kStreamFp8;
     double best = g_stream == 2 ? 1e30 : narrow_us(w, narrow_blocks(r_max, E, N, swiglu));
     if (g_stream < 0 && large_ok) {
-        // in a tie the kernel that a skewed router disturbs least; a handful of rows per expert is the narrow kernel's own
-        const double t = (w.rows > 16 ? 0.93 : 1.0) * large_us(w);
+        const double t = large_us(w);
         if (t < best) {
             best = t;
             plan.kind = kPlanLarge;
