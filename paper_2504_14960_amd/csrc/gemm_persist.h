@@ -65,6 +65,36 @@ __device__ __forceinline__ int pick_height(const TileCosts& c, const int32_t* __
     return __builtin_amdgcn_readfirstlane(h);
 }
 
+// A block of at most 32 output rows as a buffer: `rows` rows of `pitch` bytes from `base` on, and stores past them are dropped by the hardware.  A
+// store is thus one instruction whatever lanes have rows or columns to store, so that a wait can count it (see persist_body).
+struct RowBuffer {
+    __amdgpu_buffer_rsrc_t rsrc;
+    __device__ __forceinline__ RowBuffer(void* base, int rows, uint32_t pitch)
+        : rsrc(__builtin_amdgcn_make_buffer_rsrc(base, 0, (int)((uint32_t)min(max(rows, 0), 32) * pitch), 0x00027000)) {}
+    // streamed past the caches, as __builtin_nontemporal_store
+    __device__ __forceinline__ void store(u32x4 v, uint32_t offset) const {
+        __builtin_amdgcn_raw_buffer_store_b128(v, rsrc, (int)offset, 0, 2);
+    }
+};
+constexpr uint32_t kNoColumn = 0x80000000u;   // an offset past the end of every row buffer
+constexpr int kMaxColumns = 1 << 24;          // 32 rows of so many bf16 columns end below kNoColumn
+
+// All but the LOADS youngest vector memory operations of this wave are complete, or, with stores_too (wave-uniform), all but the
+// LOADS + STORES youngest; and its LDS reads are in registers.  stores_too is false afterwards.  In one asm block: of a branch
+// that only the first turn of the k loop takes the compiler makes a second copy of the loop's body, and with 256 accumulators
+// per lane (four waves) that costs 100 registers of scratch memory.
+template <int LOADS, int STORES>
+__device__ __forceinline__ void wait_memory(int& stores_too) {
+    constexpr int ALL = LOADS + STORES;
+    __builtin_amdgcn_s_waitcnt((ALL & 0xF) | ((ALL >> 4) << 14));   // vmcnt(ALL), lgkmcnt(0)
+    if constexpr (STORES != 0) {
+        int flag = uni(stores_too);
+        asm volatile("s_cmp_lg_u32 %0, 0\n\ts_cbranch_scc1 .Lstores%=\n\ts_waitcnt vmcnt(%1)\n.Lstores%=:\n\ts_mov_b32 %0, 0"
+                     : "+s"(flag) : "n"(LOADS) : "scc", "memory");
+        stores_too = flag;
+    }
+}
+
 // wave-uniform description of one output tile
 struct PTile {
     const uint8_t* a;   // first activation row of the tile (k = 0)

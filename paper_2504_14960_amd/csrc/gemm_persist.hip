@@ -82,6 +82,8 @@ __device__ __forceinline__ void store_tile_staged(f32x16 (&acc)[FM][FN], int t_r
     uint8_t* wrow = stage + fr * W + 8 * fk;
     const int rl = lane / GPR, gl = lane % GPR;
     const int col = t_n0 + wn * (FO * 32) + gl * 8;
+    const uint32_t pitch = (uint32_t)N * 2u;
+    const uint32_t c_off = col < N ? (uint32_t)rl * pitch + (uint32_t)col * 2u : kNoColumn;   // STREAM_OUT
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
         // one row block at a time.  With 256 accumulators per lane they live in
@@ -184,6 +186,16 @@ __device__ __forceinline__ void store_tile_staged(f32x16 (&acc)[FM][FN], int t_r
                     *reinterpret_cast<u32x4*>(dst + N) = ou;
                 }
             }
+        } else if constexpr (STREAM_OUT) {
+            const int first = wm * WM + i * 32;
+            const RowBuffer out(C + (size_t)(t_row0 + first) * N, t_rows - first, pitch);
+#pragma unroll
+            for (int it = 0; it < 32 / RPI; ++it) {
+                const int row = it * RPI + rl;
+                const int xr = (row / RP256) & (GPR - 1);
+                const u32x4 v = *reinterpret_cast<const u32x4*>(stage + row * W + ((gl ^ xr) << 4));
+                out.store(v, c_off + (uint32_t)(it * RPI) * pitch);
+            }
         } else {
 #pragma unroll
             for (int it = 0; it < 32 / RPI; ++it) {
@@ -191,11 +203,7 @@ __device__ __forceinline__ void store_tile_staged(f32x16 (&acc)[FM][FN], int t_r
                 const int xr = (row / RP256) & (GPR - 1);
                 const u32x4 v = *reinterpret_cast<const u32x4*>(stage + row * W + ((gl ^ xr) << 4));
                 const int grow = wm * WM + i * 32 + row;
-                if (grow < t_rows && col < N) {
-                    u32x4* const dst = reinterpret_cast<u32x4*>(C + (size_t)(t_row0 + grow) * N + col);
-                    if constexpr (STREAM_OUT) __builtin_nontemporal_store(v, dst);
-                    else *dst = v;
-                }
+                if (grow < t_rows && col < N) *reinterpret_cast<u32x4*>(C + (size_t)(t_row0 + grow) * N + col) = v;
             }
         }
     }
@@ -219,7 +227,7 @@ __device__ __forceinline__ void store_tile_staged(f32x16 (&acc)[FM][FN], int t_r
 // ahead) and two stages for the weight tile; true: the other way round -- the weights are what streams in from
 // HBM (every weight byte is used by one M-group only), the activation panels are re-read from the caches.
 template <int BM, int BN, int WGM, int WGN, int MODE, bool GROUPK, bool KMAJ, bool IDLE_SKIP, bool DEEP_B, bool BY_ROUND,
-          bool STREAM_OUT>
+          bool STREAM_OUT, bool AHEAD>
 __device__ __forceinline__ void persist_body(
     const bf16_t* __restrict__ A, const int32_t* __restrict__ offsets, int E, int N, int K,
     const bf16_t* __restrict__ B0, const bf16_t* __restrict__ B1, bf16_t* __restrict__ C, bf16_t* __restrict__ GU,
@@ -248,8 +256,15 @@ __device__ __forceinline__ void persist_body(
     constexpr int NMFMA = FM * FN;
     constexpr int NSLOT = NREAD;
     constexpr int MPS = NMFMA / NSLOT;
-    // a period's loads are spread over the k-steps 3 (of the previous k-tile), 0 and 1
-    constexpr int LA = NLOAD / 3;
+    // A period's loads are spread over the k-steps 3 (of the previous k-tile), 0 and 1; AHEAD: all of the early operand's
+    // under k-step 3
+    constexpr int LA = AHEAD ? PE : NLOAD / 3;
+    // STREAM_OUT: stores of a tile's epilogue, per wave (RowBuffer).  Loads and stores are counted together and complete in
+    // order, and a wait for the loads behind an epilogue is a wait for its stores.  All that the first period of a tile waits
+    // for was asked for in front of the stores of the tile before (LA = PE), so it need not wait for them; the second period,
+    // 1.5 us later, does.  (Three gradients of 64 experts x 172 rows, 6144 x 2048: 1738 us waiting at once, 1643 so, 1222 with
+    // no stores at all; of 64 x 390, 5248 x 1792: 1780 and 1720.)
+    constexpr int NSTORE = STREAM_OUT ? FM * (32 / (1024 / (FN * 64))) : 0;
     constexpr int LB = LA + (NLOAD - LA + 1) / 2;
     constexpr int LC = NLOAD;
     // fragment reads per slot of a k-step: one (spread over the whole k-step) with eight waves, whose LDS pipe is
@@ -259,8 +274,9 @@ __device__ __forceinline__ void persist_body(
     static_assert(BM % RPP == 0 && BN % RPP == 0 && RPP % 8 == 0, "tile rows must divide into fetch passes");
     static_assert(!SWIGLU || ((BN / 2) % RPP == 0 && FN % 2 == 0), "gate/up halves must be pass- and fragment-aligned");
     static_assert(LA <= PE, "only loads of the early operand may be issued under k-step 3");
+    static_assert(PL + NSTORE < 64, "vmcnt holds 6 bits");
+    static_assert(NSTORE == 0 || LA == PE, "all that a tile's first period waits for precedes the epilogue");
     static_assert(LB - LA <= NSLOT && LC - LB <= NSLOT && LA <= NSLOT, "not enough slots for the loads");
-    static_assert(PL < 64, "vmcnt holds 6 bits");
     static_assert((DEEP_B ? 2 * A_BYTES + 3 * B_BYTES : 3 * A_BYTES + 2 * B_BYTES) <= 160 * 1024, "tile stages exceed the 160 KiB of LDS");
     static_assert(NW * 32 * FO * 64 <= (DEEP_B ? B_BYTES : A_BYTES), "epilogue patches must fit into one slot of the late operand");
 
@@ -545,6 +561,7 @@ __device__ __forceinline__ void persist_body(
             const int tb = b0; b0 = b1; b1 = tb;
         }
     };
+    int stored = 0;   // the epilogue of a tile has just been through
     for (;;) {
         // (IDLE_SKIP instantiations, chosen for launches with many experts, i.e. many ragged tails; the test costs
         // the plain kernel half a per cent.)  A wave whose rows of the tile all lie past the tile's last valid row
@@ -570,7 +587,7 @@ __device__ __forceinline__ void persist_body(
             }
             const uint8_t* ca = a_region + a0;
             const uint8_t* cb = b_region + b0;
-            // this period fills early(kt+1) and late(kt+2)
+            // this period fills the rest of early(kt+1), late(kt+2) and, once k-tile kt is read, the head of early(kt+2)
             uint8_t* lb = b_region + (DEEP_B ? b2 : b1);
             uint8_t* la = a_region + (DEEP_B ? a1 : a2);
             __builtin_amdgcn_sched_barrier(0);
@@ -580,10 +597,9 @@ __device__ __forceinline__ void persist_body(
                 kstep(0, ca, cb, 3, LC, LC, s1, s2, lb, la, [&] { s3 = src(kt + 3); });  // k-step 2
             else
                 kstep(0, ca, cb, 3, LC, LC, s1, s2, lb, la, nothing);
-            // early(kt+1) was issued before late(kt+2) in this period and late(kt+1) a period
-            // ago: all but the PL youngest loads must have landed; this wave's
-            // fragment reads of k-tile kt are in registers (lgkmcnt(0))
-            __builtin_amdgcn_s_waitcnt((PL & 0xF) | ((PL >> 4) << 14));
+            // early(kt+1) was issued before late(kt+2) in this period and late(kt+1) a period ago: all but the PL youngest
+            // loads must have landed; this wave's fragment reads of k-tile kt are in registers
+            wait_memory<PL, NSTORE>(stored);
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
             // k-step 3: first fragments of k-tile kt+1; the early operand's slot of k-tile
@@ -602,7 +618,7 @@ __device__ __forceinline__ void persist_body(
                 uint8_t* la = a_region + (DEEP_B ? a1 : a2);
 #pragma unroll
                 for (int i = LA; i < LC; ++i) fetch_one(i, s1, s2, lb, la);
-                __builtin_amdgcn_s_waitcnt((PL & 0xF) | ((PL >> 4) << 14));
+                wait_memory<PL, NSTORE>(stored);
                 __builtin_amdgcn_s_barrier();
 #pragma unroll
                 for (int i = 0; i < LA; ++i) fetch_one(i, s2, s2, b_region + b0, a_region + a0);
@@ -625,6 +641,7 @@ __device__ __forceinline__ void persist_body(
         if (GROUPK) c_kt = n_kt;
         if (KMAJ) c_krows = n_krows;
         ++ti;
+        stored = 1;
         fetch_next_tile(ti + 1);
 #pragma unroll
         for (int i = 0; i < FM; ++i)
@@ -645,19 +662,19 @@ __device__ __forceinline__ void persist_body(
 // BM = 0: the height of the tiles is chosen on the device, from the rows that every expert really has (pick_height);
 // 256, 192 or 128 rows, all of BN = 256 columns (ldb: a height to be taken instead, or 0).  A row's sums are formed in the same order whatever the height.
 template <int BM, int BN, int WGM, int WGN, int MODE, bool GROUPK = false, bool KMAJ = false, bool IDLE_SKIP = false,
-          bool DEEP_B = false, bool BY_ROUND = true, bool STREAM_OUT = false>
+          bool DEEP_B = false, bool BY_ROUND = true, bool STREAM_OUT = false, bool AHEAD = false>
 __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_persist_kernel(
     const bf16_t* __restrict__ A, const int32_t* __restrict__ offsets, int E, int N, int K,
     const bf16_t* __restrict__ B0, const bf16_t* __restrict__ B1, bf16_t* __restrict__ C, bf16_t* __restrict__ GU,
     int ntn, int ldb, unsigned long long* __restrict__ ticks) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     if constexpr (BM != 0) {
-        persist_body<BM, BN, WGM, WGN, MODE, GROUPK, KMAJ, IDLE_SKIP, DEEP_B, BY_ROUND, STREAM_OUT>(A, offsets, E, N, K, B0, B1, C,
-                                                                                                  GU, ntn, ldb, ticks, smem);
+        persist_body<BM, BN, WGM, WGN, MODE, GROUPK, KMAJ, IDLE_SKIP, DEEP_B, BY_ROUND, STREAM_OUT, AHEAD>(
+            A, offsets, E, N, K, B0, B1, C, GU, ntn, ldb, ticks, smem);
     } else {
         const int height = ldb != 0 ? ldb : pick_height(kCostBf16, offsets, E, ntn, K / 64, threadIdx.x & 63);
         auto run = [&](auto rows) {
-            persist_body<decltype(rows)::value, BN, WGM, WGN, MODE, false, false, IDLE_SKIP, DEEP_B, BY_ROUND, false>(
+            persist_body<decltype(rows)::value, BN, WGM, WGN, MODE, false, false, IDLE_SKIP, DEEP_B, BY_ROUND, false, AHEAD>(
                 A, offsets, E, N, K, B0, B1, C, GU, ntn, ldb, ticks, smem);
         };
         if (height == 256) run(std::integral_constant<int, 256>{});
@@ -685,15 +702,29 @@ void launch_persist(const void* A, const int32_t* offsets, int r_max, int E, int
     const bool idle_skip = MODE != 3 && persist_idle_skip(E);
     // few experts: whole rounds of tiles are dealt to the XCDs round by round; many: contiguous shares (measured)
     const bool by_round = MODE == 3 || E < 16;
-    auto kern = idle_skip ? (by_round ? gemm_bf16_persist_kernel<BM, BN, WGM, WGN, MODE, false, false, (MODE != 3), DEEP_B, true>
-                                      : gemm_bf16_persist_kernel<BM, BN, WGM, WGN, MODE, false, false, (MODE != 3), DEEP_B, false>)
-                          : (by_round ? gemm_bf16_persist_kernel<BM, BN, WGM, WGN, MODE, false, false, false, DEEP_B, true>
-                                      : gemm_bf16_persist_kernel<BM, BN, WGM, WGN, MODE, false, false, false, DEEP_B, false>);
-    static bool attr_set[2][2] = {{false, false}, {false, false}};
-    if (!attr_set[idle_skip][by_round]) {
+    // Few rows per expert: all of the early operand's loads a whole period ahead.  The launch is a stream of weights then, and
+    // the activations, queued behind them, are what the barrier waits for (us, as usual / ahead: 64 experts x 390 rows, 5248 x
+    // 1792, gate/up 1120 / 988; 64 x 345, 6784 x 896, gate/up 613 / 589, dx 565 / 523; 8 x 512 rows, 4096 x 14336, down 548 /
+    // 496).  With more rows the loads after the barrier get in the way of its fragment reads: 8 x 600 rows, gate/up 1036 /
+    // 1110, while the down product (half the output per row read) is 560 / 516 there; from 2000 rows on both lose 2 to 8 %.
+    // The backward's dh (MODE 3) loses 3 to 13 % at every size.
+    constexpr bool CAN_AHEAD = BM == 0 && MODE != 3;
+    const bool ahead = CAN_AHEAD && r_max < (MODE == 0 ? 640ll : 448ll) * E;
+    constexpr bool SKIP = MODE != 3;
+    auto pick = [&](auto skip, auto round) {
+        constexpr bool S = decltype(skip)::value, R = decltype(round)::value;
+        return ahead ? gemm_bf16_persist_kernel<BM, BN, WGM, WGN, MODE, false, false, S, DEEP_B, R, false, CAN_AHEAD>
+                     : gemm_bf16_persist_kernel<BM, BN, WGM, WGN, MODE, false, false, S, DEEP_B, R, false, false>;
+    };
+    using Yes = std::true_type;
+    using No = std::false_type;
+    using Skip = std::integral_constant<bool, SKIP>;
+    auto kern = idle_skip ? (by_round ? pick(Skip{}, Yes{}) : pick(Skip{}, No{})) : (by_round ? pick(No{}, Yes{}) : pick(No{}, No{}));
+    static bool attr_set[2][2][2] = {};
+    if (!attr_set[idle_skip][by_round][ahead]) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
                                   (int)smem);
-        attr_set[idle_skip][by_round] = true;
+        attr_set[idle_skip][by_round][ahead] = true;
     }
     // never more workgroups than the static bound on the tile count
     const int grid = min(persist_grid(), grid_for(r_max, E, HMIN, ntn));
@@ -718,7 +749,7 @@ template <int BM, int BN, int WGM, int WGN, bool STREAM_OUT>
 void launch_persist_groupk(const void* A, const void* B, const int32_t* offsets, int E, int M, int N, int ld,
                            void* C, hipStream_t s) {
     constexpr size_t smem = (size_t)(3 * BM + 2 * BN) * 64 * 2;
-    auto kern = gemm_bf16_persist_kernel<BM, BN, WGM, WGN, 0, true, false, false, false, true, STREAM_OUT>;
+    auto kern = gemm_bf16_persist_kernel<BM, BN, WGM, WGN, 0, true, false, false, false, true, STREAM_OUT, STREAM_OUT>;
     static bool attr_set = false;
     if (!attr_set) {
         (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
@@ -798,7 +829,7 @@ void launch_persist_wgrad(const void* a_t, const void* b_t, const int32_t* offse
     //   8 experts, 4096 x 4096:  256 rows 703 / 625, 512 rows 900 / 832, 1024 rows 1539 / 1505, 1536 rows 2178 / 2169
     // With 8 experts x 2048 rows, 6144 x 16384, the layer's forward and backward are 0.4 % slower for it: the line lies below
     // where the two meet.
-    if (ld <= 640ll * E)   // up to some 512 rows per expert, the padding included
+    if (ld <= 640ll * E && N <= kMaxColumns)   // up to some 512 rows per expert, the padding included
         launch_persist_groupk<256, 256, 2, 4, true>(a_t, b_t, offsets, E, M, N, ld, dw, s);
     else
         launch_persist_groupk<256, 256, 2, 4, false>(a_t, b_t, offsets, E, M, N, ld, dw, s);
