@@ -376,12 +376,14 @@ __global__ __launch_bounds__(256) void router_bf16_kernel(
 // straight from memory to the matrix instruction's registers (lane group j holds bytes 32 j .. 32 j + 31 of a 128-byte
 // step of both, so whole lines are asked for; the order inside a step plays no part in a dot product).  The partial
 // sums are added in wave order (fixed => reproducible).
+// SELECT (E <= 16: a workgroup holds all logits of its tokens): the selection as well, sixteen lanes per token.
 constexpr int kSplitWaves = 16;
 
-template <int MB>
+template <int MB, bool SELECT>
 __global__ __launch_bounds__(kSplitWaves * 64) void router_logits_kernel(
     const bf16_t* __restrict__ x, const bf16_t* __restrict__ w, const float* __restrict__ bias,
-    float* __restrict__ logits, int T, int H, int E, int tb, int eg) {
+    float* __restrict__ logits, int T, int H, int E, int tb, int eg, int K, int renorm,
+    int32_t* __restrict__ topk_idx, float* __restrict__ topk_gate) {
     constexpr int LD = 20;                     // row of a partial tile: the four lane groups of a store hit different banks
     constexpr int U = MB == 1 ? 4 : 3;         // steps in flight
     __shared__ float part[kSplitWaves][16 * MB][LD];
@@ -435,6 +437,36 @@ __global__ __launch_bounds__(kSplitWaves * 64) void router_logits_kernel(
         for (int ww = 1; ww < kSplitWaves; ++ww) v += part[ww][lt][le];
         if (bias) v += bias[e0 + le];
         logits[(size_t)(t0 + lt) * E + e0 + le] = v;
+        if (SELECT) part[0][lt][le] = (v != v) ? -INFINITY : v;   // NaN ranks last; read back by its own wave's lanes only
+    }
+    if constexpr (SELECT) {
+        // the sixteen lanes that summed a token's logits select its experts: the rank of an expert is the number of experts in
+        // front of it (value descending, index ascending), as in topk_rank_kernel
+        const int le = lane & 15;
+        for (int lt = threadIdx.x >> 4; lt < 16 * MB; lt += kSplitWaves * 4) {
+            if (lt >= tb || t0 + lt >= T) break;
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const float v = le < E ? part[0][lt][le] : -INFINITY;
+            float m = v;
+            int rank = 0;
+            for (int e = 0; e < E; ++e) {
+                const float s = part[0][lt][e];
+                rank += e < le ? s >= v : s > v;
+                m = fmaxf(m, s);
+            }
+            float p = le < E ? expf(v - m) : 0.f, z = p;
+            for (int off = 8; off > 0; off >>= 1) z += __shfl_xor(z, off, 16);
+            p = p / z;
+            const bool chosen = le < E && rank < K;
+            float gsum = chosen ? p : 0.f;
+            if (renorm)
+                for (int off = 8; off > 0; off >>= 1) gsum += __shfl_xor(gsum, off, 16);
+            if (chosen) {
+                topk_idx[(size_t)(t0 + lt) * K + rank] = le;
+                topk_gate[(size_t)(t0 + lt) * K + rank] = renorm ? p / gsum : p;
+            }
+        }
     }
 }
 
@@ -609,6 +641,10 @@ void launch_bf16(const void* x, const void* w, const float* bias, float* logits,
 // The line lies at 64 KB of router weight, from where on the two launches are ahead for every number of tokens; below, down to
 // some 24 KB, they are by up to 3 us for most.
 constexpr int kSplitMaxTokens = 2048, kSplitMinWeights = 32768;
+// Up to 16 experts, logits and selection in one launch of the split kernel (us, H x experts; the kernel for many tokens / logits +
+// selection / so): 4096 x 8, 1 token 8.3 / 6.7 / 5.8, 64 tokens 8.6 / 7.3 / 6.2, 2048 11.2 / 10.5 / 7.9, 4096 14.2 / - / 9.5, 8192
+// 21.2 / - / 19.3; 6144 x 8, 8192 tokens 25.2 / - / 27.9; 1000 x 12, 777 tokens 7.1 / 6.3 / 4.2; 1600 x 16, 11500 14.8 / - / 15.3.
+constexpr int kOneBlockMaxTokens = 4096;
 // Selection alone, lists of eight lanes / by rank (us, 64 experts, K = 8): 1024 tokens 10.2 / 4.1, 4096 tokens 10.3 / 6.7,
 // 16384 tokens 13.3 / 13.1; 128 experts 17.1 / 13.1 at 4096.
 constexpr int kRankMaxTokens = 4096;
@@ -644,6 +680,16 @@ void launch_router(const void* x, const void* w, const float* bias, float* logit
         return;
     }
     const int nb = (E + 15) / 16;
+    if (nb == 1 && g_router_tile == 0 && T <= kOneBlockMaxTokens) {
+        // all experts in a workgroup; tokens per workgroup: as few as leave every workgroup a compute unit
+        int tb = T >= 1024 ? 32 : 16;
+        while (tb > 2 && (T + tb / 2 - 1) / (tb / 2) <= 256) tb /= 2;
+        const dim3 grid((T + tb - 1) / tb);
+        auto kern = tb > 16 ? router_logits_kernel<2, true> : router_logits_kernel<1, true>;
+        hipLaunchKernelGGL(kern, grid, dim3(kSplitWaves * 64), 0, s, static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(w), bias,
+                           logits, T, H, E, tb, 16, K, renorm, idx, gate);
+        return;
+    }
     if (nb <= 8 && (g_router_tile == 8 || (g_router_tile == 0 && T <= kSplitMaxTokens && (long long)E * H >= kSplitMinWeights))) {
         // Tokens and experts per workgroup: halve the larger side while that still gives every workgroup a compute unit
         const bool wide = T >= 1024;
@@ -657,11 +703,11 @@ void launch_router(const void* x, const void* w, const float* bias, float* logit
         }
         const dim3 grid((T + tb - 1) / tb, (E + eg - 1) / eg);
         if (tb > 16)
-            hipLaunchKernelGGL((router_logits_kernel<2>), grid, dim3(kSplitWaves * 64), 0, s, static_cast<const bf16_t*>(x),
-                               static_cast<const bf16_t*>(w), bias, logits, T, H, E, tb, eg);
+            hipLaunchKernelGGL((router_logits_kernel<2, false>), grid, dim3(kSplitWaves * 64), 0, s, static_cast<const bf16_t*>(x),
+                               static_cast<const bf16_t*>(w), bias, logits, T, H, E, tb, eg, K, renorm, idx, gate);
         else
-            hipLaunchKernelGGL((router_logits_kernel<1>), grid, dim3(kSplitWaves * 64), 0, s, static_cast<const bf16_t*>(x),
-                               static_cast<const bf16_t*>(w), bias, logits, T, H, E, tb, eg);
+            hipLaunchKernelGGL((router_logits_kernel<1, false>), grid, dim3(kSplitWaves * 64), 0, s, static_cast<const bf16_t*>(x),
+                               static_cast<const bf16_t*>(w), bias, logits, T, H, E, tb, eg, K, renorm, idx, gate);
         launch_topk(logits, T, E, K, renorm, idx, gate, s);
         return;
     }

@@ -35,6 +35,34 @@ def test_experts_spread_over_workgroups(T, H, E, K, bias, renorm):
     np.testing.assert_allclose(gate, want_gate, rtol=GATE_RTOL, atol=2e-5)   # a softmax moves by at most delta / 4
 
 
+@pytest.mark.parametrize("T,H,E,K,bias,renorm", [
+    (1, 4096, 8, 2, None, True),            # one token
+    (3, 40, 1, 1, None, False),             # one expert; a step that is mostly past the row
+    (255, 264, 5, 5, "normal", True),       # every expert selected
+    (513, 1032, 12, 3, None, False),        # four tokens per workgroup, one of them in the last
+    (1023, 136, 16, 4, "normal", True),     # sixteen experts, no padding
+    (2048, 72, 15, 9, None, True),          # 32 tokens per workgroup in two blocks
+    (4096, 64, 3, 2, "normal", False),      # the most tokens
+])
+def test_router_and_selection_of_up_to_16_experts_in_one_launch(T, H, E, K, bias, renorm):
+    cfg = get_config("mixtral8x7b").scaled(T=T, H=H, E=E, K=K, bias=bias, seed=3200 + E)
+    inp = make_layer_inputs(cfg, ["x", "w_router", "bias"])
+    guard_margins(inp, K)
+    l64 = oracle.router_logits(inp["x"], inp["w_router"], inp.bias)
+    logits, idx, gate = _gpu_topk(np.zeros((T, E), np.float32), K, renorm, inp["x"], inp["w_router"], inp.bias)
+    assert np.abs(logits - l64).max() <= LOGIT_ATOL
+    want_idx, want_gate = oracle.topk_gates(logits, K, renorm)     # the selection on the kernel's own logits
+    np.testing.assert_array_equal(idx, want_idx)
+    np.testing.assert_allclose(gate, want_gate, rtol=GATE_RTOL, atol=1e-6)
+    if E > 1:                                                      # equal weight rows: exact ties, lower index first
+        w = inp["w_router"].copy()
+        w[1::2] = w[0]
+        logits, idx, gate = _gpu_topk(np.zeros((T, E), np.float32), K, renorm, inp["x"], w, None)
+        want_idx, want_gate = oracle.topk_gates(logits, K, renorm)
+        np.testing.assert_array_equal(idx, want_idx)
+        np.testing.assert_allclose(gate, want_gate, rtol=GATE_RTOL, atol=1e-6)
+
+
 @pytest.mark.parametrize("kind", ["ties", "all_equal", "subnormal"])
 @pytest.mark.parametrize("T,E,K", [(3, 64, 64), (5, 63, 8), (4, 128, 5), (4096, 65, 2), (4097, 65, 2)])
 def test_selection_by_rank(kind, T, E, K):
