@@ -553,7 +553,8 @@ moe_status_t moe_gemm_clock_sample(uint64_t* ticks);
  * are raised to 8); "gemm_tile_rows" (rows of the tiles of the persistent expert kernels,
  * 256, 192 or 128; 0, the default = chosen on the device from the rows every expert has; the
  * results do not depend on it); "router_tile" (16-token blocks per router workgroup: 1, 2
- * or 4; 8 = experts spread over workgroups, the selection a launch of its own; 0 = chosen by size); "wgrad_rowmajor" (1 = the expert FFN's backward
+ * or 4; 8 = experts spread over workgroups, the selection a launch of its own; 16 = tiles of
+ * tokens and experts for 17 to 128 experts and H a multiple of 64; 0 = chosen by size); "wgrad_rowmajor" (1 = the expert FFN's backward
  * forms the weight gradients straight from the row-major activations with
  * transposing LDS loads instead of from transposed copies: about 1.8x slower
  * weight-gradient GEMMs, no ragged transposes; default 0); "permute_fused" (1, the default: layers with at most 8 experts and at most

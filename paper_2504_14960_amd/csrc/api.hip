@@ -935,8 +935,8 @@ moe_status_t moe_set_option(const char* name, int value) {
         return MOE_OK;
     }
     if (name && strcmp(name, "router_tile") == 0) {
-        if (value != 0 && value != 1 && value != 2 && value != 4 && value != 8)
-            return fail(MOE_ERR_INVALID_ARG, "moe_set_option: router_tile must be 0, 1, 2, 4 or 8");
+        if (value != 0 && value != 1 && value != 2 && value != 4 && value != 8 && value != 16)
+            return fail(MOE_ERR_INVALID_ARG, "moe_set_option: router_tile must be 0, 1, 2, 4, 8 or 16");
         moe::set_router_tile(value);
         return MOE_OK;
     }

@@ -11,6 +11,7 @@
 // group per token, with butterfly reductions on (value desc, index asc) keys.
 // With few tokens the same work is spread over more workgroups (router_logits_kernel), the selection a launch of its own.
 #include "common.h"
+#include "once_per_device.h"
 
 namespace moe {
 
@@ -470,6 +471,120 @@ __global__ __launch_bounds__(kSplitWaves * 64) void router_logits_kernel(
     }
 }
 
+// ------------------------------------------------------------------ bf16 / MFMA, many experts and many tokens
+// TM tokens x TE experts a workgroup, both operands through one ring of LDS stages (64 elements of the TM + TE rows, direct
+// global-to-LDS loads, rows swizzled as in the grouped GEMMs).  What bounds it is what a compute unit takes in, (TM + TE) rows
+// for TM x TE logits, so both sides are tall; router_bf16_kernel reads all experts for 16 to 64 tokens.  The four waves
+// share the 32 x 32 blocks, or split a stage's contraction where there are fewer than four (the partial sums are added in
+// wave order).  SELECT: TE >= E, and the workgroup selects for its tokens.  H is a multiple of 64.
+template <int TM, int TE>
+constexpr int router_tile_stages() {
+    constexpr int per = (TM + TE) / 32, fit = 144 * 1024 / ((TM + TE) * 128);
+    return fit < 8 ? fit : per * 6 < 64 ? 8 : 63 / per + 2;
+}
+
+template <int TM, int TE, bool SELECT>
+__global__ __launch_bounds__(256) void router_tile_kernel(
+    const bf16_t* __restrict__ x, const bf16_t* __restrict__ w, const float* __restrict__ bias,
+    float* __restrict__ logits, int T, int H, int E, int K, int renorm,
+    int32_t* __restrict__ topk_idx, float* __restrict__ topk_gate) {
+    constexpr int PER = (TM + TE) / 32;                 // direct loads per thread and stage: 32 rows each
+    constexpr int STAGE = (TM + TE) * 128;
+    constexpr int S = router_tile_stages<TM, TE>();
+    constexpr int NTE = TE / 32, NT = TM / 32 * NTE;    // 32 x 32 blocks
+    constexpr int KS = NT >= 4 ? 1 : 4 / NT;            // waves that share a block's contraction
+    constexpr int BPW = NT >= 4 ? NT / 4 : 1;           // blocks per wave, of the same tokens
+    constexpr int LD = TE + 1;
+    static_assert(S >= 3 && (S - 2) * PER < 64 && BPW <= NTE && TM * LD * 4 <= S * STAGE, "ring");
+    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int t0 = blockIdx.x * TM, e0 = blockIdx.y * TE;
+    const int block = KS == 1 ? wave * BPW : wave % NT, ks = KS == 1 ? 0 : wave / NT;
+    const int tm = block / NTE, te = block % NTE;
+
+    // load q covers rows 32 q .. 32 q + 31 of the stage: the tokens, then the experts (the last one again past the end)
+    const uint8_t* src[PER];
+#pragma unroll
+    for (int q = 0; q < PER; ++q) {
+        const int row = 32 * q + (tid >> 3);
+        const bf16_t* r = 32 * q < TM ? x + (size_t)min(t0 + row, T - 1) * H : w + (size_t)min(e0 + row - TM, E - 1) * H;
+        src[q] = reinterpret_cast<const uint8_t*>(r) + 16 * ((tid & 7) ^ lds_swizzle(row));
+    }
+    const int nst = H / 64;
+    const int rot = (int)(((blockIdx.x + blockIdx.y * 5u) * 7u) % (unsigned)nst);   // see router_bf16_kernel
+    auto issue = [&](int slot, int s) {
+        int sr = s + rot;
+        sr = sr >= nst ? sr - nst : sr;
+        const size_t k = s >= nst ? 0 : (size_t)sr * 128;   // past the last stage: the first again, never used
+#pragma unroll
+        for (int q = 0; q < PER; ++q)
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(src[q] + k),
+                                             (__attribute__((address_space(3))) void*)(smem + slot * STAGE + (q * 32 + wave * 8) * 128),
+                                             16, 0, 0);
+    };
+    f32x16 acc[BPW];
+#pragma unroll
+    for (int b = 0; b < BPW; ++b)
+#pragma unroll
+        for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
+    const int fr = lane & 31, fk = lane >> 5, sw = lds_swizzle(fr);
+    const uint8_t* const xrow = smem + (tm * 32 + fr) * 128;
+    const uint8_t* const wrow = smem + (TM + te * 32 + fr) * 128;
+#pragma unroll
+    for (int d = 0; d < S - 1; ++d) issue(d, d);
+    int slot = 0, fill = S - 1;
+    for (int s = 0; s < nst; ++s) {
+        // this wave's loads of the stage have landed, its reads of the stage before are in registers
+        constexpr int W = (S - 2) * PER;
+        __builtin_amdgcn_s_waitcnt((W & 0xF) | ((W >> 4) << 14) | 0x70);
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_sched_barrier(0);
+        issue(fill, s + S - 1);
+#pragma unroll
+        for (int q = 0; q < 4 / KS; ++q) {
+            const int c = ((2 * (ks * (4 / KS) + q) + fk) ^ sw) * 16;
+            const bf16x8 a = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(xrow + slot * STAGE + c));
+#pragma unroll
+            for (int b = 0; b < BPW; ++b) {
+                const bf16x8 e = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(wrow + slot * STAGE + b * 4096 + c));
+                acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(e, a, acc[b], 0, 0, 0);
+            }
+        }
+        slot = slot + 1 == S ? 0 : slot + 1;
+        fill = fill + 1 == S ? 0 : fill + 1;
+    }
+    __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0), lgkmcnt(0): nothing lands in the ring any more
+    __syncthreads();
+    // a lane holds token 32 tm + fr and, of each block, experts 8 q + 4 fk + 0 .. 3
+    float* const red = reinterpret_cast<float*>(smem);
+#pragma unroll
+    for (int kk = 0; kk < KS; ++kk) {
+        if (ks == kk) {
+#pragma unroll
+            for (int b = 0; b < BPW; ++b)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    float* p = red + (tm * 32 + fr) * LD + (te + b) * 32 + 8 * (v >> 2) + 4 * fk + (v & 3);
+                    *p = kk == 0 ? acc[b][v] : *p + acc[b][v];
+                }
+        }
+        __syncthreads();
+    }
+    const int cols = min(TE, E - e0);
+    for (int i = tid; i < TM * cols; i += 256) {
+        const int lt = i / cols, e = i - lt * cols;
+        float v = red[lt * LD + e];
+        if (bias) v += bias[e0 + e];
+        if (SELECT) red[lt * LD + e] = v;
+        if (t0 + lt < T) logits[(size_t)(t0 + lt) * E + e0 + e] = v;
+    }
+    if constexpr (SELECT) {
+        __syncthreads();
+        select_tokens(red, LD, TM, t0, T, E, K, renorm, topk_idx, topk_gate);
+    }
+}
+
 // Selection by rank, one wave per token: lane l holds the logits of experts l, l + 64, ..; the rank of an expert is the
 // number of experts in front of it (value descending, index ascending), counted against every logit in turn, and the
 // experts of rank < K write the slots.  No sorted lists, so the chain of dependent instructions is short: what counts
@@ -629,6 +744,19 @@ void launch_bf16(const void* x, const void* w, const float* bias, float* logits,
                        H, E, K, renorm, idx, gate);
 }
 
+template <int TM, int TE, bool SELECT>
+void launch_tile(const void* x, const void* w, const float* bias, float* logits, int T, int H, int E, int K, int renorm,
+                 int32_t* idx, float* gate, hipStream_t s) {
+    constexpr int smem = router_tile_stages<TM, TE>() * (TM + TE) * 128;
+    auto kern = router_tile_kernel<TM, TE, SELECT>;
+    static OncePerDevice lds;
+    int device = -1;   // unknown: set it every time
+    (void)hipGetDevice(&device);
+    lds.run(device, [&] { (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem); });
+    hipLaunchKernelGGL(kern, dim3((T + TM - 1) / TM, (E + TE - 1) / TE), dim3(256), smem, s, static_cast<const bf16_t*>(x),
+                       static_cast<const bf16_t*>(w), bias, logits, T, H, E, K, renorm, idx, gate);
+}
+
 }  // namespace
 
 // Where the experts are spread over workgroups (one launch before / logits + selection after, us, H = 3584):
@@ -644,7 +772,35 @@ constexpr int kSplitMaxTokens = 2048, kSplitMinWeights = 32768;
 // Up to 16 experts, logits and selection in one launch of the split kernel (us, H x experts; the kernel for many tokens / logits +
 // selection / so): 4096 x 8, 1 token 8.3 / 6.7 / 5.8, 64 tokens 8.6 / 7.3 / 6.2, 2048 11.2 / 10.5 / 7.9, 4096 14.2 / - / 9.5, 8192
 // 21.2 / - / 19.3; 6144 x 8, 8192 tokens 25.2 / - / 27.9; 1000 x 12, 777 tokens 7.1 / 6.3 / 4.2; 1600 x 16, 11500 14.8 / - / 15.3.
+// With a large router weight a handful of tokens is better off with the experts spread (6 tokens, 6144 x 16: 1.5 us).
 constexpr int kOneBlockMaxTokens = 4096;
+// router_tile_kernel, from so many logits on (us in the layer, the kernels before / so): 2048 tokens, 6144 x 64 24.8 / 19.8, 1400,
+// 5248 x 128 34.4 / 15.5, 1473, 4096 x 60 16.4 / 12.3, 3684, 6784 x 64 53 / 25 + 7 for the selection, 4164, 5248 x 64 44 / 32, 20882,
+// 5760 x 128 239 / 120 + 24; 905, 4032 x 64 10.9 / 11.8; 32768, 2048 x 64 113 / 117 (the read of x, whatever the tile).
+constexpr long long kTileMinLogits = 80000;
+struct RouterTile {
+    int tokens, experts;
+};
+constexpr RouterTile kTiles[4] = {{32, 32}, {32, 64}, {64, 64}, {128, 64}};
+
+// The tile with the least estimated time (us): rounds of workgroups at 45 bytes per nanosecond each, then the selection, in the
+// workgroup (passes of 256 lanes) or a launch of its own.  Alone, 3684 tokens, 6784 x 64: 28 / 34 / 50 / 82 for the four; 8192,
+// 3584 x 64: 35 / 26 / 39 / 64; 22980, 5376 x 64: 102 / 96 / 97 / 86; 20882, 5760 x 128: 172 / 151 / 124 / 134.
+static int pick_tile(int T, int H, int E) {
+    int best = 0;
+    double least = 1e30;
+    for (int i = 0; i < 4; ++i) {
+        const RouterTile t = kTiles[i];
+        const long long groups = (long long)((T + t.tokens - 1) / t.tokens) * ((E + t.experts - 1) / t.experts);
+        const double select = E <= t.experts ? 1.0 + 4.0 * ((t.tokens * lanes_per_token(E) + 255) / 256) : 4.0 + 9.4e-6 * T * (double)E;
+        const double us = (double)((groups + 255) / 256) * (t.tokens + t.experts) * (2.0 * H) / 45e3 + select;
+        if (us < least) {
+            least = us;
+            best = i;
+        }
+    }
+    return best;
+}
 // Selection alone, lists of eight lanes / by rank (us, 64 experts, K = 8): 1024 tokens 10.2 / 4.1, 4096 tokens 10.3 / 6.7,
 // 16384 tokens 13.3 / 13.1; 128 experts 17.1 / 13.1 at 4096.
 constexpr int kRankMaxTokens = 4096;
@@ -663,7 +819,7 @@ static void launch_topk(const float* logits, int T, int E, int K, int renorm, in
     hipLaunchKernelGGL(topk_only_kernel, dim3(grid), dim3(256), 0, s, logits, T, E, K, renorm, idx, gate);
 }
 
-static int g_router_tile = 0;  // 16-token blocks per workgroup; 0 = chosen by size, 8 = experts spread over workgroups
+static int g_router_tile = 0;  // 16-token blocks per workgroup; 0 = chosen by size, 8 = experts spread over workgroups, 16 = tiles
 void set_router_tile(int mb) { g_router_tile = mb; }
 
 void launch_router(const void* x, const void* w, const float* bias, float* logits, int T, int H,
@@ -680,7 +836,21 @@ void launch_router(const void* x, const void* w, const float* bias, float* logit
         return;
     }
     const int nb = (E + 15) / 16;
-    if (nb == 1 && g_router_tile == 0 && T <= kOneBlockMaxTokens) {
+    const int tile = nb >= 2 && E <= 128 && H % 64 == 0 &&
+                             (g_router_tile == 16 || (g_router_tile == 0 && (long long)T * E >= kTileMinLogits && !(T >= 32768 && E <= 64)))
+                         ? pick_tile(T, H, E) : -1;
+    if (tile >= 0) {
+        const bool fused = E <= kTiles[tile].experts;
+#define ROUTER_TILE(TM, TE)                                                                                              \
+    if (fused) launch_tile<TM, TE, true>(x, w, bias, logits, T, H, E, K, renorm, idx, gate, s);                          \
+    else launch_tile<TM, TE, false>(x, w, bias, logits, T, H, E, K, renorm, idx, gate, s);
+        if (tile == 0) { ROUTER_TILE(32, 32) } else if (tile == 1) { ROUTER_TILE(32, 64) }
+        else if (tile == 2) { ROUTER_TILE(64, 64) } else { ROUTER_TILE(128, 64) }
+#undef ROUTER_TILE
+        if (!fused) launch_topk(logits, T, E, K, renorm, idx, gate, s);
+        return;
+    }
+    if (nb == 1 && g_router_tile == 0 && T <= kOneBlockMaxTokens && (T > 512 || (long long)E * H <= 65536)) {
         // all experts in a workgroup; tokens per workgroup: as few as leave every workgroup a compute unit
         int tb = T >= 1024 ? 32 : 16;
         while (tb > 2 && (T + tb / 2 - 1) / (tb / 2) <= 256) tb /= 2;

@@ -63,6 +63,33 @@ def test_router_and_selection_of_up_to_16_experts_in_one_launch(T, H, E, K, bias
         np.testing.assert_allclose(gate, want_gate, rtol=GATE_RTOL, atol=1e-6)
 
 
+@pytest.mark.parametrize("T,H,E,K,bias,renorm", [
+    (5, 64, 17, 2, None, True),             # 32 x 32, one stage; fewer tokens than a tile, the selection in the workgroup
+    (300, 512, 32, 4, "normal", False),     # as many stages as the ring
+    (333, 704, 33, 3, None, True),          # two expert blocks, one expert in the second; three stages past the ring
+    (4164, 1280, 64, 6, "normal", True),    # 32 x 64
+    (2300, 2048, 128, 9, None, False),      # 32 x 64, two blocks, more slots than the list form takes
+    (20000, 576, 40, 4, "normal", True),    # 64 x 64, a ragged last tile
+    (9500, 3072, 100, 8, None, True),       # 64 x 64, two blocks
+    (8200, 640, 128, 9, None, False),       # 128 x 64, two blocks
+    (17000, 4096, 64, 6, "normal", True),   # 128 x 64, the selection in the workgroup
+])
+def test_router_tiles_of_tokens_and_experts(T, H, E, K, bias, renorm):
+    import paper_2504_14960_amd as moe
+    cfg = get_config("mixtral8x7b").scaled(T=T, H=H, E=E, K=K, bias=bias, seed=3300 + E)
+    inp = make_layer_inputs(cfg, ["x", "w_router", "bias"])
+    l64 = oracle.router_logits(inp["x"], inp["w_router"], inp.bias)
+    moe.set_option("router_tile", 16)
+    try:
+        logits, idx, gate = _gpu_topk(np.zeros((T, E), np.float32), K, renorm, inp["x"], inp["w_router"], inp.bias)
+    finally:
+        moe.set_option("router_tile", 0)
+    assert np.abs(logits - l64).max() <= LOGIT_ATOL
+    want_idx, want_gate = oracle.topk_gates(logits, K, renorm)     # the selection on the kernel's own logits
+    np.testing.assert_array_equal(idx, want_idx)
+    np.testing.assert_allclose(gate, want_gate, rtol=GATE_RTOL, atol=1e-6)
+
+
 @pytest.mark.parametrize("kind", ["ties", "all_equal", "subnormal"])
 @pytest.mark.parametrize("T,E,K", [(3, 64, 64), (5, 63, 8), (4, 128, 5), (4096, 65, 2), (4097, 65, 2)])
 def test_selection_by_rank(kind, T, E, K):
