@@ -547,7 +547,8 @@ moe_status_t moe_gemm_clock_sample(uint64_t* ticks);
  * where the type has them; 11, 12, 14, 18 = as 1 with 16, 32, 64, 128 weight rows
  * per workgroup; 100 S + U = as 2 with U = 3 to 8 times 32 weight rows per
  * workgroup and, where there is room for partial sums, the contraction in S = 1,
- * 2, 4, 8 or 16 parts); "fp8_deep_weights" (FP8 expert GEMMs: 1, the default = three LDS stages for
+ * 2, 4, 8 or 16 parts; 2000 + S = the large tiles, and where there is room the contraction in S = 2 to
+ * 16 parts); "fp8_deep_weights" (FP8 expert GEMMs: 1, the default = three LDS stages for
  * the weight tile, 0 = for the activation tile); "gemm_workgroups" (workgroups launched by the
  * persistent grouped-GEMM kernels; 0 = one per compute unit, values below 8
  * are raised to 8); "gemm_tile_rows" (rows of the tiles of the persistent expert kernels,

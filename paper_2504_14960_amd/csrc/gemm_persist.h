@@ -104,6 +104,7 @@ struct PTile {
     uint32_t b_lim;     // byte offset (from b0 / b1) of the last valid weight row
     int row0, rows, n0;
     int kt;             // k-tiles of this output tile (weight-gradient form; 0 = the launch's common count)
+    int split;          // contraction in parts: which one
     int krows;          // row-major weight-gradient form: rows of the expert, i.e. valid length of the contraction
     bool valid;
 };
@@ -115,7 +116,8 @@ struct TileSched {
     int lo[4], n[4], pex[4], pend;
     int MT, ntn, per, nwx, wgx, xcd, total;
 
-    __device__ __forceinline__ void init(const int32_t* __restrict__ offsets, int E, int ntn_, int lane) {
+    // splits: parts of the contraction, each a tile list of its own
+    __device__ __forceinline__ void init(const int32_t* __restrict__ offsets, int E, int ntn_, int lane, int splits = 1) {
         int mt[4], s = 0;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -141,7 +143,7 @@ struct TileSched {
         pend = incl;
         MT = __builtin_amdgcn_readlane(incl, 63);
         ntn = ntn_;
-        total = MT * ntn;
+        total = MT * ntn * splits;
         per = (total + 7) / 8;              // tiles per XCD share
         xcd = blockIdx.x & 7;               // workgroups are dealt round-robin to the 8 XCDs
         wgx = blockIdx.x >> 3;
@@ -150,11 +152,12 @@ struct TileSched {
 
     // the i-th tile of this workgroup
     // row_bytes: bytes per operand row (contraction length times element size)
+    template <bool SPLIT = false>
     __device__ __forceinline__ PTile get(int i, const uint8_t* A, const uint8_t* B0, const uint8_t* B1, int N,
-                                         size_t row_bytes, int outn) const {
+                                         size_t row_bytes, int outn, int splits = 1) const {
         constexpr int MG = 8;
         PTile t;
-        t.a = A; t.b0 = B0; t.b1 = B1; t.a_lim = 0; t.b_lim = 0; t.row0 = 0; t.rows = 0; t.n0 = 0; t.kt = 0; t.krows = 0;
+        t.a = A; t.b0 = B0; t.b1 = B1; t.a_lim = 0; t.b_lim = 0; t.row0 = 0; t.rows = 0; t.n0 = 0; t.kt = 0; t.split = 0; t.krows = 0;
         // BY_ROUND: whole rounds (one tile per workgroup of the launch) are dealt to the XCDs round by round: in
         // round i XCD x runs the nwx consecutive tiles from (8 i + x) nwx on, so at any time the eight XCDs work on
         // neighbouring stretches of the list and what they have in common (activation panels of one M-group) is
@@ -179,6 +182,10 @@ struct TileSched {
             t.valid = (j < per) && (L < total);
         }
         if (!t.valid) return t;
+        if constexpr (SPLIT) {
+            t.split = uni(L / (MT * ntn));
+            L -= t.split * (MT * ntn);
+        }
         const int qm = L / ntn;
         int hit = -1, my_p = 0, my_end = 0, my_lo = 0, my_n = 0;
 #pragma unroll
@@ -225,6 +232,13 @@ struct TileSched {
         t.b1 = uni(B1 + brow);
         t.a_lim = uni((uint32_t)(t.rows - 1) * (uint32_t)k2);
         t.b_lim = uni((uint32_t)(min(outn, N - t.n0) - 1) * (uint32_t)k2);
+        if constexpr (SPLIT) {
+            const int all = (int)(row_bytes / 128), k0 = uni((int)((long long)all * t.split / splits));
+            t.kt = uni((int)((long long)all * (t.split + 1) / splits)) - k0;
+            t.a += (size_t)k0 * 128;
+            t.b0 += (size_t)k0 * 128;
+            t.b1 += (size_t)k0 * 128;
+        }
         return t;
     }
 };
@@ -286,7 +300,7 @@ struct WgradSched {
     __device__ __forceinline__ PTile get(int i, const uint8_t* A, const uint8_t* B, int M, int N, int ld) const {
         constexpr int MG = 8;
         PTile t;
-        t.a = A; t.b0 = B; t.b1 = B; t.a_lim = 0; t.b_lim = 0; t.row0 = 0; t.rows = 0; t.n0 = 0; t.kt = 0; t.krows = 0;
+        t.a = A; t.b0 = B; t.b1 = B; t.a_lim = 0; t.b_lim = 0; t.row0 = 0; t.rows = 0; t.n0 = 0; t.kt = 0; t.split = 0; t.krows = 0;
         const int j = wgx + i * nwx;
         t.valid = j < total;
         if (!t.valid) return t;
@@ -378,7 +392,7 @@ struct WgradSchedKM {
                                          int ldb) const {
         constexpr int MG = 8;
         PTile t;
-        t.a = A; t.b0 = B; t.b1 = B; t.a_lim = 0; t.b_lim = 0; t.row0 = 0; t.rows = 0; t.n0 = 0; t.kt = 0; t.krows = 0;
+        t.a = A; t.b0 = B; t.b1 = B; t.a_lim = 0; t.b_lim = 0; t.row0 = 0; t.rows = 0; t.n0 = 0; t.kt = 0; t.split = 0; t.krows = 0;
         const int j = wgx + i * nwx;
         t.valid = j < total;
         if (!t.valid) return t;

@@ -23,6 +23,7 @@
 
 #include "gemm_persist.h"
 #include "gemm_stream.h"
+#include "once_per_device.h"
 
 
 namespace moe {
@@ -209,6 +210,30 @@ __device__ __forceinline__ void store_tile_staged(f32x16 (&acc)[FM][FN], int t_r
     }
 }
 
+// Partial sums as they are, [rows, N] or, gate and up, [rows, 2 N] fp32: a lane holds one row and four columns at a time.
+template <int FM, int FN, int WM, int WN, bool SWIGLU>
+__device__ __forceinline__ void store_partial(f32x16 (&acc)[FM][FN], int t_row0, int t_rows, int t_n0, float* __restrict__ part,
+                                              int N, int wm, int wn, int lane) {
+    asm volatile("" : "+v"(lane));   // see store_tile_staged
+    const int fr = lane & 31, fk = lane >> 5;
+    constexpr int FO = SWIGLU ? FN / 2 : FN;
+    const int pitch = SWIGLU ? 2 * N : N;
+#pragma unroll
+    for (int i = 0; i < FM; ++i) {
+        const int row = wm * WM + i * 32 + fr;
+        if (row >= t_rows) continue;
+        float* const prow = part + (size_t)(t_row0 + row) * pitch;
+#pragma unroll
+        for (int j = 0; j < FN; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const int col = t_n0 + wn * (FO * 32) + (j % FO) * 32 + 8 * q + 4 * fk;
+                const f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
+                if (col < N) *reinterpret_cast<f32x4*>(prow + (j >= FO ? N : 0) + col) = v;
+            }
+    }
+}
+
 // GROUPK (MODE 0 only): the weight-gradient form C [E, M, N]; A and B0 are the
 // transposed operands [M, K] and [N, K] with K = elements per row, every expert
 // contracting over its own zero-padded column segment (see WgradSched); `ntn`
@@ -227,11 +252,12 @@ __device__ __forceinline__ void store_tile_staged(f32x16 (&acc)[FM][FN], int t_r
 // ahead) and two stages for the weight tile; true: the other way round -- the weights are what streams in from
 // HBM (every weight byte is used by one M-group only), the activation panels are re-read from the caches.
 template <int BM, int BN, int WGM, int WGN, int MODE, bool GROUPK, bool KMAJ, bool IDLE_SKIP, bool DEEP_B, bool BY_ROUND,
-          bool STREAM_OUT, bool AHEAD>
+          bool STREAM_OUT, bool AHEAD, bool SPLIT>
 __device__ __forceinline__ void persist_body(
     const bf16_t* __restrict__ A, const int32_t* __restrict__ offsets, int E, int N, int K,
     const bf16_t* __restrict__ B0, const bf16_t* __restrict__ B1, bf16_t* __restrict__ C, bf16_t* __restrict__ GU,
-    int ntn, int ldb, unsigned long long* __restrict__ ticks, uint8_t* smem) {
+    int ntn, int ldb, int splits, int plane_rows, unsigned long long* __restrict__ ticks, uint8_t* smem) {
+    static_assert(!SPLIT || (!GROUPK && MODE <= 1), "the forward's products can be split");
     static_assert(!GROUPK || MODE == 0, "the weight-gradient form has a plain epilogue");
     static_assert(!KMAJ || (GROUPK && BM == 256 && BN == 256 && WGM * WGN == 8), "row-major form: 256 x 256 tiles, 8 waves");
     static_assert(!(KMAJ && DEEP_B), "the row-major form keeps three activation stages");
@@ -303,14 +329,14 @@ __device__ __forceinline__ void persist_body(
     if constexpr (GROUPK)
         sched.init(offsets, E, ntn, N, lane);
     else
-        sched.init(offsets, E, ntn, lane);
+        sched.init(offsets, E, ntn, lane, SPLIT ? splits : 1);
     auto get_tile = [&](int i) -> PTile {
         if constexpr (KMAJ)
             return sched.get(i, Ab, B0b, ntn, N, K, ldb);
         else if constexpr (GROUPK)
             return sched.get(i, Ab, B0b, ntn, N, K);
         else
-            return sched.get(i, Ab, B0b, B1b, N, (size_t)K * 2, OUTN);
+            return sched.template get<SPLIT>(i, Ab, B0b, B1b, N, (size_t)K * 2, OUTN, splits);
     };
     // current and next tile of this workgroup, as plain wave-uniform scalars
     int ti = 0;
@@ -318,6 +344,7 @@ __device__ __forceinline__ void persist_body(
     uint32_t c_alim, c_blim, n_alim, n_blim;
     int c_row0, c_rows, c_n0, n_row0, n_rows, n_n0;
     int c_kt = K / BK, n_kt = K / BK;   // k-tiles per output tile: per tile in the weight-gradient form
+    int c_split = 0, n_split = 0;       // part of the contraction
     int c_krows = 0, n_krows = 0;       // row-major form: rows of the tile's expert
     bool n_valid;
     {
@@ -325,14 +352,16 @@ __device__ __forceinline__ void persist_body(
         if (!t.valid) return;
         c_a = t.a; c_b0 = t.b0; c_b1 = t.b1; c_alim = t.a_lim; c_blim = t.b_lim;
         c_row0 = t.row0; c_rows = t.rows; c_n0 = t.n0;
-        if (GROUPK) c_kt = t.kt;
+        if (GROUPK || SPLIT) c_kt = t.kt;
+        if (SPLIT) c_split = t.split;
         if (KMAJ) c_krows = t.krows;
     }
     auto fetch_next_tile = [&](int i) {
         const PTile t = get_tile(i);
         n_a = t.a; n_b0 = t.b0; n_b1 = t.b1; n_alim = t.a_lim; n_blim = t.b_lim;
         n_row0 = t.row0; n_rows = t.rows; n_n0 = t.n0; n_valid = t.valid;
-        if (GROUPK) n_kt = t.kt;
+        if (GROUPK || SPLIT) n_kt = t.kt;
+        if (SPLIT) n_split = t.split;
         if (KMAJ) n_krows = t.krows;
     };
     fetch_next_tile(1);
@@ -633,12 +662,19 @@ __device__ __forceinline__ void persist_body(
         // Epilogue.  The late operand's slot that held the last k-tile (now its third) is
         // idle: every wave finished reading it before the last barrier, and the
         // next loads into it are issued only after the barrier below.
-        store_tile_staged<FM, FN, WM, MODE, (FM * FN * 16 > 128), STREAM_OUT>(acc, c_row0, c_rows, c_n0, C, GU, N, wm, wn, lane,
-                                              (DEEP_B ? b_region + b2 : a_region + a2) + wave * (32 * FO * 64));
+        if constexpr (SPLIT)
+            store_partial<FM, FN, WM, WN, SWIGLU>(acc, c_row0, c_rows, c_n0,
+                                                  reinterpret_cast<float*>(C) + (size_t)c_split * plane_rows * (SWIGLU ? 2 * N : N), N, wm,
+                                                  wn, lane);
+        else
+            store_tile_staged<FM, FN, WM, MODE, (FM * FN * 16 > 128), STREAM_OUT>(
+                acc, c_row0, c_rows, c_n0, C, GU, N, wm, wn, lane,
+                (DEEP_B ? b_region + b2 : a_region + a2) + wave * (32 * FO * 64));
         if (!n_valid) break;
         c_a = n_a; c_b0 = n_b0; c_b1 = n_b1; c_alim = n_alim; c_blim = n_blim;
         c_row0 = n_row0; c_rows = n_rows; c_n0 = n_n0;
-        if (GROUPK) c_kt = n_kt;
+        if (GROUPK || SPLIT) c_kt = n_kt;
+        if (SPLIT) c_split = n_split;
         if (KMAJ) c_krows = n_krows;
         ++ti;
         stored = 1;
@@ -662,20 +698,21 @@ __device__ __forceinline__ void persist_body(
 // BM = 0: the height of the tiles is chosen on the device, from the rows that every expert really has (pick_height);
 // 256, 192 or 128 rows, all of BN = 256 columns (ldb: a height to be taken instead, or 0).  A row's sums are formed in the same order whatever the height.
 template <int BM, int BN, int WGM, int WGN, int MODE, bool GROUPK = false, bool KMAJ = false, bool IDLE_SKIP = false,
-          bool DEEP_B = false, bool BY_ROUND = true, bool STREAM_OUT = false, bool AHEAD = false>
+          bool DEEP_B = false, bool BY_ROUND = true, bool STREAM_OUT = false, bool AHEAD = false, bool SPLIT = false>
 __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_persist_kernel(
     const bf16_t* __restrict__ A, const int32_t* __restrict__ offsets, int E, int N, int K,
     const bf16_t* __restrict__ B0, const bf16_t* __restrict__ B1, bf16_t* __restrict__ C, bf16_t* __restrict__ GU,
-    int ntn, int ldb, unsigned long long* __restrict__ ticks) {
+    int ntn, int ldb, int splits, int plane_rows, unsigned long long* __restrict__ ticks) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     if constexpr (BM != 0) {
-        persist_body<BM, BN, WGM, WGN, MODE, GROUPK, KMAJ, IDLE_SKIP, DEEP_B, BY_ROUND, STREAM_OUT, AHEAD>(
-            A, offsets, E, N, K, B0, B1, C, GU, ntn, ldb, ticks, smem);
+        persist_body<BM, BN, WGM, WGN, MODE, GROUPK, KMAJ, IDLE_SKIP, DEEP_B, BY_ROUND, STREAM_OUT, AHEAD, SPLIT>(
+            A, offsets, E, N, K, B0, B1, C, GU, ntn, ldb, splits, plane_rows, ticks, smem);
     } else {
-        const int height = ldb != 0 ? ldb : pick_height(kCostBf16, offsets, E, ntn, K / 64, threadIdx.x & 63);
+        const int height = ldb != 0 ? ldb : pick_height(kCostBf16, offsets, E, ntn * (SPLIT ? splits : 1), K / 64 / (SPLIT ? splits : 1),
+                                                        threadIdx.x & 63);
         auto run = [&](auto rows) {
-            persist_body<decltype(rows)::value, BN, WGM, WGN, MODE, false, false, IDLE_SKIP, DEEP_B, BY_ROUND, false, AHEAD>(
-                A, offsets, E, N, K, B0, B1, C, GU, ntn, ldb, ticks, smem);
+            persist_body<decltype(rows)::value, BN, WGM, WGN, MODE, false, false, IDLE_SKIP, DEEP_B, BY_ROUND, false, AHEAD, SPLIT>(
+                A, offsets, E, N, K, B0, B1, C, GU, ntn, ldb, splits, plane_rows, ticks, smem);
         };
         if (height == 256) run(std::integral_constant<int, 256>{});
         else if (height == 192) run(std::integral_constant<int, 192>{});
@@ -730,7 +767,7 @@ void launch_persist(const void* A, const int32_t* offsets, int r_max, int E, int
     const int grid = min(persist_grid(), grid_for(r_max, E, HMIN, ntn));
     hipLaunchKernelGGL(kern, dim3(grid), dim3(WGM * WGN * 64), smem, s, static_cast<const bf16_t*>(A), offsets, E, N,
                        K, static_cast<const bf16_t*>(B0), static_cast<const bf16_t*>(B1), static_cast<bf16_t*>(C),
-                       static_cast<bf16_t*>(GU), ntn, g_persist_tile_rows, g_persist_ticks);
+                       static_cast<bf16_t*>(GU), ntn, g_persist_tile_rows, 1, 0, g_persist_ticks);
 }
 
 // dw[e] = 0 for every expert without rows (the persistent weight-gradient kernel gives them no tiles)
@@ -760,7 +797,7 @@ void launch_persist_groupk(const void* A, const void* B, const int32_t* offsets,
     const int grid = (int)min((long long)persist_grid(), (tiles + 7) / 8 * 8);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(WGM * WGN * 64), smem, s, static_cast<const bf16_t*>(A), offsets, E, N,
                        ld, static_cast<const bf16_t*>(B), static_cast<const bf16_t*>(B), static_cast<bf16_t*>(C),
-                       static_cast<bf16_t*>(nullptr), M, 0, g_persist_ticks);
+                       static_cast<bf16_t*>(nullptr), M, 0, 1, 0, g_persist_ticks);
 }
 
 // weight gradients straight from the row-major activations (no transposed copies): see the kernel's KMAJ form
@@ -779,7 +816,7 @@ void launch_persist_groupk_rowmajor(const void* A, int lda, const void* B, int l
     const int grid = (int)min((long long)persist_grid(), (tiles + 7) / 8 * 8);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(WGM * WGN * 64), smem, s, static_cast<const bf16_t*>(A), offsets, E, N,
                        lda, static_cast<const bf16_t*>(B), static_cast<const bf16_t*>(B), static_cast<bf16_t*>(C),
-                       static_cast<bf16_t*>(const_cast<void*>(zero_row)), M, ldb, g_persist_ticks);
+                       static_cast<bf16_t*>(const_cast<void*>(zero_row)), M, ldb, 1, 0, g_persist_ticks);
 }
 
 template <int BM, int BN, int WGM, int WGN, bool DEEP_B = false>
@@ -860,6 +897,29 @@ bool launch_gate_up_saving(const void* x_perm, const int32_t* offsets, int r_max
         return true;
     }
     launch_persist<0, 256, 2, 4, 2, true>(x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, gu, s);
+    return true;
+}
+
+// One product with its contraction in `splits` parts, fp32 planes [splits][r_max][N, or 2 N with w_up] in part
+bool launch_persist_split(const void* A, const int32_t* offsets, int r_max, int E, int N, int K, const void* B0, const void* B1,
+                          float* part, int splits, hipStream_t s) {
+    if (K % 64 || N % 8 || K / 64 < 2 * splits) return false;
+    auto go = [&](auto mode) {
+        constexpr int MODE = decltype(mode)::value, OUTN = MODE == 1 ? 128 : 256;
+        constexpr size_t smem = (size_t)(2 * 256 + 3 * 256) * 64 * 2;
+        auto kern = gemm_bf16_persist_kernel<0, 256, 2, 4, MODE, false, false, false, true, true, false, false, true>;
+        static OncePerDevice lds;
+        int device = -1;   // unknown: set it every time
+        (void)hipGetDevice(&device);
+        lds.run(device, [&] { (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem); });
+        const int ntn = (N + OUTN - 1) / OUTN;
+        const int grid = min(persist_grid(), grid_for(r_max, E, 128, ntn * splits));
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(512), smem, s, static_cast<const bf16_t*>(A), offsets, E, N, K,
+                           static_cast<const bf16_t*>(B0), static_cast<const bf16_t*>(B1), reinterpret_cast<bf16_t*>(part),
+                           static_cast<bf16_t*>(nullptr), ntn, g_persist_tile_rows, splits, r_max, g_persist_ticks);
+    };
+    if (B1) go(std::integral_constant<int, 1>{});
+    else go(std::integral_constant<int, 0>{});
     return true;
 }
 

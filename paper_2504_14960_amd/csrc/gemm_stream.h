@@ -11,7 +11,7 @@ enum { kPlanLarge = 0, kPlanNarrow = 1, kPlanWide = 2 };    // 256-row tiles (an
 struct StreamPlan {
     int kind;
     int units;    // wide: blocks of 32 weight rows per workgroup
-    int splits;   // wide: parts of the contraction
+    int splits;   // wide, large: parts of the contraction
 };
 
 // rows of at most 16 MiB (32-bit offsets inside a tile)
@@ -21,9 +21,13 @@ bool stream_covers(long long K_bytes);
 StreamPlan plan_stream(int elt, int r_max, int E, int N, int K, bool swiglu, bool large_ok, size_t part_bytes);
 // room for partial sums that the plan wants, at most 64 MiB
 size_t stream_part_bytes(int elt, int r_max, int E, int N, int K, bool swiglu, bool large_ok);
+// C [rows, N] in bf16 from the partial planes [splits][r_max][N, or 2 N: gate and up] fp32, added in split order
+void launch_stream_reduce(bool swiglu, const float* part, const int32_t* offsets, int E, int splits, int r_max, int N, void* C,
+                          hipStream_t s);
 // -1 (default): by size; 0: only the shapes no other kernel takes; 1: always the narrow, 2: always the wide form.  10 + FB:
 // narrow with FB (1, 2, 4, 8) blocks of 16 weight rows per workgroup (2 for 1 with SwiGLU; 2 or 4 for at most 16 rows in
-// all); 100 S + U: wide with U (3 .. 8) units and S (1, 2, 4, 8, 16) splits, halved until they fit the contraction and the room
+// all); 100 S + U: wide with U (3 .. 8) units and S (1, 2, 4, 8, 16) splits, halved until they fit the contraction and the room; 2000 + S:
+// the large tiles, their contraction in S (2 .. 16) parts where that fits the contraction and the room
 void set_gemm_stream(int v);
 
 // C [rows, N] = A [rows, K] . B0[e]^T; with B1 the SwiGLU pair silu(A B0^T) * (A B1^T), and with GU (bf16) also its two

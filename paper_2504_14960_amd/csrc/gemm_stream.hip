@@ -618,6 +618,13 @@ __global__ __launch_bounds__(256) void stream_reduce_kernel(const float* __restr
     }
 }
 
+template <int MODE>
+void reduce_planes(const float* part, const int32_t* offsets, int E, int S, int r_max, int N, void* C, hipStream_t s) {
+    const long long groups = ((long long)r_max * N / 4 + 255) / 256;
+    hipLaunchKernelGGL((stream_reduce_kernel<MODE>), dim3((int)(groups < 2048 ? groups : 2048)), dim3(256), 0, s, part, offsets, E, S,
+                       r_max, N, static_cast<bf16_t*>(C));
+}
+
 // The LDS limit of a kernel on the current device (`lds`: the kernel's own)
 void allow_lds(OncePerDevice& lds, const void* kern, int bytes) {
     int device = -1;   // unknown: set it every time
@@ -678,7 +685,8 @@ void launch(StreamArgs p, int r_max, hipStream_t s) {
 
 int g_stream = -1;   // see set_gemm_stream
 int forced_blocks() { return g_stream > 10 && g_stream < 20 ? g_stream - 10 : 0; }
-bool forced_wide() { return g_stream >= 100; }
+bool forced_wide() { return g_stream >= 100 && g_stream < 2000; }
+int forced_large_splits() { return g_stream >= 2000 ? g_stream - 2000 : 0; }
 
 // Weight blocks of a narrow workgroup: as many as leave enough workgroups.  A wider workgroup reads the rows less often
 // and keeps more weight bytes in flight, but 256 compute units want work.  Measured (us, blocks 8 / 4 / 2 / 1):
@@ -727,13 +735,8 @@ void launch_wide(StreamArgs p, int r_max, const StreamPlan& plan, float* part, h
     static OncePerDevice lds;
     allow_lds(lds, reinterpret_cast<const void*>(kern), smem);
     hipLaunchKernelGGL(kern, dim3(grid_for(r_max, p.E, 128, p.ntn * p.S)), dim3(kWideWaves * 64), smem, s, p);
-    if constexpr (ELT == kEltBf16 && MODE != 2) {
-        if (p.S > 1) {
-            const long long groups = ((long long)r_max * p.N / 4 + 255) / 256;
-            hipLaunchKernelGGL((stream_reduce_kernel<MODE>), dim3((int)(groups < 2048 ? groups : 2048)), dim3(256), 0, s, part,
-                               p.offsets, p.E, p.S, r_max, p.N, static_cast<bf16_t*>(p.C));
-        }
-    }
+    if constexpr (ELT == kEltBf16 && MODE != 2)
+        if (p.S > 1) reduce_planes<MODE>(part, p.offsets, p.E, p.S, r_max, p.N, p.C, s);
 }
 
 template <int ELT, int MODE>
@@ -780,9 +783,14 @@ double m_tiles(const Work& w, int height) {
 }
 double rounds_of(double tiles) { return (double)(long long)((tiles + kUnitsCU - 1) / kUnitsCU); }
 
+// the partial planes written, read and added
+double reduce_us(const Work& w, int S) {
+    return S > 1 ? 4.0 + (double)S * w.r_max * w.N * (w.swiglu ? 16.0 : 8.0) / 4.5e6 : 0.0;
+}
+
 // The large tiles choose their height on the device, from the rows every expert has.  Here only the average is known: the
 // time for equal experts and the time for experts of 0.4 to 1.8 times the average, half of each.
-double large_us(const Work& w) {
+double large_us(const Work& w, int S = 1) {
     constexpr double kSpread[8] = {0.386, 0.552, 0.717, 0.883, 1.048, 1.214, 1.434, 1.766};
     const TileCosts& c = w.fp8 ? kCostFp8 : kCostBf16;
     const int ntn = blocks_of(w.N, w.swiglu ? 128 : 256);
@@ -795,11 +803,11 @@ double large_us(const Work& w) {
                 for (const double f : kSpread) mt += w.experts / 8.0 * (double)(long long)((w.rows * f + height - 1e-6) / height);
             }
             const HeightCost& h = height == 256 ? c.h256 : height == 192 ? c.h192 : c.h128;
-            t = fmin(t, tiles_us(h, (float)mt, (float)w.experts, ntn, kUnitsCU, w.kbytes / 128));
+            t = fmin(t, tiles_us(h, (float)mt, (float)w.experts, ntn * S, kUnitsCU, w.kbytes / 128 / S));
         }
         return t;
     };
-    return 4.0 + (w.experts == 1 ? best(true) : 0.5 * (best(true) + best(false)));
+    return 4.0 + (w.experts == 1 ? best(true) : 0.5 * (best(true) + best(false))) + reduce_us(w, S);
 }
 
 double narrow_us(const Work& w, int fb) {
@@ -822,9 +830,8 @@ double wide_us(const Work& w, int units, int S) {
     const double tiles = m_tiles(w, 128) * blocks_of(w.N, units * (w.swiglu ? 16 : 32)) * S;
     const int rows = w.rows < 128 ? w.rows : 128;
     const double round = w.kbytes / (double)S * (32 * units * (mt > 1 ? 36e-6 : 43e-6) + rows * (rows <= 64 ? 5e-6 : 12e-6)) + 10.0;
-    const double reduce = S > 1 ? 4.0 + (double)S * w.r_max * w.N * (w.swiglu ? 16.0 : 8.0) / 4.5e6 : 0.0;
     // one workgroup to a compute unit: a tile too many costs a round, so a plan for skewed experts keeps some slack
-    return rounds_of(tiles * (1.0 + 0.12 * skew_share(w, 128))) * round + reduce;
+    return rounds_of(tiles * (1.0 + 0.12 * skew_share(w, 128))) * round + reduce_us(w, S);
 }
 
 constexpr size_t kMaxPartBytes = 64u << 20;   // partial planes of one product, at most
@@ -832,6 +839,12 @@ constexpr size_t kMaxPartBytes = 64u << 20;   // partial planes of one product, 
 }  // namespace
 
 void set_gemm_stream(int v) { g_stream = v; }
+
+void launch_stream_reduce(bool swiglu, const float* part, const int32_t* offsets, int E, int splits, int r_max, int N, void* C,
+                          hipStream_t s) {
+    if (swiglu) reduce_planes<1>(part, offsets, E, splits, r_max, N, C, s);
+    else reduce_planes<0>(part, offsets, E, splits, r_max, N, C, s);
+}
 
 bool stream_covers(long long K_bytes) { return K_bytes <= (1 << 24); }
 
@@ -859,6 +872,15 @@ StreamPlan plan_stream(int elt, int r_max, int E, int N, int K, bool swiglu, boo
         while (!splits_fit(plan.splits)) plan.splits /= 2;
         return plan;
     }
+    // a split of the large tiles leaves at least eight k-tiles to a tile
+    auto large_splits_fit = [&](int S) {
+        return large_ok && elt == kEltBf16 && kbytes / 128 >= 8 * S && (size_t)S * r_max * N * (swiglu ? 8 : 4) <= part_bytes;
+    };
+    if (forced_large_splits()) {
+        plan.kind = large_ok ? kPlanLarge : kPlanNarrow;
+        if (large_splits_fit(forced_large_splits())) plan.splits = forced_large_splits();
+        return plan;
+    }
     w.kbytes = (int)kbytes;
     w.r_max = r_max;
     w.swiglu = swiglu;
@@ -871,6 +893,18 @@ StreamPlan plan_stream(int elt, int r_max, int E, int N, int K, bool swiglu, boo
             plan.kind = kPlanLarge;
         }
     }
+    // Only the layer's shared expert has room for partial sums, and of one expert the M-tiles are known.  The
+    // shared expert's two products, H x Fs = 3584 x 20480 (us, large tiles whole / split wide workgroups / so): 300 tokens 363 / 247
+    // / 188, 500 tokens 423 / 334 / 255, 1000 534 / 574 / 422, 2000 771 / 1040 / 749; 1500 tokens, 2048 x 8192 195 / 231 / 161.
+    if (g_stream < 0 && w.experts == 1)
+        for (int S = 2; S <= 16 && large_splits_fit(S); ++S) {
+            const double t = large_us(w, S);
+            if (t < best) {
+                best = t;
+                plan.kind = kPlanLarge;
+                plan.splits = S;
+            }
+        }
     for (int units = 8; units >= 3; --units)
         for (int S = 1; S <= 16; S *= 2) {
             if (!splits_fit(S)) break;

@@ -175,4 +175,8 @@ bool launch_persist_ffn(const void* x_perm, const int32_t* offsets, int r_max, i
                         const void* w_gate, const void* w_up, const void* w_down, void* h,
                         void* y_perm, int variant, int phase, hipStream_t s);
 
+// the same kernels with the contraction in `splits` parts, fp32 planes [splits][r_max][N, or 2 N with B1] in part
+bool launch_persist_split(const void* A, const int32_t* offsets, int r_max, int E, int N, int K, const void* B0, const void* B1,
+                          float* part, int splits, hipStream_t s);
+
 }  // namespace moe

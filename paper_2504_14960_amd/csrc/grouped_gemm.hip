@@ -164,6 +164,9 @@ bool launch_expert_ffn(const void* x_perm, const int32_t* offsets, int r_max, in
                 launch_stream(plan, elt, ph == 1 ? x_perm : h, offsets, r_max, E, N, K, ph == 1 ? w_gate : w_down,
                               ph == 1 ? w_up : nullptr, ph == 1 ? h : y_perm, nullptr, 0.f, 0.f, 0.f, nullptr,
                               static_cast<float*>(part), s);
+            else if (plan.splits > 1 && launch_persist_split(ph == 1 ? x_perm : h, offsets, r_max, E, N, K, ph == 1 ? w_gate : w_down,
+                                                             ph == 1 ? w_up : nullptr, static_cast<float*>(part), plan.splits, s))
+                launch_stream_reduce(ph == 1, static_cast<float*>(part), offsets, E, plan.splits, r_max, N, ph == 1 ? h : y_perm, s);
             else if (!launch_persist_ffn(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, 43, ph, s))
                 ok = ok && launch_pipe3_ffn(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm,
                                             ph == 1 ? 31 : 30, ph, s);

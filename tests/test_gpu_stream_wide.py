@@ -134,3 +134,23 @@ def test_every_number_of_parts(long_shared, units, splits):
     c = long_shared[0].cfg
     per = c.shared_F * 8 if c.H > c.shared_F else c.H * 4         # gate/up with its two sums, or down; the other stays whole
     _check_split_layer(long_shared, splits * c.T * per if splits > 1 else 0)
+
+
+# the large tiles, contraction in parts: 41 k-tiles, no whole number to a part; rows at the edges of the three tile heights;
+# columns that end inside a tile; gate/up (H > Fs) and down
+@pytest.fixture(scope="module", params=[(129, 2624, 320), (193, 320, 2624), (257, 2624, 448), (385, 448, 2624)])
+def deep_shared(request):
+    T, H, Fs = request.param
+    return _layer_case(T, H, 64, Fs, 4, 2)
+
+
+@pytest.mark.parametrize("splits,rows", [(2, 0), (3, 256), (3, 192), (3, 128), (5, 0)])
+def test_large_tiles_in_parts(deep_shared, splits, rows):
+    import paper_2504_14960_amd as moe
+    moe.set_option("gemm_stream", 2000 + splits)
+    moe.set_option("gemm_tile_rows", rows)
+    try:
+        c = deep_shared[0].cfg
+        _check_split_layer(deep_shared, splits * c.T * (c.shared_F * 8 if c.H > c.shared_F else c.H * 4))
+    finally:
+        moe.set_option("gemm_tile_rows", 0)
