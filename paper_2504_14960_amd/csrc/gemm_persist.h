@@ -26,10 +26,10 @@ __device__ __forceinline__ const uint8_t* uni(const uint8_t* p) {
     return reinterpret_cast<const uint8_t*>(((uint64_t)hi << 32) | lo);
 }
 
-__device__ __forceinline__ int wave_sum(int v) {
-#pragma unroll
-    for (int d = 32; d > 0; d >>= 1) v += __shfl_xor(v, d, 64);
-    return v;
+// sum of v over the lanes that describe E experts, four to a lane (the others hold nothing), in lane 0
+__device__ __forceinline__ int expert_sum(int v, int E) {
+    for (int d = 1; 4 * d < E; d <<= 1) v += __shfl_xor(v, d, 64);
+    return __builtin_amdgcn_readfirstlane(v);
 }
 
 // The height of the tiles of a launch: 256, 192 or 128 rows, whichever takes least by the estimate (a lower one only where
@@ -48,10 +48,10 @@ __device__ __forceinline__ int pick_height(const TileCosts& c, const int32_t* __
         m128 += (n + 127) / 128;
         some += n > 0;
     }
-    m256 = wave_sum(m256);
-    m192 = wave_sum(m192);
-    m128 = wave_sum(m128);
-    some = wave_sum(some);
+    m256 = expert_sum(m256, E);
+    m192 = expert_sum(m192, E);
+    m128 = expert_sum(m128, E);
+    some = expert_sum(some, E);
     if (some == 0) return 256;
     const int slots = gridDim.x;
     float best = 0.97f * tiles_us(c.h256, m256, some, ntn, slots, kt);
@@ -132,8 +132,7 @@ struct TileSched {
             s += mt[j];
         }
         int incl = s;
-#pragma unroll
-        for (int d = 1; d < 64; d <<= 1) {
+        for (int d = 1; 4 * d < E; d <<= 1) {   // lanes past the last expert have nothing to add
             const int o = __shfl_up(incl, d, 64);
             if (lane >= d) incl += o;
         }
@@ -141,7 +140,7 @@ struct TileSched {
 #pragma unroll
         for (int j = 1; j < 4; ++j) pex[j] = pex[j - 1] + mt[j - 1];
         pend = incl;
-        MT = __builtin_amdgcn_readlane(incl, 63);
+        MT = __builtin_amdgcn_readlane(incl, (E - 1) >> 2);
         ntn = ntn_;
         total = MT * ntn * splits;
         per = (total + 7) / 8;              // tiles per XCD share
