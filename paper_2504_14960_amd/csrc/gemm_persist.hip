@@ -1,10 +1,11 @@
 // Grouped expert GEMM (a3), persistent kernel: one workgroup per compute unit
 // walks a static list of output tiles and treats their k-tiles as ONE stream.
 //
-// Same tile engine as gemm_pipe3.hip (256 x 256 x 64 tiles, three LDS stages
-// for the activation tile and two for the weight tile, direct global->LDS
+// Same tile engine as gemm_pipe3.hip (256 x 256 x 64 tiles, direct global->LDS
 // loads spread in source order between the MFMA groups, one barrier per
-// k-tile).  What changes is what happens at a tile boundary:
+// k-tile), with the three LDS stages given to the weight tile and two to the
+// activation tile, and with tiles of 256, 192 or 128 rows (pick_height).  What
+// changes further is what happens at a tile boundary:
 //
 //  * the loads issued during the last two k-tiles of a tile already fetch the
 //    first two k-tiles of the workgroup's NEXT tile, so the pipeline never

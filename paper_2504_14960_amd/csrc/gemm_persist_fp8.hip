@@ -2,15 +2,15 @@
 // (Section 4.5, "FP8 Training Performance").
 //
 // Same persistent engine as gemm_persist.hip, byte for byte on the memory
-// side: 256 x 256 output tiles, LDS rows of 128 bytes (here 128 E4M3 values,
-// so a k-tile spans 128 of the contraction index), three LDS stages for the
-// activation tile and two for the weight tile filled by direct global->LDS
-// loads, the k-tiles of successive output tiles as one stream, register-
+// side: output tiles of 256, 192 or 128 rows x 256 columns, LDS rows of 128
+// bytes (here 128 E4M3 values, so a k-tile spans 128 of the contraction index),
+// three LDS stages for the weight tile and two for the activation tile filled
+// by direct global->LDS loads, the k-tiles of successive output tiles as one stream, register-
 // resident tile scheduler, epilogue staged through the idle LDS stage.
 //
 // What differs: the matrix instruction is the 32x32x64 FP8 MFMA (each lane
 // feeds 32 consecutive bytes of a row, two k-steps per k-tile, twice the math
-// per byte moved); 4 waves of 128 x 128 (the accumulators fill the accumulation
+// per byte moved); 4 waves of 128 x 128 (with 256 rows; the accumulators fill the accumulation
 // registers, the 2 x 64 fragment registers double-buffer the two k-steps);
 // and the epilogues: the gate/up GEMM dequantises g and u, applies SwiGLU,
 // records max |h| for the next step's scale and writes h as E4M3 with this

@@ -487,9 +487,11 @@ __device__ __forceinline__ float shared_tile(const StreamArgs& p, const Tile& t,
 // up to 256 weight rows on one ring of row stages, one workgroup per compute unit.  The number of weight rows is
 // chosen per launch (units x 32) so that the tiles fill whole rounds of the compute units, and where that leaves too
 // few of them and there is room (the layer's shared expert) the contraction is split: the splits leave fp32 partial sums
-// that stream_reduce_kernel adds in split order.  Measured (us, the better of the narrow and the large-tile kernel / here):
+// that stream_reduce_kernel adds in split order.  Measured (us, the better of the narrow kernel
+// and large tiles of 256 rows / here):
 //   one expert, gate/up 20480 x 3584: 64 rows 84 / 61 (160 weight rows each on 256 workgroups), 125 rows 86 / 74
 //   the same, down: 64 rows 70 / 185 whole, 42 in 16 parts; 250 rows 126 / 68 and 500 rows 162 / 110 in parts
+//   (500 rows: the large tiles in parts take 87)
 //   8 experts, gate/up 14336 x 4096, 125 rows 421 / 404;  16 experts, gate/up 1408 x 2048, 64 rows 51 / 44
 constexpr int kWideWaves = 8, kWideRing = 128 * 1024;
 

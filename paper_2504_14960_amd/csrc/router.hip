@@ -9,7 +9,9 @@
 // from global memory.  Partial sums are folded in a fixed wave order, so the
 // logits are bit-reproducible.  Selection is done by groups of lanes, one
 // group per token, with butterfly reductions on (value desc, index asc) keys.
-// With few tokens the same work is spread over more workgroups (router_logits_kernel), the selection a launch of its own.
+// With few tokens the same work is spread over more workgroups (router_logits_kernel; the selection in the same launch for up
+// to 16 experts, else one of its own); with many tokens and 17 to 128 experts the logits are computed in tiles of tokens and
+// experts (router_tile_kernel).
 #include "common.h"
 #include "once_per_device.h"
 
@@ -523,36 +525,62 @@ __global__ __launch_bounds__(256) void router_tile_kernel(
                                              (__attribute__((address_space(3))) void*)(smem + slot * STAGE + (q * 32 + wave * 8) * 128),
                                              16, 0, 0);
     };
-    f32x16 acc[BPW];
+    // A logit is the sum of several separate sums (at least 4, 16 for the smallest tile), as in the kernels for fewer tokens: one
+    // sum over the whole row doubles the error (20882 tokens, 5760 x 128: 4.7e-7 against 64 bits; in four 2.3e-7).
+    constexpr int Q = 4 / KS;                                       // of a stage's four steps, this wave's
+    constexpr int U = KS > 1 ? 4 : BPW == 1 ? 2 : 1;                // stages that follow one another in sums of their own
+    f32x16 acc[U][Q][BPW];
 #pragma unroll
-    for (int b = 0; b < BPW; ++b)
+    for (int u = 0; u < U; ++u)
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[b][v] = 0.f;
+        for (int q = 0; q < Q; ++q)
+#pragma unroll
+            for (int b = 0; b < BPW; ++b)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[u][q][b][v] = 0.f;
     const int fr = lane & 31, fk = lane >> 5, sw = lds_swizzle(fr);
     const uint8_t* const xrow = smem + (tm * 32 + fr) * 128;
     const uint8_t* const wrow = smem + (TM + te * 32 + fr) * 128;
 #pragma unroll
     for (int d = 0; d < S - 1; ++d) issue(d, d);
     int slot = 0, fill = S - 1;
-    for (int s = 0; s < nst; ++s) {
-        // this wave's loads of the stage have landed, its reads of the stage before are in registers
-        constexpr int W = (S - 2) * PER;
-        __builtin_amdgcn_s_waitcnt((W & 0xF) | ((W >> 4) << 14) | 0x70);
-        __builtin_amdgcn_s_barrier();
-        __builtin_amdgcn_sched_barrier(0);
-        issue(fill, s + S - 1);
+    for (int s0 = 0; s0 < nst; s0 += U) {
 #pragma unroll
-        for (int q = 0; q < 4 / KS; ++q) {
-            const int c = ((2 * (ks * (4 / KS) + q) + fk) ^ sw) * 16;
-            const bf16x8 a = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(xrow + slot * STAGE + c));
+        for (int u = 0; u < U; ++u) {
+            if (s0 + u >= nst) break;
+            // this wave's loads of the stage have landed, its reads of the stage before are in registers
+            constexpr int W = (S - 2) * PER;
+            __builtin_amdgcn_s_waitcnt((W & 0xF) | ((W >> 4) << 14) | 0x70);
+            __builtin_amdgcn_s_barrier();
+            __builtin_amdgcn_sched_barrier(0);
+            issue(fill, s0 + u + S - 1);
 #pragma unroll
-            for (int b = 0; b < BPW; ++b) {
-                const bf16x8 e = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(wrow + slot * STAGE + b * 4096 + c));
-                acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(e, a, acc[b], 0, 0, 0);
+            for (int q = 0; q < Q; ++q) {
+                const int c = ((2 * (ks * Q + q) + fk) ^ sw) * 16;
+                const bf16x8 a = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(xrow + slot * STAGE + c));
+#pragma unroll
+                for (int b = 0; b < BPW; ++b) {
+                    const bf16x8 e = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(wrow + slot * STAGE + b * 4096 + c));
+                    acc[u][q][b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(e, a, acc[u][q][b], 0, 0, 0);
+                }
             }
+            slot = slot + 1 == S ? 0 : slot + 1;
+            fill = fill + 1 == S ? 0 : fill + 1;
         }
-        slot = slot + 1 == S ? 0 : slot + 1;
-        fill = fill + 1 == S ? 0 : fill + 1;
+    }
+    // pairwise: the sums of a stage's steps, then those of successive stages
+#pragma unroll
+    for (int b = 0; b < BPW; ++b) {
+#pragma unroll
+        for (int d = 1; d < Q; d *= 2)
+#pragma unroll
+            for (int q = 0; q < Q; q += 2 * d)
+#pragma unroll
+                for (int u = 0; u < U; ++u) acc[u][q][b] += acc[u][q + d][b];
+#pragma unroll
+        for (int d = 1; d < U; d *= 2)
+#pragma unroll
+            for (int u = 0; u < U; u += 2 * d) acc[u][0][b] += acc[u + d][0][b];
     }
     __builtin_amdgcn_s_waitcnt(0x0070);   // vmcnt(0), lgkmcnt(0): nothing lands in the ring any more
     __syncthreads();
@@ -566,7 +594,7 @@ __global__ __launch_bounds__(256) void router_tile_kernel(
 #pragma unroll
                 for (int v = 0; v < 16; ++v) {
                     float* p = red + (tm * 32 + fr) * LD + (te + b) * 32 + 8 * (v >> 2) + 4 * fk + (v & 3);
-                    *p = kk == 0 ? acc[b][v] : *p + acc[b][v];
+                    *p = kk == 0 ? acc[0][0][b][v] : *p + acc[0][0][b][v];
                 }
         }
         __syncthreads();
