@@ -767,33 +767,9 @@ int narrow_blocks(int r_max, int E, int N, bool swiglu) {
     return groups(8) >= want ? 8 : groups(4) >= want ? 4 : swiglu || groups(2) >= want ? 2 : 1;
 }
 
-// The same for fp32, where the matrix instructions (a sixteenth of the bf16 rate) are what takes the time, so that it counts
-// how evenly the workgroups fall on the compute units: workgroups per compute unit, halfway to the next whole number, times
-// what one takes (fitted; 2 and 1 blocks leave one workgroup to a compute unit, whose barriers nothing covers).  Over 144
-// products (16 to 4096 tokens on 4 to 16 experts, H and F up to 1024 and 2048) 5.1 % faster than by the rule above, 2.1 % behind
-// the best of the four; at worst 36 % slower (down, 614 tokens on 8 experts, 416 x 620: 22.3 for 19.8 us; 428 on 16: 84 for 67).
-int narrow_blocks_f32(int r_max, int E, int N, bool swiglu) {
-    if (forced_blocks() || r_max <= 16) return narrow_blocks(r_max, E, N, swiglu);
-    const int experts = E < r_max ? E : r_max, rows = (r_max + experts - 1) / experts;
-    int best = 8;
-    double least = 1e30;
-    for (int fb = 8; fb >= (swiglu ? 2 : 1); fb /= 2) {
-        const int height = fb == 1 ? 64 : 128, bn = 16 * (swiglu ? fb / 2 : fb);
-        const double mt = rows > height ? 0.5 * experts + (double)r_max / height : experts;
-        const double per_cu = mt * ((N + bn - 1) / bn) / 256.0;
-        const double one = fb == 8 ? 11.0 : fb == 4 ? 6.0 : fb == 2 ? 4.5 : 3.5;
-        const double cost = (per_cu <= 1.0 ? 1.0 : 0.5 * (per_cu + ceil(per_cu))) * one;
-        if (cost < least) {
-            least = cost;
-            best = fb;
-        }
-    }
-    return best;
-}
-
 template <int ELT, int MODE>
 void launch_narrow(const StreamArgs& p, int r_max, hipStream_t s) {
-    const int fb = ELT == kEltF32 ? narrow_blocks_f32(r_max, p.E, p.N, MODE != 0) : narrow_blocks(r_max, p.E, p.N, MODE != 0);
+    const int fb = narrow_blocks(r_max, p.E, p.N, MODE != 0);
     if (r_max <= 16) {
         if (fb == 4) launch<ELT, MODE, 4, true>(p, r_max, s);
         else launch<ELT, MODE, 2, true>(p, r_max, s);
