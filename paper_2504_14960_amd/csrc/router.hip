@@ -813,7 +813,8 @@ constexpr RouterTile kTiles[4] = {{32, 32}, {32, 64}, {64, 64}, {128, 64}};
 
 // The tile with the least estimated time (us): rounds of workgroups at 45 bytes per nanosecond each, then the selection, in the
 // workgroup (passes of 256 lanes) or a launch of its own.  Alone, 3684 tokens, 6784 x 64: 28 / 34 / 50 / 82 for the four; 8192,
-// 3584 x 64: 35 / 26 / 39 / 64; 22980, 5376 x 64: 102 / 96 / 97 / 86; 20882, 5760 x 128: 172 / 151 / 124 / 134.
+// 3584 x 64: 35 / 29 / 39 / 64; 22980, 5376 x 64: 102 / 96 / 97 / 90; 20882, 5760 x 128: 172 / 151 / 127 / 134 (the kernel before,
+// 32 or 64 tokens x all experts: 47, 36, 106 and 212).
 static int pick_tile(int T, int H, int E) {
     int best = 0;
     double least = 1e30;
