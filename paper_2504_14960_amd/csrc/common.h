@@ -6,6 +6,7 @@
 #include <stdint.h>
 
 #include "../../include/moe.h"
+#include "once_per_device.h"
 
 namespace moe {
 
@@ -16,6 +17,13 @@ typedef __attribute__((ext_vector_type(4))) float f32x4;
 typedef __attribute__((ext_vector_type(16))) float f32x16;
 typedef __attribute__((ext_vector_type(4))) uint32_t u32x4;
 typedef __attribute__((ext_vector_type(2))) uint32_t u32x2;
+
+// The dynamic LDS limit of a kernel on the current device (`lds`: the kernel's own)
+inline void allow_lds(OncePerDevice& lds, const void* kern, int bytes) {
+    int device = -1;   // unknown: set it every time
+    (void)hipGetDevice(&device);
+    lds.run(device, [&] { (void)hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); });
+}
 
 constexpr int kWave = 64;
 constexpr int kMaxExperts = 256;

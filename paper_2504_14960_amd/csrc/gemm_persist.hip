@@ -24,7 +24,6 @@
 
 #include "gemm_persist.h"
 #include "gemm_stream.h"
-#include "once_per_device.h"
 
 
 namespace moe {
@@ -758,12 +757,8 @@ void launch_persist(const void* A, const int32_t* offsets, int r_max, int E, int
     using No = std::false_type;
     using Skip = std::integral_constant<bool, SKIP>;
     auto kern = idle_skip ? (by_round ? pick(Skip{}, Yes{}) : pick(Skip{}, No{})) : (by_round ? pick(No{}, Yes{}) : pick(No{}, No{}));
-    static bool attr_set[2][2][2] = {};
-    if (!attr_set[idle_skip][by_round][ahead]) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)smem);
-        attr_set[idle_skip][by_round][ahead] = true;
-    }
+    static OncePerDevice lds[2][2][2];
+    allow_lds(lds[idle_skip][by_round][ahead], reinterpret_cast<const void*>(kern), (int)smem);
     // never more workgroups than the static bound on the tile count
     const int grid = min(persist_grid(), grid_for(r_max, E, HMIN, ntn));
     hipLaunchKernelGGL(kern, dim3(grid), dim3(WGM * WGN * 64), smem, s, static_cast<const bf16_t*>(A), offsets, E, N,
@@ -788,12 +783,8 @@ void launch_persist_groupk(const void* A, const void* B, const int32_t* offsets,
                            void* C, hipStream_t s) {
     constexpr size_t smem = (size_t)(3 * BM + 2 * BN) * 64 * 2;
     auto kern = gemm_bf16_persist_kernel<BM, BN, WGM, WGN, 0, true, false, false, false, true, STREAM_OUT, STREAM_OUT>;
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)smem);
-        attr_set = true;
-    }
+    static OncePerDevice lds;
+    allow_lds(lds, reinterpret_cast<const void*>(kern), (int)smem);
     const long long tiles = (long long)E * ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
     const int grid = (int)min((long long)persist_grid(), (tiles + 7) / 8 * 8);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(WGM * WGN * 64), smem, s, static_cast<const bf16_t*>(A), offsets, E, N,
@@ -807,12 +798,8 @@ void launch_persist_groupk_rowmajor(const void* A, int lda, const void* B, int l
                                     int M, int N, const void* zero_row, void* C, hipStream_t s) {
     constexpr size_t smem = (size_t)(3 * BM + 2 * BN) * 64 * 2;
     auto kern = gemm_bf16_persist_kernel<BM, BN, WGM, WGN, 0, true, true>;
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)smem);
-        attr_set = true;
-    }
+    static OncePerDevice lds;
+    allow_lds(lds, reinterpret_cast<const void*>(kern), (int)smem);
     const long long tiles = (long long)E * ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
     const int grid = (int)min((long long)persist_grid(), (tiles + 7) / 8 * 8);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(WGM * WGN * 64), smem, s, static_cast<const bf16_t*>(A), offsets, E, N,
@@ -910,9 +897,7 @@ bool launch_persist_split(const void* A, const int32_t* offsets, int r_max, int 
         constexpr size_t smem = (size_t)(2 * 256 + 3 * 256) * 64 * 2;
         auto kern = gemm_bf16_persist_kernel<0, 256, 2, 4, MODE, false, false, false, true, true, false, false, true>;
         static OncePerDevice lds;
-        int device = -1;   // unknown: set it every time
-        (void)hipGetDevice(&device);
-        lds.run(device, [&] { (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem); });
+        allow_lds(lds, reinterpret_cast<const void*>(kern), (int)smem);
         const int ntn = (N + OUTN - 1) / OUTN;
         const int grid = min(persist_grid(), grid_for(r_max, E, 128, ntn * splits));
         hipLaunchKernelGGL(kern, dim3(grid), dim3(512), smem, s, static_cast<const bf16_t*>(A), offsets, E, N, K,

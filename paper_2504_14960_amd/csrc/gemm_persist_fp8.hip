@@ -462,12 +462,8 @@ void launch_fp8(const void* A, const int32_t* offsets, int r_max, int E, int N, 
     const bool deep = g_fp8_deep_b != 0;
     auto kern = deep ? (idle_skip ? gemm_fp8_persist_kernel<SWIGLU, !SWIGLU, true> : gemm_fp8_persist_kernel<SWIGLU, false, true>)
                      : (idle_skip ? gemm_fp8_persist_kernel<SWIGLU, !SWIGLU, false> : gemm_fp8_persist_kernel<SWIGLU, false, false>);
-    static bool attr_set[2][2] = {{false, false}, {false, false}};
-    if (!attr_set[deep][idle_skip]) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)smem);
-        attr_set[deep][idle_skip] = true;
-    }
+    static OncePerDevice lds[2][2];
+    allow_lds(lds[deep][idle_skip], reinterpret_cast<const void*>(kern), (int)smem);
     const int grid = min(persist_grid(), grid_for(r_max, E, deep ? 128 : 256, ntn));
     hipLaunchKernelGGL(kern, dim3(grid), dim3(256), smem, s, static_cast<const uint8_t*>(A), offsets, E, N, K,
                        static_cast<const uint8_t*>(B0), static_cast<const uint8_t*>(B1), C, ntn, s0, s1, s2, amax,

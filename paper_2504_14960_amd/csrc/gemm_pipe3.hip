@@ -295,12 +295,8 @@ void launch_pipe3(const void* A, const int32_t* offsets, int r_max, int E, int N
     constexpr size_t smem = (size_t)(3 * BM + 2 * BN) * 64 * 2;
     const int ntn = (N + OUTN - 1) / OUTN;
     auto kern = gemm_bf16_pipe3_kernel<BM, BN, WGM, WGN, SWIGLU, false>;
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        attr_set = true;
-    }
+    static OncePerDevice lds;
+    allow_lds(lds, reinterpret_cast<const void*>(kern), (int)smem);
     const int grid = grid_for(r_max, E, BM, ntn);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(WGM * WGN * 64), smem, s, static_cast<const bf16_t*>(A),
                        offsets, E, N, K, static_cast<const bf16_t*>(B0),
@@ -314,12 +310,8 @@ void launch_pipe3_groupk(const void* A, const void* B, const int32_t* offsets, i
     constexpr size_t smem = (size_t)(3 * BM + 2 * BN) * 64 * 2;
     const int ntn = (N + BN - 1) / BN, mt = (M + BM - 1) / BM;
     auto kern = gemm_bf16_pipe3_kernel<BM, BN, WGM, WGN, false, true>;
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, (int)smem);
-        attr_set = true;
-    }
+    static OncePerDevice lds;
+    allow_lds(lds, reinterpret_cast<const void*>(kern), (int)smem);
     hipLaunchKernelGGL(kern, dim3(E * mt * ntn), dim3(WGM * WGN * 64), smem, s, static_cast<const bf16_t*>(A),
                        offsets, E, N, ld, static_cast<const bf16_t*>(B), static_cast<const bf16_t*>(B),
                        static_cast<bf16_t*>(C), ntn, M);

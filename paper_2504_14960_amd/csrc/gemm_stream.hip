@@ -25,7 +25,6 @@
 #include "fp8_convert.h"
 #include "gemm_stream.h"
 #include "gemm_tile.h"
-#include "once_per_device.h"
 #include "tile_cost.h"
 
 namespace moe {
@@ -683,13 +682,6 @@ void reduce_planes(const float* part, const int32_t* offsets, int E, int S, int 
     const long long groups = ((long long)r_max * N / 4 + 255) / 256;
     hipLaunchKernelGGL((stream_reduce_kernel<MODE>), dim3((int)(groups < 2048 ? groups : 2048)), dim3(256), 0, s, part, offsets, E, S,
                        r_max, N, static_cast<bf16_t*>(C));
-}
-
-// The LDS limit of a kernel on the current device (`lds`: the kernel's own)
-void allow_lds(OncePerDevice& lds, const void* kern, int bytes) {
-    int device = -1;   // unknown: set it every time
-    (void)hipGetDevice(&device);
-    lds.run(device, [&] { (void)hipFuncSetAttribute(kern, hipFuncAttributeMaxDynamicSharedMemorySize, bytes); });
 }
 
 template <int FB> constexpr int tile_rows() { return FB == 1 ? 64 : 128; }

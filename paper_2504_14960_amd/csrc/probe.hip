@@ -139,24 +139,16 @@ __global__ __launch_bounds__(256) void probe_mfma_fp8_kernel(const uint32_t* __r
 
 void launch_probe_mfma_fp8(const void* image, int iters, int workgroups, float* sink, unsigned long long* ticks,
                            hipStream_t s) {
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(probe_mfma_fp8_kernel),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, 65536);
-        attr_set = true;
-    }
+    static OncePerDevice lds;
+    allow_lds(lds, reinterpret_cast<const void*>(probe_mfma_fp8_kernel), 65536);
     hipLaunchKernelGGL(probe_mfma_fp8_kernel, dim3(workgroups), dim3(256), 65536, s,
                        static_cast<const uint32_t*>(image), iters, sink, ticks);
 }
 
 void launch_probe_mfma_bf16(const void* image, int iters, int workgroups, float* sink, unsigned long long* ticks,
                             hipStream_t s) {
-    static bool attr_set = false;
-    if (!attr_set) {
-        (void)hipFuncSetAttribute(reinterpret_cast<const void*>(probe_mfma_bf16_kernel),
-                                  hipFuncAttributeMaxDynamicSharedMemorySize, 65536);
-        attr_set = true;
-    }
+    static OncePerDevice lds;
+    allow_lds(lds, reinterpret_cast<const void*>(probe_mfma_bf16_kernel), 65536);
     hipLaunchKernelGGL(probe_mfma_bf16_kernel, dim3(workgroups), dim3(256), 65536, s,
                        static_cast<const uint32_t*>(image), iters, sink, ticks);
 }

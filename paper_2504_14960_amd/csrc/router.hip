@@ -13,7 +13,6 @@
 // to 16 experts, else one of its own); with many tokens and 17 to 128 experts the logits are computed in tiles of tokens and
 // experts (router_tile_kernel).
 #include "common.h"
-#include "once_per_device.h"
 
 namespace moe {
 
@@ -778,9 +777,7 @@ void launch_tile(const void* x, const void* w, const float* bias, float* logits,
     constexpr int smem = router_tile_stages<TM, TE>() * (TM + TE) * 128;
     auto kern = router_tile_kernel<TM, TE, SELECT>;
     static OncePerDevice lds;
-    int device = -1;   // unknown: set it every time
-    (void)hipGetDevice(&device);
-    lds.run(device, [&] { (void)hipFuncSetAttribute(reinterpret_cast<const void*>(kern), hipFuncAttributeMaxDynamicSharedMemorySize, smem); });
+    allow_lds(lds, reinterpret_cast<const void*>(kern), smem);
     hipLaunchKernelGGL(kern, dim3((T + TM - 1) / TM, (E + TE - 1) / TE), dim3(256), smem, s, static_cast<const bf16_t*>(x),
                        static_cast<const bf16_t*>(w), bias, logits, T, H, E, K, renorm, idx, gate);
 }

@@ -1,5 +1,6 @@
 """The host helper that sets a kernel's LDS limit: once on every device, not once per process.  CPU only."""
 import os
+import re
 import subprocess
 import tempfile
 
@@ -41,7 +42,13 @@ def test_once_on_every_device():
         assert subprocess.run([exe], timeout=60).returncode == 0
 
 
-def test_streaming_kernels_keep_no_process_wide_flag():
-    """fp32 and odd-size layers run on these kernels on whatever device is current."""
-    text = open(os.path.join(ROOT, "paper_2504_14960_amd", "csrc", "gemm_stream.hip")).read()
-    assert "static bool" not in text
+def test_no_launch_keeps_a_process_wide_flag():
+    """A kernel with more than 64 KiB of LDS needs its limit set on whatever device is current: every launch goes through the
+    helper, with a once-per-device flag of its own for each kernel that it chooses from."""
+    csrc = os.path.join(ROOT, "paper_2504_14960_amd", "csrc")
+    calls = []
+    for name in sorted(os.listdir(csrc)):
+        text = open(os.path.join(csrc, name)).read()
+        assert "static bool" not in re.sub(r"static bool \w+\(", "", text), name     # functions apart
+        calls += [name] * text.count("hipFuncSetAttribute(")
+    assert calls == ["common.h"], calls
