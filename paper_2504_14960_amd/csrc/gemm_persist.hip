@@ -756,7 +756,8 @@ void launch_persist(const void* A, const int32_t* offsets, int r_max, int E, int
     using Yes = std::true_type;
     using No = std::false_type;
     using Skip = std::integral_constant<bool, SKIP>;
-    auto kern = idle_skip ? (by_round ? pick(Skip{}, Yes{}) : pick(Skip{}, No{})) : (by_round ? pick(No{}, Yes{}) : pick(No{}, No{}));
+    using Shares = std::integral_constant<bool, MODE == 3>;   // MODE 3 has the rounds only
+    auto kern = idle_skip ? (by_round ? pick(Skip{}, Yes{}) : pick(Skip{}, Shares{})) : (by_round ? pick(No{}, Yes{}) : pick(No{}, Shares{}));
     static OncePerDevice lds[2][2][2];
     allow_lds(lds[idle_skip][by_round][ahead], reinterpret_cast<const void*>(kern), (int)smem);
     // never more workgroups than the static bound on the tile count
