@@ -388,6 +388,7 @@ __global__ __launch_bounds__(kSplitWaves * 64) void router_logits_kernel(
     int32_t* __restrict__ topk_idx, float* __restrict__ topk_gate) {
     constexpr int LD = 20;                     // row of a partial tile: the four lane groups of a store hit different banks
     constexpr int U = MB == 1 ? 4 : 3;         // steps in flight
+    static_assert(MB == 1 || !SELECT, "the lanes that sum a token's logits are the first turn's");
     __shared__ float part[kSplitWaves][16 * MB][LD];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int t0 = blockIdx.x * tb, e0 = blockIdx.y * eg;
@@ -444,30 +445,28 @@ __global__ __launch_bounds__(kSplitWaves * 64) void router_logits_kernel(
     if constexpr (SELECT) {
         // the sixteen lanes that summed a token's logits select its experts: the rank of an expert is the number of experts in
         // front of it (value descending, index ascending), as in topk_rank_kernel
-        const int le = lane & 15;
-        for (int lt = threadIdx.x >> 4; lt < 16 * MB; lt += kSplitWaves * 4) {
-            if (lt >= tb || t0 + lt >= T) break;
-            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            const float v = le < E ? part[0][lt][le] : -INFINITY;
-            float m = v;
-            int rank = 0;
-            for (int e = 0; e < E; ++e) {
-                const float s = part[0][lt][e];
-                rank += e < le ? s >= v : s > v;
-                m = fmaxf(m, s);
-            }
-            float p = le < E ? expf(v - m) : 0.f, z = p;
-            for (int off = 8; off > 0; off >>= 1) z += __shfl_xor(z, off, 16);
-            p = p / z;
-            const bool chosen = le < E && rank < K;
-            float gsum = chosen ? p : 0.f;
-            if (renorm)
-                for (int off = 8; off > 0; off >>= 1) gsum += __shfl_xor(gsum, off, 16);
-            if (chosen) {
-                topk_idx[(size_t)(t0 + lt) * K + rank] = le;
-                topk_gate[(size_t)(t0 + lt) * K + rank] = renorm ? p / gsum : p;
-            }
+        const int lt = threadIdx.x >> 4, le = lane & 15;
+        if (lt >= tb || t0 + lt >= T) return;
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const float v = le < E ? part[0][lt][le] : -INFINITY;
+        float m = v;
+        int rank = 0;
+        for (int e = 0; e < E; ++e) {
+            const float s = part[0][lt][e];
+            rank += e < le ? s >= v : s > v;
+            m = fmaxf(m, s);
+        }
+        float p = le < E ? expf(v - m) : 0.f, z = p;
+        for (int off = 8; off > 0; off >>= 1) z += __shfl_xor(z, off, 16);
+        p = p / z;
+        const bool chosen = le < E && rank < K;
+        float gsum = chosen ? p : 0.f;
+        if (renorm)
+            for (int off = 8; off > 0; off >>= 1) gsum += __shfl_xor(gsum, off, 16);
+        if (chosen) {
+            topk_idx[(size_t)(t0 + lt) * K + rank] = le;
+            topk_gate[(size_t)(t0 + lt) * K + rank] = renorm ? p / gsum : p;
         }
     }
 }
@@ -877,12 +876,12 @@ void launch_router(const void* x, const void* w, const float* bias, float* logit
         return;
     }
     if (nb == 1 && g_router_tile == 0 && T <= kOneBlockMaxTokens && (T > 512 || (long long)E * H <= 65536)) {
-        // all experts in a workgroup; tokens per workgroup: as few as leave every workgroup a compute unit
-        int tb = T >= 1024 ? 32 : 16;
+        // all experts in a workgroup; tokens per workgroup: as few as leave every workgroup a compute unit (16 at the most tokens)
+        static_assert(kOneBlockMaxTokens <= 16 * 256, "a workgroup of router_logits_kernel<1> holds 16 tokens");
+        int tb = 16;
         while (tb > 2 && (T + tb / 2 - 1) / (tb / 2) <= 256) tb /= 2;
         const dim3 grid((T + tb - 1) / tb);
-        auto kern = tb > 16 ? router_logits_kernel<2, true> : router_logits_kernel<1, true>;
-        hipLaunchKernelGGL(kern, grid, dim3(kSplitWaves * 64), 0, s, static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(w), bias,
+        hipLaunchKernelGGL((router_logits_kernel<1, true>), grid, dim3(kSplitWaves * 64), 0, s, static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(w), bias,
                            logits, T, H, E, tb, 16, K, renorm, idx, gate);
         return;
     }

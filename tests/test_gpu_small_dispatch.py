@@ -41,7 +41,8 @@ def test_experts_spread_over_workgroups(T, H, E, K, bias, renorm):
     (255, 264, 5, 5, "normal", True),       # every expert selected
     (513, 1032, 12, 3, None, False),        # four tokens per workgroup, one of them in the last
     (1023, 136, 16, 4, "normal", True),     # sixteen experts, no padding
-    (2048, 72, 15, 9, None, True),          # 32 tokens per workgroup in two blocks
+    (2048, 72, 15, 9, None, True),          # eight tokens per workgroup
+    (3001, 264, 16, 8, None, True),         # sixteen, nine of them in the last
     (4096, 64, 3, 2, "normal", False),      # the most tokens
 ])
 def test_router_and_selection_of_up_to_16_experts_in_one_launch(T, H, E, K, bias, renorm):
