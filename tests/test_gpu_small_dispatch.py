@@ -71,7 +71,8 @@ def test_router_and_selection_of_up_to_16_experts_in_one_launch(T, H, E, K, bias
     (4164, 1280, 64, 6, "normal", True),    # 32 x 64
     (2300, 2048, 128, 9, None, False),      # 32 x 64, two blocks, more slots than the list form takes
     (20000, 576, 40, 4, "normal", True),    # 64 x 64, a ragged last tile
-    (9500, 3072, 100, 8, None, True),       # 64 x 64, two blocks
+    (8100, 512, 100, 8, "normal", False),   # 64 x 64, two blocks, a ragged last tile
+    (9500, 3072, 100, 8, None, True),       # 128 x 64, two blocks, several stages past the ring
     (8200, 640, 128, 9, None, False),       # 128 x 64, two blocks
     (17000, 4096, 64, 6, "normal", True),   # 128 x 64, the selection in the workgroup
 ])
