@@ -330,3 +330,23 @@ def test_layer_training_step_in_two_calls(base, kw):
     for name, a, b in zip(("dx", "dw_router", "dbias", "dw_gate", "dw_up", "dw_down"), first, grads):
         bits = torch.int16 if a.dtype == torch.bfloat16 else torch.int32
         assert torch.equal(a.view(bits), b.view(bits)), f"{name} differs between two runs"
+
+
+@pytest.mark.parametrize("workgroups", [8, 13])
+def test_streamed_weight_gradients_of_several_tiles_per_workgroup(workgroups):
+    """Few rows per expert: a workgroup goes from the streamed stores of one tile to the next tile (two to five k-tiles), and
+    the first wait behind them leaves the stores out.  Six tiles a workgroup, against the oracle and the bits of one tile each."""
+    import paper_2504_14960_amd as moe
+    case = _ffn_backward_case(512, 640, 7, [1, 64, 65, 0, 130, 200, 300], 7900)
+    runs = []
+    moe.set_option("gemm_stream", 0)                       # the same forward kernels for both
+    try:
+        for n in (0, workgroups):                          # 0: as many as there are tiles
+            moe.set_option("gemm_workgroups", n)
+            runs.append(_run_ffn_backward(*case[:-1]))
+    finally:
+        moe.set_option("gemm_workgroups", 0)
+        moe.set_option("gemm_stream", -1)
+    for one, several, ref, what in zip(*runs, case[-1], ("dx_perm", "dw_gate", "dw_up", "dw_down")):
+        np.testing.assert_array_equal(several, one)
+        _assert_grad_close(several[:len(ref)], ref, what)

@@ -154,3 +154,15 @@ def test_large_tiles_in_parts(deep_shared, splits, rows):
         _check_split_layer(deep_shared, splits * c.T * (c.shared_F * 8 if c.H > c.shared_F else c.H * 4))
     finally:
         moe.set_option("gemm_tile_rows", 0)
+
+
+# from tile to tile the number of k-tiles (2624 elements in 3 parts: 13 or 14, in 5: 8 or 9) and the plane change
+@pytest.mark.parametrize("workgroups", [8, 13])
+@pytest.mark.parametrize("splits,rows", [(3, 0), (5, 256), (5, 192), (5, 128)])
+def test_large_tiles_in_parts_several_tiles_per_workgroup(deep_shared, splits, rows, workgroups):
+    import paper_2504_14960_amd as moe
+    moe.set_option("gemm_workgroups", workgroups)
+    try:
+        test_large_tiles_in_parts(deep_shared, splits, rows)
+    finally:
+        moe.set_option("gemm_workgroups", 0)

@@ -68,6 +68,48 @@ def test_fp8_heights_against_the_oracle_and_each_other(H, F, counts):
     assert np.linalg.norm(y - c["ref"].y) <= 5e-3 * np.linalg.norm(c["ref"].y)
 
 
+# few rows per expert (loads a period ahead) and, on average, more than 640 (the loads of both operands in step)
+MANY = [700, 1, 1300, 257, 0, 2000]
+
+
+@pytest.fixture(scope="module", params=[EDGES, MANY], ids=["few", "many"])
+def two_regimes(request):
+    return bf16_case(H=192, F=320, E=len(request.param), counts=request.param, bf16=True, seed=8300, r_pad=5)
+
+
+@pytest.mark.parametrize("workgroups", [8, 13, 0])
+def test_heights_several_tiles_per_workgroup(two_regimes, workgroups):
+    """A workgroup walks from tile to tile at every height, with the bits of one tile per workgroup."""
+    import paper_2504_14960_amd as moe
+    inp, x_perm, offsets, h_ref, y_ref = two_regimes
+    R = int(offsets[-1])
+    want_h, want_y = bf16_run(x_perm, offsets, inp, 0, r_max=R + 5)
+    assert_close(want_h[:R], h_ref, True, "h")
+    assert_close(want_y[:R], y_ref, True, "y_perm")
+    moe.set_option("gemm_workgroups", workgroups)
+    try:
+        for h, y in _each_height(lambda: bf16_run(x_perm, offsets, inp, 0, r_max=R + 5)):
+            np.testing.assert_array_equal(h, want_h)
+            np.testing.assert_array_equal(y, want_y)
+    finally:
+        moe.set_option("gemm_workgroups", 0)
+
+
+@pytest.mark.parametrize("workgroups", [8, 13])
+def test_fp8_heights_several_tiles_per_workgroup(workgroups):
+    import paper_2504_14960_amd as moe
+    c = fp8_case(seed=8400, H=256, F=384, E=len(EDGES), counts=EDGES)
+    want = fp8_run(c, r_pad=5)
+    moe.set_option("gemm_workgroups", workgroups)
+    try:
+        for got in _each_height(lambda: fp8_run(c, r_pad=5)):
+            np.testing.assert_array_equal(got[0], want[0])
+            np.testing.assert_array_equal(got[1], want[1])
+            assert got[2] == want[2]
+    finally:
+        moe.set_option("gemm_workgroups", 0)
+
+
 # the saving forward, dh with the SwiGLU's derivative and dx, at the heights that the sizes would not choose
 @pytest.mark.parametrize("rows", [256, 192, 128])
 @pytest.mark.parametrize("saved", [False, True])
@@ -75,6 +117,18 @@ def test_backward(rows, saved):
     import paper_2504_14960_amd as moe
     moe.set_option("gemm_tile_rows", rows)
     backward.test_expert_ffn_backward_against_oracle(256, 384, 7, [1, 130, 0, 192, 193, 257, 386], saved, 0)
+
+
+@pytest.mark.parametrize("rows,workgroups", [(256, 8), (192, 8), (192, 0), (128, 8), (128, 0)])
+@pytest.mark.parametrize("saved", [False, True])
+def test_backward_of_many_rows(rows, workgroups, saved):
+    import paper_2504_14960_amd as moe
+    moe.set_option("gemm_tile_rows", rows)
+    moe.set_option("gemm_workgroups", workgroups)
+    try:
+        backward.test_expert_ffn_backward_against_oracle(256, 384, len(MANY), MANY, saved, 0)
+    finally:
+        moe.set_option("gemm_workgroups", 0)
 
 
 def test_tile_rows_option_refuses_other_values():
