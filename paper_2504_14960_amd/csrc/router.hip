@@ -796,8 +796,14 @@ constexpr int kSplitMaxTokens = 2048, kSplitMinWeights = 32768;
 // Up to 16 experts, logits and selection in one launch of the split kernel (us, H x experts; the kernel for many tokens / logits +
 // selection / so): 4096 x 8, 1 token 8.3 / 6.7 / 5.8, 64 tokens 8.6 / 7.3 / 6.2, 2048 11.2 / 10.5 / 7.9, 4096 14.2 / - / 9.5, 8192
 // 21.2 / - / 19.3; 6144 x 8, 8192 tokens 25.2 / - / 27.9; 1000 x 12, 777 tokens 7.1 / 6.3 / 4.2; 1600 x 16, 11500 14.8 / - / 15.3.
-// With a large router weight a handful of tokens is better off with the experts spread (6 tokens, 6144 x 16: 1.5 us).
+// With a large router weight few tokens are better off with the experts spread (logits + selection / so: 6 tokens, 6144 x 16 1.5 us
+// less; 4096 x 16, 1 token 6.6 / 7.2, 64 tokens 7.4 / 7.8, 130 8.2 / 7.9; 5376 x 12, 1 token 7.4 / 7.9, 64 tokens 8.6 / 8.5; 7168 x 8,
+// 1 token 7.8 / 8.0, 8 tokens 9.2 / 8.5; 16384 x 4, 30 tokens 15.5 / 13.4): of more than eight experts up to 64 tokens from 57344
+// weights on, of any number up to 512 tokens from 65536.
 constexpr int kOneBlockMaxTokens = 4096;
+static bool one_block_pays(int T, int H, int E) {
+    return T <= kOneBlockMaxTokens && (T > 512 || (long long)E * H <= (T <= 64 && E > 8 ? 57344 : 65536));
+}
 // router_tile_kernel, from so many logits on (us in the layer, the kernels before / so): 2048 tokens, 6144 x 64 24.8 / 19.8, 1400,
 // 5248 x 128 34.4 / 15.5, 1473, 4096 x 60 16.4 / 12.3, 3684, 6784 x 64 53 / 25 + 7 for the selection, 4164, 5248 x 64 44 / 32, 20882,
 // 5760 x 128 239 / 120 + 24; 905, 4032 x 64 10.9 / 11.8; 32768, 2048 x 64 113 / 117 (the read of x, whatever the tile).
@@ -875,7 +881,7 @@ void launch_router(const void* x, const void* w, const float* bias, float* logit
         if (!fused) launch_topk(logits, T, E, K, renorm, idx, gate, s);
         return;
     }
-    if (nb == 1 && g_router_tile == 0 && T <= kOneBlockMaxTokens && (T > 512 || (long long)E * H <= 65536)) {
+    if (nb == 1 && g_router_tile == 0 && one_block_pays(T, H, E)) {
         // all experts in a workgroup; tokens per workgroup: as few as leave every workgroup a compute unit (16 at the most tokens)
         static_assert(kOneBlockMaxTokens <= 16 * 256, "a workgroup of router_logits_kernel<1> holds 16 tokens");
         int tb = 16;

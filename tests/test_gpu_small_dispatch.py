@@ -64,6 +64,23 @@ def test_router_and_selection_of_up_to_16_experts_in_one_launch(T, H, E, K, bias
         np.testing.assert_allclose(gate, want_gate, rtol=GATE_RTOL, atol=1e-6)
 
 
+@pytest.mark.parametrize("T,H,E", [(64, 4096, 16), (65, 4096, 16), (1, 6376, 9), (5, 8192, 8), (512, 4096, 16), (513, 4104, 16)])
+def test_both_sides_of_the_one_launch_line(T, H, E):
+    """One launch or two: the same sums in the same order, so the same bits."""
+    import paper_2504_14960_amd as moe
+    cfg = get_config("mixtral8x7b").scaled(T=T, H=H, E=E, K=3, bias="normal", seed=3250 + T)
+    inp = make_layer_inputs(cfg, ["x", "w_router", "bias"])
+    runs = []
+    for tile in (0, 8):
+        moe.set_option("router_tile", tile)
+        try:
+            runs.append(_gpu_topk(np.zeros((T, E), np.float32), 3, True, inp["x"], inp["w_router"], inp.bias))
+        finally:
+            moe.set_option("router_tile", 0)
+    for a, b in zip(*runs):
+        np.testing.assert_array_equal(a, b)
+
+
 @pytest.mark.parametrize("T,H,E,K,bias,renorm", [
     (5, 64, 17, 2, None, True),             # 32 x 32, one stage; fewer tokens than a tile, the selection in the workgroup
     (300, 512, 32, 4, "normal", False),     # as many stages as the ring
