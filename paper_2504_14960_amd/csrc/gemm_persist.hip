@@ -727,8 +727,11 @@ void launch_persist(const void* A, const int32_t* offsets, int r_max, int E, int
     constexpr int HMAX = BM != 0 ? BM : 256, HMIN = BM != 0 ? BM : 128;   // tallest and lowest tile
     constexpr size_t smem = (size_t)(DEEP_B ? 2 * HMAX + 3 * BN : 3 * HMAX + 2 * BN) * 64 * 2;
     if constexpr (BM == 0 && MODE != 3) {
-        // many rows on many experts: 256 rows would be chosen, and the kernel that holds this height alone is the faster one
-        // (32768 tokens, K = 6 of 64 experts, 2048 x 5632: 1 % of the layer; 768 to 2048 rows on 16 experts: 0.6 to 1 %)
+        // Many rows on many experts: 256 rows are mostly the best height, and the kernel that holds it alone is the faster one
+        // (32768 tokens, K = 6 of 64 experts, 4096 x 1408: 1 % of the layer; 768 to 2048 rows on 16 experts: 0.6 to 1 %).  r_max is a
+        // bound, not the rows there are, and a launch of a few rounds can be better off lower: 16 experts x 640 or 700 rows, gate/up
+        // 2048 x 1408 131 / 115 with 192 rows, 4096 x 1408 262 / 229, 1300 rows 460 / 407; down 2048 x 1408 65 / 58.  With 32 or 64
+        // experts no height was ahead by more than 5 %.  (large_us prices the best height here too.)
         if (g_persist_tile_rows == 0 && E >= 16 && r_max >= 640ll * E) {
             launch_persist<256, BN, WGM, WGN, MODE, DEEP_B>(A, offsets, r_max, E, N, K, B0, B1, C, GU, s);
             return;

@@ -6,7 +6,7 @@
 namespace moe {
 
 enum { kStreamF32 = 0, kStreamBf16 = 1, kStreamFp8 = 2 };   // operand type
-enum { kPlanLarge = 0, kPlanNarrow = 1, kPlanWide = 2 };    // 256-row tiles (another kernel), four waves, eight waves
+enum { kPlanLarge = 0, kPlanNarrow = 1, kPlanWide = 2 };    // large tiles (another kernel), four waves, eight waves
 
 struct StreamPlan {
     int kind;
@@ -16,7 +16,7 @@ struct StreamPlan {
 
 // rows of at most 16 MiB (32-bit offsets inside a tile)
 bool stream_covers(long long K_bytes);
-// The kernel for one product of r_max rows on E experts, [N, K] weights each; large_ok: the 256-row tiles cover the shape;
+// The kernel for one product of r_max rows on E experts, [N, K] weights each; large_ok: the large tiles cover the shape;
 // part_bytes: room for partial sums (0: the contraction is not split).  Depends on nothing but its arguments and options.
 StreamPlan plan_stream(int elt, int r_max, int E, int N, int K, bool swiglu, bool large_ok, size_t part_bytes);
 // room for partial sums that the plan wants, at most 64 MiB

@@ -3,8 +3,8 @@
 //
 // With few rows per expert the product is a read of the weights: what bounds it is how many bytes of them are on
 // their way from HBM at a time.  The large-tile kernel has one workgroup per 256 weight rows, so the down projection of
-// two experts (4096 outputs, one decoded token) is 32 workgroups on 256 compute units, and a 256-row tile is multiplied
-// whatever it holds.  Here a workgroup owns 16 to 256 weight rows, the weights go straight from memory into the
+// two experts (4096 outputs, one decoded token) is 32 workgroups on 256 compute units, and a tile of 128 rows or more is
+// multiplied whatever it holds.  Here a workgroup owns 16 to 256 weight rows, the weights go straight from memory into the
 // matrix instruction's operand registers (each byte is wanted by one wave only; two 16-byte loads per lane cover
 // whole 128-byte lines of 16 rows), and the rows of the tile decide how the other operand travels:
 //
@@ -807,11 +807,12 @@ void launch_any(const StreamArgs& p, int r_max, const StreamPlan& plan, float* p
 // The large tiles: tile_cost.h.  A round of the streaming workgroups takes (bytes of its weight rows) x 43 us/MB (36 where
 // several M-tiles share them), plus its rows at a smaller rate, plus its start and end, which the narrow workgroups, two to a
 // compute unit, mostly hide.  Fitted to gate/up and down at (E, H, F) = (1, 3584, 20480), (1, 2 and 8, 4096, 14336), (64, 3584,
-// 2560), (16, 2048, 1408) and (8, 2048, 4096) with 1 to 2000 rows per expert.  Over 650 products each in bf16 and FP8 (12
-// layers, 24 to 512 rows per expert, routers without bias, with a normal and a Zipf-1.2 one) the kernel they pick is behind
-// the best of the three by 1.7 % on average.  At most by 43 % (58 % in FP8): few experts, where the narrow kernel's second
-// workgroup per compute unit is priced too high (down, 4 experts x 72 rows, 4096 x 8192: wide 95, narrow 66), and by 37 %
-// for skewed routers, where it is priced too low (down, 8 experts x 24 rows, 6144 x 16384, Zipf: narrow 392, wide 287).
+// 2560), (16, 2048, 1408) and (8, 2048, 4096) with 1 to 2000 rows per expert.  Over 1260 products each in bf16 and FP8 (13
+// layers of 2 to 128 experts, 4 to 2000 rows per expert, equal, mildly and Zipf-1.2 skewed experts) the kernel they pick is
+// behind the best of the three by 2.7 % and 2.3 % on average.  At most by 72 % (70 % in FP8): two to eight experts, where the
+// narrow kernel's second workgroup per compute unit is priced too high (down, 8 experts x 48 rows, 2048 x 4096: wide 40, narrow
+// 24; 2 experts x 256 rows, 4096 x 8192: wide 89, narrow 58), and by 62 % for skewed routers, where it is priced too low (down, 16
+// experts x 24 rows, 2048 x 1408, Zipf: narrow 33, large tiles 20).
 struct Work {
     int experts, rows, N, kbytes, r_max;
     bool swiglu, fp8;

@@ -123,7 +123,7 @@ void launch_simple_gemm(const void* A, const int32_t* offsets, int r_max, int E,
 
 }  // namespace
 
-// whether the MFMA kernels with 256-row tiles take the layer
+// whether the MFMA kernels with large tiles take the layer
 static bool large_covers(moe_dtype_t dt, int H, int F) { return dt == MOE_BF16 && H % 64 == 0 && F % 64 == 0; }
 
 size_t expert_ffn_part_bytes(int r_max, int H, int F, int E, moe_dtype_t dt) {

@@ -524,7 +524,8 @@ __global__ __launch_bounds__(256) void router_tile_kernel(
                                              16, 0, 0);
     };
     // A logit is the sum of several separate sums (at least 4, 16 for the smallest tile), as in the kernels for fewer tokens: one
-    // sum over the whole row doubles the error (20882 tokens, 5760 x 128: 4.7e-7 against 64 bits; in four 2.3e-7).
+    // sum over the whole row doubles the error (20882 tokens, 5760 x 128, against 64 bits: one sum 4.7e-7, so 1.6e-7; the kernel for
+    // fewer experts 2.3e-7).
     constexpr int Q = 4 / KS;                                       // of a stage's four steps, this wave's
     constexpr int U = KS > 1 ? 4 : BPW == 1 ? 2 : 1;                // stages that follow one another in sums of their own
     f32x16 acc[U][Q][BPW];
@@ -806,7 +807,15 @@ static bool one_block_pays(int T, int H, int E) {
 }
 // router_tile_kernel, from so many logits on (us in the layer, the kernels before / so): 2048 tokens, 6144 x 64 24.8 / 19.8, 1400,
 // 5248 x 128 34.4 / 15.5, 1473, 4096 x 60 16.4 / 12.3, 3684, 6784 x 64 53 / 25 + 7 for the selection, 4164, 5248 x 64 44 / 32, 20882,
-// 5760 x 128 239 / 120 + 24; 905, 4032 x 64 10.9 / 11.8; 32768, 2048 x 64 113 / 117 (the read of x, whatever the tile).
+// 5760 x 128 239 / 127 + 24; 905, 4032 x 64 10.9 / 11.8.
+// Not for up to 64 experts from 32768 tokens on, where router_bf16_kernel takes 64 tokens a workgroup (alone): 32768 tokens, 2048 x 64
+// 46 / 57, 4096 x 64 72 / 74, 7168 x 64 132 / 117; 40000, 4096 x 64 113 / 123; 49152, 4096 x 32 87 / 89; 65536, 2048 x 48 71 / 82,
+// 6144 x 60 203 / 192.  Ahead only from some 5000 elements a row on, and not for every number of tokens.
+// The tiles are behind where the other kernel's workgroups of 32 tokens just fit the chip and the rows are short, by up to a
+// quarter at 1024 elements (alone): 64 experts, 12000 tokens 22.4 / 27.4; 32 experts, 20000 20.1 / 23.4; 72 experts, 6000 19.5 / 22.2;
+// up to 2048 tokens by 0.4 (1024 x 128, 1024 tokens 11.4 / 11.7); and for 65 to 80 experts at 8192 tokens whatever the row (7168 x 72
+// 49.4 / 53.3).  They are taken there as well: their logits are nearer to 64 bits (1024 elements 0.7 to 0.8 times the error, 4096
+// and more 0.5 to 0.7).
 constexpr long long kTileMinLogits = 80000;
 struct RouterTile {
     int tokens, experts;
@@ -814,7 +823,8 @@ struct RouterTile {
 constexpr RouterTile kTiles[4] = {{32, 32}, {32, 64}, {64, 64}, {128, 64}};
 
 // The tile with the least estimated time (us): rounds of workgroups at 45 bytes per nanosecond each, then the selection, in the
-// workgroup (passes of 256 lanes) or a launch of its own.  Alone, 3684 tokens, 6784 x 64: 28 / 34 / 50 / 82 for the four; 8192,
+// workgroup (passes of 256 lanes, counted for the last round only) or a launch of its own.  No floor for what comes from memory:
+// 32768 tokens, 4096 x 64 are estimated at 52 and take 74.  Alone, 3684 tokens, 6784 x 64: 28 / 34 / 50 / 82 for the four; 8192,
 // 3584 x 64: 35 / 29 / 39 / 64; 22980, 5376 x 64: 102 / 96 / 97 / 90; 20882, 5760 x 128: 172 / 151 / 127 / 134 (the kernel before,
 // 32 or 64 tokens x all experts: 47, 36, 106 and 212).
 static int pick_tile(int T, int H, int E) {
