@@ -52,3 +52,9 @@ def test_no_launch_keeps_a_process_wide_flag():
         assert "static bool" not in re.sub(r"static bool \w+\(", "", text), name     # functions apart
         calls += [name] * text.count("hipFuncSetAttribute(")
     assert calls == ["common.h"], calls
+
+
+def test_streaming_kernels_keep_no_process_wide_flag():
+    """fp32 and odd-size layers run on these kernels on whatever device is current."""
+    text = open(os.path.join(ROOT, "paper_2504_14960_amd", "csrc", "gemm_stream.hip")).read()
+    assert "static bool" not in text
