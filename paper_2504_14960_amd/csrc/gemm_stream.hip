@@ -22,9 +22,9 @@
 // and against the plain FMA kernel, which took these shapes before:
 //   12 experts, 2331 rows, 1000 x 1416         gate/up 310 /  50,                       down 271 /  30
 //   fp32, 8 experts x 64 rows, 128 x 256       gate/up  29 /   8,                       down  36 /   7
+// (fp32 with more than some 12 rows per expert: gemm_f32.hip, 6.3 and 6.6 us for the last one)
 #include "fp8_convert.h"
-#include "gemm_stream.h"
-#include "gemm_tile.h"
+#include "stream_tile.h"
 #include "tile_cost.h"
 
 namespace moe {
@@ -38,76 +38,6 @@ constexpr int kScratch = 64;   // bytes of LDS behind the ring: one float per wa
 // that the persistent large tiles do not take (see silu_mul)
 
 constexpr int kEltF32 = kStreamF32, kEltBf16 = kStreamBf16, kEltFp8 = kStreamFp8;
-
-// The tile of a workgroup, as find_tile orders them, worked out by every wave for itself with its lanes (lane l: experts 4 l ..
-// 4 l + 3): one read of the offsets, no LDS and no barrier in front of the first load of the operands.  The LDS form reads the
-// tile's two offsets from memory once more and meets two barriers; a launch of one round of workgroups shows all of it (us of
-// the layer: 256 fp32 tokens, 128 x 256 27.0 / 25.7; one token of Mixtral-8x7B 141.9 / 140.0; FP8, 32 tokens 276.7 / 274.8).
-template <int BM>
-__device__ __forceinline__ Tile locate_tile(const int32_t* __restrict__ offsets, int E, int ntn) {
-    constexpr int MG = 8;
-    const int lane = threadIdx.x & 63;
-    int lo[5], mt[4], s = 0;
-#pragma unroll
-    for (int j = 0; j < 5; ++j) lo[j] = offsets[min(4 * lane + j, E)];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-        mt[j] = max(0, (lo[j + 1] - lo[j] + BM - 1) / BM);
-        s += mt[j];
-    }
-    int incl = s;
-    for (int d = 1; 4 * d < E; d <<= 1) {   // lanes past the last expert have nothing to add
-        const int o = __shfl_up(incl, d, 64);
-        if (lane >= d) incl += o;
-    }
-    Tile t;
-    t.valid = false;
-    t.expert = 0; t.row0 = 0; t.rows = 0; t.row_end = 0; t.ntile = 0;
-    const int MT = __builtin_amdgcn_readlane(incl, (E - 1) >> 2);
-    const int total = MT * ntn, per = (total + 7) / 8;
-    const int j = (int)(blockIdx.x >> 3), L = (int)(blockIdx.x & 7) * per + j;
-    if (j >= per || L >= total) return t;
-    const int qm = L / ntn;
-    int hit = -1, my_p = 0, my_mt = 0, my_lo = 0, my_hi = 0, p = incl - s;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-        if (p <= qm && qm < p + mt[q]) {
-            hit = q; my_p = p; my_mt = mt[q]; my_lo = lo[q]; my_hi = lo[q + 1];
-        }
-        p += mt[q];
-    }
-    // the M-tile ranges of the experts partition [0, MT): exactly one lane (those past the last expert hold empty ones)
-    const int src = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)__ballot(hit >= 0)) - 1);
-    const int p_e = __builtin_amdgcn_readlane(my_p, src), mt_e = __builtin_amdgcn_readlane(my_mt, src);
-    const int row_lo = __builtin_amdgcn_readlane(my_lo, src);
-    t.expert = 4 * src + __builtin_amdgcn_readlane(hit, src);
-    t.row_end = __builtin_amdgcn_readlane(my_hi, src);
-    // the expert's M-tiles in groups of nearly equal size (see find_tile)
-    const int Le = L - p_e * ntn;
-    const int ng = (mt_e + MG - 1) / MG, gbase = mt_e / ng, grem = mt_e % ng;
-    const int big = grem * (gbase + 1) * ntn;
-    const bool first = Le < big;
-    const int gsz = first ? gbase + 1 : gbase, at = first ? Le : Le - big;
-    const int g = at / (gsz * ntn), rem = at - g * gsz * ntn;
-    const int n = rem / gsz, m = (first ? 0 : grem * (gbase + 1)) + g * gsz + rem - n * gsz;
-    t.row0 = row_lo + m * BM;
-    t.rows = min(BM, t.row_end - t.row0);
-    t.ntile = n;
-    t.valid = true;
-    return t;
-}
-
-// What a lane holds of a 128-byte k-step of one operand row: lane group j = lane / 16 of row lane % 16 holds the 32 bytes
-// from 32 j (two 16-byte loads; the four groups together ask for the row's whole line).  The contraction order inside a step
-// is the same for both operands, so any assignment of bytes to contraction slots is right.
-struct Piece {
-    u32x4 lo, hi;
-};
-
-// 16 bytes of global memory (the pointer arithmetic below hides from the compiler where its pointers point)
-__device__ __forceinline__ u32x4 ld16(const uint8_t* p) {
-    return *(const __attribute__((address_space(1))) u32x4*)p;
-}
 
 template <int ELT>
 __device__ __forceinline__ f32x4 mul_step(const Piece& w, const Piece& a, f32x4 acc) {
@@ -134,21 +64,6 @@ __device__ __forceinline__ f32x4 mul_step(const Piece& w, const Piece& a, f32x4 
     return acc;
 }
 
-struct StreamArgs {
-    const uint8_t* A;
-    const int32_t* offsets;
-    const uint8_t* B0;
-    const uint8_t* B1;
-    void* C;
-    void* GU;
-    float* amax;
-    unsigned long long* ticks;   // clock sample of workgroup 0, or null
-    float s0, s1, s2;
-    int E, N, kbytes, ntn;
-    int units, S, r_max;   // wide kernel: 32-row units per tile, splits of the contraction; rows of a partial plane
-    float* part;           // split partial sums [S][r_max][N, or 2 N with SwiGLU], or null
-};
-
 // Where a workgroup's tile lies: FB blocks of 16 weight rows (with SwiGLU half of them gate rows and half the matching
 // up rows) against the rows of one expert.
 template <int MODE, int FB>
@@ -165,27 +80,6 @@ struct TileAt {
         b[1] = (MODE != 0 ? p.B1 : p.B0) + wrow;
     }
 };
-
-// Where a workgroup starts in its n steps of the contraction.  Operand rows lie a whole row apart, so workgroups that
-// walk the contraction in step ask the same few memory channels at a time.  The order of a row's sum is thus that of its
-// weight tile and expert, and beyond that of the form: the number of rows in its tile, and the plan, which follows r_max.  The
-// same call gives the same bits; another batch around a row may not.  Measured (us, all from step 0 / so): down 4096 x 14336,
-// 2 experts x 8 rows 51.0 / 44.6, 8 experts x 32 rows 187.7 / 175.1; gate/up 1408 x 2048, 16 experts x 8 rows 43.2 / 38.7.
-__device__ __forceinline__ int rotation(const Tile& t, int n) {
-    return n > 0 ? __builtin_amdgcn_readfirstlane((int)((unsigned)(t.ntile * 3 + t.expert * 5) % (unsigned)n)) : 0;
-}
-
-// One lane's piece of a row's last, partial 128-byte block: bytes past the row's end count as zeros (`row`: the row at
-// the block's start; rem: bytes left, a multiple of 16).
-__device__ __forceinline__ Piece tail_piece(const uint8_t* row, int j, int rem) {
-    const bool lo_in = 32 * j < rem, hi_in = 32 * j + 16 < rem;
-    Piece v;
-    v.lo = ld16(row + (lo_in ? 32 * j : 0));
-    v.hi = ld16(row + (hi_in ? 32 * j + 16 : 0));
-    if (!lo_in) v.lo = u32x4{0u, 0u, 0u, 0u};
-    if (!hi_in) v.hi = u32x4{0u, 0u, 0u, 0u};
-    return v;
-}
 
 // silu(g) * u as the persistent large tiles form it for the shapes they take, with the fast exponential and reciprocal; for
 // the rest (fp32; MODE 3: H or F not a multiple of 64, or H = 64) with the full expf and divide of the plain FMA kernel:
@@ -738,6 +632,7 @@ void launch(StreamArgs p, int r_max, hipStream_t s) {
 int g_stream = -1;   // see set_gemm_stream
 int forced_blocks() { return g_stream > 10 && g_stream < 20 ? g_stream - 10 : 0; }
 bool forced_wide() { return g_stream >= 100 && g_stream < 2000; }
+int forced_f32_form() { return g_stream >= 20 && g_stream < 25 ? g_stream - 20 : -1; }
 int forced_large_splits() { return g_stream >= 2000 ? g_stream - 2000 : 0; }
 
 // Weight blocks of a narrow workgroup: as many as leave enough workgroups.  A wider workgroup reads the rows less often
@@ -798,6 +693,9 @@ void launch_any(const StreamArgs& p, int r_max, const StreamPlan& plan, float* p
             launch_wide<ELT, MODE>(p, r_max, plan, part, s);
             return;
         }
+    } else if (plan.kind == kPlanF32) {
+        launch_f32_tiles(p, plan.units, r_max, s);
+        return;
     }
     launch_narrow<ELT, MODE>(p, r_max, s);
 }
@@ -887,6 +785,28 @@ double wide_us(const Work& w, int units, int S) {
     return rounds_of(tiles * (1.0 + 0.12 * skew_share(w, 128))) * round + reduce_us(w, S);
 }
 
+// fp32 tiles: a start and, for every block of the contraction that a group of waves takes, the longer of what one workgroup needs
+// alone and what the workgroups of a compute unit need together; forms 0 and 1 fill a compute unit's LDS, so they take whole rounds
+// (with a margin: the experts are not equal).  Fitted to 220 products (see gemm_f32.hip), rms error 9 to 15 %; the form they choose
+// is behind the best by 4 % on average, where the fp32 instruction is the better one included.
+double f32_us(const Work& w, int form) {
+    struct Form {
+        int rows, weights, groups;
+        double start, alone, load, power;
+    };
+    constexpr Form kForms[5] = {{32, 32, 8, 1.0, 1.40, 2.87, 0.0}, {32, 64, 4, 0.6, 1.31, 3.49, 0.0}, {32, 128, 1, 4.6, 0.62, 0.64, 1.75},
+                                {64, 64, 2, 4.8, 0.95, 1.28, 3.5}, {128, 128, 1, 7.1, 1.13, 1.76, 4.1}};
+    constexpr double kSpread[8] = {0.386, 0.552, 0.717, 0.883, 1.048, 1.214, 1.434, 1.766};   // as large_us
+    const Form& f = kForms[form];
+    double mt = 0.0;
+    for (const double x : kSpread) mt += w.experts / 8.0 * (double)(long long)((w.rows * x + f.rows - 1e-6) / f.rows);
+    mt = 0.5 * (mt + (double)w.experts * blocks_of(w.rows, f.rows));
+    const double per_cu = mt * blocks_of(w.N, w.swiglu ? f.weights / 2 : f.weights) / kUnitsCU;
+    const double blocks = (double)blocks_of(w.kbytes, 128 * f.groups);
+    if (f.power == 0.0) return f.start + (per_cu <= 0.85 ? 1.0 : per_cu + 0.6) * (f.load + blocks * f.alone);
+    return f.start + blocks * pow(pow(f.alone, f.power) + pow(f.load * per_cu, f.power), 1.0 / f.power);
+}
+
 constexpr size_t kMaxPartBytes = 64u << 20;   // partial planes of one product, at most
 
 }  // namespace
@@ -913,7 +833,26 @@ StreamPlan plan_stream(int elt, int r_max, int E, int N, int K, bool swiglu, boo
         plan.kind = kPlanLarge;
         return plan;
     }
-    if (elt == kEltF32 || g_stream == 1 || forced_blocks() || !stream_covers(kbytes)) return plan;
+    w.kbytes = (int)kbytes;
+    w.r_max = r_max;
+    w.swiglu = swiglu;
+    w.fp8 = elt == kStreamFp8;
+    if (g_stream == 1 || forced_blocks() || !stream_covers(kbytes)) return plan;
+    if (elt == kEltF32) {
+        // Up to 12 rows per expert most tiles have at most 16 and the narrow kernel's form for those is the better one (us, fp32
+        // instruction / tiles: 4 experts x 4 rows, 572 x 632 4.6 / 7.5; 8 x 12, 308 x 456 6.0 / 8.5; 16 x 12, 996 x 460 27 / 18)
+        if (forced_f32_form() < 0 && 2 * r_max <= 25 * w.experts) return plan;
+        plan.kind = kPlanF32;
+        double best = 1e30;
+        for (int form = 0; form < 5; ++form) {
+            const double t = f32_us(w, form);
+            if (forced_f32_form() >= 0 ? form == forced_f32_form() : t < best) {
+                best = t;
+                plan.units = form;
+            }
+        }
+        return plan;
+    }
     // a split leaves at least 16 blocks of the contraction to a workgroup
     auto splits_fit = [&](int S) {
         return S == 1 || (elt == kEltBf16 && kbytes / 128 >= 16 * S && (size_t)S * r_max * N * (swiglu ? 8 : 4) <= part_bytes);
@@ -934,10 +873,6 @@ StreamPlan plan_stream(int elt, int r_max, int E, int N, int K, bool swiglu, boo
         if (large_splits_fit(forced_large_splits())) plan.splits = forced_large_splits();
         return plan;
     }
-    w.kbytes = (int)kbytes;
-    w.r_max = r_max;
-    w.swiglu = swiglu;
-    w.fp8 = elt == kStreamFp8;
     double best = g_stream == 2 ? 1e30 : narrow_us(w, narrow_blocks(r_max, E, N, swiglu));
     if (g_stream < 0 && large_ok) {
         const double t = large_us(w);

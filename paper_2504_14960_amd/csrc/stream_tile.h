@@ -1,0 +1,123 @@
+// Pieces shared by the weight-streaming kernels (gemm_stream.hip) and the fp32 tiles (gemm_f32.hip): the tile of a workgroup, where
+// it starts in its contraction, loads of the operands.
+#pragma once
+
+#include "gemm_stream.h"
+#include "gemm_tile.h"
+
+namespace moe {
+
+struct StreamArgs {
+    const uint8_t* A;
+    const int32_t* offsets;
+    const uint8_t* B0;
+    const uint8_t* B1;
+    void* C;
+    void* GU;
+    float* amax;
+    unsigned long long* ticks;   // clock sample of workgroup 0, or null
+    float s0, s1, s2;
+    int E, N, kbytes, ntn;
+    int units, S, r_max;   // wide kernel: 32-row units per tile, splits of the contraction; rows of a partial plane
+    float* part;           // split partial sums [S][r_max][N, or 2 N with SwiGLU], or null
+};
+
+// fp32 products in tiles (gemm_f32.hip), form 0 .. 3
+void launch_f32_tiles(const StreamArgs& p, int form, int r_max, hipStream_t s);
+
+namespace {
+
+// The tile of a workgroup, as find_tile orders them, worked out by every wave for itself with its lanes (lane l: experts 4 l ..
+// 4 l + 3): one read of the offsets, no LDS and no barrier in front of the first load of the operands.  The LDS form reads the
+// tile's two offsets from memory once more and meets two barriers; a launch of one round of workgroups shows all of it (us of
+// the layer: 256 fp32 tokens, 128 x 256 27.0 / 25.7; one token of Mixtral-8x7B 141.9 / 140.0; FP8, 32 tokens 276.7 / 274.8).
+template <int BM>
+__device__ __forceinline__ Tile locate_tile(const int32_t* __restrict__ offsets, int E, int ntn) {
+    constexpr int MG = 8;
+    const int lane = threadIdx.x & 63;
+    int lo[5], mt[4], s = 0;
+#pragma unroll
+    for (int j = 0; j < 5; ++j) lo[j] = offsets[min(4 * lane + j, E)];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        mt[j] = max(0, (lo[j + 1] - lo[j] + BM - 1) / BM);
+        s += mt[j];
+    }
+    int incl = s;
+    for (int d = 1; 4 * d < E; d <<= 1) {   // lanes past the last expert have nothing to add
+        const int o = __shfl_up(incl, d, 64);
+        if (lane >= d) incl += o;
+    }
+    Tile t;
+    t.valid = false;
+    t.expert = 0; t.row0 = 0; t.rows = 0; t.row_end = 0; t.ntile = 0;
+    const int MT = __builtin_amdgcn_readlane(incl, (E - 1) >> 2);
+    const int total = MT * ntn, per = (total + 7) / 8;
+    const int j = (int)(blockIdx.x >> 3), L = (int)(blockIdx.x & 7) * per + j;
+    if (j >= per || L >= total) return t;
+    const int qm = L / ntn;
+    int hit = -1, my_p = 0, my_mt = 0, my_lo = 0, my_hi = 0, p = incl - s;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+        if (p <= qm && qm < p + mt[q]) {
+            hit = q; my_p = p; my_mt = mt[q]; my_lo = lo[q]; my_hi = lo[q + 1];
+        }
+        p += mt[q];
+    }
+    // the M-tile ranges of the experts partition [0, MT): exactly one lane (those past the last expert hold empty ones)
+    const int src = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)__ballot(hit >= 0)) - 1);
+    const int p_e = __builtin_amdgcn_readlane(my_p, src), mt_e = __builtin_amdgcn_readlane(my_mt, src);
+    const int row_lo = __builtin_amdgcn_readlane(my_lo, src);
+    t.expert = 4 * src + __builtin_amdgcn_readlane(hit, src);
+    t.row_end = __builtin_amdgcn_readlane(my_hi, src);
+    // the expert's M-tiles in groups of nearly equal size (see find_tile)
+    const int Le = L - p_e * ntn;
+    const int ng = (mt_e + MG - 1) / MG, gbase = mt_e / ng, grem = mt_e % ng;
+    const int big = grem * (gbase + 1) * ntn;
+    const bool first = Le < big;
+    const int gsz = first ? gbase + 1 : gbase, at = first ? Le : Le - big;
+    const int g = at / (gsz * ntn), rem = at - g * gsz * ntn;
+    const int n = rem / gsz, m = (first ? 0 : grem * (gbase + 1)) + g * gsz + rem - n * gsz;
+    t.row0 = row_lo + m * BM;
+    t.rows = min(BM, t.row_end - t.row0);
+    t.ntile = n;
+    t.valid = true;
+    return t;
+}
+
+// What a lane holds of a 128-byte k-step of one operand row: lane group j = lane / 16 of row lane % 16 holds the 32 bytes
+// from 32 j (two 16-byte loads; the four groups together ask for the row's whole line).  The contraction order inside a step
+// is the same for both operands, so any assignment of bytes to contraction slots is right.
+struct Piece {
+    u32x4 lo, hi;
+};
+
+// 16 bytes of global memory (the pointer arithmetic below hides from the compiler where its pointers point)
+__device__ __forceinline__ u32x4 ld16(const uint8_t* p) {
+    return *(const __attribute__((address_space(1))) u32x4*)p;
+}
+
+// Where a workgroup starts in its n steps of the contraction.  Operand rows lie a whole row apart, so workgroups that
+// walk the contraction in step ask the same few memory channels at a time.  The order of a row's sum is thus that of its
+// weight tile and expert, and beyond that of the form: the number of rows in its tile, and the plan, which follows r_max.  The
+// same call gives the same bits; another batch around a row may not.  Measured (us, all from step 0 / so): down 4096 x 14336,
+// 2 experts x 8 rows 51.0 / 44.6, 8 experts x 32 rows 187.7 / 175.1; gate/up 1408 x 2048, 16 experts x 8 rows 43.2 / 38.7.
+__device__ __forceinline__ int rotation(const Tile& t, int n) {
+    return n > 0 ? __builtin_amdgcn_readfirstlane((int)((unsigned)(t.ntile * 3 + t.expert * 5) % (unsigned)n)) : 0;
+}
+
+// One lane's piece of a row's last, partial 128-byte block: bytes past the row's end count as zeros (`row`: the row at
+// the block's start; rem: bytes left, a multiple of 16).
+__device__ __forceinline__ Piece tail_piece(const uint8_t* row, int j, int rem) {
+    const bool lo_in = 32 * j < rem, hi_in = 32 * j + 16 < rem;
+    Piece v;
+    v.lo = ld16(row + (lo_in ? 32 * j : 0));
+    v.hi = ld16(row + (hi_in ? 32 * j + 16 : 0));
+    if (!lo_in) v.lo = u32x4{0u, 0u, 0u, 0u};
+    if (!hi_in) v.hi = u32x4{0u, 0u, 0u, 0u};
+    return v;
+}
+
+}  // namespace
+
+}  // namespace moe
