@@ -545,7 +545,8 @@ moe_status_t moe_gemm_clock_sample(uint64_t* ticks);
  * chosen by size, the default; 0 = only for the shapes no other kernel takes; 1 =
  * always, under "gemm_variant" 0 and in FP8; 2 = always, with wide workgroups
  * where the type has them; 11, 12, 14, 18 = as 1 with 16, 32, 64, 128 weight rows
- * per workgroup; 20 to 24 = fp32 layers on the tiles of one of their five forms, whatever the rows per expert; 100 S + U = as 2 with U = 3 to 8 times 32 weight rows per
+ * per workgroup; 20 to 24 = always the small tiles, in
+ * the form 0 to 4 (0 to 3 in bf16 and FP8); 100 S + U = as 2 with U = 3 to 8 times 32 weight rows per
  * workgroup and, where there is room for partial sums, the contraction in S = 1,
  * 2, 4, 8 or 16 parts; 2000 + S = the large tiles, and where there is room the contraction in S = 2 to
  * 16 parts); "fp8_deep_weights" (FP8 expert GEMMs: 1, the default = three LDS stages for

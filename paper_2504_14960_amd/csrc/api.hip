@@ -919,8 +919,8 @@ moe_status_t moe_set_option(const char* name, int value) {
         const int fb = value - 10, units = value % 100, splits = value / 100;
         const bool narrow = fb == 1 || fb == 2 || fb == 4 || fb == 8;
         const bool wide = units >= 3 && units <= 8 && splits >= 1 && splits <= 16 && (splits & (splits - 1)) == 0;
-        const bool large = value >= 2002 && value <= 2016, f32 = value >= 20 && value <= 24;
-        moe::set_gemm_stream(value < 0 ? -1 : value > 2 && !narrow && !wide && !large && !f32 ? 1 : value);
+        const bool large = value >= 2002 && value <= 2016, tiles = value >= 20 && value <= 24;
+        moe::set_gemm_stream(value < 0 ? -1 : value > 2 && !narrow && !wide && !large && !tiles ? 1 : value);
         return MOE_OK;
     }
     if (name && strcmp(name, "fp8_deep_weights") == 0) {

@@ -6,12 +6,12 @@
 namespace moe {
 
 enum { kStreamF32 = 0, kStreamBf16 = 1, kStreamFp8 = 2 };   // operand type
-// large tiles (another kernel), four waves, eight waves, fp32 tiles on the bf16 instruction (gemm_f32.hip)
-enum { kPlanLarge = 0, kPlanNarrow = 1, kPlanWide = 2, kPlanF32 = 3 };
+// large tiles (another kernel), four waves, eight waves, small tiles (gemm_tiles.hip)
+enum { kPlanLarge = 0, kPlanNarrow = 1, kPlanWide = 2, kPlanTiles = 3 };
 
 struct StreamPlan {
     int kind;
-    int units;    // wide: blocks of 32 weight rows per workgroup; fp32 tiles: their form
+    int units;    // wide: blocks of 32 weight rows per workgroup; small tiles: their form
     int splits;   // wide, large: parts of the contraction
 };
 
@@ -27,7 +27,7 @@ void launch_stream_reduce(bool swiglu, const float* part, const int32_t* offsets
                           hipStream_t s);
 // -1 (default): by size; 0: only the shapes no other kernel takes; 1: always the narrow, 2: always the wide form.  10 + FB:
 // narrow with FB (1, 2, 4, 8) blocks of 16 weight rows per workgroup (2 for 1 with SwiGLU; 2 or 4 for at most 16 rows in
-// all); 20 + form (0 .. 4): fp32 tiles of that form; 100 S + U: wide with U (3 .. 8) units and S (1, 2, 4, 8, 16) splits, halved until they fit the contraction and the room; 2000 + S:
+// all); 20 + form: small tiles of that form; 100 S + U: wide with U (3 .. 8) units and S (1, 2, 4, 8, 16) splits, halved until they fit the contraction and the room; 2000 + S:
 // the large tiles, their contraction in S (2 .. 16) parts where that fits the contraction and the room
 void set_gemm_stream(int v);
 

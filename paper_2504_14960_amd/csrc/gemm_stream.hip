@@ -22,8 +22,7 @@
 // and against the plain FMA kernel, which took these shapes before:
 //   12 experts, 2331 rows, 1000 x 1416         gate/up 310 /  50,                       down 271 /  30
 //   fp32, 8 experts x 64 rows, 128 x 256       gate/up  29 /   8,                       down  36 /   7
-// (fp32 with more than some 12 rows per expert: gemm_f32.hip, 6.3 and 6.6 us for the last one)
-#include "fp8_convert.h"
+// (fp32 with more than some 12 rows per expert, and much of bf16 and FP8 between these rows and the large tiles': gemm_tiles.hip)
 #include "stream_tile.h"
 #include "tile_cost.h"
 
@@ -33,9 +32,6 @@ namespace {
 
 constexpr int NW = 4;   // waves per workgroup
 constexpr int kScratch = 64;   // bytes of LDS behind the ring: one float per wave (fold_amax)
-
-// MODE of the kernels: 0 one product, 1 the SwiGLU pair, 2 the pair with its pre-activations stored too, 3 as 1 for the shapes
-// that the persistent large tiles do not take (see silu_mul)
 
 constexpr int kEltF32 = kStreamF32, kEltBf16 = kStreamBf16, kEltFp8 = kStreamFp8;
 
@@ -81,53 +77,13 @@ struct TileAt {
     }
 };
 
-// silu(g) * u as the persistent large tiles form it for the shapes they take, with the fast exponential and reciprocal; for
-// the rest (fp32; MODE 3: H or F not a multiple of 64, or H = 64) with the full expf and divide of the plain FMA kernel:
-// the fast exponential's error grows with |g|, some 40 units in the last place at g = -60.  (gate/up of 2331 rows on 12
-// experts, 1000 x 1416: 50.4 us with the fast form, 51.6 with the full one.)
-template <int ELT, int MODE>
-__device__ __forceinline__ float silu_mul(float g, float u) {
-    if constexpr (ELT == kEltF32 || MODE == 3) return (g / (1.f + expf(-g))) * u;
-    else return g * __builtin_amdgcn_rcpf(1.f + __expf(-g)) * u;
-}
-
 // Stores the 16 x 16 output block (row block i, column block f) from its sums: v (with SwiGLU the gate's) and up.  A
 // lane holds row 16 i + lane % 16 and four consecutive columns.  Returns the largest |h| stored (FP8).
 template <int ELT, int MODE>
 __device__ __forceinline__ float store_block(const StreamArgs& p, const Tile& t, int n0, int i, int f, f32x4 v, f32x4 up) {
-    constexpr bool SWIGLU = MODE != 0;
     const int lane = threadIdx.x & 63;
     const int m = 16 * i + (lane & 15), col = n0 + 16 * f + 4 * (lane >> 4);
-    const bool in = m < t.rows && col < p.N;
-    const size_t at = (size_t)(t.row0 + m) * p.N + col;
-    float amax = 0.f;
-    if constexpr (SWIGLU) {
-        if constexpr (ELT == kEltFp8) { v *= p.s0; up *= p.s1; }
-        if (MODE == 2 && in) {
-            u32x2 g2 = {pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3])};
-            u32x2 u2 = {pack2_bf16(up[0], up[1]), pack2_bf16(up[2], up[3])};
-            bf16_t* gu = static_cast<bf16_t*>(p.GU) + (size_t)(t.row0 + m) * (2 * p.N) + col;
-            *reinterpret_cast<u32x2*>(gu) = g2;
-            *reinterpret_cast<u32x2*>(gu + p.N) = u2;
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) v[q] = silu_mul<ELT, MODE>(v[q], up[q]);
-    } else if constexpr (ELT == kEltFp8) {
-        v *= p.s0;
-    }
-    if (!in) return amax;
-    if constexpr (ELT == kEltF32) {
-        *reinterpret_cast<f32x4*>(static_cast<float*>(p.C) + at) = v;
-    } else if constexpr (ELT == kEltFp8 && SWIGLU) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q) amax = fmaxf(amax, fabsf(v[q]));
-        *reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(p.C) + at) =
-            f32x4_to_e4m3(v[0] * p.s2, v[1] * p.s2, v[2] * p.s2, v[3] * p.s2);
-    } else {
-        u32x2 o = {pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3])};
-        *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.C) + at) = o;
-    }
-    return amax;
+    return store_four<ELT, MODE>(p, m < t.rows && col < p.N, t.row0 + m, col, v, up);
 }
 
 // Sums the partial products red[slot][row block][weight block][lane] in slot order and stores the outputs.
@@ -149,20 +105,6 @@ __device__ __forceinline__ float finish_tile(const StreamArgs& p, const Tile& t,
         amax = fmaxf(amax, store_block<ELT, MODE>(p, t, n0, i, f, v, up));
     }
     return amax;
-}
-
-// max |h| of the workgroup into *amax: one atomic per workgroup at most, and none if the value read is already as large
-// (*amax only grows; as floats >= 0 compare like their bit patterns).  One per wave put thousands of them on one address
-// at the end of the first round: gate/up of 32 tokens, 8 experts, 14336 x 4096, 200 us against 162 with *amax preset.
-__device__ __forceinline__ void fold_amax(const StreamArgs& p, float amax, float* scratch) {
-    if (!p.amax) return;
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
-    if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = amax;
-    __syncthreads();
-    if (threadIdx.x != 0) return;
-    for (unsigned w = 1; w < blockDim.x / 64; ++w) amax = fmaxf(amax, scratch[w]);
-    if (amax > __builtin_nontemporal_load(p.amax)) atomicMax(reinterpret_cast<int*>(p.amax), __float_as_int(amax));
 }
 
 // At most 16 rows: both operands go straight from memory to registers, the waves take the 128-byte blocks of the
@@ -632,7 +574,7 @@ void launch(StreamArgs p, int r_max, hipStream_t s) {
 int g_stream = -1;   // see set_gemm_stream
 int forced_blocks() { return g_stream > 10 && g_stream < 20 ? g_stream - 10 : 0; }
 bool forced_wide() { return g_stream >= 100 && g_stream < 2000; }
-int forced_f32_form() { return g_stream >= 20 && g_stream < 25 ? g_stream - 20 : -1; }
+int forced_form() { return g_stream >= 20 && g_stream < 25 ? g_stream - 20 : -1; }
 int forced_large_splits() { return g_stream >= 2000 ? g_stream - 2000 : 0; }
 
 // Weight blocks of a narrow workgroup: as many as leave enough workgroups.  A wider workgroup reads the rows less often
@@ -688,14 +630,15 @@ void launch_wide(StreamArgs p, int r_max, const StreamPlan& plan, float* part, h
 
 template <int ELT, int MODE>
 void launch_any(const StreamArgs& p, int r_max, const StreamPlan& plan, float* part, hipStream_t s) {
+    if (plan.kind == kPlanTiles) {
+        launch_tiles(ELT, p, plan.units, r_max, s);
+        return;
+    }
     if constexpr (ELT != kEltF32) {
         if (plan.kind == kPlanWide) {
             launch_wide<ELT, MODE>(p, r_max, plan, part, s);
             return;
         }
-    } else if (plan.kind == kPlanF32) {
-        launch_f32_tiles(p, plan.units, r_max, s);
-        return;
     }
     launch_narrow<ELT, MODE>(p, r_max, s);
 }
@@ -713,7 +656,7 @@ void launch_any(const StreamArgs& p, int r_max, const StreamPlan& plan, float* p
 // experts x 24 rows, 2048 x 1408, Zipf: narrow 33, large tiles 20).
 struct Work {
     int experts, rows, N, kbytes, r_max;
-    bool swiglu, fp8;
+    bool swiglu, fp8, odd;   // odd: bf16 sizes that the large tiles do not take
 };
 constexpr int kUnitsCU = 256;   // compute units the estimates are made for (gfx950, not partitioned)
 
@@ -773,7 +716,11 @@ double narrow_us(const Work& w, int fb) {
     const int rows = w.rows < tr ? w.rows : tr;
     const double weight = direct ? 41e-6 : mt > 1 ? 36e-6 : 43e-6;
     const double risk = whole > 1.0 && even_tiles <= kUnitsCU ? 1.1 : 1.0;   // a skewed router would cost a round
-    return risk * q * w.kbytes * (16 * fb * weight + rows * (direct ? 8e-6 : 18e-6)) + (direct ? 2.0 : 3.0) * (long long)((whole + 1) / 2);
+    // what the same 730 products took beyond this, by weight blocks and rows per expert
+    const int some = w.rows <= 16 ? 0 : w.rows <= 64 ? 1 : 2;
+    constexpr double kBeyond[4][3] = {{1.4, 1.1, 1.1}, {1.2, 1.15, 1.0}, {1.05, 1.15, 0.95}, {1.0, 1.06, 1.0}};
+    const double beyond = w.r_max <= 16 ? 1.0 : kBeyond[fb == 1 ? 0 : fb == 2 ? 1 : fb == 4 ? 2 : 3][some] * (w.odd && some > 0 ? 1.15 : 1.0);
+    return beyond * (risk * q * w.kbytes * (16 * fb * weight + rows * (direct ? 8e-6 : 18e-6)) + (direct ? 2.0 : 3.0) * (long long)((whole + 1) / 2));
 }
 
 double wide_us(const Work& w, int units, int S) {
@@ -785,26 +732,51 @@ double wide_us(const Work& w, int units, int S) {
     return rounds_of(tiles * (1.0 + 0.12 * skew_share(w, 128))) * round + reduce_us(w, S);
 }
 
-// fp32 tiles: a start and, for every block of the contraction that a group of waves takes, the longer of what one workgroup needs
-// alone and what the workgroups of a compute unit need together; forms 0 and 1 fill a compute unit's LDS, so they take whole rounds
-// (with a margin: the experts are not equal).  Fitted to 220 products (see gemm_f32.hip), rms error 9 to 15 %; the form they choose
-// is behind the best by 4 % on average, where the fp32 instruction is the better one included.
-double f32_us(const Work& w, int form) {
-    struct Form {
-        int rows, weights, groups;
-        double start, alone, load, power;
-    };
-    constexpr Form kForms[5] = {{32, 32, 8, 1.0, 1.40, 2.87, 0.0}, {32, 64, 4, 0.6, 1.31, 3.49, 0.0}, {32, 128, 1, 4.6, 0.62, 0.64, 1.75},
-                                {64, 64, 2, 4.8, 0.95, 1.28, 3.5}, {128, 128, 1, 7.1, 1.13, 1.76, 4.1}};
+// The small tiles (gemm_tiles.hip): a start and, together with what the weights take from memory, whole rounds of workgroups (one to
+// a compute unit, or what that comes to), each a start and its stages of the contraction.  From 85 to 105 % of a round on a
+// part of another is counted: the experts are not equal.  Fitted to 380 products in bf16 (2 to 128 experts, 4 to 1500 rows per expert,
+// routers without bias, with a normal and a Zipf-1.2 one), 90 of odd sizes, 260 in FP8, 220 in fp32; rms error 15 % where a form is
+// within 40 % of the best.
+struct TileForm {
+    int rows, weights, blocks;   // of a tile, of a stage
+    double start, block, round, power, stream, fill, more;   // us; TB/s of the weights; rounds
+};
+constexpr TileForm kTilesF32[] = {{32, 32, 4, 1.70, 0.584, 3.46, 2.8, 4.7, 1.06, 0.69},
+                                  {32, 64, 2, 1.66, 0.528, 3.73, 1.9, 5.2, 1.06, 0.68},
+                                  {32, 128, 1, 4.47, 0.523, 0.60, 1.7, 6.3, 0.59, 0.40},
+                                  {64, 64, 1, 3.44, 0.507, 1.16, 6.0, 6.2, 0.60, 0.36},
+                                  {128, 128, 1, 4.17, 1.215, 3.34, 6.8, 5.0, 1.02, 0.56}};
+constexpr TileForm kTilesBf16[] = {{32, 64, 2, 0.77, 0.289, 4.25, 1.9, 5.6, 1.01, 0.59},
+                                   {64, 64, 2, 1.16, 0.438, 3.21, 2.2, 5.6, 1.00, 0.47},
+                                   {64, 128, 1, 0.70, 0.352, 3.96, 2.3, 5.6, 1.02, 0.58},
+                                   {128, 128, 1, 0.78, 0.539, 3.30, 4.1, 5.6, 1.01, 0.70}};
+constexpr TileForm kTilesOdd[] = {{32, 64, 2, 0.84, 0.340, 4.49, 8.0, 5.6, 0.45, 0.47},
+                                  {64, 64, 2, 0.81, 0.500, 3.68, 2.6, 6.0, 1.03, 0.52},
+                                  {64, 128, 1, 0.61, 0.298, 4.91, 2.0, 6.3, 1.02, 1.04},
+                                  {128, 128, 1, 3.78, 0.447, 1.08, 6.6, 6.3, 1.04, 2.47}};
+constexpr TileForm kTilesFp8[] = {{32, 64, 2, 0.87, 0.276, 4.18, 2.1, 5.6, 0.80, 0.73},
+                                  {64, 64, 2, 1.07, 0.340, 4.04, 2.4, 5.4, 0.87, 0.54},
+                                  {64, 128, 1, 0.81, 0.322, 3.41, 2.0, 5.6, 0.91, 0.55},
+                                  {128, 128, 1, 0.33, 0.538, 3.46, 7.3, 5.6, 0.82, 0.51}};
+struct TileForms {
+    const TileForm* form;
+    int count;
+};
+TileForms tile_forms(int elt, bool odd) {
+    if (elt == kStreamF32) return {kTilesF32, 5};
+    if (elt == kStreamFp8) return {kTilesFp8, 4};
+    return {odd ? kTilesOdd : kTilesBf16, 4};
+}
+
+double small_tiles_us(const Work& w, const TileForm& f) {
     constexpr double kSpread[8] = {0.386, 0.552, 0.717, 0.883, 1.048, 1.214, 1.434, 1.766};   // as large_us
-    const Form& f = kForms[form];
     double mt = 0.0;
     for (const double x : kSpread) mt += w.experts / 8.0 * (double)(long long)((w.rows * x + f.rows - 1e-6) / f.rows);
     mt = 0.5 * (mt + (double)w.experts * blocks_of(w.rows, f.rows));
     const double per_cu = mt * blocks_of(w.N, w.swiglu ? f.weights / 2 : f.weights) / kUnitsCU;
-    const double blocks = (double)blocks_of(w.kbytes, 128 * f.groups);
-    if (f.power == 0.0) return f.start + (per_cu <= 0.85 ? 1.0 : per_cu + 0.6) * (f.load + blocks * f.alone);
-    return f.start + blocks * pow(pow(f.alone, f.power) + pow(f.load * per_cu, f.power), 1.0 / f.power);
+    const double mul = (per_cu <= f.fill ? 1.0 : per_cu + f.more) * (f.round + f.block * blocks_of(w.kbytes, 128) / f.blocks);
+    const double mem = (double)w.experts * w.N * (w.swiglu ? 2 : 1) * w.kbytes / (f.stream * 1e6);
+    return f.start + pow(pow(mul, f.power) + pow(mem, f.power), 1.0 / f.power);
 }
 
 constexpr size_t kMaxPartBytes = 64u << 20;   // partial planes of one product, at most
@@ -837,20 +809,29 @@ StreamPlan plan_stream(int elt, int r_max, int E, int N, int K, bool swiglu, boo
     w.r_max = r_max;
     w.swiglu = swiglu;
     w.fp8 = elt == kStreamFp8;
+    w.odd = elt == kEltBf16 && !large_ok;
     if (g_stream == 1 || forced_blocks() || !stream_covers(kbytes)) return plan;
+    const TileForms small = tile_forms(elt, w.odd);
+    if (forced_form() >= 0) {
+        plan.kind = kPlanTiles;
+        plan.units = forced_form() < small.count ? forced_form() : small.count - 1;
+        return plan;
+    }
+    int form = 0;
+    double form_us = 1e30;
+    for (int f = 0; f < small.count; ++f) {
+        const double t = small_tiles_us(w, small.form[f]);
+        if (t < form_us) {
+            form_us = t;
+            form = f;
+        }
+    }
     if (elt == kEltF32) {
         // Up to 12 rows per expert most tiles have at most 16 and the narrow kernel's form for those is the better one (us, fp32
-        // instruction / tiles: 4 experts x 4 rows, 572 x 632 4.6 / 7.5; 8 x 12, 308 x 456 6.0 / 8.5; 16 x 12, 996 x 460 27 / 18)
-        if (forced_f32_form() < 0 && 2 * r_max <= 25 * w.experts) return plan;
-        plan.kind = kPlanF32;
-        double best = 1e30;
-        for (int form = 0; form < 5; ++form) {
-            const double t = f32_us(w, form);
-            if (forced_f32_form() >= 0 ? form == forced_f32_form() : t < best) {
-                best = t;
-                plan.units = form;
-            }
-        }
+        // instruction / tiles: 4 experts x 4 rows, 572 x 632 4.6 / 7.5; 8 x 12, 308 x 456 6.0 / 8.2; 16 x 12, 996 x 460 27 / 18)
+        if (2 * r_max <= 25 * w.experts) return plan;
+        plan.kind = kPlanTiles;
+        plan.units = form;
         return plan;
     }
     // a split leaves at least 16 blocks of the contraction to a workgroup
@@ -893,6 +874,18 @@ StreamPlan plan_stream(int elt, int r_max, int E, int N, int K, bool swiglu, boo
                 plan.splits = S;
             }
         }
+    // The small tiles where they are ahead by more than a part of what the estimates are off by (more for gate/up of odd sizes, whose
+    // silu they do not count); not with up to 16 rows in all, where the narrow kernel has no ring, nor where most tiles of an odd
+    // size have as few.  (us, as chosen without the small tiles / so, a pass: expert-parallel share, 2 experts x 302 rows, 5376 x
+    // 1408 104 / 81; FP8, 4 experts x 24 rows, 5632 x 2560 85 / 69; training, 8 x 58 rows, 2432 x 4992 727 / 559.  Over 730 products in all 7 % faster
+    // on average, 30 % where the form changes; slower by more than 3 %: 31, mostly few experts with a skewed router.)
+    const double margin = w.odd && swiglu ? 1.25 : 1.1;
+    if (g_stream < 0 && r_max > 16 && !(w.odd && w.rows <= 16) && margin * form_us < best) {
+        best = margin * form_us;
+        plan.kind = kPlanTiles;
+        plan.units = form;
+        plan.splits = 1;
+    }
     for (int units = 8; units >= 3; --units)
         for (int S = 1; S <= 16; S *= 2) {
             if (!splits_fit(S)) break;
@@ -932,7 +925,7 @@ void launch_stream(const StreamPlan& plan, int elt, const void* A, const int32_t
         if (B1) launch_any<kEltF32, 1>(p, r_max, plan, part, s); else launch_any<kEltF32, 0>(p, r_max, plan, part, s);
     } else if (elt == kEltBf16) {
         if (GU) launch_any<kEltBf16, 2>(p, r_max, plan, part, s);
-        else if (B1 && (N % 64 || K % 64 || K < 128)) launch_any<kEltBf16, 3>(p, r_max, plan, part, s);
+        else if (B1 && full_silu(p)) launch_any<kEltBf16, 3>(p, r_max, plan, part, s);
         else if (B1) launch_any<kEltBf16, 1>(p, r_max, plan, part, s);
         else launch_any<kEltBf16, 0>(p, r_max, plan, part, s);
     } else {

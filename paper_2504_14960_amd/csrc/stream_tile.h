@@ -1,7 +1,11 @@
-// Pieces shared by the weight-streaming kernels (gemm_stream.hip) and the fp32 tiles (gemm_f32.hip): the tile of a workgroup, where
-// it starts in its contraction, loads of the operands.
+// Pieces shared by the weight-streaming kernels (gemm_stream.hip) and the small tiles (gemm_tiles.hip): the tile of a workgroup,
+// where it starts in its contraction, loads of the operands, the epilogue.
+//
+// MODE of the kernels: 0 one product, 1 the SwiGLU pair, 2 the pair with its pre-activations stored too, 3 as 1 for the shapes
+// that the persistent large tiles do not take (see silu_mul)
 #pragma once
 
+#include "fp8_convert.h"
 #include "gemm_stream.h"
 #include "gemm_tile.h"
 
@@ -22,8 +26,10 @@ struct StreamArgs {
     float* part;           // split partial sums [S][r_max][N, or 2 N with SwiGLU], or null
 };
 
-// fp32 products in tiles (gemm_f32.hip), form 0 .. 3
-void launch_f32_tiles(const StreamArgs& p, int form, int r_max, hipStream_t s);
+// the small tiles (gemm_tiles.hip)
+void launch_tiles(int elt, const StreamArgs& p, int form, int r_max, hipStream_t s);
+// bf16 shapes whose silu has the full expf and divide (see silu_mul)
+inline bool full_silu(const StreamArgs& p) { return p.N % 64 || p.kbytes % 128 || p.kbytes < 256; }
 
 namespace {
 
@@ -116,6 +122,66 @@ __device__ __forceinline__ Piece tail_piece(const uint8_t* row, int j, int rem) 
     if (!lo_in) v.lo = u32x4{0u, 0u, 0u, 0u};
     if (!hi_in) v.hi = u32x4{0u, 0u, 0u, 0u};
     return v;
+}
+
+// silu(g) * u as the persistent large tiles form it for the shapes they take, with the fast exponential and reciprocal; for
+// the rest (fp32; MODE 3: H or F not a multiple of 64, or H = 64) with the full expf and divide of the plain FMA kernel:
+// the fast exponential's error grows with |g|, some 40 units in the last place at g = -60.  (gate/up of 2331 rows on 12
+// experts, 1000 x 1416: 50.4 us with the fast form, 51.6 with the full one.)
+template <int ELT, int MODE>
+__device__ __forceinline__ float silu_mul(float g, float u) {
+    if constexpr (ELT == kStreamF32 || MODE == 3) return (g / (1.f + expf(-g))) * u;
+    else return g * __builtin_amdgcn_rcpf(1.f + __expf(-g)) * u;
+}
+
+// Stores four consecutive columns of a row (if `in`) from their sums: v (with SwiGLU the gate's) and up.  Returns the largest |h|
+// stored (FP8).
+template <int ELT, int MODE>
+__device__ __forceinline__ float store_four(const StreamArgs& p, bool in, int row, int col, f32x4 v, f32x4 up) {
+    constexpr bool SWIGLU = MODE != 0;
+    const size_t at = (size_t)row * p.N + col;
+    float amax = 0.f;
+    if constexpr (SWIGLU) {
+        if constexpr (ELT == kStreamFp8) { v *= p.s0; up *= p.s1; }
+        if (MODE == 2 && in) {
+            u32x2 g2 = {pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3])};
+            u32x2 u2 = {pack2_bf16(up[0], up[1]), pack2_bf16(up[2], up[3])};
+            bf16_t* gu = static_cast<bf16_t*>(p.GU) + (size_t)row * (2 * p.N) + col;
+            *reinterpret_cast<u32x2*>(gu) = g2;
+            *reinterpret_cast<u32x2*>(gu + p.N) = u2;
+        }
+#pragma unroll
+        for (int q = 0; q < 4; ++q) v[q] = silu_mul<ELT, MODE>(v[q], up[q]);
+    } else if constexpr (ELT == kStreamFp8) {
+        v *= p.s0;
+    }
+    if (!in) return amax;
+    if constexpr (ELT == kStreamF32) {
+        *reinterpret_cast<f32x4*>(static_cast<float*>(p.C) + at) = v;
+    } else if constexpr (ELT == kStreamFp8 && SWIGLU) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) amax = fmaxf(amax, fabsf(v[q]));
+        *reinterpret_cast<uint32_t*>(static_cast<uint8_t*>(p.C) + at) =
+            f32x4_to_e4m3(v[0] * p.s2, v[1] * p.s2, v[2] * p.s2, v[3] * p.s2);
+    } else {
+        u32x2 o = {pack2_bf16(v[0], v[1]), pack2_bf16(v[2], v[3])};
+        *reinterpret_cast<u32x2*>(static_cast<bf16_t*>(p.C) + at) = o;
+    }
+    return amax;
+}
+
+// max |h| of the workgroup into *amax: one atomic per workgroup at most, and none if the value read is already as large
+// (*amax only grows; as floats >= 0 compare like their bit patterns).  One per wave put thousands of them on one address
+// at the end of the first round: gate/up of 32 tokens, 8 experts, 14336 x 4096, 200 us against 162 with *amax preset.
+__device__ __forceinline__ void fold_amax(const StreamArgs& p, float amax, float* scratch) {
+    if (!p.amax) return;
+#pragma unroll
+    for (int off = 32; off > 0; off >>= 1) amax = fmaxf(amax, __shfl_xor(amax, off, 64));
+    if ((threadIdx.x & 63) == 0) scratch[threadIdx.x >> 6] = amax;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (unsigned w = 1; w < blockDim.x / 64; ++w) amax = fmaxf(amax, scratch[w]);
+    if (amax > __builtin_nontemporal_load(p.amax)) atomicMax(reinterpret_cast<int*>(p.amax), __float_as_int(amax));
 }
 
 }  // namespace

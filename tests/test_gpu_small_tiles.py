@@ -1,0 +1,84 @@
+"""The small tiles of the expert products in bf16 and FP8, every form: row counts around the edges of the tiles, columns and
+contractions that end inside a tile, a block, a step or a group's share, and the forms that store pre-activations."""
+import numpy as np
+import pytest
+
+from helpers import assert_close, to_dev, to_host, values
+from test_gpu_experts import _case as bf16_case, _run as bf16_run
+from test_gpu_fp8 import _case as fp8_case
+from test_gpu_stream import check_fp8
+
+pytestmark = pytest.mark.gpu
+
+EDGES = [1, 31, 32, 33, 0, 63, 64, 65, 127, 128, 129, 2, 260]
+FORMS = range(4)
+
+
+@pytest.fixture(autouse=True)
+def _default_afterwards():
+    import paper_2504_14960_amd as moe
+    yield
+    moe.set_option("gemm_stream", -1)
+
+
+# less than a step, a step and a part, a block, less than a ring, ten blocks and 48 bytes; columns of less than a block of 16 on
+@pytest.fixture(scope="module", params=[(8, 16), (56, 264), (64, 64), (136, 1416), (664, 72)], ids=str)
+def case(request):
+    H, F = request.param
+    return bf16_case(H=H, F=F, E=len(EDGES), counts=EDGES, seed=7500 + H)
+
+
+@pytest.mark.parametrize("form", FORMS)
+def test_every_form_against_the_oracle(case, form):
+    import paper_2504_14960_amd as moe
+    inp, x_perm, offsets, h_ref, y_ref = case
+    moe.set_option("gemm_stream", 20 + form)
+    h, y = bf16_run(x_perm, offsets, inp, 0)
+    assert_close(h, h_ref, True, "h")
+    assert_close(y, y_ref, True, "y_perm")
+
+
+@pytest.mark.parametrize("form", FORMS)
+def test_every_form_with_the_rounds_of_its_ring(form):
+    """Contractions of 40 and 41 blocks: each ring more than twice round, a stage of two blocks left half empty."""
+    import paper_2504_14960_amd as moe
+    for H, F in ((2560, 128), (128, 2624)):
+        inp, x_perm, offsets, h_ref, y_ref = bf16_case(H=H, F=F, E=3, counts=[70, 200, 5], seed=7600)
+        moe.set_option("gemm_stream", 20 + form)
+        h, y = bf16_run(x_perm, offsets, inp, 0)
+        assert_close(h, h_ref, True, "h")
+        assert_close(y, y_ref, True, "y_perm")
+
+
+@pytest.mark.parametrize("form", FORMS)
+def test_saving_form_has_the_bits_of_the_plain_one(form):
+    import torch
+    import paper_2504_14960_amd as moe
+    inp, x_perm, offsets, h_ref, _ = bf16_case(H=256, F=384, E=4, counts=[40, 0, 129, 31], seed=7700)
+    R = int(offsets[-1])
+    dx, off, wg, wu = to_dev(x_perm), to_dev(offsets), to_dev(inp["w_gate"]), to_dev(inp["w_up"])
+    bf = dict(dtype=torch.bfloat16, device="cuda")
+    h, h2, gu = torch.empty((R, 384), **bf), torch.empty((R, 384), **bf), torch.empty((R, 768), **bf)
+    moe.set_option("gemm_stream", 20 + form)
+    moe.expert_gate_up(dx, off, wg, wu, h)
+    moe.expert_gate_up_saving(dx, off, wg, wu, h2, gu)
+    assert torch.equal(h, h2)
+    assert_close(to_host(h), h_ref, True, "h")
+    x = values(x_perm)
+    for e in range(4):
+        rows = slice(int(offsets[e]), int(offsets[e + 1]))
+        want = np.concatenate([x[rows] @ values(inp[w])[e].T for w in ("w_gate", "w_up")], axis=1)
+        got = values(to_host(gu))[rows]
+        # one rounding to bf16, 2^-9 at most
+        assert np.abs(got - want).max(initial=0.0) <= 2.0 ** -8 * np.abs(want).max(initial=0.0)
+
+
+@pytest.fixture(scope="module", params=[(256, 1408), (1536, 256), (256, 5248)], ids=str)
+def fp8(request):
+    H, F = request.param
+    return fp8_case(seed=7800 + H, H=H, F=F, E=len(EDGES), counts=EDGES)
+
+
+@pytest.mark.parametrize("form", FORMS)
+def test_every_form_in_fp8(fp8, form):
+    check_fp8(fp8, 20 + form)
