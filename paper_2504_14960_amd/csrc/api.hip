@@ -611,6 +611,31 @@ moe_status_t moe_layer_workspace_layout(int T, int H, int E, int K, int F, int F
     return MOE_OK;
 }
 
+// the routed experts and the shared one, which sees every token: one "expert" owning rows [0, T)
+static moe_status_t expert_ffn_shared(const char* fn, const void* x, const void* w_gate, const void* w_up, const void* w_down,
+                                      const void* ws_gate, const void* ws_up, const void* ws_down, int T, int H, int E, int F,
+                                      int Fs, moe_dtype_t dt, const LayerLayout& L, uint8_t* ws, size_t workspace_bytes,
+                                      moe_stream_t stream) {
+    const int vec = (dt == MOE_BF16) ? 8 : 4;
+    if (H % vec || F % vec || Fs % vec)
+        return fail(MOE_ERR_UNSUPPORTED, "%s: H=%d, F=%d and Fs=%d must be multiples of %d", fn, H, F, Fs, vec);
+    REQUIRE_PTR(fn, x);
+    REQUIRE_PTR(fn, w_gate);
+    REQUIRE_PTR(fn, w_up);
+    REQUIRE_PTR(fn, w_down);
+    REQUIRE_PTR(fn, ws_gate);
+    REQUIRE_PTR(fn, ws_up);
+    REQUIRE_PTR(fn, ws_down);
+    // all the room that is asked for or none: the order of the sums takes no other form for sizes in between or above
+    const size_t part_bytes = workspace_bytes - L.total >= L.part_bytes ? L.part_bytes : 0;
+    if (!launch_expert_ffn_shared(ws + L.x_perm, reinterpret_cast<const int32_t*>(ws + L.offsets), L.r_max, H, F, E, w_gate, w_up, w_down,
+                                  dt, ws + L.h, ws + L.y_perm, x, T, Fs, ws_gate, ws_up, ws_down, ws + L.s_h, ws + L.s_y,
+                                  reinterpret_cast<int32_t*>(ws + L.s_offsets), g_gemm_variant, ws + L.total, part_bytes,
+                                  static_cast<hipStream_t>(stream)))
+        return fail(MOE_ERR_UNSUPPORTED, "%s: no kernel for H=%d F=%d Fs=%d", fn, H, F, Fs);
+    return check_launch(fn);
+}
+
 moe_status_t moe_layer_forward(const void* x, const void* w_router, const float* logit_bias,
                                const void* w_gate, const void* w_up, const void* w_down,
                                const void* ws_gate, const void* ws_up, const void* ws_down,
@@ -624,6 +649,7 @@ moe_status_t moe_layer_forward(const void* x, const void* w_router, const float*
     if (shared && !(ws_gate && ws_up && ws_down))
         return fail(MOE_ERR_INVALID_ARG, "%s: Fs > 0 needs ws_gate, ws_up and ws_down", fn);
     if (T == 0) return MOE_OK;
+    REQUIRE_PTR(fn, x);
     REQUIRE_PTR(fn, y);
     const LayerLayout L = layer_layout(T, H, E, K, F, Fs, capacity, dt);
     if (workspace == nullptr || workspace_bytes < L.total)
@@ -642,24 +668,18 @@ moe_status_t moe_layer_forward(const void* x, const void* w_router, const float*
     moe_status_t st = moe_router_topk(x, w_router, logit_bias, logits, T, H, E, K, renormalize, dt,
                                       idx, gate, stream);
     if (st) return st;
-    st = moe_permute(x, idx, T, H, E, K, capacity, dt, ws + L.x_perm, counts, offsets, roa, aor,
-                     ws + L.perm_ws, permute_workspace_bytes(T, K, E), stream);
-    if (st) return st;
-    st = moe_grouped_gemm_swiglu(ws + L.x_perm, offsets, L.r_max, H, F, E, w_gate, w_up, w_down, dt,
-                                 ws + L.h, ws + L.y_perm, stream);
+    launch_permute(x, idx, T, H, E, K, capacity, L.r_max, dt, ws + L.x_perm, counts, offsets, roa, aor, ws + L.perm_ws,
+                   static_cast<hipStream_t>(stream), shared ? reinterpret_cast<int32_t*>(ws + L.s_offsets) : nullptr);
+    st = check_launch(fn);
     if (st) return st;
     const void* addend = nullptr;
-    if (shared) {
-        // the shared expert sees every token: one "expert" owning rows [0, T)
-        int32_t* so = reinterpret_cast<int32_t*>(ws + L.s_offsets);
-        launch_fill_i32(so, 2, 0, T, static_cast<hipStream_t>(stream));
-        // all the room that is asked for or none: the order of the sums takes no other form for sizes in between or above
-        const size_t part_bytes = workspace_bytes - L.total >= L.part_bytes ? L.part_bytes : 0;
-        st = expert_ffn("moe_grouped_gemm_swiglu", 3, x, so, T, H, Fs, 1, ws_gate, ws_up, ws_down, dt, ws + L.s_h,
-                        ws + L.s_y, stream, ws + L.total, part_bytes);
-        if (st) return st;
+    if (!shared) {
+        st = moe_grouped_gemm_swiglu(ws + L.x_perm, offsets, L.r_max, H, F, E, w_gate, w_up, w_down, dt, ws + L.h, ws + L.y_perm, stream);
+    } else {
+        st = expert_ffn_shared(fn, x, w_gate, w_up, w_down, ws_gate, ws_up, ws_down, T, H, E, F, Fs, dt, L, ws, workspace_bytes, stream);
         addend = ws + L.s_y;
     }
+    if (st) return st;
     return moe_unpermute_combine(ws + L.y_perm, roa, gate, addend, T, H, K, L.r_max, dt, y, stream);
 }
 
@@ -913,6 +933,11 @@ moe_status_t moe_gemm_clock_sample(uint64_t* ticks) {
 moe_status_t moe_set_option(const char* name, int value) {
     if (name && strcmp(name, "gemm_idle_skip") == 0) {
         moe::set_persist_idle_skip(value < 0 ? -1 : (value != 0));
+        return MOE_OK;
+    }
+    if (name && strcmp(name, "gemm_pair") == 0) {
+        auto blocks = [](int v) { return v >= 8 ? 8 : v >= 4 ? 4 : v >= 2 ? 2 : 0; };
+        moe::set_pair_blocks(value < 0 ? -1 : 10 * blocks(value / 10) + blocks(value % 10));
         return MOE_OK;
     }
     if (name && strcmp(name, "gemm_stream") == 0) {

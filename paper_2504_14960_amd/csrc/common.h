@@ -76,9 +76,10 @@ void set_router_tile(int mb);
 
 size_t permute_workspace_bytes(int T, int K, int E);
 void set_permute_fused(int v);   // 1 (default): small index arrays take the one-launch dispatch; 0: never
+// one_expert: where the offsets 0, T of an expert that takes every token (the shared one) go, or null
 void launch_permute(const void* x, const int32_t* idx, int T, int H, int E, int K, int capacity,
                     int r_max, moe_dtype_t dt, void* x_perm, int32_t* counts, int32_t* offsets,
-                    int32_t* row_of_assign, int32_t* assign_of_row, void* ws, hipStream_t s);
+                    int32_t* row_of_assign, int32_t* assign_of_row, void* ws, hipStream_t s, int32_t* one_expert = nullptr);
 
 // the library's own scratch for moe_permute_noalloc: its size, and its address on the current device
 size_t permute_scratch_bytes();
@@ -106,6 +107,11 @@ unsigned long long* persist_clock_sample();
 bool launch_expert_ffn(const void* x_perm, const int32_t* offsets, int r_max, int H, int F, int E,
                        const void* w_gate, const void* w_up, const void* w_down, moe_dtype_t dt,
                        void* h, void* y_perm, int variant, int phase, void* part, size_t part_bytes, hipStream_t s);
+// The same for the routed experts and the shared one (Fs) of a layer, side by side where that pays: x [tokens, H] -> s_h -> s_y
+bool launch_expert_ffn_shared(const void* x_perm, const int32_t* offsets, int r_max, int H, int F, int E, const void* w_gate,
+                              const void* w_up, const void* w_down, moe_dtype_t dt, void* h, void* y_perm, const void* x, int tokens,
+                              int Fs, const void* ws_gate, const void* ws_up, const void* ws_down, void* s_h, void* s_y, const int32_t* s_offsets,
+                              int variant, void* part, size_t part_bytes, hipStream_t s);
 // room for partial sums (part, part_bytes above) that the two products make use of; with less they are not split
 size_t expert_ffn_part_bytes(int r_max, int H, int F, int E, moe_dtype_t dt);
 

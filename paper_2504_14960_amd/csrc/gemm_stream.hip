@@ -23,6 +23,8 @@
 //   12 experts, 2331 rows, 1000 x 1416         gate/up 310 /  50,                       down 271 /  30
 //   fp32, 8 experts x 64 rows, 128 x 256       gate/up  29 /   8,                       down  36 /   7
 // (fp32 with more than some 12 rows per expert, and much of bf16 and FP8 between these rows and the large tiles': gemm_tiles.hip)
+#include <type_traits>
+
 #include "stream_tile.h"
 #include "tile_cost.h"
 
@@ -470,7 +472,7 @@ __device__ __forceinline__ float wide_tile(const StreamArgs& p, const Tile& t, i
 template <int ELT, int MODE>
 __global__ __launch_bounds__(kWideWaves * 64, 2) void gemm_wide_kernel(const StreamArgs p) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
-    const Tile t = locate_tile<128>(p.offsets, p.E, p.ntn * p.S);
+    const Tile t = locate_tile<128>(p.offsets, p.E, p.ntn * p.S, blockIdx.x);
     if (!t.valid) return;
     const int n = t.ntile / p.S, ks = t.ntile - n * p.S;
     const bool sample = ELT == kEltBf16 && p.ticks != nullptr && blockIdx.x == 0;
@@ -528,13 +530,11 @@ template <int FB, bool DIRECT> constexpr int lds_bytes() {
     return DIRECT ? 4 * FB * 1024 : FB >= 4 ? 64 * 1024 : 128 * 1024;
 }
 
-// DIRECT: the launch has at most 16 rows in all, so no tile needs the ring (and more workgroups fit a compute unit).
-template <int ELT, int MODE, int FB, bool DIRECT>
-__global__ __launch_bounds__(256, 2) void gemm_stream_kernel(const StreamArgs p) {
-    constexpr int RING = lds_bytes<FB, DIRECT>();
+// A narrow workgroup, number `block` of its product.
+template <int ELT, int MODE, int FB, bool DIRECT, int RING>
+__device__ __forceinline__ void narrow_workgroup(const StreamArgs& p, unsigned block, uint8_t* smem) {
     constexpr int NBW = blocks_per_wave<FB>();
-    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
-    const Tile t = locate_tile<tile_rows<FB>()>(p.offsets, p.E, p.ntn);
+    const Tile t = locate_tile<tile_rows<FB>()>(p.offsets, p.E, p.ntn, block);
     if (!t.valid) return;
     const bool sample = ELT == kEltBf16 && p.ticks != nullptr && blockIdx.x == 0;
     unsigned long long tk_entry = 0, rt_entry = 0;
@@ -560,6 +560,23 @@ __global__ __launch_bounds__(256, 2) void gemm_stream_kernel(const StreamArgs p)
     if constexpr (ELT == kEltFp8 && MODE == 1) fold_amax(p, amax, reinterpret_cast<float*>(smem + RING));
 }
 
+// DIRECT: the launch has at most 16 rows in all, so no tile needs the ring (and more workgroups fit a compute unit).
+template <int ELT, int MODE, int FB, bool DIRECT>
+__global__ __launch_bounds__(256, 2) void gemm_stream_kernel(const StreamArgs p) {
+    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+    narrow_workgroup<ELT, MODE, FB, DIRECT, lds_bytes<FB, DIRECT>()>(p, blockIdx.x, smem);
+}
+
+// The shared expert's product q and the routed experts' p in one launch (bf16): the first workgroups take q, whose tiles are the
+// longer ones where its contraction is.
+constexpr int kPairRing = 64 * 1024;   // two workgroups to a compute unit
+template <int MODE, int FB, int FBS, bool DIRECT>
+__global__ __launch_bounds__(256, 2) void gemm_stream_pair_kernel(const StreamArgs p, const StreamArgs q, unsigned first) {
+    extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
+    if (blockIdx.x < first) narrow_workgroup<kEltBf16, MODE, FBS, DIRECT, kPairRing>(q, blockIdx.x, smem);
+    else narrow_workgroup<kEltBf16, MODE, FB, DIRECT, kPairRing>(p, blockIdx.x - first, smem);
+}
+
 template <int ELT, int MODE, int FB, bool DIRECT>
 void launch(StreamArgs p, int r_max, hipStream_t s) {
     constexpr int BN = 16 * TileAt<MODE, FB>::NF;
@@ -569,6 +586,19 @@ void launch(StreamArgs p, int r_max, hipStream_t s) {
     static OncePerDevice lds;
     allow_lds(lds, reinterpret_cast<const void*>(kern), smem);
     hipLaunchKernelGGL(kern, dim3(grid_for(r_max, p.E, tile_rows<FB>(), p.ntn)), dim3(256), smem, s, p);
+}
+
+template <int MODE, int FB, int FBS, bool DIRECT>
+void launch_pair(StreamArgs p, StreamArgs q, int r_max, hipStream_t s) {
+    constexpr int BN = 16 * TileAt<MODE, FB>::NF, BNS = 16 * TileAt<MODE, FBS>::NF;
+    constexpr int smem = DIRECT ? 4 * (FB > FBS ? FB : FBS) * 1024 : kPairRing;
+    p.ntn = (p.N + BN - 1) / BN;
+    q.ntn = (q.N + BNS - 1) / BNS;
+    auto kern = gemm_stream_pair_kernel<MODE, FB, FBS, DIRECT>;
+    static OncePerDevice lds;
+    allow_lds(lds, reinterpret_cast<const void*>(kern), smem);
+    const int first = grid_for(q.r_max, 1, tile_rows<FBS>(), q.ntn);   // a multiple of eight
+    hipLaunchKernelGGL(kern, dim3(first + grid_for(r_max, p.E, tile_rows<FB>(), p.ntn)), dim3(256), smem, s, p, q, first);
 }
 
 int g_stream = -1;   // see set_gemm_stream
@@ -794,7 +824,7 @@ void launch_stream_reduce(bool swiglu, const float* part, const int32_t* offsets
 bool stream_covers(long long K_bytes) { return K_bytes <= (1 << 24); }
 
 StreamPlan plan_stream(int elt, int r_max, int E, int N, int K, bool swiglu, bool large_ok, size_t part_bytes) {
-    StreamPlan plan = {kPlanNarrow, 0, 1};
+    StreamPlan plan = {kPlanNarrow, 0, 1, 0.0};
     if (r_max <= 0) return plan;
     Work w;
     w.experts = E < r_max ? E : r_max;
@@ -897,7 +927,85 @@ StreamPlan plan_stream(int elt, int r_max, int E, int N, int K, bool swiglu, boo
                 plan.splits = S;
             }
         }
+    plan.us = best;
     return plan;
+}
+
+static StreamArgs stream_args(int elt, const void* A, const int32_t* offsets, int r_max, int E, int N, int K, const void* B0, const void* B1,
+                              void* C) {
+    StreamArgs p;
+    p.A = static_cast<const uint8_t*>(A);
+    p.offsets = offsets;
+    p.B0 = static_cast<const uint8_t*>(B0);
+    p.B1 = static_cast<const uint8_t*>(B1);
+    p.C = C;
+    p.GU = nullptr;
+    p.amax = nullptr;
+    p.ticks = persist_clock_sample();
+    p.s0 = p.s1 = p.s2 = 0.f;
+    p.E = E; p.N = N; p.ntn = 0;
+    p.units = 0; p.S = 1; p.r_max = r_max; p.part = nullptr;
+    p.kbytes = K * (elt == kEltF32 ? 4 : elt == kEltBf16 ? 2 : 1);
+    return p;
+}
+
+static int g_pair_blocks = -1;
+void set_pair_blocks(int v) { g_pair_blocks = v; }
+
+int plan_pair(int elt, const StreamPlan& routed, int r_max, int E, int N, int K, const StreamPlan& shared, int tokens, int sN, int sK,
+              bool swiglu) {
+    // silu as both products have it alone; a narrow workgroup of one weight block has no pair
+    auto plain = [&](int n, int k) { return !swiglu || (n % 64 == 0 && k % 64 == 0 && k >= 128); };
+    if (g_pair_blocks == 0 || g_stream >= 0 || elt != kStreamBf16 || routed.kind != kPlanNarrow || tokens > 128 || !plain(N, K) ||
+        !plain(sN, sK) || narrow_blocks(r_max, E, N, swiglu) == 1)
+        return 0;
+    const int forced = g_pair_blocks < 0 ? -1 : swiglu ? g_pair_blocks / 10 : g_pair_blocks % 10;
+    if (forced >= 0) return r_max <= 16 && forced == 8 ? 4 : forced;
+    // What the second launch costs are its first and last microseconds, an end of the first one in which compute units stand idle, and
+    // partial sums (us of the layer, one after the other / so: 3 tokens, 32 experts, 1152 x 1280, shared 2112 48 / 36; one token, 32,
+    // 6144 x 768, 17152 183 / 152; 27 tokens, 64, 1024 x 2176, 6144 123 / 99; 42 tokens, 16, 7040 x 4352, 14080 723 / 663).
+    if (swiglu) {
+        // Workgroups of the same length, so the two lists become one; as wide as the tokens ask for.  64 tokens on 64 experts, 3584 x
+        // 2560, with 20480 more take 7 us longer so: 5.0 rounds of routed workgroups become 5.6, and 64 rows suit the wide kernel.
+        const int fbs = r_max <= 16 ? 2 : tokens <= 16 ? 4 : 8, fb = narrow_blocks(r_max, E, N, true);
+        const int experts = E < r_max ? E : r_max, rows = (r_max + experts - 1) / experts;
+        const double own = (double)experts * blocks_of(rows, 128) * blocks_of(N, 8 * fb), more = blocks_of(sN, 8 * fbs) * (double)fbs / fb;
+        const double both = fmax(1.0, (own + more) / (2 * kUnitsCU)) / fmax(1.0, own / (2 * kUnitsCU));
+        return (tokens <= 48 ? 0.98 : tokens <= 64 ? 1.04 : 1.1) * routed.us * both < routed.us + shared.us + 4.0 ? fbs : 0;
+    }
+    // The shared expert's contraction is the longer one, and one of its workgroups takes so long for it, beside the others (us for 128
+    // bytes: 0.1 with both operands straight to registers; else the more the fewer stages of the rows the ring holds).  It should end
+    // with the routed experts' and have its own weights to read as well.
+    const double serial = blocks_of(2 * sK, 128) * (tokens <= 16 ? 0.11 : fmax(0.2, 0.0115 * tokens));
+    return serial <= routed.us + 0.5 * shared.us ? (tokens > 16 && sN >= 5632 ? 4 : 2) : 0;
+}
+
+void launch_stream_pair(int blocks, const void* A, const int32_t* offsets, int r_max, int E, int N, int K, const void* B0, const void* B1,
+                        void* C, const void* sA, const int32_t* s_offsets, int tokens, int sN, int sK, const void* sB0, const void* sB1,
+                        void* sC, hipStream_t s) {
+    const StreamArgs p = stream_args(kStreamBf16, A, offsets, r_max, E, N, K, B0, B1, C);
+    const StreamArgs q = stream_args(kStreamBf16, sA, s_offsets, tokens, 1, sN, sK, sB0, sB1, sC);
+    const int fb = narrow_blocks(r_max, E, N, B1 != nullptr);
+    auto go = [&](auto mode, auto own) {
+        constexpr int MODE = decltype(mode)::value, FB = decltype(own)::value;
+        if constexpr (FB <= 4) {
+            if (r_max <= 16) {
+                if (blocks == 4) launch_pair<MODE, FB, 4, true>(p, q, r_max, s);
+                else launch_pair<MODE, FB, 2, true>(p, q, r_max, s);
+                return;
+            }
+        }
+        if (blocks == 8) launch_pair<MODE, FB, 8, false>(p, q, r_max, s);
+        else if (blocks == 4) launch_pair<MODE, FB, 4, false>(p, q, r_max, s);
+        else launch_pair<MODE, FB, 2, false>(p, q, r_max, s);
+    };
+    auto width = [&](auto mode) {
+        if (fb == 8) go(mode, std::integral_constant<int, 8>{});
+        else if (fb == 4) go(mode, std::integral_constant<int, 4>{});
+        else go(mode, std::integral_constant<int, 2>{});
+    };
+    if (B1) width(std::integral_constant<int, 1>{});
+    else width(std::integral_constant<int, 0>{});
 }
 
 size_t stream_part_bytes(int elt, int r_max, int E, int N, int K, bool swiglu, bool large_ok) {
@@ -908,19 +1016,10 @@ size_t stream_part_bytes(int elt, int r_max, int E, int N, int K, bool swiglu, b
 void launch_stream(const StreamPlan& plan, int elt, const void* A, const int32_t* offsets, int r_max, int E, int N, int K,
                    const void* B0, const void* B1, void* C, void* GU, float s0, float s1, float s2, float* amax,
                    float* part, hipStream_t s) {
-    StreamArgs p;
-    p.A = static_cast<const uint8_t*>(A);
-    p.offsets = offsets;
-    p.B0 = static_cast<const uint8_t*>(B0);
-    p.B1 = static_cast<const uint8_t*>(B1);
-    p.C = C;
+    StreamArgs p = stream_args(elt, A, offsets, r_max, E, N, K, B0, B1, C);
     p.GU = GU;
     p.amax = amax;
-    p.ticks = persist_clock_sample();
     p.s0 = s0; p.s1 = s1; p.s2 = s2;
-    p.E = E; p.N = N; p.ntn = 0;
-    p.units = 0; p.S = 1; p.r_max = r_max; p.part = nullptr;
-    p.kbytes = K * (elt == kEltF32 ? 4 : elt == kEltBf16 ? 2 : 1);
     if (elt == kEltF32) {
         if (B1) launch_any<kEltF32, 1>(p, r_max, plan, part, s); else launch_any<kEltF32, 0>(p, r_max, plan, part, s);
     } else if (elt == kEltBf16) {

@@ -90,7 +90,7 @@ __global__ __launch_bounds__(KB * KS * WGM * WGN * 64, ELT == kStreamF32 && FM *
     static_assert(!PIPE || (ELT == kStreamF32 && STEPS == 2), "two steps to a stage");
     constexpr bool SWIGLU = MODE != 0;
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
-    const Tile t = locate_tile<BM>(p.offsets, p.E, p.ntn);
+    const Tile t = locate_tile<BM>(p.offsets, p.E, p.ntn, blockIdx.x);
     if (!t.valid) return;
     const bool sample = ELT == kStreamBf16 && p.ticks != nullptr && blockIdx.x == 0;
     unsigned long long tk_entry = 0, rt_entry = 0;

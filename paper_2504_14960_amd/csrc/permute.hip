@@ -35,6 +35,18 @@ constexpr int kMaxDevices = 64;
 static int32_t* g_scratch_ptr[kMaxDevices] = {};   // device address of `scratch`, per device ordinal
 static std::mutex g_scratch_mutex;
 
+// Offsets of the one expert that takes every token (a layer's shared one), written along with the routed experts': a launch of
+// their own took 4.7 us.
+struct OneExpert {
+    int32_t* offsets;   // or null
+    int tokens;
+    __device__ __forceinline__ void write() const {
+        if (offsets == nullptr) return;
+        offsets[0] = 0;
+        offsets[1] = tokens;
+    }
+};
+
 __global__ __launch_bounds__(256) void permute_hist_kernel(const int32_t* __restrict__ idx, int A,
                                                            int E, int32_t* __restrict__ chunk_hist) {
     __shared__ int hist[kMaxExperts];
@@ -57,7 +69,7 @@ __global__ __launch_bounds__(256) void permute_map_kernel(
     const int32_t* __restrict__ idx, const int32_t* __restrict__ chunk_hist, int A, int E,
     int capacity, int pad, int r_max, int nchunks, int32_t* __restrict__ counts,
     int32_t* __restrict__ offsets, int32_t* __restrict__ row_of_assign,
-    int32_t* __restrict__ assign_of_row) {
+    int32_t* __restrict__ assign_of_row, OneExpert one) {
     __shared__ int tot[kMaxExperts];
     __shared__ int base[kMaxExperts];
     __shared__ int scan[2][kMaxExperts];
@@ -111,7 +123,10 @@ __global__ __launch_bounds__(256) void permute_map_kernel(
             counts[tid] = cnt;
             offsets[tid + 1] = incl;
         }
-        if (tid == 0) offsets[0] = 0;
+        if (tid == 0) {
+            offsets[0] = 0;
+            one.write();
+        }
     }
 
     // rank of every assignment of this chunk inside its (expert, 64-assignment unit)
@@ -442,7 +457,7 @@ template <int NV, int TPW>
 __global__ __launch_bounds__(kFusedWaves * 64) void permute_fused_kernel(
     const uint8_t* __restrict__ x, const int32_t* __restrict__ idx, int T, int K, int E, int capacity, int row_bytes,
     int r_max, uint8_t* __restrict__ x_perm, int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
-    int32_t* __restrict__ row_of_assign, int32_t* __restrict__ assign_of_row) {
+    int32_t* __restrict__ row_of_assign, int32_t* __restrict__ assign_of_row, OneExpert one) {
     constexpr int NWV = kFusedWaves, NTH = NWV * 64;
     __shared__ unsigned long long red[NWV][4];
     __shared__ int base[kFusedMaxExperts];
@@ -545,7 +560,10 @@ __global__ __launch_bounds__(kFusedWaves * 64) void permute_fused_kernel(
         if (blockIdx.x == 0 && e < E) {
             counts[e] = cnt;
             offsets[e + 1] = incl;
-            if (e == 0) offsets[0] = 0;
+            if (e == 0) {
+                offsets[0] = 0;
+                one.write();
+            }
         }
     }
     __syncthreads();
@@ -622,7 +640,8 @@ template <int NV, int TB, bool FP8>
 __global__ __launch_bounds__(kSmallThreads) void permute_small_kernel(
     const uint8_t* __restrict__ x, const int32_t* __restrict__ idx, int T, int K, int E, int capacity, int row_bytes,
     int r_max, uint8_t* __restrict__ x_perm, int32_t* __restrict__ counts, int32_t* __restrict__ offsets,
-    int32_t* __restrict__ row_of_assign, int32_t* __restrict__ assign_of_row, float scale, float* __restrict__ amax) {
+    int32_t* __restrict__ row_of_assign, int32_t* __restrict__ assign_of_row, float scale, float* __restrict__ amax,
+    OneExpert one) {
     constexpr int P = kSmallWaves / TB;
     __shared__ int base[kMaxExperts];       // assignments of the expert before this workgroup's own, then the next rank
     __shared__ int rest[kMaxExperts];       // the others
@@ -670,7 +689,10 @@ __global__ __launch_bounds__(kSmallThreads) void permute_small_kernel(
         }
         int run = incl - s;
         if (lane == 0) off[0] = 0;
-        if (blockIdx.x == 0 && lane == 0) offsets[0] = 0;
+        if (blockIdx.x == 0 && lane == 0) {
+            offsets[0] = 0;
+            one.write();
+        }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             const int e = 4 * lane + j;
@@ -790,7 +812,7 @@ constexpr int kSmallMaxAssign = 16384;
 template <bool FP8>
 static bool launch_permute_small(const void* x, const int32_t* idx, int T, int K, int E, int capacity, int row_bytes,
                                  int r_max, void* x_perm, int32_t* counts, int32_t* offsets, int32_t* row_of_assign,
-                                 int32_t* assign_of_row, float scale, float* amax, hipStream_t s) {
+                                 int32_t* assign_of_row, float scale, float* amax, OneExpert one, hipStream_t s) {
     if (row_bytes > 16384 || row_bytes % 16) return false;
     const bool few = E <= kFusedMaxExperts ? T <= (FP8 ? 1024 : 2048) && (FP8 || (long long)T * K <= kSmallMaxAssign / 2)
                                            : T <= (FP8 ? 4096 : 8192) && (long long)T * K <= kSmallMaxAssign;
@@ -802,7 +824,7 @@ static bool launch_permute_small(const void* x, const int32_t* idx, int T, int K
 #define SMALL_CASE(NVV, TBB)                                                                                            \
     hipLaunchKernelGGL((permute_small_kernel<NVV, TBB, FP8>), dim3((T + TBB - 1) / TBB), dim3(kSmallThreads), 0, s,      \
                        static_cast<const uint8_t*>(x), idx, T, K, E, capacity, row_bytes, r_max,                         \
-                       static_cast<uint8_t*>(x_perm), counts, offsets, row_of_assign, assign_of_row, scale, amax)
+                       static_cast<uint8_t*>(x_perm), counts, offsets, row_of_assign, assign_of_row, scale, amax, one)
     if (narrow) {
         if (nv <= 2) SMALL_CASE(2, 4); else SMALL_CASE(4, 4);
     } else {
@@ -820,11 +842,12 @@ size_t permute_workspace_bytes(int T, int K, int E) {
 
 void launch_permute(const void* x, const int32_t* idx, int T, int H, int E, int K, int capacity,
                     int r_max, moe_dtype_t dt, void* x_perm, int32_t* counts, int32_t* offsets,
-                    int32_t* row_of_assign, int32_t* assign_of_row, void* ws, hipStream_t s) {
+                    int32_t* row_of_assign, int32_t* assign_of_row, void* ws, hipStream_t s, int32_t* one_expert) {
     const int A = T * K;
+    const OneExpert one = {one_expert, T};
     const int row_bytes_all = H * (dt == MOE_BF16 ? 2 : 4);
     if (launch_permute_small<false>((x != nullptr && x_perm != nullptr) ? x : nullptr, idx, T, K, E, capacity, row_bytes_all,
-                                    r_max, x_perm, counts, offsets, row_of_assign, assign_of_row, 0.f, nullptr, s))
+                                    r_max, x_perm, counts, offsets, row_of_assign, assign_of_row, 0.f, nullptr, one, s))
         return;
     if (g_permute_fused && g_permute_fused != 4 && E <= kFusedMaxExperts && A <= kFusedMaxAssign && row_bytes_all <= kFusedMaxRowVecs * 1024 &&
         row_bytes_all % 16 == 0) {
@@ -837,7 +860,7 @@ void launch_permute(const void* x, const int32_t* idx, int T, int H, int E, int 
 #define FUSED_CASE(NVV, TPWW)                                                                                           \
     hipLaunchKernelGGL((permute_fused_kernel<NVV, TPWW>), dim3((T + kFusedWaves * TPWW - 1) / (kFusedWaves * TPWW)),     \
                        dim3(kFusedWaves * 64), 0, s, xs, idx, T, K, E, capacity, row_bytes_all, r_max,                   \
-                       static_cast<uint8_t*>(x_perm), counts, offsets, row_of_assign, assign_of_row)
+                       static_cast<uint8_t*>(x_perm), counts, offsets, row_of_assign, assign_of_row, one)
         if (two && nv <= 12) {
             if (nv <= 4) FUSED_CASE(4, 2); else if (nv <= 8) FUSED_CASE(8, 2); else FUSED_CASE(12, 2);
         } else {
@@ -850,7 +873,7 @@ void launch_permute(const void* x, const int32_t* idx, int T, int H, int E, int 
     int32_t* chunk_hist = static_cast<int32_t*>(ws);
     hipLaunchKernelGGL(permute_hist_kernel, dim3(nchunks), dim3(256), 0, s, idx, A, E, chunk_hist);
     hipLaunchKernelGGL(permute_map_kernel, dim3(nchunks), dim3(256), 0, s, idx, chunk_hist, A, E,
-                       capacity, 0, r_max, nchunks, counts, offsets, row_of_assign, assign_of_row);
+                       capacity, 0, r_max, nchunks, counts, offsets, row_of_assign, assign_of_row, one);
     if (x != nullptr && x_perm != nullptr) {
         const int row_bytes = H * (dt == MOE_BF16 ? 2 : 4);
         int grid = (T + 3) / 4;
@@ -890,12 +913,12 @@ void launch_permute_variant(const void* x, const int32_t* idx, const float* scor
     if (by_score) {
         // dropless grouping first (row_of_assign serves as its scratch map), then the selection per expert
         hipLaunchKernelGGL(permute_map_kernel, dim3(nchunks), dim3(256), 0, s, idx, chunk_hist, A, E, 0, 0, A,
-                           nchunks, seg_cnt, seg_off, row_of_assign, seg_aor);
+                           nchunks, seg_cnt, seg_off, row_of_assign, seg_aor, OneExpert{nullptr, 0});
         hipLaunchKernelGGL(permute_select_kernel, dim3(E), dim3(kSelThreads), 0, s, scores, seg_off, seg_aor, keys, E,
                            capacity, pad, r_max, counts, offsets, row_of_assign, assign_of_row);
     } else {
         hipLaunchKernelGGL(permute_map_kernel, dim3(nchunks), dim3(256), 0, s, idx, chunk_hist, A, E, capacity,
-                           pad, r_max, nchunks, counts, offsets, row_of_assign, assign_of_row);
+                           pad, r_max, nchunks, counts, offsets, row_of_assign, assign_of_row, OneExpert{nullptr, 0});
     }
     if (x != nullptr && x_perm != nullptr) {
         const int row_bytes = H * (dt == MOE_BF16 ? 2 : 4);
@@ -941,7 +964,7 @@ void launch_permute_fp8(const void* x, const int32_t* idx, int T, int H, int E, 
                         float scale, void* x_perm_fp8, int32_t* counts, int32_t* offsets, int32_t* row_of_assign,
                         int32_t* assign_of_row, float* amax, void* ws, hipStream_t s) {
     if (launch_permute_small<true>(x, idx, T, K, E, capacity, H * 2, r_max, x_perm_fp8, counts, offsets, row_of_assign,
-                                   assign_of_row, scale, amax, s))
+                                   assign_of_row, scale, amax, OneExpert{nullptr, 0}, s))
         return;
     // maps as in launch_permute, then the quantising copy
     launch_permute(nullptr, idx, T, H, E, K, capacity, r_max, MOE_BF16, nullptr, counts, offsets, row_of_assign,

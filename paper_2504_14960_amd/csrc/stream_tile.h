@@ -38,7 +38,7 @@ namespace {
 // tile's two offsets from memory once more and meets two barriers; a launch of one round of workgroups shows all of it (us of
 // the layer: 256 fp32 tokens, 128 x 256 27.0 / 25.7; one token of Mixtral-8x7B 141.9 / 140.0; FP8, 32 tokens 276.7 / 274.8).
 template <int BM>
-__device__ __forceinline__ Tile locate_tile(const int32_t* __restrict__ offsets, int E, int ntn) {
+__device__ __forceinline__ Tile locate_tile(const int32_t* __restrict__ offsets, int E, int ntn, unsigned block) {
     constexpr int MG = 8;
     const int lane = threadIdx.x & 63;
     int lo[5], mt[4], s = 0;
@@ -59,7 +59,7 @@ __device__ __forceinline__ Tile locate_tile(const int32_t* __restrict__ offsets,
     t.expert = 0; t.row0 = 0; t.rows = 0; t.row_end = 0; t.ntile = 0;
     const int MT = __builtin_amdgcn_readlane(incl, (E - 1) >> 2);
     const int total = MT * ntn, per = (total + 7) / 8;
-    const int j = (int)(blockIdx.x >> 3), L = (int)(blockIdx.x & 7) * per + j;
+    const int j = (int)(block >> 3), L = (int)(block & 7) * per + j;
     if (j >= per || L >= total) return t;
     const int qm = L / ntn;
     int hit = -1, my_p = 0, my_mt = 0, my_lo = 0, my_hi = 0, p = incl - s;
