@@ -192,3 +192,35 @@ def test_ep_group_rank_by_rank_equals_the_one_gpu_layer(name, scale, S, capacity
         ref = oracle.layer_forward(x, inp["w_router"], inp.bias, inp["w_gate"], inp["w_up"], inp["w_down"], cfg.K,
                                    cfg.renormalize, capacity)
         assert_close(values(y), ref.y, inp.is_bf16, f"{name} S={S}")
+
+
+@pytest.mark.parametrize("group", [0, 1, 8])
+@pytest.mark.parametrize("n_src,n_dst", [(1, 1), (255, 256), (256, 256), (256, 257), (257, 256), (64, 256)])
+def test_plan_in_the_copy_up_to_256_chunks(n_src, n_dst, group):
+    """256 chunks: the most that one launch takes, with repeats and with indices outside the source."""
+    rng = np.random.default_rng(10 * n_src + n_dst)
+    rows = rng.integers(-1, 9, size=n_src).astype(np.int32)
+    order = rng.integers(-1, n_src + 1, size=n_dst).astype(np.int32)
+    total = int(np.maximum(rows, 0).sum())
+    src = make_tokens(n_src, max(total, 1), 24, bf16=True)
+    _check(src, rows, order, group, 8 * n_dst + 3)
+
+
+def test_sizes_written_over_the_sizes_read():
+    """chunk_rows_out may be chunk_rows: the sizes in the gathered order replace those of the source."""
+    import torch
+    import paper_2504_14960_amd as moe
+    rng = np.random.default_rng(5)
+    rows = rng.integers(0, 60, size=64).astype(np.int32)
+    order = rng.permutation(64).astype(np.int32)
+    src = make_tokens(5, int(rows.sum()), 512, bf16=True)
+    want_dst, want_rows, want_goff, _ = oracle.sort_chunks(src, rows, order, group=8, r_dst=src.shape[0])
+    d_rows, d_src = to_dev(rows), to_dev(src)
+    dst = torch.zeros_like(d_src)
+    goff = torch.empty(9, dtype=torch.int32, device="cuda")
+    ws = torch.empty(moe.sort_chunks_workspace_bytes(64), dtype=torch.uint8, device="cuda")
+    moe.sort_chunks(d_src, d_rows, to_dev(order), 8, dst, d_rows, goff, ws)
+    torch.cuda.synchronize()
+    np.testing.assert_array_equal(to_host(dst), want_dst)
+    np.testing.assert_array_equal(to_host(d_rows), want_rows)
+    np.testing.assert_array_equal(to_host(goff), want_goff)
