@@ -678,56 +678,71 @@ __global__ __launch_bounds__(256) void topk_rank_kernel(const float* __restrict_
 }
 
 // ------------------------------------------------------------------ fp32 / VALU
-// One wave per token; lanes stride the hidden dimension, eight experts at a time: their weight loads are in flight
-// together, and the eight sums are folded across the wave in ten shuffles (three halving steps that leave lane l with
-// the sum of expert l mod 8 over an eighth of the wave, then three ordinary ones).
+// A wave forms the logits of TW tokens; lanes stride the hidden dimension, eight experts at a time: their weight loads
+// are in flight together, and the eight sums are folded across the wave in ten shuffles (three halving steps that leave
+// lane l with the sum of expert l mod 8 over an eighth of the wave, then three ordinary ones).  WT waves share a
+// token's experts, eight at a time in turn.  A sum's order is the same at every TW and WT.
+// With few tokens a chain of loads bounds it (a block of experts waits for the block before it: WT waves walk E / 8 WT of
+// them), with many the weight's way from the caches (TW tokens share a load).  Further steps of the hidden dimension in
+// flight in a wave came out slower (256 x 828 x 16: 8.1 us for 7.5).
+template <int TW, int WT>
 __global__ __launch_bounds__(256) void router_f32_kernel(
     const float* __restrict__ x, const float* __restrict__ w, const float* __restrict__ bias,
     float* __restrict__ logits, int T, int H, int E, int K, int renorm,
     int32_t* __restrict__ topk_idx, float* __restrict__ topk_gate) {
-    constexpr int EB = 8;
-    __shared__ float red[4][kMaxExperts + 1];
+    constexpr int EB = 8, NT = 4 / WT * TW;
+    __shared__ float red[NT][kMaxExperts + 1];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int t0 = blockIdx.x * 4;
-    const int t = t0 + wave;
+    const int t0 = blockIdx.x * NT, slot = wave / WT * TW;
+    const int t = t0 + slot;
     if (t < T) {
-        const float* xr = x + (size_t)t * H;
-        for (int e0 = 0; e0 < E; e0 += EB) {
-            float s[EB];
+        const float* xr[TW];
 #pragma unroll
-            for (int j = 0; j < EB; ++j) s[j] = 0.f;
+        for (int u = 0; u < TW; ++u) xr[u] = x + (size_t)min(t + u, T - 1) * H;
+        for (int e0 = wave % WT * EB; e0 < E; e0 += EB * WT) {
+            float s[TW][EB];
+#pragma unroll
+            for (int u = 0; u < TW; ++u)
+#pragma unroll
+                for (int j = 0; j < EB; ++j) s[u][j] = 0.f;
             for (int h = lane * 4; h < H; h += 256) {
-                const f32x4 a = *reinterpret_cast<const f32x4*>(xr + h);
-                f32x4 b[EB];
+                f32x4 a[TW], b[EB];
+#pragma unroll
+                for (int u = 0; u < TW; ++u) a[u] = *reinterpret_cast<const f32x4*>(xr[u] + h);
 #pragma unroll
                 for (int j = 0; j < EB; ++j) b[j] = *reinterpret_cast<const f32x4*>(w + (size_t)min(e0 + j, E - 1) * H + h);
 #pragma unroll
-                for (int j = 0; j < EB; ++j)
+                for (int u = 0; u < TW; ++u)
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) s[j] = fmaf(a[q], b[j][q], s[j]);
+                    for (int j = 0; j < EB; ++j)
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) s[u][j] = fmaf(a[u][q], b[j][q], s[u][j]);
             }
 #pragma unroll
-            for (int n = EB / 2; n > 0; n >>= 1) {
-                const bool up = lane & n;   // this lane keeps the upper half of the values it still holds
+            for (int u = 0; u < TW; ++u) {
 #pragma unroll
-                for (int j = 0; j < n; ++j) {
-                    const float keep = up ? s[j + n] : s[j], give = up ? s[j] : s[j + n];
-                    s[j] = keep + __shfl_xor(give, n, 64);
+                for (int n = EB / 2; n > 0; n >>= 1) {
+                    const bool up = lane & n;   // this lane keeps the upper half of the values it still holds
+#pragma unroll
+                    for (int j = 0; j < n; ++j) {
+                        const float keep = up ? s[u][j + n] : s[u][j], give = up ? s[u][j] : s[u][j + n];
+                        s[u][j] = keep + __shfl_xor(give, n, 64);
+                    }
                 }
-            }
-            float v = s[0];
+                float v = s[u][0];
 #pragma unroll
-            for (int off = EB; off < 64; off <<= 1) v += __shfl_xor(v, off, 64);
-            const int e = e0 + lane;
-            if (lane < EB && e < E) {
-                if (bias) v += bias[e];
-                red[wave][e] = v;
-                logits[(size_t)t * E + e] = v;
+                for (int off = EB; off < 64; off <<= 1) v += __shfl_xor(v, off, 64);
+                const int e = e0 + lane;
+                if (lane < EB && e < E && t + u < T) {
+                    if (bias) v += bias[e];
+                    red[slot + u][e] = v;
+                    logits[(size_t)(t + u) * E + e] = v;
+                }
             }
         }
     }
     __syncthreads();
-    select_tokens(&red[0][0], kMaxExperts + 1, 4, t0, T, E, K, renorm, topk_idx, topk_gate);
+    select_tokens(&red[0][0], kMaxExperts + 1, NT, t0, T, E, K, renorm, topk_idx, topk_gate);
 }
 
 // ------------------------------------------------------------------ selection only
@@ -871,9 +886,20 @@ void launch_router(const void* x, const void* w, const float* bias, float* logit
         return;
     }
     if (dt == MOE_F32) {
-        hipLaunchKernelGGL(router_f32_kernel, dim3((T + 3) / 4), dim3(256), 0, s,
-                           static_cast<const float*>(x), static_cast<const float*>(w), bias, logits,
-                           T, H, E, K, renorm, idx, gate);
+        // (tokens per wave, waves per token), us, one token per wave / here: 64 x 828 x 8 experts 6.2 / 5.6; 256 x 828 x 16
+        // 10.2 / 7.2; 256 x 1024 x 64 26.3 / 13.1; 2048 x 1024 x 64 31.3 / 21.4; 4096 x 1024 x 16 17.2 / 11.7; 6000 x 1024 x 8
+        // 13.1 / 8.9; 16384 x 4096 x 8 86.4 / 52.0; 65536 x 512 x 8 74.0 / 30.5.  Four waves on a token lose above 1024
+        // tokens (2048 x 1024 x 64 22.8) and with two blocks of experts or fewer (two of them idle), two waves above 4096
+        // (6000 x 1024 x 8 11.6), and four tokens a wave below 8192 (6000 x 1024 x 8 9.9).
+#define RF32(TW, WT)                                                                                                    \
+    hipLaunchKernelGGL((router_f32_kernel<TW, WT>), dim3((T + 4 / WT * TW - 1) / (4 / WT * TW)), dim3(256), 0, s,       \
+                       static_cast<const float*>(x), static_cast<const float*>(w), bias, logits, T, H, E, K, renorm,   \
+                       idx, gate)
+        if (T >= 8192) RF32(4, 1);
+        else if (T > 4096) RF32(2, 1);
+        else if (T > 1024 || E <= 16) RF32(2, 2);
+        else RF32(2, 4);
+#undef RF32
         return;
     }
     const int nb = (E + 15) / 16;

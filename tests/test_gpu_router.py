@@ -104,3 +104,27 @@ def test_every_router_tile_height_against_oracle(T, H, E, K, bias, renorm, tile)
     assert np.abs(logits - l64).max() <= LOGIT_ATOL
     np.testing.assert_array_equal(idx, want_idx)
     np.testing.assert_allclose(gate, want_gate, rtol=GATE_RTOL, atol=2e-5)
+
+
+@pytest.mark.parametrize("T,H,E,K", [
+    (1, 4, 1, 1), (3, 260, 9, 2), (63, 828, 16, 4),            # two tokens a wave, two waves a token
+    (1023, 64, 17, 3), (1024, 252, 100, 8), (1025, 64, 17, 3),  # four waves a token, then two
+    (4096, 36, 8, 2), (4097, 36, 24, 2),                        # then one
+    (8191, 8, 8, 2), (8193, 300, 33, 2),                        # then four tokens a wave
+])
+def test_fp32_router_at_the_borders_of_its_forms(T, H, E, K):
+    """Logits against 64 bits within the bound of a sum of H products in chains of ceil(H / 256) * 4 additions per lane
+    and six across the wave (plus the bias), and the selection of those very logits."""
+    rng = np.random.default_rng(T + E)
+    x = rng.standard_normal((T, H)).astype(np.float32)
+    w = (rng.standard_normal((E, H)) / np.sqrt(H)).astype(np.float32)
+    bias = rng.standard_normal(E).astype(np.float32)
+    logits, idx, gate = _gpu_topk(np.zeros((T, E), np.float32), K, True, x, w, bias)
+    x64, w64 = x.astype(np.float64), w.astype(np.float64)
+    l64 = x64 @ w64.T + bias
+    steps = (H + 255) // 256 * 4 + 6 + 1
+    bound = steps * 2.0 ** -24 * (np.abs(x64) @ np.abs(w64).T + np.abs(bias)) * 1.01
+    assert (np.abs(logits - l64) <= bound).all()
+    want_idx, want_gate = oracle.topk_gates(logits, K, True)
+    np.testing.assert_array_equal(idx, want_idx)
+    np.testing.assert_allclose(gate, want_gate, rtol=GATE_RTOL, atol=1e-6)
