@@ -9,6 +9,14 @@
 // 1152 x 1216 17 / 12, 16 / 9; one x 60, 4416 x 12096 down 57 / 31;  FP8, 2 x 525, 1664 x 3200 down 20 / 13, 8 x 20, 1152 x 13824
 // down 64 / 31.  With many experts or rows the large tiles are ahead by up to two times.
 //
+// Odd bf16 sizes, which the large tiles do not take, have a form for many rows too: 128 x 128 in four waves of 64 x 64, a ring of
+// two stages (64 KB), two workgroups to a compute unit.  The form with one to a compute unit is bound by what its eight waves of 64 x
+// 32 read from the LDS (96 KB a stage, where four of 64 x 64 read 64) and by the first and last microseconds of every round, which
+// nothing else runs under.  us, that form / so: 16 experts x 272 rows, 1496 x 1816 down 57 / 49, 16 x 442, 1288 x 1952 gate/up 163 /
+// 134, 12 x 356, 1456 x 1272 79 / 71, 12 x 567, 1696 x 1992 down 100 / 90.  Not kept: stages of 64 bytes of the contraction, five
+// of them (134 -> 160: twice the barriers); four waves on 64 x 128, three stages (12 x 194, 1000 x 1416 gate/up 42 -> 38, but mostly
+// behind); eight waves on 256 x 128, three stages (134 -> 127, but 49 -> 73 where tiles fall badly).
+//
 // fp32 layers run here on the bf16 matrix instruction, the fp32 one having 1/16 of its rate.  An fp32 value is the sum of three
 // bf16 values (8 bits of significand each: a0 = bf16(a), a1 = bf16(a - a0), a2 = a - a0 - a1, all exact), so a product of two is
 // nine bf16 products, of which the three smallest (2^-26 of the largest and less) are left out: six instead of sixteen times the
@@ -380,7 +388,8 @@ void launch_form(int form, const StreamArgs& p, int r_max, hipStream_t s) {
         if (form == 0) launch<ELT, MODE, 2, Q, 1, 1, 1, 2, 6>(p, r_max, s);           // 32 x 64, 24 KB a stage
         else if (form == 1) launch<ELT, MODE, 2, 2, 2, 1, 1, 2, 4>(p, r_max, s);      // 64 x 64, 32 KB
         else if (form == 2) launch<ELT, MODE, 1, 2, 2, 2, 1, 2, 6>(p, r_max, s);      // 64 x 128, 24 KB
-        else launch<ELT, MODE, 1, 1, 2, 4, 2, 1, 4>(p, r_max, s);                     // 128 x 128, 32 KB
+        else if (form == 3 || ELT != kStreamBf16 || (MODE != 0 && MODE != 3)) launch<ELT, MODE, 1, 1, 2, 4, 2, 1, 4>(p, r_max, s);   // 128 x 128, 32 KB
+        else if constexpr (ELT == kStreamBf16 && (MODE == 0 || MODE == 3)) launch<ELT, MODE, 1, 1, 2, 2, 2, 2, 2>(p, r_max, s);      // the same, two to a compute unit
     }
 }
 

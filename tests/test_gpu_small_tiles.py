@@ -50,6 +50,18 @@ def test_every_form_with_the_rounds_of_its_ring(form):
         assert_close(y, y_ref, True, "y_perm")
 
 
+# sizes the large tiles do not take have a fifth form, two workgroups to a compute unit: a part of a block, one, a block and a part,
+# its ring of two often round with 16 bytes over; columns that end in each of a wave's blocks
+@pytest.mark.parametrize("H,F", [(8, 200), (72, 64), (64, 136), (1416, 1000), (264, 2632)])
+def test_form_of_the_odd_sizes(H, F):
+    import paper_2504_14960_amd as moe
+    inp, x_perm, offsets, h_ref, y_ref = bf16_case(H=H, F=F, E=len(EDGES), counts=EDGES, seed=7650 + H)
+    moe.set_option("gemm_stream", 24)
+    h, y = bf16_run(x_perm, offsets, inp, 0)
+    assert_close(h, h_ref, True, "h")
+    assert_close(y, y_ref, True, "y_perm")
+
+
 @pytest.mark.parametrize("form", FORMS)
 def test_saving_form_has_the_bits_of_the_plain_one(form):
     import torch
