@@ -113,14 +113,8 @@ size_t moe_permute_workspace_bytes(int T, int K, int E) {
     return permute_workspace_bytes(T, K, E);
 }
 
-moe_status_t moe_router_topk(const void* x, const void* w_router, const float* logit_bias,
-                             float* logits, int T, int H, int E, int K, int renormalize,
-                             moe_dtype_t dt, int32_t* topk_idx, float* topk_gate,
-                             moe_stream_t stream) {
-    static const char* fn = "moe_router_topk";
-    if (x == nullptr) H = (dt == MOE_BF16) ? 8 : 4;  // ignored, keep the shape check quiet
-    if (moe_status_t st = check_dims(fn, T, H, E, K, dt)) return st;
-    if (T == 0) return MOE_OK;
+static moe_status_t check_router_pointers(const char* fn, const void* x, const void* w_router, const float* logit_bias,
+                                          const float* logits, const int32_t* topk_idx, const float* topk_gate) {
     REQUIRE_PTR(fn, logits);
     REQUIRE_PTR(fn, topk_idx);
     REQUIRE_PTR(fn, topk_gate);
@@ -130,6 +124,18 @@ moe_status_t moe_router_topk(const void* x, const void* w_router, const float* l
         if (logit_bias && (reinterpret_cast<uintptr_t>(logit_bias) & 3u))
             return fail(MOE_ERR_INVALID_ARG, "%s: logit_bias is not 4-byte aligned", fn);
     }
+    return MOE_OK;
+}
+
+moe_status_t moe_router_topk(const void* x, const void* w_router, const float* logit_bias,
+                             float* logits, int T, int H, int E, int K, int renormalize,
+                             moe_dtype_t dt, int32_t* topk_idx, float* topk_gate,
+                             moe_stream_t stream) {
+    static const char* fn = "moe_router_topk";
+    if (x == nullptr) H = (dt == MOE_BF16) ? 8 : 4;  // ignored, keep the shape check quiet
+    if (moe_status_t st = check_dims(fn, T, H, E, K, dt)) return st;
+    if (T == 0) return MOE_OK;
+    if (moe_status_t st = check_router_pointers(fn, x, w_router, logit_bias, logits, topk_idx, topk_gate)) return st;
     launch_router(x, w_router, x ? logit_bias : nullptr, logits, T, H, E, K, renormalize != 0, dt,
                   topk_idx, topk_gate, static_cast<hipStream_t>(stream));
     return check_launch(fn);
@@ -636,6 +642,28 @@ static moe_status_t expert_ffn_shared(const char* fn, const void* x, const void*
     return check_launch(fn);
 }
 
+// the layer's routing and dispatch into its workspace
+static moe_status_t route_and_permute(const char* fn, const void* x, const void* w_router, const float* logit_bias, int T, int H, int E,
+                                      int K, int renormalize, int capacity, moe_dtype_t dt, bool shared, const LayerLayout& L,
+                                      uint8_t* ws, moe_stream_t stream) {
+    const hipStream_t s = static_cast<hipStream_t>(stream);
+    float* logits = reinterpret_cast<float*>(ws + L.logits);
+    int32_t* idx = reinterpret_cast<int32_t*>(ws + L.idx);
+    float* gate = reinterpret_cast<float*>(ws + L.gate);
+    int32_t* counts = reinterpret_cast<int32_t*>(ws + L.counts);
+    int32_t* offsets = reinterpret_cast<int32_t*>(ws + L.offsets);
+    int32_t* roa = reinterpret_cast<int32_t*>(ws + L.roa);
+    int32_t* aor = reinterpret_cast<int32_t*>(ws + L.aor);
+    int32_t* one_expert = shared ? reinterpret_cast<int32_t*>(ws + L.s_offsets) : nullptr;
+    if (moe_status_t st = check_router_pointers("moe_router_topk", x, w_router, logit_bias, logits, idx, gate)) return st;
+    if (permute_small_allowed() && launch_route_permute(x, w_router, logit_bias, logits, T, H, E, K, renormalize != 0, capacity, L.r_max, dt,
+                                                        idx, gate, ws + L.x_perm, counts, offsets, roa, aor, one_expert, s))
+        return check_launch(fn);
+    if (moe_status_t st = moe_router_topk(x, w_router, logit_bias, logits, T, H, E, K, renormalize, dt, idx, gate, stream)) return st;
+    launch_permute(x, idx, T, H, E, K, capacity, L.r_max, dt, ws + L.x_perm, counts, offsets, roa, aor, ws + L.perm_ws, s, one_expert);
+    return check_launch(fn);
+}
+
 moe_status_t moe_layer_forward(const void* x, const void* w_router, const float* logit_bias,
                                const void* w_gate, const void* w_up, const void* w_down,
                                const void* ws_gate, const void* ws_up, const void* ws_down,
@@ -657,20 +685,11 @@ moe_status_t moe_layer_forward(const void* x, const void* w_router, const float*
                     workspace ? workspace_bytes : (size_t)0);
     REQUIRE_PTR(fn, workspace);
     uint8_t* ws = static_cast<uint8_t*>(workspace);
-    float* logits = reinterpret_cast<float*>(ws + L.logits);
-    int32_t* idx = reinterpret_cast<int32_t*>(ws + L.idx);
     float* gate = reinterpret_cast<float*>(ws + L.gate);
-    int32_t* counts = reinterpret_cast<int32_t*>(ws + L.counts);
     int32_t* offsets = reinterpret_cast<int32_t*>(ws + L.offsets);
     int32_t* roa = reinterpret_cast<int32_t*>(ws + L.roa);
-    int32_t* aor = reinterpret_cast<int32_t*>(ws + L.aor);
 
-    moe_status_t st = moe_router_topk(x, w_router, logit_bias, logits, T, H, E, K, renormalize, dt,
-                                      idx, gate, stream);
-    if (st) return st;
-    launch_permute(x, idx, T, H, E, K, capacity, L.r_max, dt, ws + L.x_perm, counts, offsets, roa, aor, ws + L.perm_ws,
-                   static_cast<hipStream_t>(stream), shared ? reinterpret_cast<int32_t*>(ws + L.s_offsets) : nullptr);
-    st = check_launch(fn);
+    moe_status_t st = route_and_permute(fn, x, w_router, logit_bias, T, H, E, K, renormalize, capacity, dt, shared, L, ws, stream);
     if (st) return st;
     const void* addend = nullptr;
     if (!shared) {

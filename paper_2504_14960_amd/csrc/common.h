@@ -81,6 +81,12 @@ void launch_permute(const void* x, const int32_t* idx, int T, int H, int E, int 
                     int r_max, moe_dtype_t dt, void* x_perm, int32_t* counts, int32_t* offsets,
                     int32_t* row_of_assign, int32_t* assign_of_row, void* ws, hipStream_t s, int32_t* one_expert = nullptr);
 
+bool permute_small_allowed();    // the option above leaves the choice to the sizes
+// launch_router and launch_permute in one launch, for a handful of tokens; false if the call is none of its own
+bool launch_route_permute(const void* x, const void* w, const float* bias, float* logits, int T, int H, int E, int K, int renorm,
+                          int capacity, int r_max, moe_dtype_t dt, int32_t* idx, float* gate, void* x_perm, int32_t* counts,
+                          int32_t* offsets, int32_t* row_of_assign, int32_t* assign_of_row, int32_t* one_expert, hipStream_t s);
+
 // the library's own scratch for moe_permute_noalloc: its size, and its address on the current device
 size_t permute_scratch_bytes();
 int32_t* permute_scratch(hipError_t* err);

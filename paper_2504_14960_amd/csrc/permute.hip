@@ -796,6 +796,7 @@ __global__ void fill_i32_kernel(int32_t* p, int n, int32_t v0, int32_t step) {
 }  // namespace
 
 static int g_permute_fused = 1;   // 0: always the three-kernel path
+bool permute_small_allowed() { return g_permute_fused == 1; }
 void set_permute_fused(int v) { g_permute_fused = v; }   // 2 / 3: the packed form with one / two tokens per wave, 4: the histogram form
 
 // Where the histogram form of the one-launch dispatch takes over (us, the three launches or the packed form / this one):

@@ -379,17 +379,28 @@ __global__ __launch_bounds__(256) void router_bf16_kernel(
 // step of both, so whole lines are asked for; the order inside a step plays no part in a dot product).  The partial
 // sums are added in wave order (fixed => reproducible).
 // SELECT (E <= 16: a workgroup holds all logits of its tokens): the selection as well, sixteen lanes per token.
-constexpr int kSplitWaves = 16;
+// PLAN (one workgroup, tb <= kPlanTokens tokens): the dispatch too, whose own launch is as long as its work then.  A lane of the
+// first wave holds an assignment (at most 4 tokens x 16 experts): its row is the number of kept ones of lower experts and of its
+// own expert's lower assignments.  The token rows are requested before the plan is made.  Maps as launch_permute's, bit for bit.
+constexpr int kSplitWaves = 16, kPlanTokens = 4;
 
-template <int MB, bool SELECT>
+struct Dispatch {
+    int32_t *counts, *offsets, *row_of_assign, *assign_of_row, *one_expert;
+    uint8_t* x_perm;
+    int capacity, r_max;
+};
+
+template <int MB, bool SELECT, bool PLAN = false>
 __global__ __launch_bounds__(kSplitWaves * 64) void router_logits_kernel(
     const bf16_t* __restrict__ x, const bf16_t* __restrict__ w, const float* __restrict__ bias,
     float* __restrict__ logits, int T, int H, int E, int tb, int eg, int K, int renorm,
-    int32_t* __restrict__ topk_idx, float* __restrict__ topk_gate) {
+    int32_t* __restrict__ topk_idx, float* __restrict__ topk_gate, Dispatch d) {
+    static_assert(SELECT || !PLAN, "the dispatch follows the selection");
     constexpr int LD = 20;                     // row of a partial tile: the four lane groups of a store hit different banks
     constexpr int U = MB == 1 ? 4 : 3;         // steps in flight
     static_assert(MB == 1 || !SELECT, "the lanes that sum a token's logits are the first turn's");
     __shared__ float part[kSplitWaves][16 * MB][LD];
+    __shared__ int sel[PLAN ? 64 : 1];         // the expert of an assignment, then its row
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
     const int t0 = blockIdx.x * tb, e0 = blockIdx.y * eg;
     const int fr = lane & 15, fg = lane >> 4;
@@ -431,6 +442,12 @@ __global__ __launch_bounds__(kSplitWaves * 64) void router_logits_kernel(
     for (int a = 0; a < MB; ++a)
 #pragma unroll
         for (int r = 0; r < 4; ++r) part[wave][a * 16 + fg * 4 + r][fr] = acc[a][r];
+    const int row_bytes = 2 * H, at = 16 * (int)threadIdx.x;   // PLAN: a row has at most 16 bytes for every thread
+    u32x4 mine[PLAN ? kPlanTokens : 1];
+    if constexpr (PLAN)
+#pragma unroll
+        for (int t = 0; t < kPlanTokens; ++t)
+            if (t < T && at < row_bytes) mine[t] = *reinterpret_cast<const u32x4*>(reinterpret_cast<const uint8_t*>(x) + (size_t)t * row_bytes + at);
     __syncthreads();
     for (int i = threadIdx.x; i < 16 * MB * 16; i += kSplitWaves * 64) {
         const int lt = i >> 4, le = i & 15;
@@ -446,28 +463,72 @@ __global__ __launch_bounds__(kSplitWaves * 64) void router_logits_kernel(
         // the sixteen lanes that summed a token's logits select its experts: the rank of an expert is the number of experts in
         // front of it (value descending, index ascending), as in topk_rank_kernel
         const int lt = threadIdx.x >> 4, le = lane & 15;
-        if (lt >= tb || t0 + lt >= T) return;
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        const float v = le < E ? part[0][lt][le] : -INFINITY;
-        float m = v;
-        int rank = 0;
-        for (int e = 0; e < E; ++e) {
-            const float s = part[0][lt][e];
-            rank += e < le ? s >= v : s > v;
-            m = fmaxf(m, s);
+        if (lt < tb && t0 + lt < T) {
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
+            const float v = le < E ? part[0][lt][le] : -INFINITY;
+            float m = v;
+            int rank = 0;
+            for (int e = 0; e < E; ++e) {
+                const float s = part[0][lt][e];
+                rank += e < le ? s >= v : s > v;
+                m = fmaxf(m, s);
+            }
+            float p = le < E ? expf(v - m) : 0.f, z = p;
+            for (int off = 8; off > 0; off >>= 1) z += __shfl_xor(z, off, 16);
+            p = p / z;
+            const bool chosen = le < E && rank < K;
+            float gsum = chosen ? p : 0.f;
+            if (renorm)
+                for (int off = 8; off > 0; off >>= 1) gsum += __shfl_xor(gsum, off, 16);
+            if (chosen) {
+                topk_idx[(size_t)(t0 + lt) * K + rank] = le;
+                topk_gate[(size_t)(t0 + lt) * K + rank] = renorm ? p / gsum : p;
+                if constexpr (PLAN) sel[lt * K + rank] = le;
+            }
         }
-        float p = le < E ? expf(v - m) : 0.f, z = p;
-        for (int off = 8; off > 0; off >>= 1) z += __shfl_xor(z, off, 16);
-        p = p / z;
-        const bool chosen = le < E && rank < K;
-        float gsum = chosen ? p : 0.f;
-        if (renorm)
-            for (int off = 8; off > 0; off >>= 1) gsum += __shfl_xor(gsum, off, 16);
-        if (chosen) {
-            topk_idx[(size_t)(t0 + lt) * K + rank] = le;
-            topk_gate[(size_t)(t0 + lt) * K + rank] = renorm ? p / gsum : p;
+    }
+    if constexpr (PLAN) {
+        __syncthreads();
+        const int A = T * K;
+        if (wave == 0) {
+            const int e = lane < A ? sel[lane] : -1, limit = d.capacity > 0 ? d.capacity : A;
+            const uint64_t below = lane == 0 ? 0ull : ~0ull >> (64 - lane);
+            int row = -1, total = 0, count = 0, end = 0;
+            for (int q = 0; q < E; ++q) {
+                const uint64_t peers = __ballot(e == q);
+                const int n = min(__popcll(peers), limit), rank = __popcll(peers & below);
+                if (e == q && rank < limit && total + rank < d.r_max) row = total + rank;   // r_max holds all rows that are kept
+                total += n;
+                if (lane == q) {
+                    count = n;
+                    end = total;
+                }
+            }
+            sel[lane] = row;
+            if (lane < E) {
+                d.counts[lane] = count;
+                d.offsets[lane + 1] = end;
+            }
+            if (lane == 0) {
+                d.offsets[0] = 0;
+                if (d.one_expert != nullptr) {
+                    d.one_expert[0] = 0;
+                    d.one_expert[1] = T;
+                }
+            }
+            if (lane < A) d.row_of_assign[lane] = row;
+            if (row >= 0) d.assign_of_row[row] = lane;
+            for (int r = total + lane; r < d.r_max; r += 64) d.assign_of_row[r] = -1;
         }
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < kPlanTokens; ++t)
+            if (t < T && at < row_bytes)
+                for (int k = 0; k < K; ++k) {
+                    const int row = sel[t * K + k];
+                    if (row >= 0) *reinterpret_cast<u32x4*>(d.x_perm + (size_t)row * row_bytes + at) = mine[t];
+                }
     }
 }
 
@@ -878,6 +939,19 @@ static void launch_topk(const float* logits, int T, int E, int K, int renorm, in
 static int g_router_tile = 0;  // 16-token blocks per workgroup; 0 = chosen by size, 8 = experts spread over workgroups, 16 = tiles
 void set_router_tile(int mb) { g_router_tile = mb; }
 
+// Up to four tokens of up to 16 experts (us of the layer, two launches / so): 1024 x 8, F = 1024, 1 token 22.1 / 18.6, 4 tokens 22.8 /
+// 21.5; 4096 x 8, F = 14336 139.8 / 137.9, 384.9 / 383.6; 1768 x 16, F = 1928 31.0 / 29.3, 73.3 / 72.3; 7168 x 8, F = 768 36.2 /
+// 34.0, 45.8 / 45.7.  One compute unit reads and copies all the rows, so the gain is gone with more tokens.
+bool launch_route_permute(const void* x, const void* w, const float* bias, float* logits, int T, int H, int E, int K, int renorm,
+                          int capacity, int r_max, moe_dtype_t dt, int32_t* idx, float* gate, void* x_perm, int32_t* counts,
+                          int32_t* offsets, int32_t* row_of_assign, int32_t* assign_of_row, int32_t* one_expert, hipStream_t s) {
+    if (dt != MOE_BF16 || T > kPlanTokens || E > 16 || 2 * H > 16384 || g_router_tile != 0 || !one_block_pays(T, H, E)) return false;
+    const Dispatch d = {counts, offsets, row_of_assign, assign_of_row, one_expert, static_cast<uint8_t*>(x_perm), capacity, r_max};
+    hipLaunchKernelGGL((router_logits_kernel<1, true, true>), dim3(1), dim3(kSplitWaves * 64), 0, s, static_cast<const bf16_t*>(x),
+                       static_cast<const bf16_t*>(w), bias, logits, T, H, E, kPlanTokens, 16, K, renorm, idx, gate, d);
+    return true;
+}
+
 void launch_router(const void* x, const void* w, const float* bias, float* logits, int T, int H,
                    int E, int K, int renorm, moe_dtype_t dt, int32_t* idx, float* gate,
                    hipStream_t s) {
@@ -924,7 +998,7 @@ void launch_router(const void* x, const void* w, const float* bias, float* logit
         while (tb > 2 && (T + tb / 2 - 1) / (tb / 2) <= 256) tb /= 2;
         const dim3 grid((T + tb - 1) / tb);
         hipLaunchKernelGGL((router_logits_kernel<1, true>), grid, dim3(kSplitWaves * 64), 0, s, static_cast<const bf16_t*>(x), static_cast<const bf16_t*>(w), bias,
-                           logits, T, H, E, tb, 16, K, renorm, idx, gate);
+                           logits, T, H, E, tb, 16, K, renorm, idx, gate, Dispatch{});
         return;
     }
     if (nb <= 8 && (g_router_tile == 8 || (g_router_tile == 0 && T <= kSplitMaxTokens && (long long)E * H >= kSplitMinWeights))) {
@@ -941,10 +1015,10 @@ void launch_router(const void* x, const void* w, const float* bias, float* logit
         const dim3 grid((T + tb - 1) / tb, (E + eg - 1) / eg);
         if (tb > 16)
             hipLaunchKernelGGL((router_logits_kernel<2, false>), grid, dim3(kSplitWaves * 64), 0, s, static_cast<const bf16_t*>(x),
-                               static_cast<const bf16_t*>(w), bias, logits, T, H, E, tb, eg, K, renorm, idx, gate);
+                               static_cast<const bf16_t*>(w), bias, logits, T, H, E, tb, eg, K, renorm, idx, gate, Dispatch{});
         else
             hipLaunchKernelGGL((router_logits_kernel<1, false>), grid, dim3(kSplitWaves * 64), 0, s, static_cast<const bf16_t*>(x),
-                               static_cast<const bf16_t*>(w), bias, logits, T, H, E, tb, eg, K, renorm, idx, gate);
+                               static_cast<const bf16_t*>(w), bias, logits, T, H, E, tb, eg, K, renorm, idx, gate, Dispatch{});
         launch_topk(logits, T, E, K, renorm, idx, gate, s);
         return;
     }
