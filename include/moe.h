@@ -546,7 +546,7 @@ moe_status_t moe_gemm_clock_sample(uint64_t* ticks);
  * always, under "gemm_variant" 0 and in FP8; 2 = always, with wide workgroups
  * where the type has them; 11, 12, 14, 18 = as 1 with 16, 32, 64, 128 weight rows
  * per workgroup; 20 to 24 = always the small tiles, in
- * the form 0 to 4 (0 to 3 in bf16 and FP8); 100 S + U = as 2 with U = 3 to 8 times 32 weight rows per
+ * the form 0 to 4 (0 to 3 in FP8 and bf16; 4 also in bf16 where H or F is no multiple of 64); 100 S + U = as 2 with U = 3 to 8 times 32 weight rows per
  * workgroup and, where there is room for partial sums, the contraction in S = 1,
  * 2, 4, 8 or 16 parts; 2000 + S = the large tiles, and where there is room the contraction in S = 2 to
  * 16 parts); "gemm_pair" (the shared expert's two products in one launch each with the routed experts', where both are
