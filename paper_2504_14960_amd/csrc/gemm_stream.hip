@@ -964,6 +964,9 @@ int plan_pair(int elt, const StreamPlan& routed, int r_max, int E, int N, int K,
     if (g_pair_blocks == 0 || g_stream >= 0 || elt != kStreamBf16 || routed.kind != kPlanNarrow || tokens > 128 || !plain(N, K) ||
         !plain(sN, sK) || narrow_blocks(r_max, E, N, swiglu) == 1)
         return 0;
+    // With a capacity there may be fewer routed rows than tokens.  Workgroups for up to 16 rows in all have no ring, and the shared
+    // expert's rows would need one.
+    if (r_max <= 16 && tokens > 16) return 0;
     const int forced = g_pair_blocks < 0 ? -1 : swiglu ? g_pair_blocks / 10 : g_pair_blocks % 10;
     if (forced >= 0) return r_max <= 16 && forced == 8 ? 4 : forced;
     // What the second launch costs are its first and last microseconds, an end of the first one in which compute units stand idle, and
@@ -991,10 +994,11 @@ void launch_stream_pair(int blocks, const void* A, const int32_t* offsets, int r
     const StreamArgs p = stream_args(kStreamBf16, A, offsets, r_max, E, N, K, B0, B1, C);
     const StreamArgs q = stream_args(kStreamBf16, sA, s_offsets, tokens, 1, sN, sK, sB0, sB1, sC);
     const int fb = narrow_blocks(r_max, E, N, B1 != nullptr);
+    const bool direct = r_max <= 16 && tokens <= 16;   // both products' rows
     auto go = [&](auto mode, auto own) {
         constexpr int MODE = decltype(mode)::value, FB = decltype(own)::value;
         if constexpr (FB <= 4) {
-            if (r_max <= 16) {
+            if (direct) {
                 if (blocks == 4) launch_pair<MODE, FB, 4, true>(p, q, r_max, s);
                 else launch_pair<MODE, FB, 2, true>(p, q, r_max, s);
                 return;
