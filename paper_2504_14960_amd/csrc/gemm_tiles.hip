@@ -360,7 +360,9 @@ __global__ __launch_bounds__(KB * KS * WGM * WGN * 64, ELT == kStreamF32 && FM *
         p.ticks[1] = __builtin_amdgcn_s_memrealtime() - rt_entry;
     }
     if constexpr (ELT == kStreamFp8 && MODE == 1) {
-        if (KG > 1) __syncthreads();   // the groups' sums are read
+        // The scratch lies in the ring: the other waves have read the last stage and the groups' sums, and none of their loads, those
+        // past the last stage among them, is still to land.
+        __syncthreads();
         fold_amax(p, amax, reinterpret_cast<float*>(smem));
     }
 }

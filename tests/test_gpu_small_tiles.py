@@ -94,3 +94,13 @@ def fp8(request):
 @pytest.mark.parametrize("form", FORMS)
 def test_every_form_in_fp8(fp8, form):
     check_fp8(fp8, 20 + form)
+
+
+# the last stage of the 128 x 128 form in each slot of its ring (H = 640: the first, which the scratch of amax shares; 768: the loads past
+# the last stage end there); tiles of up to 64 rows, whose upper waves have nothing to multiply, and fuller ones
+@pytest.mark.parametrize("H", [512, 640, 768, 896])
+def test_amax_of_every_last_stage(H):
+    c = fp8_case(seed=7900 + H, H=H, F=2816, E=8, counts=[64, 20, 100, 33, 64, 1, 128, 190])
+    for form in FORMS:
+        for _ in range(3):
+            check_fp8(c, 20 + form)
