@@ -18,8 +18,12 @@
 // behind); eight waves on 256 x 128, three stages (134 -> 127, but 49 -> 73 where tiles fall badly).
 //
 // fp32 layers run here on the bf16 matrix instruction, the fp32 one having 1/16 of its rate.  An fp32 value is the sum of three
-// bf16 values (8 bits of significand each: a0 = bf16(a), a1 = bf16(a - a0), a2 = a - a0 - a1, all exact), so a product of two is
-// nine bf16 products, of which the three smallest (2^-26 of the largest and less) are left out: six instead of sixteen times the
+// bf16 values (8 bits of significand each: a0 = bf16(a), a1 = bf16(a - a0), a2 = a - a0 - a1; the splitting of Henry, Tang and
+// Heinecke, "Leveraging the bfloat16 artificial intelligence datatype for higher-precision computations", 2019).  The parts are exact
+// from 2^-110 on.  Below, they end at the smallest bf16 number, 2^-133, and an operand is up to 2^-134 off (2.6e-6 of it at 1e-35, 2.7e-4 at
+// 1e-37; below 2^-134 it counts as zero).  That is less than 2^-24 of any result from 2^-80 on, as long as the magnitudes in its two
+// rows add up to less than 2^30; smaller results are taken with the fp32 instruction once more, like those that are infinite or NaN.
+// A product of two values is nine bf16 products, of which the three smallest (2^-26 of the largest and less) are left out: six instead of sixteen times the
 // work.  The largest product, a0 b0, has an accumulator of its own; the five others, 2^-8 of it and less, share a second one that
 // is added at the end, so a sum is rounded once per 16 terms: the results are nearer to 64 bits than those of the fp32 instruction
 // (relative 2-norm, fp32 instruction / here: 256 terms 2.1e-7 to 4.2e-7 / 1.4e-7, 800 terms 7.6e-7 / 2.5e-7, 1500 terms 6.9e-7 /
@@ -41,7 +45,12 @@ struct Split {
     bf16x8 p[3];
 };
 
-// Eight values into their three parts.  (Infinities and NaN leave NaN in the second part: see `finite` below.)
+// Whether a sum of products of parts stands: not if it is infinite or NaN, nor below 2^-80, unless it is zero.
+constexpr uint32_t kInfinity2 = 0xff000000u, kSmall2 = (127u - 80u) << 24;   // bits without the sign, twice
+__device__ __forceinline__ uint32_t above_small(float v) { return (__float_as_uint(v) << 1) - kSmall2; }   // below: wraps, like a zero
+__device__ __forceinline__ bool holds(float v) { return above_small(v) < kInfinity2 - kSmall2 || v == 0.f; }
+
+// Eight values into their three parts.  (Infinities and NaN leave NaN in the second part: see `holds`.)
 __device__ __forceinline__ Split split8(u32x4 lo, u32x4 hi) {
     u32x4 out[3];
 #pragma unroll
@@ -309,33 +318,37 @@ __global__ __launch_bounds__(KB * KS * WGM * WGN * 64, ELT == kStreamF32 && FM *
         if (kg > 0 || idle) return;
     if (ELT != kStreamFp8 || MODE != 1 || (kg == 0 && !idle)) {
         if constexpr (ELT == kStreamF32) {
-            bool finite = true;
 #pragma unroll
             for (int i = 0; i < FM; ++i)
 #pragma unroll
-                for (int j = 0; j < FN; ++j)
+                for (int j = 0; j < FN; ++j) {
+                    // all at once, without zeros (each value in turn costs a product 2 %: down of 16 experts x 1024 rows, 800 x 1500 261 / 265 us)
+                    uint32_t worst = 0;
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) finite = finite && fabsf(acc[i][j][v]) < INFINITY;
-            if (!__all(finite)) {
-                // An infinity or a NaN among the operands (its parts cannot be told apart), or a sum past the largest number: the
-                // fp32 matrix instruction on the same rows says which of the results are infinite.
+                    for (int v = 0; v < 16; ++v) worst = max(worst, above_small(acc[i][j][v]));
+                    if (__all(worst < kInfinity2 - kSmall2)) continue;
+                    bool all = true;
 #pragma unroll
-                for (int i = 0; i < FM; ++i)
+                    for (int v = 0; v < 16; ++v) all = all && holds(acc[i][j][v]);
+                    if (__all(all)) continue;
+                    // An infinity or a NaN among the operands (its parts cannot be told apart), a sum past the largest number, or one
+                    // so small that its operands may have lost bits: the fp32 matrix instruction on the same rows has the result.  The other
+                    // values of the block keep theirs.  The loads follow one another, so a block that is done again takes several times
+                    // as long (us, none / a NaN in one row / in one row of 128 / all rows tiny: the product above 262 / 456 / 810 / 1500;
+                    // 16 experts x 32 rows 21 / 156 / 159 / 160).
+                    f32x16 c;
 #pragma unroll
-                    for (int j = 0; j < FN; ++j) {
-                        f32x16 c;
+                    for (int v = 0; v < 16; ++v) c[v] = 0.f;
+                    for (uint32_t k = 0; k < kb; k += 16) {
+                        const u32x2 x = *(const __attribute__((address_space(1))) u32x2*)(ga[i] + k + 8 * h);
+                        const u32x2 w = *(const __attribute__((address_space(1))) u32x2*)(gb[j] + k + 8 * h);
 #pragma unroll
-                        for (int v = 0; v < 16; ++v) c[v] = 0.f;
-                        for (uint32_t k = 0; k < kb; k += 16) {
-                            const u32x2 x = *(const __attribute__((address_space(1))) u32x2*)(ga[i] + k + 8 * h);
-                            const u32x2 w = *(const __attribute__((address_space(1))) u32x2*)(gb[j] + k + 8 * h);
-#pragma unroll
-                            for (int e = 0; e < 2; ++e)
-                                c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(w[e]), __uint_as_float(x[e]), c, 0, 0, 0);
-                        }
-                        acc[i][j] = c;
+                        for (int e = 0; e < 2; ++e)
+                            c = __builtin_amdgcn_mfma_f32_32x32x2f32(__uint_as_float(w[e]), __uint_as_float(x[e]), c, 0, 0, 0);
                     }
-            }
+#pragma unroll
+                    for (int v = 0; v < 16; ++v) acc[i][j][v] = holds(acc[i][j][v]) ? acc[i][j][v] : c[v];
+                }
         }
 #pragma unroll
         for (int i = 0; i < FM; ++i) {

@@ -92,3 +92,32 @@ def test_chosen_form_keeps_the_results_of_the_fp32_instruction():
             h, y = _run(x_perm, offsets, inp, 0)
             assert_close(h, h_ref, False, "h")
             assert_close(y, y_ref, False, "y_perm")
+
+
+@pytest.mark.parametrize("form", range(5))
+def test_operands_below_what_their_parts_can_hold(form):
+    """Rows and weights whose third bf16 part is below the smallest bf16 number (from some 1e-33 down): the results keep the bits of
+    fp32, and the rows beside them keep their own."""
+    import torch
+    import paper_2504_14960_amd as moe
+    rng = np.random.default_rng(6)
+    R, H, F = 80, 96, 48
+    h = rng.standard_normal((2 * R, F)).astype(np.float32)
+    wd = rng.standard_normal((2, H, F)).astype(np.float32)
+    wd[1] *= np.float32(1e-36)                      # the second expert: tiny weights
+    tiny = {3: 1e-32, 8: 1e-33, 20: 1e-34, 33: 1e-35, 64: 1e-36, 79: 3e-37}
+    plain, off = h.copy(), to_dev(np.array([0, R, 2 * R], np.int32))
+    for r, s in tiny.items():
+        h[r] *= np.float32(s)
+    moe.set_option("gemm_stream", 20 + form)
+    got = []
+    for rows in (h, plain):
+        y = torch.empty((2 * R, H), dtype=torch.float32, device="cuda")
+        moe.expert_down(to_dev(rows), off, to_dev(wd), y)
+        got.append(to_host(y))
+    ref = np.concatenate([h[e * R:(e + 1) * R].astype(np.float64) @ wd[e].T.astype(np.float64) for e in range(2)])
+    for r in list(tiny) + list(range(R, 2 * R)):
+        # sums of 48 terms in fp32: sqrt(48) * 6e-8 = 4e-7
+        assert np.linalg.norm(got[0][r] - ref[r]) <= 1e-6 * np.linalg.norm(ref[r]), r
+    others = [r for r in range(R) if r not in tiny]
+    np.testing.assert_array_equal(got[0][others], got[1][others])
