@@ -800,12 +800,15 @@ TileForms tile_forms(int elt, bool odd) {
     return {kTilesBf16, 4};
 }
 
-double small_tiles_us(const Work& w, const TileForm& f) {
+double small_tiles_per_cu(const Work& w, const TileForm& f) {
     constexpr double kSpread[8] = {0.386, 0.552, 0.717, 0.883, 1.048, 1.214, 1.434, 1.766};   // as large_us
     double mt = 0.0;
     for (const double x : kSpread) mt += w.experts / 8.0 * (double)(long long)((w.rows * x + f.rows - 1e-6) / f.rows);
     mt = 0.5 * (mt + (double)w.experts * blocks_of(w.rows, f.rows));
-    const double per_cu = mt * blocks_of(w.N, w.swiglu ? f.weights / 2 : f.weights) / kUnitsCU;
+    return mt * blocks_of(w.N, w.swiglu ? f.weights / 2 : f.weights) / kUnitsCU;
+}
+
+double small_tiles_us(const Work& w, const TileForm& f, double per_cu) {
     const double mul = (per_cu <= f.fill ? 1.0 : per_cu + f.more) * (f.round + f.block * blocks_of(w.kbytes, 128) / f.blocks);
     const double mem = (double)w.experts * w.N * (w.swiglu ? 2 : 1) * w.kbytes / (f.stream * 1e6);
     return f.start + pow(pow(mul, f.power) + pow(mem, f.power), 1.0 / f.power);
@@ -850,14 +853,23 @@ StreamPlan plan_stream(int elt, int r_max, int E, int N, int K, bool swiglu, boo
         return plan;
     }
     // A form is taken where it is ahead by more than a part of what the estimates are off by: more for gate/up of odd sizes, whose silu
-    // they do not count, less for the fifth form of the odd sizes, whose estimate does.  (Of 572 odd products, 1 to 64 experts, 17 to
-    // 800 rows per expert, 256 to 6144 wide, 135 go to that form, 15 % faster than what they went to before; seven are slower by
-    // more than 3 %, one by 27: 64 experts x 122 rows, 4536 x 528.)
+    // they do not count, less for the fifth form of the odd sizes, whose estimate does.
+    // The forms with one workgroup to a compute unit are estimated too low from the second round on, by up to two times (64 experts x 502
+    // rows, 816 x 3568 gate/up, 128 x 128: 456 / 908).  In FP8, and in odd sizes, which have a form for many rounds, they are taken where
+    // they come to one round (counting 5 % more, for what the experts differ): there one of them is within 2 % of the best kernel for
+    // most products, with more rounds for 1 in 20.  Compared with the choice among the other kernels alone, slower by more than 3 % / 10 %
+    // (without this line): of 400 odd products, 4 to 16 experts, 256 to 2048 wide, 38 / 12 (39 / 16 of 520 others), 11 % faster on average; of
+    // 376, 1 to 64 experts, 256 to 6144 wide, 54 / 14 (95 / 66 of 560 others), 11 %; of 262 in FP8 9 / 2 (16 / 11 of 458), 4 %.  The
+    // worst are behind by a third: few experts or a skewed router, whose tiles spill into a second round.  In bf16 the line would
+    // change nothing, the large tiles being ahead there by their estimate.
+    auto rounds_fit = [&](int f, double per_cu) { return !(w.odd || w.fp8) || f == 4 || per_cu <= 1.05; };
     auto margin = [&](int f) { return elt == kEltF32 ? 1.0 : !w.odd ? 1.1 : f == 4 ? 1.05 : swiglu ? 1.25 : 1.1; };
     int form = 0;
     double form_us = 1e30;
     for (int f = 0; f < small.count; ++f) {
-        const double t = margin(f) * small_tiles_us(w, small.form[f]);
+        const double per_cu = small_tiles_per_cu(w, small.form[f]);
+        if (!rounds_fit(f, per_cu)) continue;
+        const double t = margin(f) * small_tiles_us(w, small.form[f], per_cu);
         if (t < form_us) {
             form_us = t;
             form = f;
