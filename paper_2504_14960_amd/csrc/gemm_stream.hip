@@ -984,18 +984,34 @@ int plan_pair(int elt, const StreamPlan& routed, int r_max, int E, int N, int K,
     // What the second launch costs are its first and last microseconds, an end of the first one in which compute units stand idle, and
     // partial sums (us of the layer, one after the other / so: 3 tokens, 32 experts, 1152 x 1280, shared 2112 48 / 36; one token, 32,
     // 6144 x 768, 17152 183 / 152; 27 tokens, 64, 1024 x 2176, 6144 123 / 99; 42 tokens, 16, 7040 x 4352, 14080 723 / 663).
+    // The figures below: 731 layers of 2 to 64 experts, 1024 to 6336 x 512 to 8192, shared 512 to 20288, each product of each width
+    // paired alone, per layer against one after the other.
     if (swiglu) {
-        // Workgroups of the same length, so the two lists become one; as wide as the tokens ask for.  64 tokens on 64 experts, 3584 x
-        // 2560, with 20480 more take 7 us longer so: 5.0 rounds of routed workgroups become 5.6, and 64 rows suit the wide kernel.
-        const int fbs = r_max <= 16 ? 2 : tokens <= 16 ? 4 : 8, fb = narrow_blocks(r_max, E, N, true);
+        // Workgroups of the same length, so the two lists become one; as wide as the tokens ask for (paired always: 1 to 16 tokens 0.940 /
+        // 0.953 / 0.957 of the time with 2 / 4 / 8 blocks, 17 to 48 0.996 / 0.985 / 0.991, 65 to 128 1.011 / 0.997 / 0.992).  Where all of
+        // them find a place at once in narrower ones, an eight-block one would only last longer: 20 tokens, 4 experts, 3712 x 960, with
+        // 2112 65 one after the other, 59 / 64 / 78; 121 tokens, 8, 3968 x 704, 2752 93, 87 / 92 / 107.
+        const int fb = narrow_blocks(r_max, E, N, true), slots = 2 * kUnitsCU;
         const int experts = E < r_max ? E : r_max, rows = (r_max + experts - 1) / experts;
-        const double own = (double)experts * blocks_of(rows, 128) * blocks_of(N, 8 * fb), more = blocks_of(sN, 8 * fbs) * (double)fbs / fb;
-        const double both = fmax(1.0, (own + more) / (2 * kUnitsCU)) / fmax(1.0, own / (2 * kUnitsCU));
+        const double own = (double)experts * blocks_of(rows, 128) * blocks_of(N, 8 * fb);
+        int fbs = r_max <= 16 ? 2 : tokens <= 16 ? 4 : 8;
+        if (tokens > 16)
+            while (fbs > 2 && fbs / 2 >= fb && own + blocks_of(sN, 4 * fbs) <= slots) fbs /= 2;
+        const double more = blocks_of(sN, 8 * fbs) * (double)fbs / fb;
+        const double both = fmax(1.0, (own + more) / slots) / fmax(1.0, own / slots);
+        // More tokens take the wide kernel further ahead alone.  64 tokens on 64 experts, 3584 x 2560, with 20480 more take 7 us longer
+        // so: 5.0 rounds of routed workgroups become 5.6.  332 layers of 17 to 128 tokens take 2.8 % less on average, 47 of them more than
+        // 1 % longer, 27 more than 3 %, the worst 12 %: few experts whose workgroups leave half the chip idle, and a long shared
+        // product, whose rows suit the wide kernel.  Factors of 0.9 to 1.04 pair the same layers; from 1.06 on gains are lost before losses.
         return (tokens <= 48 ? 0.98 : tokens <= 64 ? 1.04 : 1.1) * routed.us * both < routed.us + shared.us + 4.0 ? fbs : 0;
     }
     // The shared expert's contraction is the longer one, and one of its workgroups takes so long for it, beside the others (us for 128
     // bytes: 0.1 with both operands straight to registers; else the more the fewer stages of the rows the ring holds).  It should end
-    // with the routed experts' and have its own weights to read as well.
+    // with the routed experts' and have its own weights to read as well.  (Half of the shared product's time: 1 to 16 tokens 0.972 of
+    // the time, 12 of 141 layers slower by more than 1 %, the worst by 7; none of it 0.977, 4, 4; paired always 0.978, 30, 18.  17 to 48
+    // tokens 0.981, 7 of 202, 7 / 0.983, 3, 4 / 0.996, 60, 23; more tokens 0.995, 1 of 144, 2 / 0.995, 1, 2 / 1.119, 92, 99.)
+    // Four blocks where the output is wide enough for as many workgroups as with two: above 16 tokens, from 5632 columns on, where
+    // pairing gains 1.6 % with four and 0.9 % with two, below 0.3 % and 1.4 %.
     const double serial = blocks_of(2 * sK, 128) * (tokens <= 16 ? 0.11 : fmax(0.2, 0.0115 * tokens));
     return serial <= routed.us + 0.5 * shared.us ? (tokens > 16 && sN >= 5632 ? 4 : 2) : 0;
 }
