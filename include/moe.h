@@ -551,7 +551,8 @@ moe_status_t moe_gemm_clock_sample(uint64_t* ticks);
  * 2, 4, 8 or 16 parts; 2000 + S = the large tiles, and where there is room the contraction in S = 2 to
  * 16 parts); "gemm_pair" (the shared expert's two products in one launch each with the routed experts', where both are
  * read as streams of weights and up to 128 tokens: -1, the default = chosen by size; else 10 G + D with G, D = 0 (never), 2, 4 or 8 times
- * 16 weight rows per workgroup of the shared expert's gate/up and down); "fp8_deep_weights" (FP8 expert GEMMs: 1, the default = three LDS stages for
+ * 16 weight rows per workgroup of the shared expert's gate/up and down: 2 with up to 16 rows in all, else the nearest of 8, 4 and,
+ * beside routed workgroups of 2, 2 for gate/up, of 4 and 2 for down); "fp8_deep_weights" (FP8 expert GEMMs: 1, the default = three LDS stages for
  * the weight tile, 0 = for the activation tile); "gemm_workgroups" (workgroups launched by the
  * persistent grouped-GEMM kernels; 0 = one per compute unit, values below 8
  * are raised to 8); "gemm_tile_rows" (rows of the tiles of the persistent expert kernels,

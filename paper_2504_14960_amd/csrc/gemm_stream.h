@@ -26,7 +26,7 @@ size_t stream_part_bytes(int elt, int r_max, int E, int N, int K, bool swiglu, b
 // C [rows, N] in bf16 from the partial planes [splits][r_max][N, or 2 N: gate and up] fp32, added in split order
 void launch_stream_reduce(bool swiglu, const float* part, const int32_t* offsets, int E, int splits, int r_max, int N, void* C,
                           hipStream_t s);
-// Weight blocks per workgroup (2, 4 or 8) of the shared expert's product (`tokens` rows) in one narrow launch with the routed
+// Weight blocks per workgroup (2, 4 or 8, see launch_stream_pair) of the shared expert's product (`tokens` rows) in one narrow launch with the routed
 // experts', or 0: one after the other
 int plan_pair(int elt, const StreamPlan& routed, int r_max, int E, int N, int K, const StreamPlan& shared, int tokens, int sN, int sK,
               bool swiglu);
@@ -34,7 +34,8 @@ int plan_pair(int elt, const StreamPlan& routed, int r_max, int E, int N, int K,
 void launch_stream_pair(int blocks, const void* A, const int32_t* offsets, int r_max, int E, int N, int K, const void* B0, const void* B1,
                         void* C, const void* sA, const int32_t* s_offsets, int tokens, int sN, int sK, const void* sB0, const void* sB1,
                         void* sC, hipStream_t s);
-// -1 (default): by size; else 10 G + D: G weight blocks for gate/up and D for down (0: never, 2, 4 or 8) where they can be paired
+// -1 (default): by size; else 10 G + D: G weight blocks for gate/up and D for down (0: never, 2, 4 or 8, or the nearest that is built)
+// where they can be paired
 void set_pair_blocks(int v);
 // -1 (default): by size; 0: only the shapes no other kernel takes; 1: always the narrow, 2: always the wide form.  10 + FB:
 // narrow with FB (1, 2, 4, 8) blocks of 16 weight rows per workgroup (2 for 1 with SwiGLU; 2 or 4 for at most 16 rows in

@@ -980,7 +980,7 @@ int plan_pair(int elt, const StreamPlan& routed, int r_max, int E, int N, int K,
     // expert's rows would need one.
     if (r_max <= 16 && tokens > 16) return 0;
     const int forced = g_pair_blocks < 0 ? -1 : swiglu ? g_pair_blocks / 10 : g_pair_blocks % 10;
-    if (forced >= 0) return r_max <= 16 && forced == 8 ? 4 : forced;
+    if (forced >= 0) return forced;
     // What the second launch costs are its first and last microseconds, an end of the first one in which compute units stand idle, and
     // partial sums (us of the layer, one after the other / so: 3 tokens, 32 experts, 1152 x 1280, shared 2112 48 / 36; one token, 32,
     // 6144 x 768, 17152 183 / 152; 27 tokens, 64, 1024 x 2176, 6144 123 / 99; 42 tokens, 16, 7040 x 4352, 14080 723 / 663).
@@ -1027,14 +1027,24 @@ void launch_stream_pair(int blocks, const void* A, const int32_t* offsets, int r
         constexpr int MODE = decltype(mode)::value, FB = decltype(own)::value;
         if constexpr (FB <= 4) {
             if (direct) {
-                if (blocks == 4) launch_pair<MODE, FB, 4, true>(p, q, r_max, s);
-                else launch_pair<MODE, FB, 2, true>(p, q, r_max, s);
+                launch_pair<MODE, FB, 2, true>(p, q, r_max, s);
                 return;
             }
         }
-        if (blocks == 8) launch_pair<MODE, FB, 8, false>(p, q, r_max, s);
-        else if (blocks == 4) launch_pair<MODE, FB, 4, false>(p, q, r_max, s);
-        else launch_pair<MODE, FB, 2, false>(p, q, r_max, s);
+        // the widths that plan_pair chooses: gate/up eight, four, or two beside two; down four or two
+        if constexpr (MODE == 1) {
+            if (blocks == 8) {
+                launch_pair<MODE, FB, 8, false>(p, q, r_max, s);
+                return;
+            }
+        }
+        if constexpr (MODE == 0 || FB == 2) {
+            if (blocks == 2) {
+                launch_pair<MODE, FB, 2, false>(p, q, r_max, s);
+                return;
+            }
+        }
+        launch_pair<MODE, FB, 4, false>(p, q, r_max, s);
     };
     auto width = [&](auto mode) {
         if (fb == 8) go(mode, std::integral_constant<int, 8>{});
