@@ -291,8 +291,7 @@ moe_status_t moe_sort_chunks(const void* src, int R_src, const int32_t* chunk_ro
 static moe_status_t expert_ffn(const char* fn, int phase, const void* x_perm,
                                const int32_t* expert_offsets, int R_max, int H, int F, int E,
                                const void* w_gate, const void* w_up, const void* w_down,
-                               moe_dtype_t dt, void* h, void* y_perm, moe_stream_t stream,
-                               void* part = nullptr, size_t part_bytes = 0) {
+                               moe_dtype_t dt, void* h, void* y_perm, moe_stream_t stream) {
     if (dt != MOE_F32 && dt != MOE_BF16) return fail(MOE_ERR_INVALID_ARG, "%s: unknown dtype %d", fn, (int)dt);
     if (R_max < 0 || H <= 0 || F <= 0 || E <= 0)
         return fail(MOE_ERR_INVALID_ARG, "%s: need R_max >= 0 and H, F, E > 0", fn);
@@ -313,7 +312,7 @@ static moe_status_t expert_ffn(const char* fn, int phase, const void* x_perm,
         REQUIRE_PTR(fn, y_perm);
     }
     if (!launch_expert_ffn(x_perm, expert_offsets, R_max, H, F, E, w_gate, w_up, w_down, dt, h, y_perm,
-                           g_gemm_variant, phase, part, part_bytes, static_cast<hipStream_t>(stream)))
+                           g_gemm_variant, phase, nullptr, 0, static_cast<hipStream_t>(stream)))
         return fail(MOE_ERR_UNSUPPORTED, "%s: no kernel for H=%d F=%d", fn, H, F);
     return check_launch(fn);
 }
