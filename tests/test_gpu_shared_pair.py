@@ -1,5 +1,5 @@
-"""The shared expert's products in one launch with the routed experts': every pair of workgroup widths, row counts at the edges of
-the narrow kernel's forms, and the same bits for the routed experts as without."""
+"""The shared expert's products in one launch with the routed experts': every pair of workgroup widths that the option takes, row counts
+at the edges of the narrow kernel's forms, fewer routed rows than tokens, and the same bits for the routed experts as without."""
 import pytest
 
 from helpers import assert_close, guard_margins, to_dev, to_host
