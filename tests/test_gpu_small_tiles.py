@@ -104,3 +104,17 @@ def test_amax_of_every_last_stage(H):
     for form in FORMS:
         for _ in range(3):
             check_fp8(c, 20 + form)
+
+
+# the forms chosen by size on both sides of one round of workgroups (256 compute units), in odd sizes and FP8
+@pytest.mark.parametrize("F", [1000, 1992, 3192, 3400, 6504])
+def test_chosen_form_around_one_round(F):
+    inp, x_perm, offsets, h_ref, y_ref = bf16_case(H=264, F=F, E=8, counts=[64, 20, 100, 33, 64, 1, 128, 90], seed=8000 + F)
+    h, y = bf16_run(x_perm, offsets, inp, 0)
+    assert_close(h, h_ref, True, "h")
+    assert_close(y, y_ref, True, "y_perm")
+
+
+@pytest.mark.parametrize("F", [1408, 2816, 3328, 6656])
+def test_chosen_form_around_one_round_in_fp8(F):
+    check_fp8(fp8_case(seed=8100 + F, H=512, F=F, E=8, counts=[64, 20, 100, 33, 64, 1, 128, 90]), -1)
