@@ -1,11 +1,28 @@
 // Grouped expert GEMM (a3), persistent kernel: one workgroup per compute unit
 // walks a static list of output tiles and treats their k-tiles as ONE stream.
 //
-// Same tile engine as gemm_pipe3.hip (256 x 256 x 64 tiles, direct global->LDS
-// loads spread in source order between the MFMA groups, one barrier per
-// k-tile), with the three LDS stages given to the weight tile and two to the
-// activation tile, and with tiles of 256, 192 or 128 rows (pick_height).  What
-// changes further is what happens at a tile boundary:
+// Tiles of 256, 192 or 128 rows (pick_height) x 256 columns, k-tiles of 64
+// elements through LDS: direct global->LDS loads spread in source order between
+// the matrix instructions, one barrier per k-tile, three LDS stages for the
+// weight tile and two for the activation tile.
+//
+// What bounds it with many rows per expert is power: the clock settles at what
+// the board allows, and the time is the energy of a tile.  So the matrix
+// instruction is the 16x16x32 one, which adds a contraction of 32 to its
+// accumulators where 32x32x16 adds one of 16 (half the accumulator traffic; the
+// bare loop over workload-like operands in LDS: 1955 against 1785 TFLOP/s), and
+// four waves of 128 x 128 share a tile, not eight of 128 x 64 (a third fewer LDS
+// bytes per k-tile).  With one wave per SIMD nothing covers what stands between
+// two matrix instructions, so the k loop holds little else: 128 of them, 32
+// fragment reads, 16 loads and 27 scalar and vector instructions per k-tile, the
+// sources of the loads kept from k-tile to k-tile.  Measured, gate/up and down, us,
+// eight waves of 32x32x16 / this: 8 experts of 16384 rows, 6144 x 16384, 5200 and
+// 2700 / 4850 and 2435 (1.36 PFLOP/s each); 8 x 4096 rows, 6144 x 2048, 1310 and 686 /
+// 1168 and 627; 64 skewed experts of 82000 rows, 4096 x 1408, 1663 and 919 / 1480
+// and 836.  Eight waves with the 16x16x32 instruction: 5110 and 2694, 1255 and 672,
+// 1668 and 914.
+//
+// What happens at a tile boundary:
 //
 //  * the loads issued during the last two k-tiles of a tile already fetch the
 //    first two k-tiles of the workgroup's NEXT tile, so the pipeline never
@@ -51,11 +68,11 @@ int persist_grid() {
 
 namespace {
 
-// Epilogue through LDS.  For fragment row block i the wave writes its 32 x
-// (32*FO) bf16 outputs (8 bytes per lane per store: row l%32, 4 consecutive
-// columns) into a private patch of W = 64*FO bytes per row, 16-byte granules
-// XOR-swizzled by the row so that neither side has bank conflicts, reads them
-// back as whole 16-byte granules along the rows and stores those.
+// Epilogue through LDS.  Two fragment row blocks at a time the wave writes its
+// 32 x (16*FO) bf16 outputs (8 bytes per lane per store: row l%16 of a block, 4
+// consecutive columns) into a private patch of W = 32*FO bytes per row, 16-byte
+// granules XOR-swizzled by the row so that neither side has bank conflicts, reads
+// them back as whole 16-byte granules along the rows and stores those.
 //
 // MODE 0: C = acc.  MODE 1: C = silu(gate) * up, the gate in the first half of
 // the fragments and the up projection in the second.  MODE 2: as 1, and the
@@ -64,12 +81,12 @@ namespace {
 // STREAM_OUT (weight gradients of few rows per expert): the output is as many bytes as the operands' panels that the next tiles
 // find in the L2, and nobody reads it soon, so it is streamed past them.
 template <int FM, int FN, int WM, int MODE, bool ACC_IN_AGPR, bool STREAM_OUT>
-__device__ __forceinline__ void store_tile_staged(f32x16 (&acc)[FM][FN], int t_row0, int t_rows, int t_n0,
+__device__ __forceinline__ void store_tile_staged(f32x4 (&acc)[FM][FN], int t_row0, int t_rows, int t_n0,
                                                   bf16_t* __restrict__ C, bf16_t* __restrict__ GU, int N, int wm,
                                                   int wn, int lane, uint8_t* stage) {
     constexpr bool SWIGLU = MODE == 1 || MODE == 2;
     constexpr int FO = SWIGLU ? FN / 2 : FN;
-    constexpr int W = FO * 64;        // bytes per staged row
+    constexpr int W = FO * 32;        // bytes per staged row
     constexpr int GPR = W / 16;       // granules per row
     constexpr int RP256 = 256 / W;    // rows per 256 bytes (one pass over all banks)
     constexpr int RPI = 1024 / W;     // rows per 64-lane read
@@ -78,23 +95,25 @@ __device__ __forceinline__ void store_tile_staged(f32x16 (&acc)[FM][FN], int t_r
     // the lane id keeps them from being hoisted out of the tile loop, where they
     // would occupy registers across the whole k loop
     asm volatile("" : "+v"(lane));
-    const int fr = lane & 31, fk = lane >> 5;
+    const int fr = lane & 15, fk = lane >> 4;
+    static_assert((16 / RP256) % GPR == 0, "both row blocks of a patch have the same swizzle");
     const int xw = (fr / RP256) & (GPR - 1);
-    uint8_t* wrow = stage + fr * W + 8 * fk;
+    uint8_t* wrow = stage + fr * W + 8 * (fk & 1);
+    const int gw = fk >> 1;           // a fragment is two granules wide
     const int rl = lane / GPR, gl = lane % GPR;
-    const int col = t_n0 + wn * (FO * 32) + gl * 8;
+    const int col = t_n0 + wn * (FO * 16) + gl * 8;
     const uint32_t pitch = (uint32_t)N * 2u;
     const uint32_t c_off = col < N ? (uint32_t)rl * pitch + (uint32_t)col * 2u : kNoColumn;   // STREAM_OUT
 #pragma unroll
-    for (int i = 0; i < FM; ++i) {
-        // one row block at a time.  With 256 accumulators per lane they live in
+    for (int i = 0; i < FM / 2; ++i) {
+        // 32 rows at a time.  With 256 accumulators per lane they live in
         // the accumulation registers; naming them there once more per block keeps
         // the copies into ordinary registers from being made all at once, which
         // would push the loop's long-lived values out to scratch memory
         __builtin_amdgcn_sched_barrier(0);
         if (ACC_IN_AGPR) {
 #pragma unroll
-            for (int j = 0; j < FN; ++j) asm volatile("" : "+a"(acc[i][j]));
+            for (int j = 0; j < FN; ++j) asm volatile("" : "+a"(acc[2 * i][j]), "+a"(acc[2 * i + 1][j]));
         }
         if (MODE == 2) {
             // the pre-activations first: gate half, then up half, each through the same patch
@@ -103,12 +122,12 @@ __device__ __forceinline__ void store_tile_staged(f32x16 (&acc)[FM][FN], int t_r
 #pragma unroll
                 for (int j = 0; j < FO; ++j) {
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) {
-                        const f32x16& a = acc[i][j + half * FO];
+                    for (int q = 0; q < 2; ++q) {
+                        const f32x4& a = acc[2 * i + q][j + half * FO];
                         u32x2 o;
-                        o[0] = pack2_bf16(a[4 * q], a[4 * q + 1]);
-                        o[1] = pack2_bf16(a[4 * q + 2], a[4 * q + 3]);
-                        *reinterpret_cast<u32x2*>(wrow + (((4 * j + q) ^ xw) << 4)) = o;
+                        o[0] = pack2_bf16(a[0], a[1]);
+                        o[1] = pack2_bf16(a[2], a[3]);
+                        *reinterpret_cast<u32x2*>(wrow + q * (16 * W) + (((2 * j + gw) ^ xw) << 4)) = o;
                     }
                 }
 #pragma unroll
@@ -126,22 +145,22 @@ __device__ __forceinline__ void store_tile_staged(f32x16 (&acc)[FM][FN], int t_r
 #pragma unroll
         for (int j = 0; j < FO; ++j) {
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
+            for (int q = 0; q < 2; ++q) {
                 float v[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     if (SWIGLU) {
-                        const float g = acc[i][j][4 * q + u];
-                        const float up = acc[i][j + FO][4 * q + u];
+                        const float g = acc[2 * i + q][j][u];
+                        const float up = acc[2 * i + q][j + FO][u];
                         v[u] = g * __builtin_amdgcn_rcpf(1.f + __expf(-g)) * up;  // silu(g) * up
                     } else {
-                        v[u] = acc[i][j][4 * q + u];
+                        v[u] = acc[2 * i + q][j][u];
                     }
                 }
                 u32x2 o;
                 o[0] = pack2_bf16(v[0], v[1]);
                 o[1] = pack2_bf16(v[2], v[3]);
-                *reinterpret_cast<u32x2*>(wrow + (((4 * j + q) ^ xw) << 4)) = o;
+                *reinterpret_cast<u32x2*>(wrow + q * (16 * W) + (((2 * j + gw) ^ xw) << 4)) = o;
             }
         }
         __builtin_amdgcn_sched_barrier(0);
@@ -212,25 +231,22 @@ __device__ __forceinline__ void store_tile_staged(f32x16 (&acc)[FM][FN], int t_r
 
 // Partial sums as they are, [rows, N] or, gate and up, [rows, 2 N] fp32: a lane holds one row and four columns at a time.
 template <int FM, int FN, int WM, int WN, bool SWIGLU>
-__device__ __forceinline__ void store_partial(f32x16 (&acc)[FM][FN], int t_row0, int t_rows, int t_n0, float* __restrict__ part,
+__device__ __forceinline__ void store_partial(f32x4 (&acc)[FM][FN], int t_row0, int t_rows, int t_n0, float* __restrict__ part,
                                               int N, int wm, int wn, int lane) {
     asm volatile("" : "+v"(lane));   // see store_tile_staged
-    const int fr = lane & 31, fk = lane >> 5;
+    const int fr = lane & 15, fk = lane >> 4;
     constexpr int FO = SWIGLU ? FN / 2 : FN;
     const int pitch = SWIGLU ? 2 * N : N;
 #pragma unroll
     for (int i = 0; i < FM; ++i) {
-        const int row = wm * WM + i * 32 + fr;
+        const int row = wm * WM + i * 16 + fr;
         if (row >= t_rows) continue;
         float* const prow = part + (size_t)(t_row0 + row) * pitch;
 #pragma unroll
-        for (int j = 0; j < FN; ++j)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int col = t_n0 + wn * (FO * 32) + (j % FO) * 32 + 8 * q + 4 * fk;
-                const f32x4 v = {acc[i][j][4 * q], acc[i][j][4 * q + 1], acc[i][j][4 * q + 2], acc[i][j][4 * q + 3]};
-                if (col < N) *reinterpret_cast<f32x4*>(prow + (j >= FO ? N : 0) + col) = v;
-            }
+        for (int j = 0; j < FN; ++j) {
+            const int col = t_n0 + wn * (FO * 16) + (j % FO) * 16 + 4 * fk;
+            if (col < N) *reinterpret_cast<f32x4*>(prow + (j >= FO ? N : 0) + col) = acc[i][j];
+        }
     }
 }
 
@@ -252,7 +268,7 @@ __device__ __forceinline__ void store_partial(f32x16 (&acc)[FM][FN], int t_row0,
 // ahead) and two stages for the weight tile; true: the other way round -- the weights are what streams in from
 // HBM (every weight byte is used by one M-group only), the activation panels are re-read from the caches.
 template <int BM, int BN, int WGM, int WGN, int MODE, bool GROUPK, bool KMAJ, bool IDLE_SKIP, bool DEEP_B, bool BY_ROUND,
-          bool STREAM_OUT, bool AHEAD, bool SPLIT>
+          bool STREAM_OUT, bool SPLIT>
 __device__ __forceinline__ void persist_body(
     const bf16_t* __restrict__ A, const int32_t* __restrict__ offsets, int E, int N, int K,
     const bf16_t* __restrict__ B0, const bf16_t* __restrict__ B1, bf16_t* __restrict__ C, bf16_t* __restrict__ GU,
@@ -266,45 +282,40 @@ __device__ __forceinline__ void persist_body(
     constexpr int NW = WGM * WGN;
     constexpr int NT = NW * 64;
     constexpr int WM = BM / WGM, WN = BN / WGN;
-    constexpr int FM = WM / 32, FN = WN / 32;
+    constexpr int FM = WM / 16, FN = WN / 16;
     constexpr int CPR = BK / 8;
     constexpr int RPP = NT / CPR;               // tile rows fetched per pass of the workgroup
     constexpr int PA = BM / RPP, PB = BN / RPP;
+    constexpr int PBD = SWIGLU ? PB / 2 : PB;   // passes of one weight matrix
     constexpr int ROWB = BK * 2;
     constexpr int A_BYTES = BM * ROWB, B_BYTES = BN * ROWB;
     constexpr int B_REGION = (DEEP_B ? 2 : 3) * A_BYTES;   // the activation slots, then the weight slots
-    // "early" operand: two slots, fetched one k-tile ahead, issued first in a period; "late" operand: three
-    // slots, fetched two k-tiles ahead
+    // "early" operand: two slots, a k-tile fetched as soon as the slot is read, behind the barrier of the period before;
+    // "late" operand: three slots, fetched half a period earlier
     constexpr int PE = DEEP_B ? PA : PB, PL = DEEP_B ? PB : PA;
     constexpr int OUTN = SWIGLU ? BN / 2 : BN;
-    constexpr int NLOAD = PA + PB;              // direct loads per thread per k-tile (early operand first)
+    constexpr int NLOAD = PA + PB;              // direct loads per thread per k-tile
     constexpr int NREAD = FM + FN;
-    constexpr int NMFMA = FM * FN;
-    constexpr int NSLOT = NREAD;
-    constexpr int MPS = NMFMA / NSLOT;
-    // A period's loads are spread over the k-steps 3 (of the previous k-tile), 0 and 1; AHEAD: all of the early operand's
-    // under k-step 3
-    constexpr int LA = AHEAD ? PE : NLOAD / 3;
+    constexpr int NSLOT = FM * FN;
+    // Activation fragments with one set of registers, read again as soon as the k-step has used them; the others, and the
+    // weight fragments, have two sets.  (Eight waves and 256 rows: 128 accumulators leave no room for two sets of all.)
+    constexpr int A_ONE = NW == 8 && FM == 8 ? FM - 2 : 0;
+    constexpr int NTWO = NREAD - A_ONE;
+    // The early operand's loads are issued behind the barrier, in k-step 1, the late operand's in k-step 0: what a barrier
+    // waits for is a whole period old.
     // STREAM_OUT: stores of a tile's epilogue, per wave (RowBuffer).  Loads and stores are counted together and complete in
     // order, and a wait for the loads behind an epilogue is a wait for its stores.  All that the first period of a tile waits
-    // for was asked for in front of the stores of the tile before (LA = PE), so it need not wait for them; the second period,
-    // 1.5 us later, does.  (Three gradients of 64 experts x 172 rows, 6144 x 2048: 1738 us waiting at once, 1643 so, 1222 with
+    // for was asked for in front of the stores of the tile before, so it need not wait for them; the second period, 1.5 us
+    // later, does.  (Three gradients of 64 experts x 172 rows, 6144 x 2048: 1738 us waiting at once, 1643 so, 1222 with
     // no stores at all; of 64 x 390, 5248 x 1792: 1780 and 1720.)
-    constexpr int NSTORE = STREAM_OUT ? FM * (32 / (1024 / (FN * 64))) : 0;
-    constexpr int LB = LA + (NLOAD - LA + 1) / 2;
-    constexpr int LC = NLOAD;
-    // fragment reads per slot of a k-step: one (spread over the whole k-step) with eight waves, whose LDS pipe is
-    // as busy as the matrix pipe; two with four waves
-    constexpr int RDPS = NW == 8 ? 1 : 2;
+    constexpr int NSTORE = STREAM_OUT ? FM / 2 * (32 / (1024 / (FN * 32))) : 0;
     constexpr int FO = SWIGLU ? FN / 2 : FN;
     static_assert(BM % RPP == 0 && BN % RPP == 0 && RPP % 8 == 0, "tile rows must divide into fetch passes");
     static_assert(!SWIGLU || ((BN / 2) % RPP == 0 && FN % 2 == 0), "gate/up halves must be pass- and fragment-aligned");
-    static_assert(LA <= PE, "only loads of the early operand may be issued under k-step 3");
     static_assert(PL + NSTORE < 64, "vmcnt holds 6 bits");
-    static_assert(NSTORE == 0 || LA == PE, "all that a tile's first period waits for precedes the epilogue");
-    static_assert(LB - LA <= NSLOT && LC - LB <= NSLOT && LA <= NSLOT, "not enough slots for the loads");
+    static_assert(PE <= NSLOT && PL <= NSLOT && NTWO <= NSLOT, "not enough slots for the loads and reads");
     static_assert((DEEP_B ? 2 * A_BYTES + 3 * B_BYTES : 3 * A_BYTES + 2 * B_BYTES) <= 160 * 1024, "tile stages exceed the 160 KiB of LDS");
-    static_assert(NW * 32 * FO * 64 <= (DEEP_B ? B_BYTES : A_BYTES), "epilogue patches must fit into one slot of the late operand");
+    static_assert(NW * 32 * FO * 32 <= (DEEP_B ? B_BYTES : A_BYTES), "epilogue patches must fit into one slot of the late operand");
 
     // clock sample (ticks != NULL): shader-clock and 100 MHz reference ticks workgroup 0 spends in the kernel
     const bool sample = ticks != nullptr && blockIdx.x == 0;
@@ -390,169 +401,156 @@ __device__ __forceinline__ void persist_body(
                                          (__attribute__((address_space(3))) void*)(st + p * RPP * ROWB + wbase), 16,
                                          0, 0);
     };
-    auto fetch_a = [&](int p, const uint8_t* base, uint32_t lim, uint8_t* st) {
-        const uint32_t off = min(vrow + (uint32_t)p * step, lim) + vswz;  // ragged tail: a valid row again
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(base + off),
-                                         (__attribute__((address_space(3))) void*)(st + p * RPP * ROWB + wbase), 16,
-                                         0, 0);
-    };
-    auto fetch_b = [&](int p, const uint8_t* base0, const uint8_t* base1, uint32_t lim, uint8_t* st) {
-        const int pp = SWIGLU ? p % (PB / 2) : p;
-        const uint8_t* base = (SWIGLU && p >= PB / 2) ? base1 : base0;
-        const uint32_t off = min(vrow + (uint32_t)pp * step, lim) + vswz;
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(base + off),
-                                         (__attribute__((address_space(3))) void*)(st + p * RPP * ROWB + wbase), 16,
-                                         0, 0);
-    };
-    // where k-tile kk of the stream that starts at cur's k-tile 0 comes from
-    struct Src {
-        const uint8_t* a;
-        const uint8_t* b0;
-        const uint8_t* b1;
-        uint32_t a_lim, b_lim;
-        int rows_left;   // row-major form: valid rows from this k-tile's first row on
-    };
-    // every tile has at least two k-tiles, so k-tile KT + 1 of the stream is the next tile's second
-    auto src = [&](int kk) -> Src {
-        const int KT = c_kt;
-        const bool in_cur = kk < KT;
-        const bool use_cur = in_cur || !n_valid;  // past the last tile: its last k-tile again, never used
-        const int k = in_cur ? kk : (n_valid ? kk - KT : KT - 1);
-        // a k-tile is 64 elements along the rows, or (row-major form) 64 rows
-        const size_t kbyte_a = KMAJ ? (size_t)k * 64 * ((size_t)K * 2) : (size_t)k * (BK * 2);
-        const size_t kbyte_b = KMAJ ? (size_t)k * 64 * ((size_t)ldb * 2) : (size_t)k * (BK * 2);
-        Src s;
-        s.a = (use_cur ? c_a : n_a) + kbyte_a;
-        s.b0 = (use_cur ? c_b0 : n_b0) + kbyte_b;
-        s.b1 = (use_cur ? c_b1 : n_b1) + kbyte_b;
-        s.a_lim = use_cur ? c_alim : n_alim;
-        s.b_lim = use_cur ? c_blim : n_blim;
-        s.rows_left = KMAJ ? (use_cur ? c_krows : n_krows) - k * 64 : 0;
-        return s;
-    };
-    // load i of a period: i < PE -> pass i of the early operand's tile (source se), else pass i - PE of the late
-    // operand's (source sl); ld_b / ld_a: the weight / activation slot being filled
-    auto fetch_one = [&](int i, const Src& se, const Src& sl, uint8_t* ld_b, uint8_t* ld_a) {
+    // Where the k-tile that a period fetches (kt + 2: the first two of the next tile in a tile's last two periods) lies: a
+    // pointer per operand that moves on by a k-tile each period, and what a thread adds to it in each pass, the same for all
+    // k-tiles of a tile.
+    const uint8_t *f_a, *f_b0, *f_b1;
+    uint32_t off_a[KMAJ ? 1 : PA], off_b[KMAJ ? 1 : PBD];
+    uint32_t f_alim = 0, f_blim = 0;
+    int f_rows = 0;                                            // row-major form: valid rows from the k-tile's first row on
+    const size_t kstep_a = KMAJ ? (size_t)64 * K * 2 : BK * 2;   // a k-tile is 64 elements along the rows, or 64 rows
+    const size_t kstep_b = KMAJ ? (size_t)64 * ldb * 2 : BK * 2;
+    auto fetch_from = [&](const uint8_t* a, const uint8_t* b0, const uint8_t* b1, uint32_t alim, uint32_t blim, int krows) {
+        f_a = a; f_b0 = b0; f_b1 = b1;
         if constexpr (KMAJ) {
-            if (i < PB)
-                fetch_km(i, se.b0, (uint32_t)ldb * 2u, se.b_lim, se.rows_left, ld_b);
-            else
-                fetch_km(i - PB, sl.a, k2, sl.a_lim, sl.rows_left, ld_a);
-        } else if constexpr (DEEP_B) {
-            if (i < PA)
-                fetch_a(i, se.a, se.a_lim, ld_a);
-            else
-                fetch_b(i - PA, sl.b0, sl.b1, sl.b_lim, ld_b);
+            f_alim = alim; f_blim = blim; f_rows = krows;
         } else {
-            if (i < PB)
-                fetch_b(i, se.b0, se.b1, se.b_lim, ld_b);
-            else
-                fetch_a(i - PB, sl.a, sl.a_lim, ld_a);
+#pragma unroll
+            for (int p = 0; p < PA; ++p) off_a[p] = min(vrow + (uint32_t)p * step, alim) + vswz;  // ragged tail: a valid row again
+#pragma unroll
+            for (int p = 0; p < PBD; ++p) off_b[p] = min(vrow + (uint32_t)p * step, blim) + vswz;
+        }
+    };
+    auto fetch_step = [&]() {
+        f_a += kstep_a;
+        f_b0 += kstep_b;
+        if (SWIGLU) f_b1 += kstep_b;
+        if (KMAJ) f_rows -= 64;
+    };
+    auto fetch_a = [&](int p, uint8_t* st) {
+        if constexpr (KMAJ)
+            fetch_km(p, f_a, k2, f_alim, f_rows, st);
+        else
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(f_a + off_a[p]),
+                                             (__attribute__((address_space(3))) void*)(st + p * RPP * ROWB + wbase), 16, 0, 0);
+    };
+    auto fetch_b = [&](int p, uint8_t* st) {
+        if constexpr (KMAJ)
+            fetch_km(p, f_b0, (uint32_t)ldb * 2u, f_blim, f_rows, st);
+        else
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)((p >= PBD ? f_b1 : f_b0) + off_b[p % PBD]),
+                                             (__attribute__((address_space(3))) void*)(st + p * RPP * ROWB + wbase), 16, 0, 0);
+    };
+    // load i of a period: i < PE -> pass i of the early operand's tile, else pass i - PE of the late operand's;
+    // ld_b / ld_a: the weight / activation slot being filled
+    auto fetch_one = [&](int i, uint8_t* ld_b, uint8_t* ld_a) {
+        if constexpr (DEEP_B) {
+            if (i < PA) fetch_a(i, ld_a);
+            else fetch_b(i - PA, ld_b);
+        } else {
+            if (i < PB) fetch_b(i, ld_b);
+            else fetch_a(i - PB, ld_a);
         }
     };
 
-    const int fr = lane & 31, fk = lane >> 5;
+    const int fr = lane & 15, fk = lane >> 4;
     int a_off[FM], b_off[FN];
-    const int f_sw = lds_swizzle(fr);  // fragments start at multiples of 32 rows
+    const int f_sw = lds_swizzle(fr);  // fragments start at multiples of 16 rows
     if constexpr (KMAJ) {
-        // lane (group g = lane / 16, s = lane % 16) addresses row 4 (g / 2) + s / 4 of an 8-row block, features
-        // 16 (g % 2) + 4 (s % 4) .. + 3 of the fragment's 32; its row decides the swizzle of the 64-byte unit
-        const int g = lane >> 4, sl = lane & 15;
-        const int r8 = 4 * (g >> 1) + (sl >> 2);
-        const int piece_in = 2 * (g & 1) + ((sl & 3) >> 1);   // 16-byte piece inside the fragment's 64 bytes
+        // lane (group g = lane / 16, s = lane % 16) addresses row 8 g + s / 4 (and, second load, the row four further) of a
+        // k-step's 32, features 4 (s % 4) .. + 3 of the fragment's 16; its row decides the swizzle of the 64-byte unit
+        const int sl = lane & 15;
+        const int r8 = 8 * fk + (sl >> 2);
+        const int piece_in = (sl & 3) >> 1;   // 16-byte piece inside the fragment's 32 bytes
         const int byte_in = 8 * (sl & 1);
 #pragma unroll
         for (int i = 0; i < FM; ++i)
-            a_off[i] = r8 * 512 + ((((wm * WM + i * 32) >> 3) + piece_in) ^ (2 * (r8 & 3))) * 16 + byte_in;
+            a_off[i] = r8 * 512 + ((((wm * WM + i * 16) >> 3) + piece_in) ^ (2 * (r8 & 3))) * 16 + byte_in;
 #pragma unroll
         for (int j = 0; j < FN; ++j)
-            b_off[j] = r8 * 512 + ((((wn * WN + j * 32) >> 3) + piece_in) ^ (2 * (r8 & 3))) * 16 + byte_in;
+            b_off[j] = r8 * 512 + ((((wn * WN + j * 16) >> 3) + piece_in) ^ (2 * (r8 & 3))) * 16 + byte_in;
     } else {
 #pragma unroll
-    for (int i = 0; i < FM; ++i) a_off[i] = (wm * WM + i * 32 + fr) * ROWB;
+        for (int i = 0; i < FM; ++i) a_off[i] = (wm * WM + i * 16 + fr) * ROWB;
 #pragma unroll
-    for (int j = 0; j < FN; ++j) {
-        int r;
-        if (SWIGLU) {
-            constexpr int half = FN / 2;
-            r = (j < half) ? (wn * (WN / 2) + j * 32 + fr) : (BN / 2 + wn * (WN / 2) + (j - half) * 32 + fr);
-        } else {
-            r = wn * WN + j * 32 + fr;
+        for (int j = 0; j < FN; ++j) {
+            int r;
+            if (SWIGLU) {
+                constexpr int half = FN / 2;
+                r = (j < half) ? (wn * (WN / 2) + j * 16 + fr) : (BN / 2 + wn * (WN / 2) + (j - half) * 16 + fr);
+            } else {
+                r = wn * WN + j * 16 + fr;
+            }
+            b_off[j] = r * ROWB;
         }
-        b_off[j] = r * ROWB;
-    }
     }
 
-    f32x16 acc[FM][FN];
+    f32x4 acc[FM][FN];
 #pragma unroll
     for (int i = 0; i < FM; ++i)
 #pragma unroll
         for (int j = 0; j < FN; ++j)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+            for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
 
     bf16x8 af[2][FM], bfg[2][FN];
+    auto set_of = [](int q, int buf) { return q < A_ONE ? 0 : buf; };
+    // fragment q (the activations', then the weights') of k-step s (32 elements along the rows) into set buf
     auto read_one = [&](const uint8_t* sa, const uint8_t* sb, int s, int buf, int q) {
         if constexpr (KMAJ) {
-            // k-step s = rows 16 s .. 16 s + 15: one transposing load for its first 8 rows, one for the last 8
+            // k-step s = rows 32 s .. 32 s + 31: two transposing loads of four rows for a lane's eight values
             typedef __attribute__((ext_vector_type(4))) short s16x4;
             typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-            const uint8_t* p = (q < FM ? sa + a_off[q] : sb + b_off[q - FM]) + s * (16 * 512);
+            const uint8_t* p = (q < FM ? sa + a_off[q] : sb + b_off[q - FM]) + s * (32 * 512);
             const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p));
-            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 8 * 512));
+            const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * 512));
             typedef __attribute__((ext_vector_type(8))) short s16x8;
             const s16x8 v = __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7);
             if (q < FM)
-                af[buf][q] = __builtin_bit_cast(bf16x8, v);
+                af[set_of(q, buf)][q] = __builtin_bit_cast(bf16x8, v);
             else
                 bfg[buf][q - FM] = __builtin_bit_cast(bf16x8, v);
             return;
         }
-        const int c = ((2 * s + fk) ^ f_sw) << 4;
+        const int c = ((4 * s + fk) ^ f_sw) << 4;
         if (q < FM)
-            af[buf][q] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(sa + a_off[q] + c));
+            af[set_of(q, buf)][q] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(sa + a_off[q] + c));
         else
             bfg[buf][q - FM] = __builtin_bit_cast(bf16x8, *reinterpret_cast<const u32x4*>(sb + b_off[q - FM] + c));
     };
     auto mfma_one = [&](int buf, int m) {
         // boustrophedon over the wave's blocks: successive MFMAs share one operand fragment
         const int i = m / FN, j = (i & 1) ? FN - 1 - m % FN : m % FN;
-        acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(bfg[buf][j], af[buf][i], acc[i][j], 0, 0, 0);
+        acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(bfg[buf][j], af[set_of(i, buf)][i], acc[i][j], 0, 0, 0);
     };
-    // one k-step in issue order: NSLOT slots of {MPS MFMAs on set mf_buf; up to
-    // 2 fragment reads of k-step rd_s into the other set; one direct load}
-    // `aside`: scalar bookkeeping run under the MFMAs of slot 1 (the next period's load sources), so that it does
-    // not sit between two k-tiles with the matrix pipe empty
-    auto kstep = [&](int mf_buf, const uint8_t* rd_a, const uint8_t* rd_b, int rd_s, int ld_begin, int ld_end,
-                     const Src& se, const Src& sl, uint8_t* ld_b, uint8_t* ld_a, auto&& aside) {
-        int m = 0, rd = 0, ld = ld_begin;
+    // the order in which fragments with two sets of registers are read: the first a k-step needs first
+    auto two_sets = [](int r) {
+        if (A_ONE == 0) return r == 0 ? 0 : r <= FN ? FM + r - 1 : r - FN;
+        return r < FN ? FM + r : A_ONE + r - FN;
+    };
+    // one k-step in issue order: NSLOT slots of {one matrix instruction on set mf_buf; at most a fragment read or two of k-step
+    // rd_s into the other set; at most one direct load}
+    auto kstep = [&](int mf_buf, const uint8_t* rd_a, const uint8_t* rd_b, int rd_s, int ld_begin, int ld_end, uint8_t* ld_b,
+                     uint8_t* ld_a) {
+        int ld = ld_begin;
 #pragma unroll
         for (int slot = 0; slot < NSLOT; ++slot) {
-#pragma unroll
-            for (int q = 0; q < MPS; ++q) {
-                mfma_one(mf_buf, m);
-                ++m;
-            }
-            if (slot == 1) aside();
+            mfma_one(mf_buf, slot);
             // the k-step's first MFMA waits (lgkmcnt) for the fragments read during the previous k-step; keep
             // this k-step's reads behind it, or the compiler hoists them and that wait also covers reads issued
             // a moment ago (a full LDS round trip in front of every k-step)
             if (slot == 0) __builtin_amdgcn_sched_barrier(0);
+            constexpr int RS = NSLOT * 7 / 8;   // the barrier behind k-step 0 waits for the last of them
 #pragma unroll
-            for (int q = 0; q < RDPS; ++q)
-                if (rd < NREAD) {
-                    read_one(rd_a, rd_b, rd_s, mf_buf ^ 1, rd);
-                    ++rd;
-                }
-            if (ld < ld_end) {
-                fetch_one(ld, se, sl, ld_b, ld_a);
+            for (int r = (slot * NTWO + RS - 1) / RS; r < ((slot + 1) * NTWO + RS - 1) / RS && r < NTWO; ++r)
+                read_one(rd_a, rd_b, rd_s, mf_buf ^ 1, two_sets(r));
+            if (A_ONE > 0 && slot % FN == FN - 1 && slot / FN < A_ONE) read_one(rd_a, rd_b, rd_s, mf_buf ^ 1, slot / FN);
+            if (ld < ld_end && slot == 1 + (ld - ld_begin) * NSLOT / (ld_end - ld_begin)) {
+                fetch_one(ld, ld_b, ld_a);
                 ++ld;
             }
             __builtin_amdgcn_sched_barrier(0);
         }
-#pragma unroll
-        for (int mm = NSLOT * MPS; mm < NMFMA; ++mm) mfma_one(mf_buf, mm);
-        __builtin_amdgcn_sched_barrier(0);
     };
 
     uint8_t* const a_region = smem;
@@ -561,21 +559,21 @@ __device__ __forceinline__ void persist_body(
     // prologue (first tile of this workgroup only): late(0), early(0), then late(1); only the first two must have
     // landed before the first fragment reads
     {
-        const Src s0 = src(0), s1 = src(1);
+        fetch_from(c_a, c_b0, c_b1, c_alim, c_blim, c_krows);
 #pragma unroll
-        for (int i = PE; i < NLOAD; ++i) fetch_one(i, s0, s0, b_region, a_region);
+        for (int i = PE; i < NLOAD; ++i) fetch_one(i, b_region, a_region);
 #pragma unroll
-        for (int i = 0; i < PE; ++i) fetch_one(i, s0, s0, b_region, a_region);
+        for (int i = 0; i < PE; ++i) fetch_one(i, b_region, a_region);
+        fetch_step();
 #pragma unroll
-        for (int i = PE; i < NLOAD; ++i)
-            fetch_one(i, s1, s1, b_region + (DEEP_B ? B_BYTES : 0), a_region + (DEEP_B ? 0 : A_BYTES));
+        for (int i = PE; i < NLOAD; ++i) fetch_one(i, b_region + (DEEP_B ? B_BYTES : 0), a_region + (DEEP_B ? 0 : A_BYTES));
         __builtin_amdgcn_s_waitcnt(0x0F70 | (PL & 0xF) | ((PL >> 4) << 14));  // vmcnt(PL)
         __builtin_amdgcn_s_barrier();
 #pragma unroll
         for (int q = 0; q < NREAD; ++q) read_one(a_region, b_region, 0, 0, q);
-        // head of early(1) into the early operand's slot 1
+        // early(1) into the early operand's slot 1
 #pragma unroll
-        for (int i = 0; i < LA; ++i) fetch_one(i, s1, s1, b_region + B_BYTES, a_region + A_BYTES);
+        for (int i = 0; i < PE; ++i) fetch_one(i, b_region + B_BYTES, a_region + A_BYTES);
     }
 
     // slots of k-tiles kt, kt+1 (, kt+2): three for the late operand, two for the early one
@@ -590,6 +588,22 @@ __device__ __forceinline__ void persist_body(
             const int tb = b0; b0 = b1; b1 = tb;
         }
     };
+    // the source of the loads of period kt: k-tile kt + 2 of the stream that starts at the current tile's first.  Every tile has
+    // at least two k-tiles, so that is one of this tile's or of the next one's first two; behind the last tile the last two
+    // k-tiles are fetched again, and never used.
+    auto advance = [&](int kt) {
+        fetch_step();
+        if (kt == c_kt - 2) {
+            if (n_valid)
+                fetch_from(n_a, n_b0, n_b1, n_alim, n_blim, n_krows);
+            else {
+                f_a -= 2 * kstep_a;
+                f_b0 -= 2 * kstep_b;
+                if (SWIGLU) f_b1 -= 2 * kstep_b;
+                if (KMAJ) f_rows += 128;
+            }
+        }
+    };
     int stored = 0;   // the epilogue of a tile has just been through
     for (;;) {
         // (IDLE_SKIP instantiations, chosen for launches with many experts, i.e. many ragged tails; the test costs
@@ -598,59 +612,36 @@ __device__ __forceinline__ void persist_body(
         // matrix pipe and the LDS reads alone (under a power cap that is clock for the other workgroups).
         const bool wave_idle = IDLE_SKIP && wm * WM >= c_rows;   // wave-uniform
         if (!wave_idle) {
-        // sources of the loads of k-tiles kt+1 and kt+2.  With one wave per SIMD (four waves) nothing covers the
-        // scalar arithmetic that forms them if it sits between two k-tiles (some fifty instructions with the
-        // matrix pipe empty), so there they are carried from period to period: the pair a period needs is the
-        // previous period's second source and one computed under the MFMAs of the previous period's k-step 2 (a
-        // tile's first period forms its own: the next tile's third k-tile need not exist).  With two waves per
-        // SIMD the other wave covers it, and the carried form measured 1.7 % slower; there only the first of the
-        // pair is carried and the second is formed at the top of the period.
-        constexpr bool CARRY = NW == 4;
-        Src s1 = src(1), s2 = src(2), s3 = s2;
-        auto nothing = [] {};
         for (int kt = 0; kt < c_kt; ++kt) {
-            if constexpr (!CARRY) {
-                // the source of k-tile kt+1 is last period's second source; only the new one is formed here
-                if (kt > 0) s1 = s2;
-                s2 = src(kt + 2);
-            }
+            advance(kt);
             const uint8_t* ca = a_region + a0;
             const uint8_t* cb = b_region + b0;
-            // this period fills the rest of early(kt+1), late(kt+2) and, once k-tile kt is read, the head of early(kt+2)
+            // this period fills late(kt+2) and, once k-tile kt is read, early(kt+2)
             uint8_t* lb = b_region + (DEEP_B ? b2 : b1);
             uint8_t* la = a_region + (DEEP_B ? a1 : a2);
             __builtin_amdgcn_sched_barrier(0);
-            kstep(0, ca, cb, 1, LA, LB, s1, s2, lb, la, nothing);  // k-step 0
-            kstep(1, ca, cb, 2, LB, LC, s1, s2, lb, la, nothing);  // k-step 1
-            if constexpr (CARRY)
-                kstep(0, ca, cb, 3, LC, LC, s1, s2, lb, la, [&] { s3 = src(kt + 3); });  // k-step 2
-            else
-                kstep(0, ca, cb, 3, LC, LC, s1, s2, lb, la, nothing);
-            // early(kt+1) was issued before late(kt+2) in this period and late(kt+1) a period ago: all but the PL youngest
+            kstep(0, ca, cb, 1, PE, NLOAD, lb, la);  // k-step 0
+            // early(kt+1) and late(kt+1) were issued a period ago, late(kt+2) in this one: all but the PL youngest
             // loads must have landed; this wave's fragment reads of k-tile kt are in registers
             wait_memory<PL, NSTORE>(stored);
             __builtin_amdgcn_s_barrier();
             __builtin_amdgcn_sched_barrier(0);
-            // k-step 3: first fragments of k-tile kt+1; the early operand's slot of k-tile
-            // kt is free, the head of early(kt+2) goes into it
-            kstep(1, a_region + a1, b_region + b1, 0, 0, LA, s2, s2, b_region + b0, a_region + a0, nothing);
+            // k-step 1: first fragments of k-tile kt+1; the early operand's slot of k-tile
+            // kt is free, early(kt+2) goes into it
+            kstep(1, a_region + a1, b_region + b1, 0, 0, PE, b_region + b0, a_region + a0);
             rotate();
-            if constexpr (CARRY) {
-                s1 = s2;
-                s2 = s3;
-            }
         }
         } else {
             for (int kt = 0; kt < c_kt; ++kt) {
-                const Src s1 = src(kt + 1), s2 = src(kt + 2);
+                advance(kt);
                 uint8_t* lb = b_region + (DEEP_B ? b2 : b1);
                 uint8_t* la = a_region + (DEEP_B ? a1 : a2);
 #pragma unroll
-                for (int i = LA; i < LC; ++i) fetch_one(i, s1, s2, lb, la);
+                for (int i = PE; i < NLOAD; ++i) fetch_one(i, lb, la);
                 wait_memory<PL, NSTORE>(stored);
                 __builtin_amdgcn_s_barrier();
 #pragma unroll
-                for (int i = 0; i < LA; ++i) fetch_one(i, s2, s2, b_region + b0, a_region + a0);
+                for (int i = 0; i < PE; ++i) fetch_one(i, b_region + b0, a_region + a0);
                 rotate();
             }
             // the next tile may have rows for this wave: its first fragments, as the last k-step would have read them
@@ -667,9 +658,9 @@ __device__ __forceinline__ void persist_body(
                                                   reinterpret_cast<float*>(C) + (size_t)c_split * plane_rows * (SWIGLU ? 2 * N : N), N, wm,
                                                   wn, lane);
         else
-            store_tile_staged<FM, FN, WM, MODE, (FM * FN * 16 > 128), STREAM_OUT>(
+            store_tile_staged<FM, FN, WM, MODE, (FM * FN * 4 > 128), STREAM_OUT>(
                 acc, c_row0, c_rows, c_n0, C, GU, N, wm, wn, lane,
-                (DEEP_B ? b_region + b2 : a_region + a2) + wave * (32 * FO * 64));
+                (DEEP_B ? b_region + b2 : a_region + a2) + wave * (32 * FO * 32));
         if (!n_valid) break;
         c_a = n_a; c_b0 = n_b0; c_b1 = n_b1; c_alim = n_alim; c_blim = n_blim;
         c_row0 = n_row0; c_rows = n_rows; c_n0 = n_n0;
@@ -684,7 +675,7 @@ __device__ __forceinline__ void persist_body(
 #pragma unroll
             for (int j = 0; j < FN; ++j)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[i][j][v] = 0.f;
+                for (int v = 0; v < 4; ++v) acc[i][j][v] = 0.f;
         __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave is done with its patch
         __builtin_amdgcn_s_barrier();
     }
@@ -698,20 +689,20 @@ __device__ __forceinline__ void persist_body(
 // BM = 0: the height of the tiles is chosen on the device, from the rows that every expert really has (pick_height);
 // 256, 192 or 128 rows, all of BN = 256 columns (ldb: a height to be taken instead, or 0).  A row's sums are formed in the same order whatever the height.
 template <int BM, int BN, int WGM, int WGN, int MODE, bool GROUPK = false, bool KMAJ = false, bool IDLE_SKIP = false,
-          bool DEEP_B = false, bool BY_ROUND = true, bool STREAM_OUT = false, bool AHEAD = false, bool SPLIT = false>
+          bool DEEP_B = false, bool BY_ROUND = true, bool STREAM_OUT = false, bool SPLIT = false>
 __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_persist_kernel(
     const bf16_t* __restrict__ A, const int32_t* __restrict__ offsets, int E, int N, int K,
     const bf16_t* __restrict__ B0, const bf16_t* __restrict__ B1, bf16_t* __restrict__ C, bf16_t* __restrict__ GU,
     int ntn, int ldb, int splits, int plane_rows, unsigned long long* __restrict__ ticks) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     if constexpr (BM != 0) {
-        persist_body<BM, BN, WGM, WGN, MODE, GROUPK, KMAJ, IDLE_SKIP, DEEP_B, BY_ROUND, STREAM_OUT, AHEAD, SPLIT>(
+        persist_body<BM, BN, WGM, WGN, MODE, GROUPK, KMAJ, IDLE_SKIP, DEEP_B, BY_ROUND, STREAM_OUT, SPLIT>(
             A, offsets, E, N, K, B0, B1, C, GU, ntn, ldb, splits, plane_rows, ticks, smem);
     } else {
         const int height = ldb != 0 ? ldb : pick_height(kCostBf16, offsets, E, ntn * (SPLIT ? splits : 1), K / 64 / (SPLIT ? splits : 1),
                                                         threadIdx.x & 63);
         auto run = [&](auto rows) {
-            persist_body<decltype(rows)::value, BN, WGM, WGN, MODE, false, false, IDLE_SKIP, DEEP_B, BY_ROUND, false, AHEAD, SPLIT>(
+            persist_body<decltype(rows)::value, BN, WGM, WGN, MODE, false, false, IDLE_SKIP, DEEP_B, BY_ROUND, false, SPLIT>(
                 A, offsets, E, N, K, B0, B1, C, GU, ntn, ldb, splits, plane_rows, ticks, smem);
         };
         if (height == 256) run(std::integral_constant<int, 256>{});
@@ -742,27 +733,18 @@ void launch_persist(const void* A, const int32_t* offsets, int r_max, int E, int
     const bool idle_skip = MODE != 3 && persist_idle_skip(E);
     // few experts: whole rounds of tiles are dealt to the XCDs round by round; many: contiguous shares (measured)
     const bool by_round = MODE == 3 || E < 16;
-    // Few rows per expert: all of the early operand's loads a whole period ahead.  The launch is a stream of weights then, and
-    // the activations, queued behind them, are what the barrier waits for (us, as usual / ahead: 64 experts x 390 rows, 5248 x
-    // 1792, gate/up 1120 / 988; 64 x 345, 6784 x 896, gate/up 613 / 589, dx 565 / 523; 8 x 512 rows, 4096 x 14336, down 548 /
-    // 496).  With more rows the loads after the barrier get in the way of its fragment reads: 8 x 600 rows, gate/up 1036 /
-    // 1110, while the down product (half the output per row read) is 560 / 516 there; from 2000 rows on both lose 2 to 8 %.
-    // The backward's dh (MODE 3) loses 3 to 13 % at every size.
-    constexpr bool CAN_AHEAD = BM == 0 && MODE != 3;
-    const bool ahead = CAN_AHEAD && r_max < (MODE == 0 ? 640ll : 448ll) * E;
     constexpr bool SKIP = MODE != 3;
     auto pick = [&](auto skip, auto round) {
         constexpr bool S = decltype(skip)::value, R = decltype(round)::value;
-        return ahead ? gemm_bf16_persist_kernel<BM, BN, WGM, WGN, MODE, false, false, S, DEEP_B, R, false, CAN_AHEAD>
-                     : gemm_bf16_persist_kernel<BM, BN, WGM, WGN, MODE, false, false, S, DEEP_B, R, false, false>;
+        return gemm_bf16_persist_kernel<BM, BN, WGM, WGN, MODE, false, false, S, DEEP_B, R>;
     };
     using Yes = std::true_type;
     using No = std::false_type;
     using Skip = std::integral_constant<bool, SKIP>;
     using Shares = std::integral_constant<bool, MODE == 3>;   // MODE 3 has the rounds only
     auto kern = idle_skip ? (by_round ? pick(Skip{}, Yes{}) : pick(Skip{}, Shares{})) : (by_round ? pick(No{}, Yes{}) : pick(No{}, Shares{}));
-    static OncePerDevice lds[2][2][2];
-    allow_lds(lds[idle_skip][by_round][ahead], reinterpret_cast<const void*>(kern), (int)smem);
+    static OncePerDevice lds[2][2];
+    allow_lds(lds[idle_skip][by_round], reinterpret_cast<const void*>(kern), (int)smem);
     // never more workgroups than the static bound on the tile count
     const int grid = min(persist_grid(), grid_for(r_max, E, HMIN, ntn));
     hipLaunchKernelGGL(kern, dim3(grid), dim3(WGM * WGN * 64), smem, s, static_cast<const bf16_t*>(A), offsets, E, N,
@@ -786,7 +768,7 @@ template <int BM, int BN, int WGM, int WGN, bool STREAM_OUT>
 void launch_persist_groupk(const void* A, const void* B, const int32_t* offsets, int E, int M, int N, int ld,
                            void* C, hipStream_t s) {
     constexpr size_t smem = (size_t)(3 * BM + 2 * BN) * 64 * 2;
-    auto kern = gemm_bf16_persist_kernel<BM, BN, WGM, WGN, 0, true, false, false, false, true, STREAM_OUT, STREAM_OUT>;
+    auto kern = gemm_bf16_persist_kernel<BM, BN, WGM, WGN, 0, true, false, false, false, true, STREAM_OUT>;
     static OncePerDevice lds;
     allow_lds(lds, reinterpret_cast<const void*>(kern), (int)smem);
     const long long tiles = (long long)E * ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
@@ -839,7 +821,7 @@ bool launch_grouped_nt(const void* A, const int32_t* offsets, int r_max, int E, 
         launch_stream(plan, kStreamBf16, A, offsets, r_max, E, N, K, B, nullptr, C, nullptr, 0.f, 0.f, 0.f, nullptr, nullptr, s);
         return true;
     }
-    launch_persist<0, 256, 2, 4, 0, true>(A, offsets, r_max, E, N, K, B, nullptr, C, nullptr, s);
+    launch_persist<0, 256, 2, 2, 0, true>(A, offsets, r_max, E, N, K, B, nullptr, C, nullptr, s);
     return true;
 }
 
@@ -859,9 +841,9 @@ void launch_persist_wgrad(const void* a_t, const void* b_t, const int32_t* offse
     // With 8 experts x 2048 rows, 6144 x 16384, the layer's forward and backward are 0.4 % slower for it: the line lies below
     // where the two meet.
     if (ld <= 640ll * E && N <= kMaxColumns)   // up to some 512 rows per expert, the padding included
-        launch_persist_groupk<256, 256, 2, 4, true>(a_t, b_t, offsets, E, M, N, ld, dw, s);
+        launch_persist_groupk<256, 256, 2, 2, true>(a_t, b_t, offsets, E, M, N, ld, dw, s);
     else
-        launch_persist_groupk<256, 256, 2, 4, false>(a_t, b_t, offsets, E, M, N, ld, dw, s);
+        launch_persist_groupk<256, 256, 2, 2, false>(a_t, b_t, offsets, E, M, N, ld, dw, s);
 }
 
 // dw [E, M, N] = per expert A[rows_e, 0:M]^T . B[rows_e, 0:N], A [rows, lda] and B [rows, ldb] row-major; M, N
@@ -875,7 +857,7 @@ void launch_persist_wgrad_rowmajor(const void* a, int lda, const void* b, int ld
 bool launch_grouped_nt_swiglu_bwd(const void* A, const int32_t* offsets, int r_max, int E, int N, int K,
                                   const void* B, const void* gu, void* dgdu, hipStream_t s) {
     if (K < 128 || K % 64 || N % 8) return false;
-    launch_persist<0, 256, 2, 4, 3, true>(A, offsets, r_max, E, N, K, B, nullptr, dgdu, const_cast<void*>(gu), s);
+    launch_persist<0, 256, 2, 2, 3, true>(A, offsets, r_max, E, N, K, B, nullptr, dgdu, const_cast<void*>(gu), s);
     return true;
 }
 
@@ -888,7 +870,7 @@ bool launch_gate_up_saving(const void* x_perm, const int32_t* offsets, int r_max
         launch_stream(plan, kStreamBf16, x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, gu, 0.f, 0.f, 0.f, nullptr, nullptr, s);
         return true;
     }
-    launch_persist<0, 256, 2, 4, 2, true>(x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, gu, s);
+    launch_persist<0, 256, 2, 2, 2, true>(x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, gu, s);
     return true;
 }
 
@@ -899,12 +881,12 @@ bool launch_persist_split(const void* A, const int32_t* offsets, int r_max, int 
     auto go = [&](auto mode) {
         constexpr int MODE = decltype(mode)::value, OUTN = MODE == 1 ? 128 : 256;
         constexpr size_t smem = (size_t)(2 * 256 + 3 * 256) * 64 * 2;
-        auto kern = gemm_bf16_persist_kernel<0, 256, 2, 4, MODE, false, false, false, true, true, false, false, true>;
+        auto kern = gemm_bf16_persist_kernel<0, 256, 2, 2, MODE, false, false, false, true, true, false, true>;
         static OncePerDevice lds;
         allow_lds(lds, reinterpret_cast<const void*>(kern), (int)smem);
         const int ntn = (N + OUTN - 1) / OUTN;
         const int grid = min(persist_grid(), grid_for(r_max, E, 128, ntn * splits));
-        hipLaunchKernelGGL(kern, dim3(grid), dim3(512), smem, s, static_cast<const bf16_t*>(A), offsets, E, N, K,
+        hipLaunchKernelGGL(kern, dim3(grid), dim3(256), smem, s, static_cast<const bf16_t*>(A), offsets, E, N, K,
                            static_cast<const bf16_t*>(B0), static_cast<const bf16_t*>(B1), reinterpret_cast<bf16_t*>(part),
                            static_cast<bf16_t*>(nullptr), ntn, g_persist_tile_rows, splits, r_max, g_persist_ticks);
     };
@@ -920,8 +902,8 @@ bool launch_persist_ffn(const void* x_perm, const int32_t* offsets, int r_max, i
     switch (variant) {
         case 40: run_persist_pair<256, 256, 2, 2>(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, phase, s); return true;
         case 41: run_persist_pair<256, 256, 2, 4>(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, phase, s); return true;
-        case 42: run_persist_pair<256, 256, 2, 2, true>(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, phase, s); return true;
-        case 43: run_persist_pair<0, 256, 2, 4, true>(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, phase, s); return true;
+        case 42: run_persist_pair<0, 256, 2, 2, true>(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, phase, s); return true;
+        case 43: run_persist_pair<256, 256, 2, 4, true>(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, phase, s); return true;
         default: return false;
     }
 }

@@ -150,7 +150,7 @@ static bool launch_phase(const StreamPlan& plan, int ph, int elt, const void* x_
         launch_stream_reduce(ph == 1, static_cast<float*>(part), offsets, E, plan.splits, r_max, N, C, s);
         return true;
     }
-    return launch_persist_ffn(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, 43, ph, s) ||
+    return launch_persist_ffn(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, 42, ph, s) ||
            launch_pipe3_ffn(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, ph == 1 ? 31 : 30, ph, s);
 }
 
