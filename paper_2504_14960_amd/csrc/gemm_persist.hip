@@ -606,13 +606,28 @@ __device__ __forceinline__ void persist_body(
     };
     int stored = 0;   // the epilogue of a tile has just been through
     for (;;) {
-        // (IDLE_SKIP instantiations, chosen for launches with many experts, i.e. many ragged tails; the test costs
-        // the plain kernel half a per cent.)  A wave whose rows of the tile all lie past the tile's last valid row
-        // (ragged tail of an expert) has nothing to multiply: it keeps issuing its share of the loads and meeting the barriers, and leaves the
-        // matrix pipe and the LDS reads alone (under a power cap that is clock for the other workgroups).
-        const bool wave_idle = IDLE_SKIP && wm * WM >= c_rows;   // wave-uniform
-        if (!wave_idle) {
-        for (int kt = 0; kt < c_kt; ++kt) {
+        // (IDLE_SKIP instantiations, chosen for launches with many experts, i.e. many ragged tails.)  A wave whose rows of the
+        // tile all lie past the tile's last valid row (ragged tail of an expert) has nothing to multiply: it keeps issuing its
+        // share of the loads and meeting the barriers, and leaves the matrix pipe and the LDS reads alone (under a power cap
+        // that is clock for the other workgroups).  The last k-tile it multiplies like the others, whatever its registers
+        // hold: that leaves the next tile's first fragments in the registers where the loop expects them, and the sums are
+        // not stored.
+        int kt = 0;
+        if (IDLE_SKIP) {
+            for (const int idle = wm * WM >= c_rows ? c_kt - 1 : 0; kt < idle; ++kt) {   // wave-uniform
+                advance(kt);
+                uint8_t* lb = b_region + (DEEP_B ? b2 : b1);
+                uint8_t* la = a_region + (DEEP_B ? a1 : a2);
+#pragma unroll
+                for (int i = PE; i < NLOAD; ++i) fetch_one(i, lb, la);
+                wait_memory<PL, NSTORE>(stored);
+                __builtin_amdgcn_s_barrier();
+#pragma unroll
+                for (int i = 0; i < PE; ++i) fetch_one(i, b_region + b0, a_region + a0);
+                rotate();
+            }
+        }
+        for (; kt < c_kt; ++kt) {
             advance(kt);
             const uint8_t* ca = a_region + a0;
             const uint8_t* cb = b_region + b0;
@@ -630,25 +645,6 @@ __device__ __forceinline__ void persist_body(
             // kt is free, early(kt+2) goes into it
             kstep(1, a_region + a1, b_region + b1, 0, 0, PE, b_region + b0, a_region + a0);
             rotate();
-        }
-        } else {
-            for (int kt = 0; kt < c_kt; ++kt) {
-                advance(kt);
-                uint8_t* lb = b_region + (DEEP_B ? b2 : b1);
-                uint8_t* la = a_region + (DEEP_B ? a1 : a2);
-#pragma unroll
-                for (int i = PE; i < NLOAD; ++i) fetch_one(i, lb, la);
-                wait_memory<PL, NSTORE>(stored);
-                __builtin_amdgcn_s_barrier();
-#pragma unroll
-                for (int i = 0; i < PE; ++i) fetch_one(i, b_region + b0, a_region + a0);
-                rotate();
-            }
-            // the next tile may have rows for this wave: its first fragments, as the last k-step would have read them
-            if (n_valid) {
-#pragma unroll
-                for (int q = 0; q < NREAD; ++q) read_one(a_region + a0, b_region + b0, 0, 0, q);
-            }
         }
         // Epilogue.  The late operand's slot that held the last k-tile (now its third) is
         // idle: every wave finished reading it before the last barrier, and the
