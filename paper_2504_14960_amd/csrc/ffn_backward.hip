@@ -14,77 +14,102 @@
 //                              weight-gradient GEMMs contract over whole k-tiles
 //   swiglu_backward_kernel     (dh, g, u) -> dg | du side by side
 //
-// All bf16, 128 x 128 tiles through LDS for the transposes.
+// All bf16, tiles through LDS for the transposes.
 #include "common.h"
 
 namespace moe {
 
 namespace {
 
-// ---- 128 x 128 transposes ----
-// Bound by HBM: every byte is read once and written once.  Rows of 256 bytes on both sides (64 x 64 tiles, 128 bytes,
-// ran at 5.0 TB/s, these at 5.2, the rate of a plain copy), all eight loads of a thread in flight, and 32-bit LDS traffic: a thread takes the same eight
-// columns of two adjacent rows, so that a dword of the transposed tile is one of its element pairs, and the tile
-// [column][row pair] is read back 16 bytes at a time.  Group g of four dwords of column c lies at g ^ (c / 8): the 64
-// dwords a wave writes at a time then fall into 64 different banks, and a read covers whole 256-byte rows.
-constexpr int TT = 128, TP = TT / 2;   // tile; row pairs
-
-struct TransposeRows {   // where a half of the tile's rows (64 positions) comes from
+// ---- transposes ----
+// Bound by HBM: every byte is read once and written once.  What counts is where the workgroups that run at the same time
+// read and write.
+// Weights: tiles of 256 rows x 64 columns, neighbours below one another, so that together they write whole rows of the
+// result, 512 bytes each (and read whole 128-byte lines, some rows apart), loads and stores streamed past the caches.  64
+// matrices of 2048 x 6144, into rows of 4096, and of 6144 x 2048, us: 128 x 128 tiles, neighbours beside one another, 631 and
+// 601 (5.1 and 5.4 TB/s); below one another and streamed, 593 and 576; 256 x 64 so 532 and 535 (6.0 TB/s), not streamed 574
+// and 576.  A plain copy of 1 GiB runs at 5.5 TB/s, streamed at 6.0 to 6.2.
+// Activations: 128 x 128 tiles, neighbours beside one another.  Their rows are often a power of two of bytes long, where
+// reads of 128 bytes from row after row meet in few channels: the four of a training step of 2048 tokens, 64 experts,
+// 6144 x 2048, 174 so and 191 in tiles of 256 x 64, 8192 tokens of 8 experts, 6144 x 16384, 787 and 772.
+// All eight loads of a thread in flight, and 32-bit LDS traffic: a thread takes the same eight columns of two adjacent
+// rows, so that a dword of the transposed tile is one of its element pairs, and the tile [column][row pair] is read back 16
+// bytes at a time.  Group g of four dwords of column c lies at g ^ (c / 8) (64 columns: g ^ 2 (c / 8)): the 64 dwords a wave
+// writes at a time then fall into 64 different banks.
+struct TransposeRows {   // where 64 of the tile's rows come from
     int first, valid;    // first source row; how many of the 64 exist, the rest count as zeros
 };
 
-// The transposed tile of columns c0 .. c0 + 127 (below `cols`) of two times 64 rows of `src`.
-__device__ __forceinline__ void load_tile(const uint16_t* __restrict__ src, size_t ld, int c0, int cols,
-                                          const TransposeRows (&half)[2], uint32_t (*tile)[TP]) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int cv = lane & 15, c = cv * 8;
-    u32x4 v[4][2];
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const int r = 2 * (4 * (4 * p + wave) + (lane >> 4));   // even row of the pair
-        const TransposeRows h = half[p / 2];
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const int rr = (r & 63) + k;
-            v[p][k] = u32x4{0u, 0u, 0u, 0u};
-            if (rr < h.valid && c0 + c < cols)   // cols is a multiple of 8
-                v[p][k] = *reinterpret_cast<const u32x4*>(src + (size_t)(h.first + rr) * ld + c0 + c);
-        }
-    }
-#pragma unroll
-    for (int p = 0; p < 4; ++p) {
-        const int at = (4 * ((4 * p + wave) ^ cv)) + (lane >> 4);
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            tile[c + 2 * j][at] = (v[p][0][j] & 0xffffu) | (v[p][1][j] << 16);
-            tile[c + 2 * j + 1][at] = (v[p][0][j] >> 16) | (v[p][1][j] & 0xffff0000u);
-        }
-    }
-}
+template <int TR, int TC, bool STREAM>   // tile: rows, columns
+struct TransposeTile {
+    static constexpr int PARTS = TR / 64, TP = TR / 2;                  // row pairs
+    static constexpr int VC = TC / 8, RPT = 256 / VC, NP = TP / RPT;    // 16-byte pieces across; row pairs a pass; passes
+    static constexpr int VR = TR / 8, CPT = 256 / VR;                   // pieces along a row of the result; columns a pass
+    static_assert(RPT <= 32 && 32 % RPT == 0, "a pass lies in one part");
+    uint32_t pair[TC][TP];
 
-// Output row c0 + c gets the tile's column c at dst[(c0 + c) * ldo + o0 ..], n_out elements of it (a multiple of 8).
-__device__ __forceinline__ void store_tile_t(uint16_t* __restrict__ dst, size_t ldo, int c0, int cols, size_t o0,
-                                             int n_out, const uint32_t (*tile)[TP]) {
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const int g = lane & 15;
+    static __device__ __forceinline__ int at(int group, int c) { return 4 * (group ^ ((c >> 3) * (128 / TC))); }
+
+    // columns c0 .. c0 + TC - 1 (below `cols`) of PARTS times 64 rows of `src`
+    __device__ __forceinline__ void load(const uint16_t* __restrict__ src, size_t ld, int c0, int cols,
+                                         const TransposeRows (&part)[PARTS]) {
+        const int c = (threadIdx.x % VC) * 8, rp = threadIdx.x / VC;
+        u32x4 v[NP][2];
 #pragma unroll
-    for (int p = 0; p < 8; ++p) {
-        const int c = 4 * (4 * p + wave) + (lane >> 4);
-        if (c0 + c >= cols || g * 8 >= n_out) continue;
-        const u32x4 v = *reinterpret_cast<const u32x4*>(&tile[c][4 * (g ^ (c >> 3))]);
-        *reinterpret_cast<u32x4*>(dst + (size_t)(c0 + c) * ldo + o0 + g * 8) = v;
+        for (int p = 0; p < NP; ++p) {
+            const TransposeRows h = part[p * RPT / 32];
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                const int rr = 2 * (p * RPT % 32 + rp) + k;
+                v[p][k] = u32x4{0u, 0u, 0u, 0u};
+                if (rr < h.valid && c0 + c < cols) {   // cols is a multiple of 8
+                    const u32x4* from = reinterpret_cast<const u32x4*>(src + (size_t)(h.first + rr) * ld + c0 + c);
+                    v[p][k] = STREAM ? __builtin_nontemporal_load(from) : *from;
+                }
+            }
+        }
+#pragma unroll
+        for (int p = 0; p < NP; ++p) {
+            const int q = p * RPT + rp, to = at(q >> 2, c) + (q & 3);
+#pragma unroll
+            for (int j = 0; j < 4; ++j) {
+                pair[c + 2 * j][to] = (v[p][0][j] & 0xffffu) | (v[p][1][j] << 16);
+                pair[c + 2 * j + 1][to] = (v[p][0][j] >> 16) | (v[p][1][j] & 0xffff0000u);
+            }
+        }
     }
-}
+
+    // output row c0 + c gets the tile's column c at dst[(c0 + c) * ldo + o0 ..], n_out elements of it (a multiple of 8)
+    __device__ __forceinline__ void store(uint16_t* __restrict__ dst, size_t ldo, int c0, int cols, size_t o0, int n_out) const {
+        const int g = threadIdx.x % VR;
+#pragma unroll
+        for (int p = 0; p < TC / CPT; ++p) {
+            const int c = CPT * p + threadIdx.x / VR;
+            if (c0 + c >= cols || g * 8 >= n_out) continue;
+            const u32x4 v = *reinterpret_cast<const u32x4*>(&pair[c][at(g, c)]);
+            u32x4* const to = reinterpret_cast<u32x4*>(dst + (size_t)(c0 + c) * ldo + o0 + g * 8);
+            if (STREAM) __builtin_nontemporal_store(v, to);
+            else *to = v;
+        }
+    }
+};
+using WeightTile = TransposeTile<256, 64, true>;
+constexpr int kWeightRows = 256, kWeightCols = 64;
+using ActTile = TransposeTile<128, 128, false>;
+constexpr int kActTile = 128;
 
 // dst[b][c][col0 + r] = src[b][r][c];  R, C multiples of 8.
 __global__ __launch_bounds__(256) void transpose_batched_kernel(const uint16_t* __restrict__ src, int R, int C,
                                                                 uint16_t* __restrict__ dst, size_t ldo, int col0) {
-    __shared__ __attribute__((aligned(16))) uint32_t tile[TT][TP];
-    const int b = blockIdx.z, r0 = blockIdx.y * TT, c0 = blockIdx.x * TT;
-    const TransposeRows half[2] = {{r0, min(64, R - r0)}, {r0 + 64, min(64, R - r0 - 64)}};
-    load_tile(src + (size_t)b * R * C, (size_t)C, c0, C, half, tile);
+    __shared__ __attribute__((aligned(16))) WeightTile tile;
+    const int nr = (R + kWeightRows - 1) / kWeightRows;
+    const int b = blockIdx.z, r0 = (int)(blockIdx.x % nr) * kWeightRows, c0 = (int)(blockIdx.x / nr) * kWeightCols;
+    TransposeRows part[WeightTile::PARTS];
+#pragma unroll
+    for (int q = 0; q < WeightTile::PARTS; ++q) part[q] = {r0 + 64 * q, R - r0 - 64 * q};
+    tile.load(src + (size_t)b * R * C, (size_t)C, c0, C, part);
     __syncthreads();
-    store_tile_t(dst + (size_t)b * C * ldo, ldo, c0, C, (size_t)col0 + r0, min(TT, R - r0), tile);
+    tile.store(dst + (size_t)b * C * ldo, ldo, c0, C, (size_t)col0 + r0, min(kWeightRows, R - r0));
 }
 
 // padded length of an expert's column segment in the transposed activations
@@ -117,9 +142,9 @@ __global__ __launch_bounds__(256) void ragged_transpose_kernel(const uint16_t* _
                                                                const int32_t* __restrict__ offsets,
                                                                const int32_t* __restrict__ poff, int E, int C,
                                                                uint16_t* __restrict__ dst, size_t ldo) {
-    __shared__ __attribute__((aligned(16))) uint32_t tile[TT][TP];
+    __shared__ __attribute__((aligned(16))) ActTile tile;
     __shared__ int seg[2][2];   // of each half: first source row, valid rows from there on (-1: past the last segment)
-    const int p0 = blockIdx.y * TT, c0 = blockIdx.x * TT;
+    const int p0 = blockIdx.y * kActTile, c0 = blockIdx.x * kActTile;
     if (threadIdx.x < 2) seg[threadIdx.x][1] = -1;
     __syncthreads();
     for (int e = threadIdx.x; e < E; e += 256) {
@@ -137,10 +162,10 @@ __global__ __launch_bounds__(256) void ragged_transpose_kernel(const uint16_t* _
     __syncthreads();
     if (seg[0][1] < 0) return;   // past the last expert's padding: nothing to write
     const TransposeRows half[2] = {{seg[0][0], min(64, seg[0][1])}, {seg[1][0], min(64, seg[1][1])}};
-    const int n_out = seg[1][1] < 0 ? 64 : TT;
-    load_tile(src, (size_t)C, c0, C, half, tile);
+    const int n_out = seg[1][1] < 0 ? 64 : kActTile;
+    tile.load(src, (size_t)C, c0, C, half);
     __syncthreads();
-    store_tile_t(dst, ldo, c0, C, (size_t)p0, n_out, tile);
+    tile.store(dst, ldo, c0, C, (size_t)p0, n_out);
 }
 
 // dg | du from dh [rows, F] and g, u (bf16, rows ld_gu elements apart; out [rows, 2F]): with s = 1/(1+e^-g),
@@ -185,7 +210,7 @@ __global__ __launch_bounds__(256) void swiglu_backward_kernel(const uint16_t* __
 
 void launch_transpose_batched(const void* src, int B, int R, int C, void* dst, size_t ldo, int col0, hipStream_t s) {
     if (B <= 0 || R <= 0 || C <= 0) return;
-    hipLaunchKernelGGL(transpose_batched_kernel, dim3((C + TT - 1) / TT, (R + TT - 1) / TT, B), dim3(256), 0, s,
+    hipLaunchKernelGGL(transpose_batched_kernel, dim3((unsigned)((R + kWeightRows - 1) / kWeightRows) * ((C + kWeightCols - 1) / kWeightCols), 1, B), dim3(256), 0, s,
                        static_cast<const uint16_t*>(src), R, C, static_cast<uint16_t*>(dst), ldo, col0);
 }
 
@@ -198,8 +223,8 @@ void launch_ragged_offsets(const int32_t* offsets, int E, int32_t* poff, hipStre
 void launch_ragged_transpose(const void* src, const int32_t* offsets, const int32_t* poff, int E, int C, int rp_max,
                              void* dst, hipStream_t s) {
     if (rp_max <= 0 || C <= 0) return;
-    hipLaunchKernelGGL(ragged_transpose_kernel, dim3((C + TT - 1) / TT, (rp_max + TT - 1) / TT), dim3(256), 0, s,
-                       static_cast<const uint16_t*>(src), offsets, poff, E, C, static_cast<uint16_t*>(dst),
+    hipLaunchKernelGGL(ragged_transpose_kernel, dim3((C + kActTile - 1) / kActTile, (rp_max + kActTile - 1) / kActTile), dim3(256),
+                       0, s, static_cast<const uint16_t*>(src), offsets, poff, E, C, static_cast<uint16_t*>(dst),
                        (size_t)rp_max);
 }
 
