@@ -240,6 +240,36 @@ struct TileSched {
     }
 };
 
+// What lane l of a wave holds of experts 4l .. 4l+3, and the search over it: `first[q]` ascends over the experts.  All lanes of
+// the wave take part in both calls: a lane's values can be read while it is active only.
+struct ExpertLanes {
+    int first[4];   // exclusive prefix of what the experts have
+
+    // The last expert whose prefix is at most v (v differs from lane to lane): its lane, and its place q in that lane's four
+    __device__ __forceinline__ void find(int v, int E, int& lane_of, int& q) const {
+        lane_of = 0;
+#pragma unroll
+        for (int d = 32; d > 0; d >>= 1) {
+            const int c = lane_of + d;
+            if (__shfl(first[0], c, 64) <= v && 4 * c < E) lane_of = c;
+        }
+        q = 0;
+#pragma unroll
+        for (int j = 1; j < 4; ++j)
+            if (__shfl(first[j], lane_of, 64) <= v) q = j;
+    }
+    // of four values per lane, the one of the expert found
+    static __device__ __forceinline__ int at(const int (&v)[4], int lane_of, int q) {
+        int r = __shfl(v[0], lane_of, 64);
+#pragma unroll
+        for (int j = 1; j < 4; ++j) {
+            const int o = __shfl(v[j], lane_of, 64);
+            if (q == j) r = o;
+        }
+        return r;
+    }
+};
+
 // Schedule of the weight-gradient form: C [E, M, N], for expert e the product of
 // A_t[:, seg_e] and B_t[:, seg_e]^T over the expert's zero-padded column segment
 // (padded length = 0 for an expert without rows, else max(128, n rounded up to
@@ -248,13 +278,31 @@ struct TileSched {
 // not by tile count: every XCD takes the same eighth of EVERY expert's tiles (a
 // contiguous block of the expert's tile order, so the tiles an XCD runs at once
 // still share panels in its L2), and its workgroups walk that list round-robin.
-// Lane l describes experts 4l..4l+3.
+// The tiles of a workgroup are worked out 64 at a time: lane l of every wave describes the l-th of them, so that the search for
+// its expert and the divisions are made once for 64 tiles, and a tile costs a few readlanes.  A tile of these is a few k-tiles,
+// and finding it anew stood between two of them with the matrix pipe empty (three gradients of 64 experts x 172 rows, 6144 x
+// 2048: 1660 / 1628 us.  In the forward's schedule it made the down product 0.5 % faster and the gate/up product 1 % slower.)
 template <int BM, int BN>
 struct WgradSched {
-    int seg[4], len[4], pex[4], pend;   // segment start / padded length (elements), prefix of non-empty experts
-    int mt, nt, tpe, nwx, wgx, part0, part_n, total;   // part0/part_n: this XCD's slice of an expert's tiles
+    int t_m, t_n, t_e, t_seg, t_kt;                        // this lane's tile: k-tiles 0 = none
+    const int32_t* offsets;
+    int E, lane, batch, mt, nt;
 
-    __device__ __forceinline__ void init(const int32_t* __restrict__ offsets, int E, int M, int N, int lane) {
+    __device__ __forceinline__ void init(const int32_t* __restrict__ offsets_, int E_, int M, int N, int lane_) {
+        offsets = offsets_;
+        E = E_;
+        lane = lane_;
+        mt = (M + BM - 1) / BM;
+        nt = (N + BN - 1) / BN;
+        fill(0);
+    }
+
+    // tiles 64 b .. 64 b + 63 of this workgroup
+    __device__ __forceinline__ void fill(int b) {
+        constexpr int MG = 8;
+        batch = b;
+        int seg[4], len[4];   // segment start / padded length (elements)
+        ExpertLanes x;        // over the experts with rows
         int s_len = 0, s_cnt = 0;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -275,62 +323,55 @@ struct WgradSched {
             }
         }
         seg[0] = incl_len - s_len;
-        pex[0] = incl_cnt - s_cnt;
+        x.first[0] = incl_cnt - s_cnt;
 #pragma unroll
         for (int j = 1; j < 4; ++j) {
             seg[j] = seg[j - 1] + len[j - 1];
-            pex[j] = pex[j - 1] + (len[j - 1] > 0);
+            x.first[j] = x.first[j - 1] + (len[j - 1] > 0);
         }
-        pend = incl_cnt;
-        mt = (M + BM - 1) / BM;
-        nt = (N + BN - 1) / BN;
-        tpe = mt * nt;
-        const int xcd = blockIdx.x & 7;
-        part0 = (int)((long long)xcd * tpe / 8);
-        part_n = (int)((long long)(xcd + 1) * tpe / 8) - part0;
-        total = __builtin_amdgcn_readlane(incl_cnt, 63) * part_n;   // tiles of this XCD
-        wgx = blockIdx.x >> 3;
-        nwx = (gridDim.x + 7 - xcd) >> 3;
-    }
-
-    // the i-th tile of this workgroup; ld = elements per row of A_t and B_t
-    __device__ __forceinline__ PTile get(int i, const uint8_t* A, const uint8_t* B, int M, int N, int ld) const {
-        constexpr int MG = 8;
-        PTile t;
-        t.a = A; t.b0 = B; t.b1 = B; t.a_lim = 0; t.b_lim = 0; t.row0 = 0; t.rows = 0; t.n0 = 0; t.kt = 0; t.split = 0; t.krows = 0;
-        const int j = wgx + i * nwx;
-        t.valid = j < total;
-        if (!t.valid) return t;
-        const int qe = j / part_n;   // index among the non-empty experts (part_n > 0 since total > 0)
-        int hit = -1, my_seg = 0, my_len = 0;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-            if (len[q] > 0 && pex[q] == qe) {
-                hit = q; my_seg = seg[q]; my_len = len[q];
-            }
-        const uint64_t bal = __ballot(hit >= 0);  // exactly one lane holds the qe-th non-empty expert
-        const int src = __builtin_amdgcn_readfirstlane(__ffsll((unsigned long long)bal) - 1);
-        const int e = 4 * src + __builtin_amdgcn_readlane(hit, src);
-        const int seg_e = __builtin_amdgcn_readlane(my_seg, src);
-        const int len_e = __builtin_amdgcn_readlane(my_len, src);
+        const int xcd = blockIdx.x & 7, tpe = mt * nt;
+        const int part0 = (int)((long long)xcd * tpe / 8);           // this XCD's slice of an expert's tiles
+        const int part_n = (int)((long long)(xcd + 1) * tpe / 8) - part0;
+        const int total = __builtin_amdgcn_readlane(incl_cnt, 63) * part_n;   // tiles of this XCD
+        const int nwx = (gridDim.x + 7 - xcd) >> 3;
+        const int j = (int)(blockIdx.x >> 3) + (64 * b + lane) * nwx;
+        const bool valid = j < total;
+        const int qe = valid ? j / part_n : 0;   // index among the experts with rows (part_n > 0 since total > 0)
+        int at, q;
+        x.find(qe, E, at, q);   // experts without rows behind the qe-th one have the next index, those in front come first
+        t_e = 4 * at + q;
+        t_seg = ExpertLanes::at(seg, at, q);
+        const int len_e = ExpertLanes::at(len, at, q);
+        t_kt = valid ? len_e / 64 : 0;
         // inside an expert: groups of MG M-tiles, ordered (M-group, N, M-in-group)
-        const int Le = part0 + j - qe * part_n;
+        const int Le = part0 + (valid ? j - qe * part_n : 0);
         const int full = (mt / MG) * MG * nt;
-        int m, n;
         if (Le < full) {
             const int g = Le / (MG * nt), rem = Le - g * MG * nt;
-            n = rem / MG;
-            m = g * MG + rem - n * MG;
+            t_n = rem / MG;
+            t_m = g * MG + rem - t_n * MG;
         } else {
-            const int tail = mt % MG, rem = Le - full;   // tail > 0 here
-            n = rem / tail;
-            m = (mt / MG) * MG + rem - n * tail;
+            const int tail = max(mt % MG, 1), rem = Le - full;   // a tile here has tail > 0
+            t_n = rem / tail;
+            t_m = (mt / MG) * MG + rem - t_n * tail;
         }
+    }
+
+    // the i-th tile of this workgroup (asked for in ascending order); ld = elements per row of A_t and B_t
+    __device__ __forceinline__ PTile get(int i, const uint8_t* A, const uint8_t* B, int M, int N, int ld) {
+        PTile t;
+        t.a = A; t.b0 = B; t.b1 = B; t.a_lim = 0; t.b_lim = 0; t.row0 = 0; t.rows = 0; t.n0 = 0; t.kt = 0; t.split = 0; t.krows = 0;
+        if (uni(i >> 6) != batch) fill(uni(i >> 6));
+        const int l = uni(i & 63);
+        t.kt = __builtin_amdgcn_readlane(t_kt, l);
+        t.valid = t.kt > 0;
+        if (!t.valid) return t;
+        const int m = __builtin_amdgcn_readlane(t_m, l), n = __builtin_amdgcn_readlane(t_n, l);
+        const int e = __builtin_amdgcn_readlane(t_e, l), seg_e = __builtin_amdgcn_readlane(t_seg, l);
         const size_t k2 = (size_t)ld * 2;
         t.rows = uni(min(BM, M - m * BM));
         t.row0 = uni(e * M + m * BM);
         t.n0 = uni(n * BN);
-        t.kt = uni(len_e / 64);
         t.a = uni(A + (size_t)(m * BM) * k2 + (size_t)seg_e * 2);
         t.b0 = uni(B + (size_t)(n * BN) * k2 + (size_t)seg_e * 2);
         t.b1 = t.b0;
