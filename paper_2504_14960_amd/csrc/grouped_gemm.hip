@@ -172,7 +172,7 @@ bool launch_expert_ffn(const void* x_perm, const int32_t* offsets, int r_max, in
     }
     if (variant == 0 || !large) {
         // Tuned default, phase by phase (the second product reads what the first wrote): few rows per expert, and shapes
-        // without a large-tile kernel, go to the streaming kernel, the rest to the persistent 8-wave kernel with three
+        // without a large-tile kernel, go to the streaming kernel, the rest to the persistent four-wave kernel with three
         // LDS stages for the weight tile, and layers too shallow for its k stream to the one-workgroup-per-tile kernels
         // (8 waves gate/up, 4 waves down).
         bool ok = true;
