@@ -538,8 +538,8 @@ moe_status_t moe_gemm_clock_sample(uint64_t* ticks);
  * "gemm_variant" (bf16 expert FFN: 0 = auto = 42 with the one-workgroup-per-tile
  * kernel for layers whose H or F is below 128; 40 / 41 = persistent kernel with
  * three LDS stages for the activation tile, 4 / 8 waves; 42 / 43 = three stages
- * for the weight tile, 4 waves and the tile height chosen / 8 waves; 30 / 31 = one workgroup per tile, 4 / 8
- * waves; 99 = a plain LDS-tiled FMA kernel for any shape and type;
+ * for the weight tile and the tile height chosen, 4 / 8 waves; 30 / 31 = one
+ * workgroup per tile, 4 / 8 waves; 99 = a plain LDS-tiled FMA kernel for any shape and type;
  * any other value makes the expert calls return MOE_ERR_UNSUPPORTED);
  * "gemm_stream" (the weight-streaming expert kernel for few rows per expert: -1 =
  * chosen by size, the default; 0 = only for the shapes no other kernel takes; 1 =

@@ -19,8 +19,9 @@
 // eight waves of 32x32x16 / this: 8 experts of 16384 rows, 6144 x 16384, 5200 and
 // 2700 / 4850 and 2435 (1.36 PFLOP/s each); 8 x 4096 rows, 6144 x 2048, 1310 and 686 /
 // 1168 and 627; 64 skewed experts of 82000 rows, 4096 x 1408, 1663 and 919 / 1480
-// and 836.  Eight waves with the 16x16x32 instruction: 5110 and 2694, 1255 and 672,
-// 1668 and 914.
+// and 836.  Eight waves with the 16x16x32 instruction against this, on another card,
+// neither with scratch memory: 5122 and 2618 / 4875 and 2434; 1255 and 668 / 1188 and
+// 636; 1632 and 896 / 1487 and 834.
 //
 // What happens at a tile boundary:
 //
@@ -403,22 +404,28 @@ __device__ __forceinline__ void persist_body(
     };
     // Where the k-tile that a period fetches (kt + 2: the first two of the next tile in a tile's last two periods) lies: a
     // pointer per operand that moves on by a k-tile each period, and what a thread adds to it in each pass, the same for all
-    // k-tiles of a tile.
+    // k-tiles of a tile: kept with four waves, formed for every load with eight, which have no registers left for it.
+    constexpr bool KEEP = !KMAJ && NW == 4;
     const uint8_t *f_a, *f_b0, *f_b1;
-    uint32_t off_a[KMAJ ? 1 : PA], off_b[KMAJ ? 1 : PBD];
+    uint32_t off_a[KEEP ? PA : 1], off_b[KEEP ? PBD : 1];
     uint32_t f_alim = 0, f_blim = 0;
     int f_rows = 0;                                            // row-major form: valid rows from the k-tile's first row on
     const size_t kstep_a = KMAJ ? (size_t)64 * K * 2 : BK * 2;   // a k-tile is 64 elements along the rows, or 64 rows
     const size_t kstep_b = KMAJ ? (size_t)64 * ldb * 2 : BK * 2;
+    auto pass_offset = [&](int p, uint32_t lim) {   // ragged tail: a valid row again
+        uint32_t first = vrow;
+        if (!KEEP) asm volatile("" : "+v"(first));   // hidden, or the rows' sums are kept across the whole loop
+        return min(first + (uint32_t)p * step, lim) + vswz;
+    };
     auto fetch_from = [&](const uint8_t* a, const uint8_t* b0, const uint8_t* b1, uint32_t alim, uint32_t blim, int krows) {
         f_a = a; f_b0 = b0; f_b1 = b1;
-        if constexpr (KMAJ) {
-            f_alim = alim; f_blim = blim; f_rows = krows;
+        if constexpr (KEEP) {
+#pragma unroll
+            for (int p = 0; p < PA; ++p) off_a[p] = pass_offset(p, alim);
+#pragma unroll
+            for (int p = 0; p < PBD; ++p) off_b[p] = pass_offset(p, blim);
         } else {
-#pragma unroll
-            for (int p = 0; p < PA; ++p) off_a[p] = min(vrow + (uint32_t)p * step, alim) + vswz;  // ragged tail: a valid row again
-#pragma unroll
-            for (int p = 0; p < PBD; ++p) off_b[p] = min(vrow + (uint32_t)p * step, blim) + vswz;
+            f_alim = alim; f_blim = blim; f_rows = krows;
         }
     };
     auto fetch_step = [&]() {
@@ -431,14 +438,14 @@ __device__ __forceinline__ void persist_body(
         if constexpr (KMAJ)
             fetch_km(p, f_a, k2, f_alim, f_rows, st);
         else
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(f_a + off_a[p]),
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)(f_a + (KEEP ? off_a[KEEP ? p : 0] : pass_offset(p, f_alim))),
                                              (__attribute__((address_space(3))) void*)(st + p * RPP * ROWB + wbase), 16, 0, 0);
     };
     auto fetch_b = [&](int p, uint8_t* st) {
         if constexpr (KMAJ)
             fetch_km(p, f_b0, (uint32_t)ldb * 2u, f_blim, f_rows, st);
         else
-            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)((p >= PBD ? f_b1 : f_b0) + off_b[p % PBD]),
+            __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)((p >= PBD ? f_b1 : f_b0) + (KEEP ? off_b[KEEP ? p % PBD : 0] : pass_offset(p % PBD, f_blim))),
                                              (__attribute__((address_space(3))) void*)(st + p * RPP * ROWB + wbase), 16, 0, 0);
     };
     // load i of a period: i < PE -> pass i of the early operand's tile, else pass i - PE of the late operand's;
@@ -454,21 +461,18 @@ __device__ __forceinline__ void persist_body(
     };
 
     const int fr = lane & 15, fk = lane >> 4;
-    int a_off[FM], b_off[FN];
+    int a_off[FM], b_off[FN];   // row-major form: see km_off
+    int km_off[4];
     const int f_sw = lds_swizzle(fr);  // fragments start at multiples of 16 rows
     if constexpr (KMAJ) {
         // lane (group g = lane / 16, s = lane % 16) addresses row 8 g + s / 4 (and, second load, the row four further) of a
-        // k-step's 32, features 4 (s % 4) .. + 3 of the fragment's 16; its row decides the swizzle of the 64-byte unit
+        // k-step's 32, features 4 (s % 4) .. + 3 of the fragment's 16; its row decides the swizzle of the 64-byte unit.  The
+        // swizzle moves a fragment inside its 128 bytes only: four offsets do for all fragments of both operands.
         const int sl = lane & 15;
         const int r8 = 8 * fk + (sl >> 2);
         const int piece_in = (sl & 3) >> 1;   // 16-byte piece inside the fragment's 32 bytes
-        const int byte_in = 8 * (sl & 1);
 #pragma unroll
-        for (int i = 0; i < FM; ++i)
-            a_off[i] = r8 * 512 + ((((wm * WM + i * 16) >> 3) + piece_in) ^ (2 * (r8 & 3))) * 16 + byte_in;
-#pragma unroll
-        for (int j = 0; j < FN; ++j)
-            b_off[j] = r8 * 512 + ((((wn * WN + j * 16) >> 3) + piece_in) ^ (2 * (r8 & 3))) * 16 + byte_in;
+        for (int i = 0; i < 4; ++i) km_off[i] = r8 * 512 + ((2 * i + piece_in) ^ (2 * (r8 & 3))) * 16 + 8 * (sl & 1);
     } else {
 #pragma unroll
         for (int i = 0; i < FM; ++i) a_off[i] = (wm * WM + i * 16 + fr) * ROWB;
@@ -501,7 +505,8 @@ __device__ __forceinline__ void persist_body(
             // k-step s = rows 32 s .. 32 s + 31: two transposing loads of four rows for a lane's eight values
             typedef __attribute__((ext_vector_type(4))) short s16x4;
             typedef __attribute__((address_space(3))) s16x4 lds_s16x4;
-            const uint8_t* p = (q < FM ? sa + a_off[q] : sb + b_off[q - FM]) + s * (32 * 512);
+            const int t = q < FM ? q : q - FM;   // 16 features each, 32 bytes
+            const uint8_t* p = (q < FM ? sa + wm * (WM * 2) : sb + wn * (WN * 2)) + (t >> 2) * 128 + s * (32 * 512) + km_off[t & 3];
             const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p));
             const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s16x4*)(p + 4 * 512));
             typedef __attribute__((ext_vector_type(8))) short s16x8;
@@ -899,7 +904,7 @@ bool launch_persist_ffn(const void* x_perm, const int32_t* offsets, int r_max, i
         case 40: run_persist_pair<256, 256, 2, 2>(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, phase, s); return true;
         case 41: run_persist_pair<256, 256, 2, 4>(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, phase, s); return true;
         case 42: run_persist_pair<0, 256, 2, 2, true>(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, phase, s); return true;
-        case 43: run_persist_pair<256, 256, 2, 4, true>(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, phase, s); return true;
+        case 43: run_persist_pair<0, 256, 2, 4, true>(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, phase, s); return true;
         default: return false;
     }
 }
