@@ -482,9 +482,7 @@ moe_status_t moe_expert_weights_transpose(const void* w_gate, const void* w_up, 
     REQUIRE_PTR(fn, wgu_t);
     REQUIRE_PTR(fn, wd_t);
     hipStream_t s = static_cast<hipStream_t>(stream);
-    launch_transpose_batched(w_gate, E, F, H, wgu_t, (size_t)2 * F, 0, s);   // [E,F,H] -> [E,H,0:F]
-    launch_transpose_batched(w_up, E, F, H, wgu_t, (size_t)2 * F, F, s);     //            [E,H,F:2F]
-    launch_transpose_batched(w_down, E, H, F, wd_t, (size_t)H, 0, s);        // [E,H,F] -> [E,F,H]
+    launch_weights_transpose(w_gate, w_up, w_down, E, H, F, wgu_t, wd_t, s);
     return check_launch(fn);
 }
 

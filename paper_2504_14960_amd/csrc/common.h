@@ -145,8 +145,9 @@ void launch_sort_chunks(const void* src, int r_src, const int32_t* chunk_rows, i
 // C [rows, N] = A [rows, K] . B[e]^T, B [E, N, K], rows grouped by expert; false if the shape is not covered
 bool launch_grouped_nt(const void* A, const int32_t* offsets, int r_max, int E, int N, int K, const void* B,
                        void* C, hipStream_t s);
-// dst[b][c][col0 + r] = src[b][r][c], dst rows ld_out elements long
-void launch_transpose_batched(const void* src, int B, int R, int C, void* dst, size_t ld_out, int col0, hipStream_t s);
+// wgu_t [E,H,2F] = gate and up transposed side by side, wd_t [E,F,H] = down transposed; H, F multiples of 8
+void launch_weights_transpose(const void* w_gate, const void* w_up, const void* w_down, int E, int H, int F, void* wgu_t,
+                              void* wd_t, hipStream_t s);
 // dst [C, rp_max]: rows of expert e of src [rows, C] become the columns of its zero-padded segment
 void launch_ragged_offsets(const int32_t* offsets, int E, int32_t* poff, hipStream_t s);   // poff [E + 1]
 void launch_ragged_transpose(const void* src, const int32_t* offsets, const int32_t* poff, int E, int C, int rp_max,

@@ -24,14 +24,21 @@ namespace {
 // ---- transposes ----
 // Bound by HBM: every byte is read once and written once.  What counts is where the workgroups that run at the same time
 // read and write.
-// Weights: tiles of 256 rows x 64 columns, neighbours below one another, so that together they write whole rows of the
-// result, 512 bytes each (and read whole 128-byte lines, some rows apart), loads and stores streamed past the caches.  64
-// matrices of 2048 x 6144, into rows of 4096, and of 6144 x 2048, us: 128 x 128 tiles, neighbours beside one another, 631 and
-// 601 (5.1 and 5.4 TB/s); below one another and streamed, 593 and 576; 256 x 64 so 532 and 535 (6.0 TB/s), not streamed 574
-// and 576.  A plain copy of 1 GiB runs at 5.5 TB/s, streamed at 6.0 to 6.2.
-// Activations: 128 x 128 tiles, neighbours beside one another.  Their rows are often a power of two of bytes long, where
-// reads of 128 bytes from row after row meet in few channels: the four of a training step of 2048 tokens, 64 experts,
-// 6144 x 2048, 174 so and 191 in tiles of 256 x 64, 8192 tokens of 8 experts, 6144 x 16384, 787 and 772.
+// Weights, results of more than 140 MiB (gate, up and down together): tiles of 256 rows x 64 columns, neighbours below one
+// another, so that together they write whole rows of the result, 512 bytes each (and read whole 128-byte lines, some rows
+// apart), loads and stores streamed past the caches.  64 matrices of 2048 x 6144, into rows of 4096, and of 6144 x 2048, us:
+// 128 x 128 tiles, neighbours beside one another, 631 and 601 (5.1 and 5.4 TB/s); below one another and streamed, 593 and
+// 576; 256 x 64 so 532 and 535 (6.0 TB/s), not streamed 574 and 576.  A plain copy of 1 GiB runs at 5.5 TB/s, streamed at 6.0
+// to 6.2.
+// Weights, smaller results: 128 x 128 tiles, neighbours beside one another, not streamed.  The products behind find the results
+// in the 256 MB memory-side cache; larger ones they would not, and what is still to be written back holds them up.  The
+// three transposes, dh and dx, us, streamed in tiles of 256 x 64 / so: 4 experts x 53 rows, 1024 x 1024 (25 MB) 55 / 47; 8 x
+// 60, 1024 x 2048 (101 MB) 97 / 74; 8 x 100 and 8 x 800, 1024 x 2560 (126 MB) 113 / 102 and 216 / 223; 16 x 50 and 16 x 200,
+// 1024 x 1408 (138 MB) 114 / 109 and 144 / 147; 8 x 100 and 8 x 600, 1024 x 3072 (151 MB) 127 / 126 and 229 / 236; 8 x 200,
+// 2048 x 1536 (151 MB) 139 / 146.
+// Activations: 128 x 128 tiles, neighbours beside one another; which of the two forms is ahead depends on the sizes: the four of
+// a training step of 2048 tokens, 64 experts, 6144 x 2048, 174 so and 191 in tiles of 256 x 64, of 8192 tokens, 8 experts,
+// 6144 x 16384, 787 and 772.
 // All eight loads of a thread in flight, and 32-bit LDS traffic: a thread takes the same eight columns of two adjacent
 // rows, so that a dword of the transposed tile is one of its element pairs, and the tile [column][row pair] is read back 16
 // bytes at a time.  Group g of four dwords of column c lies at g ^ (c / 8) (64 columns: g ^ 2 (c / 8)): the 64 dwords a wave
@@ -93,23 +100,31 @@ struct TransposeTile {
         }
     }
 };
-using WeightTile = TransposeTile<256, 64, true>;
-constexpr int kWeightRows = 256, kWeightCols = 64;
 using ActTile = TransposeTile<128, 128, false>;
 constexpr int kActTile = 128;
+constexpr size_t kCachedBytes = 140u << 20;   // results up to here are left to the caches
 
-// dst[b][c][col0 + r] = src[b][r][c];  R, C multiples of 8.
+// dst[b][c][col0 + r] = src[b][r][c];  R, C multiples of 8.  DOWN: neighbouring workgroups below one another.
+template <int TR, int TC, bool STREAM, bool DOWN>
 __global__ __launch_bounds__(256) void transpose_batched_kernel(const uint16_t* __restrict__ src, int R, int C,
                                                                 uint16_t* __restrict__ dst, size_t ldo, int col0) {
-    __shared__ __attribute__((aligned(16))) WeightTile tile;
-    const int nr = (R + kWeightRows - 1) / kWeightRows;
-    const int b = blockIdx.z, r0 = (int)(blockIdx.x % nr) * kWeightRows, c0 = (int)(blockIdx.x / nr) * kWeightCols;
-    TransposeRows part[WeightTile::PARTS];
+    using Tile = TransposeTile<TR, TC, STREAM>;
+    __shared__ __attribute__((aligned(16))) Tile tile;
+    const unsigned across = DOWN ? (R + TR - 1) / TR : (C + TC - 1) / TC;
+    const int near = (int)(blockIdx.x % across), far = (int)(blockIdx.x / across);
+    const int b = blockIdx.z, r0 = (DOWN ? near : far) * TR, c0 = (DOWN ? far : near) * TC;
+    TransposeRows part[Tile::PARTS];
 #pragma unroll
-    for (int q = 0; q < WeightTile::PARTS; ++q) part[q] = {r0 + 64 * q, R - r0 - 64 * q};
+    for (int q = 0; q < Tile::PARTS; ++q) part[q] = {r0 + 64 * q, R - r0 - 64 * q};
     tile.load(src + (size_t)b * R * C, (size_t)C, c0, C, part);
     __syncthreads();
-    tile.store(dst + (size_t)b * C * ldo, ldo, c0, C, (size_t)col0 + r0, min(kWeightRows, R - r0));
+    tile.store(dst + (size_t)b * C * ldo, ldo, c0, C, (size_t)col0 + r0, min(TR, R - r0));
+}
+
+template <int TR, int TC, bool STREAM, bool DOWN>
+void transpose_batched(const void* src, int B, int R, int C, void* dst, size_t ldo, int col0, hipStream_t s) {
+    hipLaunchKernelGGL((transpose_batched_kernel<TR, TC, STREAM, DOWN>), dim3((unsigned)((R + TR - 1) / TR) * ((C + TC - 1) / TC), 1, B),
+                       dim3(256), 0, s, static_cast<const uint16_t*>(src), R, C, static_cast<uint16_t*>(dst), ldo, col0);
 }
 
 // padded length of an expert's column segment in the transposed activations
@@ -208,10 +223,13 @@ __global__ __launch_bounds__(256) void swiglu_backward_kernel(const uint16_t* __
 
 }  // namespace
 
-void launch_transpose_batched(const void* src, int B, int R, int C, void* dst, size_t ldo, int col0, hipStream_t s) {
-    if (B <= 0 || R <= 0 || C <= 0) return;
-    hipLaunchKernelGGL(transpose_batched_kernel, dim3((unsigned)((R + kWeightRows - 1) / kWeightRows) * ((C + kWeightCols - 1) / kWeightCols), 1, B), dim3(256), 0, s,
-                       static_cast<const uint16_t*>(src), R, C, static_cast<uint16_t*>(dst), ldo, col0);
+void launch_weights_transpose(const void* w_gate, const void* w_up, const void* w_down, int E, int H, int F, void* wgu_t,
+                              void* wd_t, hipStream_t s) {
+    const auto transpose = (size_t)6 * E * H * F <= kCachedBytes ? transpose_batched<128, 128, false, false>
+                                                                 : transpose_batched<256, 64, true, true>;
+    transpose(w_gate, E, F, H, wgu_t, (size_t)2 * F, 0, s);   // [E,F,H] -> [E,H,0:F]
+    transpose(w_up, E, F, H, wgu_t, (size_t)2 * F, F, s);     //            [E,H,F:2F]
+    transpose(w_down, E, H, F, wd_t, (size_t)H, 0, s);        // [E,H,F] -> [E,F,H]
 }
 
 void launch_ragged_offsets(const int32_t* offsets, int E, int32_t* poff, hipStream_t s) {

@@ -1,4 +1,5 @@
-"""The weights' transposes in tiles of 256 rows x 64 columns: bit for bit, where rows and columns do not divide into tiles."""
+"""The weights' transposes, bit for bit: in tiles of 128 x 128, and, with results of more than 140 MiB, of 256 rows x 64 columns,
+where rows do not divide into tiles (rows and columns are multiples of 128: columns always do)."""
 import pytest
 import torch
 
@@ -7,7 +8,9 @@ import paper_2504_14960_amd as moe
 pytestmark = pytest.mark.gpu
 
 
-@pytest.mark.parametrize("E,H,F", [(1, 128, 128), (3, 384, 128), (2, 128, 640), (2, 640, 896), (1, 256, 2048)])
+@pytest.mark.parametrize("E,H,F", [(1, 128, 128), (3, 384, 128), (2, 128, 640), (2, 640, 896), (1, 256, 2048),
+                                   (42, 640, 896), (43, 640, 896),      # results on both sides of 140 MiB
+                                   (33, 2304, 384), (256, 384, 256)])
 def test_weights_transposed_bit_for_bit(E, H, F):
     gen = torch.Generator(device="cuda").manual_seed(E * H + F)
 
