@@ -765,11 +765,11 @@ __global__ __launch_bounds__(256) void wgrad_zero_empty_kernel(const int32_t* __
         dst[i] = u32x4{0u, 0u, 0u, 0u};
 }
 
-template <int BM, int BN, int WGM, int WGN, bool STREAM_OUT>
+template <int BM, int BN, int WGM, int WGN, bool STREAM_OUT, bool DEEP_B = false>
 void launch_persist_groupk(const void* A, const void* B, const int32_t* offsets, int E, int M, int N, int ld,
                            void* C, hipStream_t s) {
-    constexpr size_t smem = (size_t)(3 * BM + 2 * BN) * 64 * 2;
-    auto kern = gemm_bf16_persist_kernel<BM, BN, WGM, WGN, 0, true, false, false, false, true, STREAM_OUT>;
+    constexpr size_t smem = (size_t)(DEEP_B ? 2 * BM + 3 * BN : 3 * BM + 2 * BN) * 64 * 2;
+    auto kern = gemm_bf16_persist_kernel<BM, BN, WGM, WGN, 0, true, false, false, DEEP_B, true, STREAM_OUT>;
     static OncePerDevice lds;
     allow_lds(lds, reinterpret_cast<const void*>(kern), (int)smem);
     const long long tiles = (long long)E * ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
@@ -836,6 +836,16 @@ void launch_wgrad_zero_empty(const int32_t* offsets, int E, size_t per_expert, v
 // dw [E, M, N] = per expert a_t[:, seg_e] . b_t[:, seg_e]^T (see WgradSched); M, N multiples of 8, ld of 64
 void launch_persist_wgrad(const void* a_t, const void* b_t, const int32_t* offsets, int E, int M, int N, int ld,
                           void* dw, hipStream_t s) {
+    // Tiles of 128 rows where those of 256 are at most one to every second workgroup: a compute unit has one tile then, as long
+    // as its k-tiles are one after the other, and with four waves nothing covers what they wait for.  One gradient, us, 256 rows /
+    // 128 (streamed too, at any number of rows): 4 experts x 53 rows, 1024 x 1024, 9.8 / 8.4 not streamed; 4 x 60, 4 x 250 and
+    // 4 x 600, 1024 x 1792, 15.1, 21.4 and 36.6 / 8.0, 10.3 and 16.1; 8 x 60, 500 and 2000, 1024 x 1024 (128 tiles of 256)
+    // 10.4, 18.3 and 53.0 / 8.3, 15.6 and 41.6, not streamed 10.1, 18.9 and 42.1.
+    const long long tiles = (long long)E * ((M + 255) / 256) * ((N + 255) / 256);
+    if (2 * tiles <= persist_grid() && N <= kMaxColumns) {
+        launch_persist_groupk<128, 256, 2, 2, true, true>(a_t, b_t, offsets, E, M, N, ld, dw, s);
+        return;
+    }
     // Gradients streamed past the L2 (us, the expert FFN's backward, stored as usual / so):
     //   64 experts, 6144 x 2048: 256 rows 3364 / 3155, 512 rows 5260 / 5180, 768 rows 7368 / 7306, 1024 rows 9350 / 9314
     //   8 experts, 4096 x 4096:  256 rows 703 / 625, 512 rows 900 / 832, 1024 rows 1539 / 1505, 1536 rows 2178 / 2169

@@ -48,3 +48,20 @@ def test_more_tiles_than_are_worked_out_at_a_time(E, H, F):
         want = dy[off[e]:off[e + 1]].float().T @ h[off[e]:off[e + 1]].float()
         # products and sums in fp32 on both sides, the result rounded once: half a bf16 step of the largest, and the sums' noise
         assert (few[2][e].float() - want).abs().max() <= 2.0 ** -8 * max(want.abs().max().item(), 1e-30) * 1.01, f"expert {e}"
+
+
+@pytest.mark.parametrize("E,H,F", [(1, 128, 128), (4, 1024, 1024), (3, 384, 640), (8, 1024, 1024), (5, 896, 1152)])
+def test_few_tiles_are_128_rows_high(E, H, F):
+    """Launches whose 256-row tiles would leave half of the workgroups without one: the bits of the 256-row tiles, which eight
+    workgroups get, with many rows and few, and experts without rows."""
+    rng = np.random.default_rng(E * H)
+    counts = rng.integers(1, 900, size=E)
+    if E > 2:
+        counts[1], counts[E // 2] = 0, 3
+    low, dy, h, off = _gradients(E, H, F, counts, 0)
+    tall, _, _, _ = _gradients(E, H, F, counts, 8)
+    for a, b in zip(low, tall):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+    for e in range(E):
+        want = dy[off[e]:off[e + 1]].float().T @ h[off[e]:off[e + 1]].float()
+        assert (low[2][e].float() - want).abs().max() <= 2.0 ** -8 * max(want.abs().max().item(), 1e-30) * 1.01, f"expert {e}"
