@@ -1,5 +1,6 @@
-"""Weight gradients of more tiles than a workgroup works out at a time (64), with several experts to a lane and empty ones
-between them: every tile is written, at its place, with the bits that one tile per workgroup gives."""
+"""Schedules of the weight gradients.  More tiles than a workgroup works out at a time (64): several experts to a lane and empty
+ones between them; several tiles of an expert and tiles of different lengths on both sides of the 64th.  Every tile is written, at
+its place, with the bits that other numbers of workgroups give.  And tiles of 128 rows, where there are few."""
 import numpy as np
 import pytest
 import torch
@@ -31,7 +32,7 @@ def _gradients(E, H, F, counts, workgroups):
         torch.cuda.synchronize()
     finally:
         moe.set_option("gemm_workgroups", 0)
-    return dw, dy, h, offsets.tolist()
+    return dw, (x, dy, h, gu, wd_t), offsets.tolist()
 
 
 @pytest.mark.parametrize("E,H,F", [(150, 384, 256), (256, 128, 128), (9, 2304, 2048)])
@@ -40,14 +41,46 @@ def test_more_tiles_than_are_worked_out_at_a_time(E, H, F):
     counts = rng.integers(0, 70, size=E)
     counts[rng.integers(0, E, size=E // 4)] = 0            # empty experts, next to one another too
     counts[-1] = 0
-    one, dy, h, off = _gradients(E, H, F, counts, 0)       # as many workgroups as there are tiles, at most one per compute unit
-    few, _, _, _ = _gradients(E, H, F, counts, 8)          # one per XCD
+    one, (_, dy, h, _, _), off = _gradients(E, H, F, counts, 0)   # as many workgroups as there are tiles, at most one per compute unit
+    few, _, _ = _gradients(E, H, F, counts, 8)                    # one per XCD
     for a, b in zip(one, few):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
     for e in range(E):
         want = dy[off[e]:off[e + 1]].float().T @ h[off[e]:off[e + 1]].float()
         # products and sums in fp32 on both sides, the result rounded once: half a bf16 step of the largest, and the sums' noise
         assert (few[2][e].float() - want).abs().max() <= 2.0 ** -8 * max(want.abs().max().item(), 1e-30) * 1.01, f"expert {e}"
+
+
+def _fewest_tiles(M, N, experts):
+    """256-row tiles of the workgroup that has least of them, eight workgroups, one per XCD: an eighth of every expert's each."""
+    per_expert = -(-M // 256) * -(-N // 256)
+    return experts * min((x + 1) * per_expert // 8 - x * per_expert // 8 for x in range(8))
+
+
+# 9 and 3 or 4 tiles of an expert to a workgroup, M-groups of eight and the M-tiles left over; two to seven k-tiles (results
+# streamed), and nine to twelve (up to 640 padded rows per expert on average they are streamed, here they are not)
+@pytest.mark.parametrize("E,H,F,rows", [(26, 2304, 2048, (1, 70, 130, 200, 400, 0)), (28, 1536, 1280, (520, 700, 560, 750, 600, 0))])
+def test_tiles_of_several_lengths_on_both_sides_of_the_64th(E, H, F, rows):
+    counts = np.array([rows[(e * e + e // 4) % len(rows)] for e in range(E)])
+    assert min(_fewest_tiles(H, F, (counts > 0).sum()), _fewest_tiles(F, H, (counts > 0).sum())) > 64
+    padded = counts.sum() + 127 * E
+    assert (padded <= 640 * E) == (max(rows) < 500)
+    few, (x, dy, h, gu, wd_t), off = _gradients(E, H, F, counts, 8)
+    one, _, _ = _gradients(E, H, F, counts, 0)
+    for a, b in zip(one, few):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+    for e in range(E):
+        r = slice(off[e], off[e + 1])
+        g, u = gu[r].float().split(F, dim=1)
+        dh = (dy[r].float() @ wd_t[e].float().T).bfloat16().float()      # rounded before the derivative, as the library does
+        sig = torch.sigmoid(g)
+        dg, du = (dh * u * sig * (1 + g * (1 - sig))).bfloat16().float(), (dh * g * sig).bfloat16().float()
+        for got, left, right, steps in ((few[0], dg, x[r].float(), 4), (few[1], du, x[r].float(), 4), (few[2], dy[r].float(), h[r].float(), 0)):
+            want = left.T @ right
+            # the result rounded once (as above); and an element of dg or du that falls on the neighbouring bf16 step, through
+            # dh's rounding or its own, moves a sum by up to 2^-7 of its product: four of those
+            moved = 0.0 if off[e] == off[e + 1] else steps * 2.0 ** -7 * (left.abs().max() * right.abs().max()).item()
+            assert (got[e].float() - want).abs().max() <= 2.0 ** -8 * want.abs().max() + moved, f"expert {e}"
 
 
 @pytest.mark.parametrize("E,H,F", [(1, 128, 128), (4, 1024, 1024), (3, 384, 640), (8, 1024, 1024), (5, 896, 1152)])
@@ -58,8 +91,8 @@ def test_few_tiles_are_128_rows_high(E, H, F):
     counts = rng.integers(1, 900, size=E)
     if E > 2:
         counts[1], counts[E // 2] = 0, 3
-    low, dy, h, off = _gradients(E, H, F, counts, 0)
-    tall, _, _, _ = _gradients(E, H, F, counts, 8)
+    low, (_, dy, h, _, _), off = _gradients(E, H, F, counts, 0)
+    tall, _, _ = _gradients(E, H, F, counts, 8)
     for a, b in zip(low, tall):
         assert torch.equal(a.view(torch.int16), b.view(torch.int16))
     for e in range(E):
