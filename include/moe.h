@@ -535,8 +535,8 @@ moe_status_t moe_gemm_clock_sample(uint64_t* ticks);
 
 /* Tuning knobs for experiments (process-wide, not thread-safe; defaults are
  * the tuned ones).  Unknown names return MOE_ERR_INVALID_ARG.  Names:
- * "gemm_variant" (bf16 expert FFN: 0 = auto = 42 with the one-workgroup-per-tile
- * kernel for layers whose H or F is below 128; 40 / 41 = persistent kernel with
+ * "gemm_variant" (bf16 expert FFN: 0 = auto = 42, or 43 for few rows and short
+ * contractions, with the one-workgroup-per-tile kernel for layers whose H or F is below 128; 40 / 41 = persistent kernel with
  * three LDS stages for the activation tile, 4 / 8 waves; 42 / 43 = three stages
  * for the weight tile and the tile height chosen, 4 / 8 waves; 30 / 31 = one
  * workgroup per tile, 4 / 8 waves; 99 = a plain LDS-tiled FMA kernel for any shape and type;

@@ -303,7 +303,12 @@ __device__ __forceinline__ void persist_body(
     constexpr int A_ONE = NW == 8 && FM == 8 ? FM - 2 : 0;
     constexpr int NTWO = NREAD - A_ONE;
     // The early operand's loads are issued behind the barrier, in k-step 1, the late operand's in k-step 0: what a barrier
-    // waits for is a whole period old.
+    // waits for is a whole period old.  In tiles of 128 rows, chosen where the weights are what is waited for, the early ones
+    // are issued one behind the other and not spread over the k-step: queued behind the weights, the activations are what the
+    // barrier waits for.  (Four waves, us, spread / so: 16 experts x 60 rows, 4096 x 1408, gate/up 77.8 / 75.3; 16 x 40, 6144 x 2048,
+    // down 104 / 100; 60 x 40, 2048 x 1408, gate/up 139 / 135; 64 x 170, 3584 x 2560, gate/up 590 / 565.  With the weights' loads one
+    // behind the other too 564 there, but 8 x 90, 2048 x 4096, down takes 45.1 and not 41.5.)
+    constexpr int EARLY_STEP = BM == 128 ? 1 : (FM * FN) / PE;
     // STREAM_OUT: stores of a tile's epilogue, per wave (RowBuffer).  Loads and stores are counted together and complete in
     // order, and a wait for the loads behind an epilogue is a wait for its stores.  All that the first period of a tile waits
     // for was asked for in front of the stores of the tile before, so it need not wait for them; the second period, 1.5 us
@@ -550,7 +555,7 @@ __device__ __forceinline__ void persist_body(
             for (int r = (slot * NTWO + RS - 1) / RS; r < ((slot + 1) * NTWO + RS - 1) / RS && r < NTWO; ++r)
                 read_one(rd_a, rd_b, rd_s, mf_buf ^ 1, two_sets(r));
             if (A_ONE > 0 && slot % FN == FN - 1 && slot / FN < A_ONE) read_one(rd_a, rd_b, rd_s, mf_buf ^ 1, slot / FN);
-            if (ld < ld_end && slot == 1 + (ld - ld_begin) * NSLOT / (ld_end - ld_begin)) {
+            if (ld < ld_end && slot == 1 + (ld_begin == 0 ? ld * EARLY_STEP : (ld - ld_begin) * NSLOT / (ld_end - ld_begin))) {
                 fetch_one(ld, ld_b, ld_a);
                 ++ld;
             }
@@ -794,6 +799,26 @@ void launch_persist_groupk_rowmajor(const void* A, int lda, const void* B, int l
                        static_cast<bf16_t*>(const_cast<void*>(zero_row)), M, ldb, 1, 0, g_persist_ticks);
 }
 
+// Four waves or eight, the tile's height chosen on the device.  Four are ahead where power is what bounds a product.  With few rows
+// and a short contraction a tile is a few k-tiles of which memory is waited for, and two waves to a SIMD cover more of that, of the
+// epilogue and of the tails that leave waves idle.  (us, four / eight: 60 experts x 40 rows, 1664 x 512, gate/up 38.3 / 36.7 as it is saved,
+// down 24.7 / 22.6; 24 x 40, 3584 x 896, down 32.6 / 30.0; 64 x 110, 2048 x 512, down 35.0 / 32.5; 48 x 40, 2048 x 2048, gate/up 187 / 181,
+// down 106 / 103; 60 x 110, 1664 x 1920, down 96.8 / 96.3.  At 200 rows: 16 experts, 2048 x 1408, gate/up 45.1 / 45.6; 24, 3584 x 896,
+// 88.5 / 93.0; 64, 1536 x 1152, down 65.1 / 66.7.  Longer contractions are level, or behind: 64 x 64 rows, 6144 x 2048, dx 577 / 594.)
+// The gate/up product that saves its pre-activations stores three times as much, and eight waves stay ahead for longer (96 x 200 rows, 1280 x
+// 1792, 292 / 275; 48 x 152, 2048 x 2048, 211 / 204; 60 x 154, 1664 x 1920, 218 / 208).
+template <int MODE>
+void launch_persist_chosen(const void* A, const int32_t* offsets, int r_max, int E, int N, int K, const void* B0, const void* B1,
+                           void* C, void* GU, hipStream_t s) {
+    if constexpr (MODE != 3) {
+        if (K <= 2048 && r_max <= (MODE == 2 ? 224ll : 128ll) * E) {
+            launch_persist<0, 256, 2, 4, MODE, true>(A, offsets, r_max, E, N, K, B0, B1, C, GU, s);
+            return;
+        }
+    }
+    launch_persist<0, 256, 2, 2, MODE, true>(A, offsets, r_max, E, N, K, B0, B1, C, GU, s);
+}
+
 template <int BM, int BN, int WGM, int WGN, bool DEEP_B = false>
 void run_persist_pair(const void* x_perm, const int32_t* offsets, int r_max, int H, int F, int E,
                       const void* w_gate, const void* w_up, const void* w_down, void* h, void* y_perm, int phase,
@@ -822,7 +847,7 @@ bool launch_grouped_nt(const void* A, const int32_t* offsets, int r_max, int E, 
         launch_stream(plan, kStreamBf16, A, offsets, r_max, E, N, K, B, nullptr, C, nullptr, 0.f, 0.f, 0.f, nullptr, nullptr, s);
         return true;
     }
-    launch_persist<0, 256, 2, 2, 0, true>(A, offsets, r_max, E, N, K, B, nullptr, C, nullptr, s);
+    launch_persist_chosen<0>(A, offsets, r_max, E, N, K, B, nullptr, C, nullptr, s);
     return true;
 }
 
@@ -868,7 +893,7 @@ void launch_persist_wgrad_rowmajor(const void* a, int lda, const void* b, int ld
 bool launch_grouped_nt_swiglu_bwd(const void* A, const int32_t* offsets, int r_max, int E, int N, int K,
                                   const void* B, const void* gu, void* dgdu, hipStream_t s) {
     if (K < 128 || K % 64 || N % 8) return false;
-    launch_persist<0, 256, 2, 2, 3, true>(A, offsets, r_max, E, N, K, B, nullptr, dgdu, const_cast<void*>(gu), s);
+    launch_persist_chosen<3>(A, offsets, r_max, E, N, K, B, nullptr, dgdu, const_cast<void*>(gu), s);
     return true;
 }
 
@@ -881,7 +906,7 @@ bool launch_gate_up_saving(const void* x_perm, const int32_t* offsets, int r_max
         launch_stream(plan, kStreamBf16, x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, gu, 0.f, 0.f, 0.f, nullptr, nullptr, s);
         return true;
     }
-    launch_persist<0, 256, 2, 2, 2, true>(x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, gu, s);
+    launch_persist_chosen<2>(x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, gu, s);
     return true;
 }
 
@@ -911,6 +936,10 @@ bool launch_persist_ffn(const void* x_perm, const int32_t* offsets, int r_max, i
                         int variant, int phase, hipStream_t s) {
     if (H < 128 || F < 128) return false;  // the k stream needs at least two k-tiles per output tile
     switch (variant) {
+        case 0:
+            if (phase & 1) launch_persist_chosen<1>(x_perm, offsets, r_max, E, F, H, w_gate, w_up, h, nullptr, s);
+            if (phase & 2) launch_persist_chosen<0>(h, offsets, r_max, E, H, F, w_down, nullptr, y_perm, nullptr, s);
+            return true;
         case 40: run_persist_pair<256, 256, 2, 2>(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, phase, s); return true;
         case 41: run_persist_pair<256, 256, 2, 4>(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, phase, s); return true;
         case 42: run_persist_pair<0, 256, 2, 2, true>(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, phase, s); return true;

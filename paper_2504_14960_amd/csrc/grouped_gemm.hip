@@ -150,7 +150,7 @@ static bool launch_phase(const StreamPlan& plan, int ph, int elt, const void* x_
         launch_stream_reduce(ph == 1, static_cast<float*>(part), offsets, E, plan.splits, r_max, N, C, s);
         return true;
     }
-    return launch_persist_ffn(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, 42, ph, s) ||
+    return launch_persist_ffn(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, 0, ph, s) ||
            launch_pipe3_ffn(x_perm, offsets, r_max, H, F, E, w_gate, w_up, w_down, h, y_perm, ph == 1 ? 31 : 30, ph, s);
 }
 
@@ -172,8 +172,8 @@ bool launch_expert_ffn(const void* x_perm, const int32_t* offsets, int r_max, in
     }
     if (variant == 0 || !large) {
         // Tuned default, phase by phase (the second product reads what the first wrote): few rows per expert, and shapes
-        // without a large-tile kernel, go to the streaming kernel, the rest to the persistent four-wave kernel with three
-        // LDS stages for the weight tile, and layers too shallow for its k stream to the one-workgroup-per-tile kernels
+        // without a large-tile kernel, go to the streaming kernel, the rest to the persistent kernel with three
+        // LDS stages for the weight tile, on four or eight waves, and layers too shallow for its k stream to the one-workgroup-per-tile kernels
         // (8 waves gate/up, 4 waves down).
         bool ok = true;
         for (int ph = 1; ph <= 2; ph <<= 1) {

@@ -69,3 +69,32 @@ def test_waves_without_rows_leave_no_trace(H, F, rows):
         return h, y, amax
 
     _both(fp8, rows)
+
+
+@pytest.mark.parametrize("rows", [256, 192, 128])
+@pytest.mark.parametrize("H,F", [(256, 384), (384, 256)])
+def test_waves_without_rows_in_fp8_with_three_activation_stages(H, F, rows):
+    off, R = _offsets()
+    E = len(COUNTS)
+    gen = torch.Generator(device="cuda").manual_seed(H + 1)
+
+    def codes(*shape):
+        c = torch.empty(shape, dtype=torch.uint8, device="cuda")
+        moe.fp8_quantize(torch.empty(shape, dtype=torch.bfloat16, device="cuda").normal_(generator=gen), 448 / 5.5, c)
+        return c
+
+    x8, wg8, wu8, wd8 = codes(R, H), codes(E, F, H), codes(E, F, H), codes(E, H, F)
+
+    def fp8():
+        h, y = torch.zeros(R, F, dtype=torch.uint8, device="cuda"), torch.zeros(R, H, dtype=torch.bfloat16, device="cuda")
+        amax = torch.zeros(1, device="cuda")
+        moe.expert_gate_up_fp8(x8, off, wg8, wu8, 1e-4, 1e-4, 64.0, h, amax)
+        moe.expert_down_fp8(h, off, wd8, 1e-4, y)
+        assert bool(torch.isfinite(amax).all()) and float(amax) > 0
+        return h, y, amax
+
+    moe.set_option("fp8_deep_weights", 0)
+    try:
+        _both(fp8, rows)
+    finally:
+        moe.set_option("fp8_deep_weights", 1)
