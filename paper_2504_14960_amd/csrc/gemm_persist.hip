@@ -861,12 +861,22 @@ void launch_wgrad_zero_empty(const int32_t* offsets, int E, size_t per_expert, v
 // dw [E, M, N] = per expert a_t[:, seg_e] . b_t[:, seg_e]^T (see WgradSched); M, N multiples of 8, ld of 64
 void launch_persist_wgrad(const void* a_t, const void* b_t, const int32_t* offsets, int E, int M, int N, int ld,
                           void* dw, hipStream_t s) {
+    const long long per_expert = (long long)((M + 255) / 256) * ((N + 255) / 256), tiles = E * per_expert;
+    // Up to some 97 rows per expert (the padding included, a tile is then two k-tiles and its store): four waves wait between the two,
+    // eight of 64 x 64 cover it.  Tiles of 128 rows, the 256 columns in three stages, streamed.  The backward, us, four waves of 256 rows / so:
+    // 4 experts x 60 rows, 2048 x 2048, 114 / 100; 24 x 60, 2048 x 512, 139 / 126; 32 x 40, 2048 x 2048, 468 / 426; 60 x 40, 1664 x 1920, 639 / 585;
+    // 40 x 60, 3072 x 1792, 670 / 640; 16 x 60, 6144 x 2048, 580 / 576; 64 x 100, 2560 x 1536, level.  On the other side of the lines: 128 experts
+    // x 60 rows, 2048 x 768, 698 / 722; 96 x 59, 2048 x 1024, 694 / 717; 64 x 60, 2816 x 2048, 1054 / 1080; 4 x 60, 4096 x 4096, 257 / 261; 48 x 122, 4096 x
+    // 1024, 710 / 742 (8 to 16 experts gain up to 160 rows, 2 to 9 %).  The tiles' operands, one and a half times as many, are what costs.
+    if (ld <= 224ll * E && E <= 64 && per_expert < 256 && (long long)E * M * N <= 1ll << 28 && N <= kMaxColumns) {
+        launch_persist_groupk<128, 256, 2, 4, true, true>(a_t, b_t, offsets, E, M, N, ld, dw, s);
+        return;
+    }
     // Tiles of 128 rows where those of 256 are at most one to every second workgroup: a compute unit has one tile then, as long
     // as its k-tiles are one after the other, and with four waves nothing covers what they wait for.  One gradient, us, 256 rows /
     // 128 (streamed too, at any number of rows): 4 experts x 53 rows, 1024 x 1024, 9.8 / 8.4 not streamed; 4 x 60, 4 x 250 and
     // 4 x 600, 1024 x 1792, 15.1, 21.4 and 36.6 / 8.0, 10.3 and 16.1; 8 x 60, 500 and 2000, 1024 x 1024 (128 tiles of 256)
     // 10.4, 18.3 and 53.0 / 8.3, 15.6 and 41.6, not streamed 10.1, 18.9 and 42.1.
-    const long long tiles = (long long)E * ((M + 255) / 256) * ((N + 255) / 256);
     if (2 * tiles <= persist_grid() && N <= kMaxColumns) {
         launch_persist_groupk<128, 256, 2, 2, true, true>(a_t, b_t, offsets, E, M, N, ld, dw, s);
         return;

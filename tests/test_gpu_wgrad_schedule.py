@@ -98,3 +98,33 @@ def test_few_tiles_are_128_rows_high(E, H, F):
     for e in range(E):
         want = dy[off[e]:off[e + 1]].float().T @ h[off[e]:off[e + 1]].float()
         assert (low[2][e].float() - want).abs().max() <= 2.0 ** -8 * max(want.abs().max().item(), 1e-30) * 1.01, f"expert {e}"
+
+
+# one expert and 64, M- and N-tiles that end inside a tile of 128 x 256, several tiles to a workgroup and less than one, up to 97 rows
+@pytest.mark.parametrize("E,H,F,most", [(1, 128, 128, 97), (3, 384, 640, 150), (17, 896, 1152, 190), (64, 256, 384, 170), (64, 1024, 896, 120)])
+def test_gradients_of_few_rows(E, H, F, most):
+    """On eight waves: what eight workgroups and one per compute unit write are the same bits, and right."""
+    rng = np.random.default_rng(E + H)
+    counts = rng.integers(1, most + 1, size=E)
+    if E > 2:
+        counts[1], counts[E // 2], counts[-1] = 0, 1, 0
+    assert (counts.sum() + 127 * min(E, counts.sum()) + 63) // 64 * 64 <= 224 * E
+    few, (x, dy, h, gu, wd_t), off = _gradients(E, H, F, counts, 8)
+    one, _, _ = _gradients(E, H, F, counts, 0)
+    for a, b in zip(one, few):
+        assert torch.equal(a.view(torch.int16), b.view(torch.int16))
+    for e in range(E):
+        r = slice(off[e], off[e + 1])
+        if counts[e] == 0:
+            assert not any(t[e].any() for t in few), f"expert {e}"
+            continue
+        want = dy[r].float().T @ h[r].float()
+        assert (few[2][e].float() - want).abs().max() <= 2.0 ** -8 * max(want.abs().max().item(), 1e-30) * 1.01, f"expert {e}"
+        g, u = gu[r].float().split(F, dim=1)
+        dh = (dy[r].float() @ wd_t[e].float().T).bfloat16().float()
+        sig = torch.sigmoid(g)
+        du = (dh * g * sig).bfloat16().float()
+        want = du.T @ x[r].float()
+        # the result rounded once, and four products of an element of du on the neighbouring step, as above
+        moved = 4 * 2.0 ** -7 * (du.abs().max() * x[r].abs().max()).item()
+        assert (few[1][e].float() - want).abs().max() <= 2.0 ** -8 * want.abs().max() + moved, f"expert {e}"
