@@ -801,17 +801,19 @@ void launch_persist_groupk_rowmajor(const void* A, int lda, const void* B, int l
 
 // Four waves or eight, the tile's height chosen on the device.  Four are ahead where power is what bounds a product.  With few rows
 // and a short contraction a tile is a few k-tiles of which memory is waited for, and two waves to a SIMD cover more of that, of the
-// epilogue and of the tails that leave waves idle.  (us, four / eight: 60 experts x 40 rows, 1664 x 512, gate/up 38.3 / 36.7 as it is saved,
-// down 24.7 / 22.6; 24 x 40, 3584 x 896, down 32.6 / 30.0; 64 x 110, 2048 x 512, down 35.0 / 32.5; 48 x 40, 2048 x 2048, gate/up 187 / 181,
-// down 106 / 103; 60 x 110, 1664 x 1920, down 96.8 / 96.3.  At 200 rows: 16 experts, 2048 x 1408, gate/up 45.1 / 45.6; 24, 3584 x 896,
-// 88.5 / 93.0; 64, 1536 x 1152, down 65.1 / 66.7.  Longer contractions are level, or behind: 64 x 64 rows, 6144 x 2048, dx 577 / 594.)
-// The gate/up product that saves its pre-activations stores three times as much, and eight waves stay ahead for longer (96 x 200 rows, 1280 x
-// 1792, 292 / 275; 48 x 152, 2048 x 2048, 211 / 204; 60 x 154, 1664 x 1920, 218 / 208).
+// epilogue and of the tails that leave waves idle.  The line: rows per expert x contraction.  (Down, us, four / eight: K = 384, 40 experts, N =
+// 3968, 140, 300 and 500 rows 39.3, 60.9 and 92.8 / 36.3, 57.0 and 88.5; 640, 32, 2688, 140, 300 and 400 32.6, 44.9 and 51.9 / 30.6, 42.4 and
+// 52.7; 896, 32, 1664, 140, 220 and 400 26.3, 30.9 and 45.1 / 25.9, 29.9 and 46.9; 1024, 60, 2688, 140 and 220 86.5 and 111 / 86.9 and
+// 114; 1280, 24, 1536, 140 and 260 24.4 and 31.9 / 23.5 and 32.4; 2048, 48, 2048, 40, 110 and 200 106, 109 and 126 / 103, 109 and
+// 129.  Gate/up, K = 2048, 48 experts x 40 rows, N = 2048, 187 / 181; 3584, 24 x 200, 896, 88.5 / 93.0.  Longer contractions are level, or
+// behind: dx, K = 4096, 64 x 64 rows, N = 6144, 577 / 594.)
+// The gate/up product that saves its pre-activations stores three times as much, and eight waves stay ahead for twice the rows (96 x 200
+// rows, 1280 x 1792, 292 / 275; 48 x 152 and x 400, 2048 x 2048, 211 and 347 / 204 and 338; 60 x 154, 1664 x 1920, 218 / 208).
 template <int MODE>
 void launch_persist_chosen(const void* A, const int32_t* offsets, int r_max, int E, int N, int K, const void* B0, const void* B1,
                            void* C, void* GU, hipStream_t s) {
     if constexpr (MODE != 3) {
-        if (K <= 2048 && r_max <= (MODE == 2 ? 224ll : 128ll) * E) {
+        if (K <= 2048 && (long long)r_max * K <= (MODE == 2 ? 440000ll : 220000ll) * E) {
             launch_persist<0, 256, 2, 4, MODE, true>(A, offsets, r_max, E, N, K, B0, B1, C, GU, s);
             return;
         }
