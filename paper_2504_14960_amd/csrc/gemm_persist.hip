@@ -868,9 +868,9 @@ void launch_persist_wgrad(const void* a_t, const void* b_t, const int32_t* offse
     // eight of 64 x 64 cover it.  Tiles of 128 rows, the 256 columns in three stages, streamed.  The backward, us, four waves of 256 rows / so:
     // 4 experts x 60 rows, 2048 x 2048, 114 / 100; 24 x 60, 2048 x 512, 139 / 126; 32 x 40, 2048 x 2048, 468 / 426; 60 x 40, 1664 x 1920, 639 / 585;
     // 40 x 60, 3072 x 1792, 670 / 640; 16 x 60, 6144 x 2048, 580 / 576; 64 x 100, 2560 x 1536, level.  On the other side of the lines: 128 experts
-    // x 60 rows, 2048 x 768, 698 / 722; 96 x 59, 2048 x 1024, 694 / 717; 64 x 60, 2816 x 2048, 1054 / 1080; 4 x 60, 4096 x 4096, 257 / 261; 48 x 122, 4096 x
+    // x 60 rows, 2048 x 768, 698 / 722; 96 x 59, 2048 x 1024, 694 / 717; 64 x 60, 2816 x 2048, 1054 / 1080; 32 x 43, 4096 x 2048, 759 / 797; 4 x 60, 4096 x 4096, 257 / 261; 48 x 122, 4096 x
     // 1024, 710 / 742 (8 to 16 experts gain up to 160 rows, 2 to 9 %).  The tiles' operands, one and a half times as many, are what costs.
-    if (ld <= 224ll * E && E <= 64 && per_expert < 256 && (long long)E * M * N <= 1ll << 28 && N <= kMaxColumns) {
+    if (ld <= 224ll * E && E <= 64 && per_expert < 256 && (long long)E * M * N < 1ll << 28 && N <= kMaxColumns) {
         launch_persist_groupk<128, 256, 2, 4, true, true>(a_t, b_t, offsets, E, M, N, ld, dw, s);
         return;
     }
@@ -883,12 +883,10 @@ void launch_persist_wgrad(const void* a_t, const void* b_t, const int32_t* offse
         launch_persist_groupk<128, 256, 2, 2, true, true>(a_t, b_t, offsets, E, M, N, ld, dw, s);
         return;
     }
-    // Gradients streamed past the L2 (us, the expert FFN's backward, stored as usual / so):
-    //   64 experts, 6144 x 2048: 256 rows 3364 / 3155, 512 rows 5260 / 5180, 768 rows 7368 / 7306, 1024 rows 9350 / 9314
-    //   8 experts, 4096 x 4096:  256 rows 703 / 625, 512 rows 900 / 832, 1024 rows 1539 / 1505, 1536 rows 2178 / 2169
-    // With 8 experts x 2048 rows, 6144 x 16384, the layer's forward and backward are 0.4 % slower for it: the line lies below
-    // where the two meet.
-    if (ld <= 640ll * E && N <= kMaxColumns)   // up to some 512 rows per expert, the padding included
+    // Streamed past the L2 whatever the rows (the expert FFN's backward streamed, of what it takes stored as usual; 19 layers of 1 to 128
+    // experts: 200 rows per expert 0.83 to 0.94, 450 rows 0.86 to 1.02, 800 rows 0.93 to 1.02, 1280 rows 0.95 to 1.01, 2048 rows 0.98 to
+    // 0.99; the two above 1 are 8 experts, 6144 x 16384, 1.6 and 2.1 % at 450 and 800 rows, which at 2048 take 0.7 % less).
+    if (N <= kMaxColumns)
         launch_persist_groupk<256, 256, 2, 2, true>(a_t, b_t, offsets, E, M, N, ld, dw, s);
     else
         launch_persist_groupk<256, 256, 2, 2, false>(a_t, b_t, offsets, E, M, N, ld, dw, s);

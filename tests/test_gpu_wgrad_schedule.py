@@ -57,8 +57,8 @@ def _fewest_tiles(M, N, experts):
     return experts * min((x + 1) * per_expert // 8 - x * per_expert // 8 for x in range(8))
 
 
-# 9 and 3 or 4 tiles of an expert to a workgroup, M-groups of eight and the M-tiles left over; two to seven k-tiles (results
-# streamed), and nine to twelve (up to 640 padded rows per expert on average they are streamed, here they are not)
+# 9 and 3 or 4 tiles of an expert to a workgroup, M-groups of eight and the M-tiles left over; two to seven k-tiles, and nine to
+# twelve (640 padded rows per expert on average lie between the two)
 @pytest.mark.parametrize("E,H,F,rows", [(26, 2304, 2048, (1, 70, 130, 200, 400, 0)), (28, 1536, 1280, (520, 700, 560, 750, 600, 0))])
 def test_tiles_of_several_lengths_on_both_sides_of_the_64th(E, H, F, rows):
     counts = np.array([rows[(e * e + e // 4) % len(rows)] for e in range(E)])
