@@ -268,8 +268,8 @@ __device__ __forceinline__ void store_partial(f32x4 (&acc)[FM][FN], int t_row0, 
 // DEEP_B: which operand gets the three LDS stages.  false: the activation tile (three stages, fetched two k-tiles
 // ahead) and two stages for the weight tile; true: the other way round -- the weights are what streams in from
 // HBM (every weight byte is used by one M-group only), the activation panels are re-read from the caches.
-template <int BM, int BN, int WGM, int WGN, int MODE, bool GROUPK, bool KMAJ, bool IDLE_SKIP, bool DEEP_B, bool BY_ROUND,
-          bool STREAM_OUT, bool SPLIT>
+template <int BM, int BN, int WGM, int WGN, int MODE, bool GROUPK, bool KMAJ, bool IDLE_SKIP, bool DEEP_B, bool STREAM_OUT,
+          bool SPLIT>
 __device__ __forceinline__ void persist_body(
     const bf16_t* __restrict__ A, const int32_t* __restrict__ offsets, int E, int N, int K,
     const bf16_t* __restrict__ B0, const bf16_t* __restrict__ B1, bf16_t* __restrict__ C, bf16_t* __restrict__ GU,
@@ -339,10 +339,8 @@ __device__ __forceinline__ void persist_body(
     const uint8_t* const B0b = reinterpret_cast<const uint8_t*>(B0);
     const uint8_t* const B1b = SWIGLU ? reinterpret_cast<const uint8_t*>(B1) : B0b;
 
-    // tiles are dealt to the XCDs round by round, except in the many-expert instantiations (measured: there the
-    // gate/up GEMM loses 1 %, and the two GEMMs of a layer must walk the rows in the same order)
     typename std::conditional<KMAJ, WgradSchedKM<BM, BN>,
-                              typename std::conditional<GROUPK, WgradSched<BM, BN>, TileSched<BM, BY_ROUND>>::type>::type sched;
+                              typename std::conditional<GROUPK, WgradSched<BM, BN>, TileSched<BM>>::type>::type sched;
     if constexpr (GROUPK)
         sched.init(offsets, E, ntn, N, lane);
     else
@@ -695,20 +693,20 @@ __device__ __forceinline__ void persist_body(
 // BM = 0: the height of the tiles is chosen on the device, from the rows that every expert really has (pick_height);
 // 256, 192 or 128 rows, all of BN = 256 columns (ldb: a height to be taken instead, or 0).  A row's sums are formed in the same order whatever the height.
 template <int BM, int BN, int WGM, int WGN, int MODE, bool GROUPK = false, bool KMAJ = false, bool IDLE_SKIP = false,
-          bool DEEP_B = false, bool BY_ROUND = true, bool STREAM_OUT = false, bool SPLIT = false>
+          bool DEEP_B = false, bool STREAM_OUT = false, bool SPLIT = false>
 __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_persist_kernel(
     const bf16_t* __restrict__ A, const int32_t* __restrict__ offsets, int E, int N, int K,
     const bf16_t* __restrict__ B0, const bf16_t* __restrict__ B1, bf16_t* __restrict__ C, bf16_t* __restrict__ GU,
     int ntn, int ldb, int splits, int plane_rows, unsigned long long* __restrict__ ticks) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     if constexpr (BM != 0) {
-        persist_body<BM, BN, WGM, WGN, MODE, GROUPK, KMAJ, IDLE_SKIP, DEEP_B, BY_ROUND, STREAM_OUT, SPLIT>(
+        persist_body<BM, BN, WGM, WGN, MODE, GROUPK, KMAJ, IDLE_SKIP, DEEP_B, STREAM_OUT, SPLIT>(
             A, offsets, E, N, K, B0, B1, C, GU, ntn, ldb, splits, plane_rows, ticks, smem);
     } else {
         const int height = ldb != 0 ? ldb : pick_height(kCostBf16, offsets, E, ntn * (SPLIT ? splits : 1), K / 64 / (SPLIT ? splits : 1),
                                                         threadIdx.x & 63);
         auto run = [&](auto rows) {
-            persist_body<decltype(rows)::value, BN, WGM, WGN, MODE, false, false, IDLE_SKIP, DEEP_B, BY_ROUND, false, SPLIT>(
+            persist_body<decltype(rows)::value, BN, WGM, WGN, MODE, false, false, IDLE_SKIP, DEEP_B, false, SPLIT>(
                 A, offsets, E, N, K, B0, B1, C, GU, ntn, ldb, splits, plane_rows, ticks, smem);
         };
         if (height == 256) run(std::integral_constant<int, 256>{});
@@ -723,34 +721,27 @@ void launch_persist(const void* A, const int32_t* offsets, int r_max, int E, int
     constexpr int OUTN = (MODE == 1 || MODE == 2) ? BN / 2 : BN;
     constexpr int HMAX = BM != 0 ? BM : 256, HMIN = BM != 0 ? BM : 128;   // tallest and lowest tile
     constexpr size_t smem = (size_t)(DEEP_B ? 2 * HMAX + 3 * BN : 3 * HMAX + 2 * BN) * 64 * 2;
-    if constexpr (BM == 0 && MODE != 3) {
-        // Many rows on many experts: 256 rows are mostly the best height, and the kernel that holds it alone is the faster one
-        // (32768 tokens, K = 6 of 64 experts, 4096 x 1408: 1 % of the layer; 768 to 2048 rows on 16 experts: 0.6 to 1 %).  r_max is a
-        // bound, not the rows there are, and a launch of a few rounds can be better off lower: 16 experts x 640 or 700 rows, gate/up
-        // 2048 x 1408 131 / 115 with 192 rows, 4096 x 1408 262 / 229, 1300 rows 460 / 407; down 2048 x 1408 65 / 58.  With 32 or 64
-        // experts no height was ahead by more than 5 %.  (large_us prices the best height here too.)
+    if constexpr (BM == 0 && MODE != 3 && WGM * WGN == 4) {
+        // Many rows on many experts: 256 rows are mostly the best height, and the kernel that holds it alone has no choice to make.
+        // r_max is a bound, not the rows there are, and a launch of a few rounds can be better off lower.  (The height chosen, of the
+        // time so, 660 to 3500 rows per expert: 7 layers of 32 to 128 experts, gate/up 1.003 to 1.010, down 0.984 to 1.003; 16 and 24
+        // experts 0.978 to 1.017 and 0.970 to 1.006, between 0.86 and 1.09: 16 x 660 rows, 2048 x 1408, gate/up 126 us so and 113 with
+        // the height chosen, 16 x 1024, 1024 x 4096, down 154 and 137; 24 x 800, 2048 x 1024, gate/up 132 and 143.)
         if (g_persist_tile_rows == 0 && E >= 16 && r_max >= 640ll * E) {
             launch_persist<256, BN, WGM, WGN, MODE, DEEP_B>(A, offsets, r_max, E, N, K, B0, B1, C, GU, s);
             return;
         }
     }
     const int ntn = (N + OUTN - 1) / OUTN;
-    // many experts = many ragged tail tiles: the instantiation whose idle waves skip the multiplication
+    // many experts = many ragged tail tiles: the instantiation whose idle waves skip the multiplication.  (With the skip, of the time
+    // without: 11 layers of 16 to 128 experts, 660 to 3500 rows, gate/up 0.978, down 0.989, saved gate/up 0.994; 8 layers of 1 to 12, 150 to
+    // 3333 rows, 0.995, 0.990 and 1.000, gate/up slower by 2 to 7 % in a tenth of them.)
     const bool idle_skip = MODE != 3 && persist_idle_skip(E);
-    // few experts: whole rounds of tiles are dealt to the XCDs round by round; many: contiguous shares (measured)
-    const bool by_round = MODE == 3 || E < 16;
     constexpr bool SKIP = MODE != 3;
-    auto pick = [&](auto skip, auto round) {
-        constexpr bool S = decltype(skip)::value, R = decltype(round)::value;
-        return gemm_bf16_persist_kernel<BM, BN, WGM, WGN, MODE, false, false, S, DEEP_B, R>;
-    };
-    using Yes = std::true_type;
-    using No = std::false_type;
-    using Skip = std::integral_constant<bool, SKIP>;
-    using Shares = std::integral_constant<bool, MODE == 3>;   // MODE 3 has the rounds only
-    auto kern = idle_skip ? (by_round ? pick(Skip{}, Yes{}) : pick(Skip{}, Shares{})) : (by_round ? pick(No{}, Yes{}) : pick(No{}, Shares{}));
-    static OncePerDevice lds[2][2];
-    allow_lds(lds[idle_skip][by_round], reinterpret_cast<const void*>(kern), (int)smem);
+    auto kern = idle_skip ? gemm_bf16_persist_kernel<BM, BN, WGM, WGN, MODE, false, false, SKIP, DEEP_B>
+                          : gemm_bf16_persist_kernel<BM, BN, WGM, WGN, MODE, false, false, false, DEEP_B>;
+    static OncePerDevice lds[2];
+    allow_lds(lds[idle_skip], reinterpret_cast<const void*>(kern), (int)smem);
     // never more workgroups than the static bound on the tile count
     const int grid = min(persist_grid(), grid_for(r_max, E, HMIN, ntn));
     hipLaunchKernelGGL(kern, dim3(grid), dim3(WGM * WGN * 64), smem, s, static_cast<const bf16_t*>(A), offsets, E, N,
@@ -774,7 +765,7 @@ template <int BM, int BN, int WGM, int WGN, bool STREAM_OUT, bool DEEP_B = false
 void launch_persist_groupk(const void* A, const void* B, const int32_t* offsets, int E, int M, int N, int ld,
                            void* C, hipStream_t s) {
     constexpr size_t smem = (size_t)(DEEP_B ? 2 * BM + 3 * BN : 3 * BM + 2 * BN) * 64 * 2;
-    auto kern = gemm_bf16_persist_kernel<BM, BN, WGM, WGN, 0, true, false, false, DEEP_B, true, STREAM_OUT>;
+    auto kern = gemm_bf16_persist_kernel<BM, BN, WGM, WGN, 0, true, false, false, DEEP_B, STREAM_OUT>;
     static OncePerDevice lds;
     allow_lds(lds, reinterpret_cast<const void*>(kern), (int)smem);
     const long long tiles = (long long)E * ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
@@ -927,7 +918,7 @@ bool launch_persist_split(const void* A, const int32_t* offsets, int r_max, int 
     auto go = [&](auto mode) {
         constexpr int MODE = decltype(mode)::value, OUTN = MODE == 1 ? 128 : 256;
         constexpr size_t smem = (size_t)(2 * 256 + 3 * 256) * 64 * 2;
-        auto kern = gemm_bf16_persist_kernel<0, 256, 2, 2, MODE, false, false, false, true, true, false, true>;
+        auto kern = gemm_bf16_persist_kernel<0, 256, 2, 2, MODE, false, false, false, true, false, true>;
         static OncePerDevice lds;
         allow_lds(lds, reinterpret_cast<const void*>(kern), (int)smem);
         const int ntn = (N + OUTN - 1) / OUTN;
