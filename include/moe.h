@@ -504,7 +504,7 @@ moe_status_t moe_expert_down_fp8(const void* h_fp8, const int32_t* expert_offset
  * the chip's sustained matrix rate otherwise, e.g. bench.py's roofline note).
  * Runs the bare inner loop of the bf16 grouped GEMM: `workgroups` workgroups of
  * four waves, each wave a 128 x 128 accumulator block, LDS fragment reads and
- * 32x32x16 bf16 MFMAs over a 64 KiB operand image, nothing else.  image: 65536
+ * 16x16x32 bf16 MFMAs over a 64 KiB operand image, nothing else.  image: 65536
  * bytes, two blocks of [256 rows][64 bf16] (first operand, second operand).
  * One launch executes workgroups * iters * 8388608 FLOP.  sink: workgroups*256
  * floats (written, meaningless).  ticks (may be NULL): 2 x uint64, shader
@@ -515,7 +515,7 @@ moe_status_t moe_expert_down_fp8(const void* h_fp8, const int32_t* expert_offset
 moe_status_t moe_probe_mfma_bf16(const void* image, int iters, int workgroups, float* sink,
                                  uint64_t* ticks, moe_stream_t stream);
 /* The same probe for the FP8 path: image = two blocks of [256 rows][128 E4M3
- * bytes], 32x32x64 FP8 MFMAs; one launch executes workgroups * iters * 16777216
+ * bytes], 16x16x128 FP8 MFMAs; one launch executes workgroups * iters * 16777216
  * FLOP. */
 moe_status_t moe_probe_mfma_fp8(const void* image, int iters, int workgroups, float* sink,
                                 uint64_t* ticks, moe_stream_t stream);

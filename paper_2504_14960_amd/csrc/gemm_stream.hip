@@ -678,12 +678,13 @@ void launch_any(const StreamArgs& p, int r_max, const StreamPlan& plan, float* p
 // The large tiles: tile_cost.h.  A round of the streaming workgroups takes (bytes of its weight rows) x 43 us/MB (36 where
 // several M-tiles share them), plus its rows at a smaller rate, plus its start and end, which the narrow workgroups, two to a
 // compute unit, mostly hide.  Fitted to gate/up and down at (E, H, F) = (1, 3584, 20480), (1, 2 and 8, 4096, 14336), (64, 3584,
-// 2560), (16, 2048, 1408) and (8, 2048, 4096) with 1 to 2000 rows per expert.  Over 1260 products each in bf16 and FP8 (13
-// layers of 2 to 128 experts, 4 to 2000 rows per expert, equal, mildly and Zipf-1.2 skewed experts) the kernel they pick is
-// behind the best of the three by 2.7 % and 2.3 % on average.  At most by 72 % (70 % in FP8): two to eight experts, where the
-// narrow kernel's second workgroup per compute unit is priced too high (down, 8 experts x 48 rows, 2048 x 4096: wide 40, narrow
-// 24; 2 experts x 256 rows, 4096 x 8192: wide 89, narrow 58), and by 62 % for skewed routers, where it is priced too low (down, 16
-// experts x 24 rows, 2048 x 1408, Zipf: narrow 33, large tiles 20).
+// 2560), (16, 2048, 1408) and (8, 2048, 4096) with 1 to 2000 rows per expert.  Over 682
+// products each (31 layers of 2 to 128 experts, 40 to 2200 rows per expert, even and skewed experts) the kernel they pick is behind
+// the best of all (the large tiles at each height, narrow, wide, small tiles) by 2.9 % (gate/up), 3.3 % (down), 3.6 and 4.3 % (FP8) on
+// average, by more than a tenth in 47, 32, 44 and 52 of them: up to 64 rows per expert above all, on 8 to 16 experts or with a skewed
+// router, which the host cannot know (us, as picked / best: down, 12 experts x 40 rows, skewed, 3072 x 2048, 62 / 28 on the large
+// tiles; 10 x 64, 2560 x 4096, 55 / 38 on the small ones; gate/up, 16 x 40, 2048 x 1408, 40 / 30 on the large; 8 x 64, 5120 x 1536, 76 / 50 on
+// the small).
 struct Work {
     int experts, rows, N, kbytes, r_max;
     bool swiglu, fp8, odd;   // odd: bf16 sizes that the large tiles do not take
