@@ -108,7 +108,7 @@ struct PTile {
 
 // Every wave keeps the whole schedule in registers: lane l describes experts
 // 4l .. 4l+3 (first row, row count, exclusive prefix of M-tile counts).
-template <int BM>
+template <int BM, bool BY_ROUND = true>
 struct TileSched {
     int lo[4], n[4], pex[4], pend;
     int MT, ntn, per, nwx, wgx, xcd, total;
@@ -154,16 +154,14 @@ struct TileSched {
         constexpr int MG = 8;
         PTile t;
         t.a = A; t.b0 = B0; t.b1 = B1; t.a_lim = 0; t.b_lim = 0; t.row0 = 0; t.rows = 0; t.n0 = 0; t.kt = 0; t.split = 0; t.krows = 0;
-        // Whole rounds (one tile per workgroup of the launch) are dealt to the XCDs round by round: in round i XCD x runs
-        // the nwx consecutive tiles from (8 i + x) nwx on, so at any time the eight XCDs work on neighbouring stretches of
-        // the list and what they have in common (activation panels of one M-group) is fetched from memory once and found
-        // in the memory-side cache by the others.  The tiles left over after the last whole round are cut into eight
-        // contiguous shares; so is the whole list where the launch is no multiple of eight workgroups.  (A contiguous eighth
-        // of the list to every XCD, bf16, both products of a layer, of the time by rounds: 8 layers of 1 to 12 experts, 200
-        // to 2048 rows, 1.004, 11 layers of 16 to 128 experts 1.006, with pre-activations saved 1.001 and 1.011; by layer 0.994
-        // to 1.022.)
+        // BY_ROUND: whole rounds (one tile per workgroup of the launch) are dealt to the XCDs round by round: in
+        // round i XCD x runs the nwx consecutive tiles from (8 i + x) nwx on, so at any time the eight XCDs work on
+        // neighbouring stretches of the list and what they have in common (activation panels of one M-group) is
+        // fetched from memory once and found in the memory-side cache by the others.  The tiles left over after
+        // the last whole round are cut into eight contiguous shares.  Otherwise every XCD takes a contiguous
+        // eighth of the list.
         int L;
-        if ((gridDim.x & 7) == 0) {
+        if (BY_ROUND && (gridDim.x & 7) == 0) {
             const int round_tiles = 8 * nwx, whole = total / round_tiles;
             if (i < whole) {
                 L = (i * 8 + xcd) * nwx + wgx;

@@ -268,8 +268,8 @@ __device__ __forceinline__ void store_partial(f32x4 (&acc)[FM][FN], int t_row0, 
 // DEEP_B: which operand gets the three LDS stages.  false: the activation tile (three stages, fetched two k-tiles
 // ahead) and two stages for the weight tile; true: the other way round -- the weights are what streams in from
 // HBM (every weight byte is used by one M-group only), the activation panels are re-read from the caches.
-template <int BM, int BN, int WGM, int WGN, int MODE, bool GROUPK, bool KMAJ, bool IDLE_SKIP, bool DEEP_B, bool STREAM_OUT,
-          bool SPLIT>
+template <int BM, int BN, int WGM, int WGN, int MODE, bool GROUPK, bool KMAJ, bool IDLE_SKIP, bool DEEP_B, bool BY_ROUND,
+          bool STREAM_OUT, bool SPLIT>
 __device__ __forceinline__ void persist_body(
     const bf16_t* __restrict__ A, const int32_t* __restrict__ offsets, int E, int N, int K,
     const bf16_t* __restrict__ B0, const bf16_t* __restrict__ B1, bf16_t* __restrict__ C, bf16_t* __restrict__ GU,
@@ -340,7 +340,7 @@ __device__ __forceinline__ void persist_body(
     const uint8_t* const B1b = SWIGLU ? reinterpret_cast<const uint8_t*>(B1) : B0b;
 
     typename std::conditional<KMAJ, WgradSchedKM<BM, BN>,
-                              typename std::conditional<GROUPK, WgradSched<BM, BN>, TileSched<BM>>::type>::type sched;
+                              typename std::conditional<GROUPK, WgradSched<BM, BN>, TileSched<BM, BY_ROUND>>::type>::type sched;
     if constexpr (GROUPK)
         sched.init(offsets, E, ntn, N, lane);
     else
@@ -693,20 +693,20 @@ __device__ __forceinline__ void persist_body(
 // BM = 0: the height of the tiles is chosen on the device, from the rows that every expert really has (pick_height);
 // 256, 192 or 128 rows, all of BN = 256 columns (ldb: a height to be taken instead, or 0).  A row's sums are formed in the same order whatever the height.
 template <int BM, int BN, int WGM, int WGN, int MODE, bool GROUPK = false, bool KMAJ = false, bool IDLE_SKIP = false,
-          bool DEEP_B = false, bool STREAM_OUT = false, bool SPLIT = false>
+          bool DEEP_B = false, bool BY_ROUND = true, bool STREAM_OUT = false, bool SPLIT = false>
 __global__ __launch_bounds__(WGM* WGN * 64) void gemm_bf16_persist_kernel(
     const bf16_t* __restrict__ A, const int32_t* __restrict__ offsets, int E, int N, int K,
     const bf16_t* __restrict__ B0, const bf16_t* __restrict__ B1, bf16_t* __restrict__ C, bf16_t* __restrict__ GU,
     int ntn, int ldb, int splits, int plane_rows, unsigned long long* __restrict__ ticks) {
     extern __shared__ __attribute__((aligned(1024))) uint8_t smem[];
     if constexpr (BM != 0) {
-        persist_body<BM, BN, WGM, WGN, MODE, GROUPK, KMAJ, IDLE_SKIP, DEEP_B, STREAM_OUT, SPLIT>(
+        persist_body<BM, BN, WGM, WGN, MODE, GROUPK, KMAJ, IDLE_SKIP, DEEP_B, BY_ROUND, STREAM_OUT, SPLIT>(
             A, offsets, E, N, K, B0, B1, C, GU, ntn, ldb, splits, plane_rows, ticks, smem);
     } else {
         const int height = ldb != 0 ? ldb : pick_height(kCostBf16, offsets, E, ntn * (SPLIT ? splits : 1), K / 64 / (SPLIT ? splits : 1),
                                                         threadIdx.x & 63);
         auto run = [&](auto rows) {
-            persist_body<decltype(rows)::value, BN, WGM, WGN, MODE, false, false, IDLE_SKIP, DEEP_B, false, SPLIT>(
+            persist_body<decltype(rows)::value, BN, WGM, WGN, MODE, false, false, IDLE_SKIP, DEEP_B, BY_ROUND, false, SPLIT>(
                 A, offsets, E, N, K, B0, B1, C, GU, ntn, ldb, splits, plane_rows, ticks, smem);
         };
         if (height == 256) run(std::integral_constant<int, 256>{});
@@ -738,10 +738,23 @@ void launch_persist(const void* A, const int32_t* offsets, int r_max, int E, int
     // 3333 rows, 0.995, 0.990 and 1.000, gate/up slower by 2 to 7 % in a tenth of them.)
     const bool idle_skip = MODE != 3 && persist_idle_skip(E);
     constexpr bool SKIP = MODE != 3;
-    auto kern = idle_skip ? gemm_bf16_persist_kernel<BM, BN, WGM, WGN, MODE, false, false, SKIP, DEEP_B>
-                          : gemm_bf16_persist_kernel<BM, BN, WGM, WGN, MODE, false, false, false, DEEP_B>;
-    static OncePerDevice lds[2];
-    allow_lds(lds[idle_skip], reinterpret_cast<const void*>(kern), (int)smem);
+    // Whole rounds of tiles are dealt to the XCDs round by round, but for many experts of few rows: contiguous shares.  (Both products of a
+    // layer by rounds, of the time by shares: 8 layers of 1 to 12 experts, 200 to 2048 rows, 0.996; 11 layers of 16 to 128 experts, 800 and 1280
+    // rows, 0.993 and 0.997, with the pre-activations saved 0.984 and 0.991; with 200 rows 0.993, between 0.962 and 1.027; the
+    // training step of 64 experts x 172 rows, 6144 x 2048, takes 5882 us by shares and 5922 by rounds, dx 675 and 715 of them.)
+    constexpr bool SHARES = BM == 0 && MODE != 3;
+    const bool by_round = !SHARES || E < 16;
+    auto pick = [&](auto skip, auto round) {
+        constexpr bool S = decltype(skip)::value, R = decltype(round)::value;
+        return gemm_bf16_persist_kernel<BM, BN, WGM, WGN, MODE, false, false, S, DEEP_B, R>;
+    };
+    using Yes = std::true_type;
+    using No = std::false_type;
+    using Skip = std::integral_constant<bool, SKIP>;
+    using Shares = std::integral_constant<bool, !SHARES>;
+    auto kern = idle_skip ? (by_round ? pick(Skip{}, Yes{}) : pick(Skip{}, Shares{})) : (by_round ? pick(No{}, Yes{}) : pick(No{}, Shares{}));
+    static OncePerDevice lds[2][2];
+    allow_lds(lds[idle_skip][by_round], reinterpret_cast<const void*>(kern), (int)smem);
     // never more workgroups than the static bound on the tile count
     const int grid = min(persist_grid(), grid_for(r_max, E, HMIN, ntn));
     hipLaunchKernelGGL(kern, dim3(grid), dim3(WGM * WGN * 64), smem, s, static_cast<const bf16_t*>(A), offsets, E, N,
@@ -765,7 +778,7 @@ template <int BM, int BN, int WGM, int WGN, bool STREAM_OUT, bool DEEP_B = false
 void launch_persist_groupk(const void* A, const void* B, const int32_t* offsets, int E, int M, int N, int ld,
                            void* C, hipStream_t s) {
     constexpr size_t smem = (size_t)(DEEP_B ? 2 * BM + 3 * BN : 3 * BM + 2 * BN) * 64 * 2;
-    auto kern = gemm_bf16_persist_kernel<BM, BN, WGM, WGN, 0, true, false, false, DEEP_B, STREAM_OUT>;
+    auto kern = gemm_bf16_persist_kernel<BM, BN, WGM, WGN, 0, true, false, false, DEEP_B, true, STREAM_OUT>;
     static OncePerDevice lds;
     allow_lds(lds, reinterpret_cast<const void*>(kern), (int)smem);
     const long long tiles = (long long)E * ((M + BM - 1) / BM) * ((N + BN - 1) / BN);
@@ -918,7 +931,7 @@ bool launch_persist_split(const void* A, const int32_t* offsets, int r_max, int 
     auto go = [&](auto mode) {
         constexpr int MODE = decltype(mode)::value, OUTN = MODE == 1 ? 128 : 256;
         constexpr size_t smem = (size_t)(2 * 256 + 3 * 256) * 64 * 2;
-        auto kern = gemm_bf16_persist_kernel<0, 256, 2, 2, MODE, false, false, false, true, false, true>;
+        auto kern = gemm_bf16_persist_kernel<0, 256, 2, 2, MODE, false, false, false, true, true, false, true>;
         static OncePerDevice lds;
         allow_lds(lds, reinterpret_cast<const void*>(kern), (int)smem);
         const int ntn = (N + OUTN - 1) / OUTN;
