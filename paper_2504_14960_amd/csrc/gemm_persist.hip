@@ -10,7 +10,8 @@
 // the board allows, and the time is the energy of a tile.  So the matrix
 // instruction is the 16x16x32 one, which adds a contraction of 32 to its
 // accumulators where 32x32x16 adds one of 16 (half the accumulator traffic; the
-// bare loop over workload-like operands in LDS: 1955 against 1785 TFLOP/s), and
+// bare loop over workload-like operands in LDS, probe.hip: 1889 TFLOP/s, with the
+// other 1777 to 1826), and
 // four waves of 128 x 128 share a tile, not eight of 128 x 64 (a third fewer LDS
 // bytes per k-tile).  With one wave per SIMD nothing covers what stands between
 // two matrix instructions, so the k loop holds little else: 128 of them, 32
@@ -19,7 +20,8 @@
 // eight waves of 32x32x16 / this: 8 experts of 16384 rows, 6144 x 16384, 5200 and
 // 2700 / 4850 and 2435 (1.36 PFLOP/s each); 8 x 4096 rows, 6144 x 2048, 1310 and 686 /
 // 1168 and 627; 64 skewed experts of 82000 rows, 4096 x 1408, 1663 and 919 / 1480
-// and 836.  Eight waves with the 16x16x32 instruction against this, on another card,
+// and 836.  Few rows and short contractions run on eight waves (launch_persist_chosen);
+// with many, eight waves against this, on another card,
 // neither with scratch memory: 5122 and 2618 / 4875 and 2434; 1255 and 668 / 1188 and
 // 636; 1632 and 896 / 1487 and 834.
 //
@@ -30,7 +32,9 @@
 //    drains and there is no per-tile prologue;
 //  * the tile scheduler (prefix of per-expert M-tile counts) lives in registers
 //    of every wave and is evaluated with wave-level operations only: no LDS, no
-//    barrier, no memory access per tile;
+//    barrier, no memory access per tile (the weight gradients', whose tiles are
+//    short: 64 tiles at a time, which reads the offsets and searches them across
+//    the lanes once more, behind the stores of the 64th);
 //  * the epilogue goes through the one LDS stage that is idle at that moment:
 //    every wave transposes its accumulators through a private, XOR-swizzled
 //    patch of it and writes whole 16-byte-per-lane row segments, instead of
@@ -303,12 +307,9 @@ __device__ __forceinline__ void persist_body(
     constexpr int A_ONE = NW == 8 && FM == 8 ? FM - 2 : 0;
     constexpr int NTWO = NREAD - A_ONE;
     // The early operand's loads are issued behind the barrier, in k-step 1, the late operand's in k-step 0: what a barrier
-    // waits for is a whole period old.  In tiles of 128 rows, chosen where the weights are what is waited for, the early ones
-    // are issued one behind the other and not spread over the k-step: queued behind the weights, the activations are what the
-    // barrier waits for.  (Four waves, us, spread / so: 16 experts x 60 rows, 4096 x 1408, gate/up 77.8 / 75.3; 16 x 40, 6144 x 2048,
-    // down 104 / 100; 60 x 40, 2048 x 1408, gate/up 139 / 135; 64 x 170, 3584 x 2560, gate/up 590 / 565.  With the weights' loads one
-    // behind the other too 564 there, but 8 x 90, 2048 x 4096, down takes 45.1 and not 41.5.)
-    constexpr int EARLY_STEP = BM == 128 ? 1 : (FM * FN) / PE;
+    // waits for is a whole period old.  (Tiles of 128 rows with the early ones, the activations',
+    // one behind the other and not spread over the k-step: us, spread / so, 16 experts x 60 rows, 4096 x 1408, gate/up 77.8 / 75.3, but 24 x
+    // 130, 2816 x 768, 39.1 / 41.1 and 12 x 315, 2944 x 512, 33.4 / 34.6; over 96 products of 12 layers level.)
     // STREAM_OUT: stores of a tile's epilogue, per wave (RowBuffer).  Loads and stores are counted together and complete in
     // order, and a wait for the loads behind an epilogue is a wait for its stores.  All that the first period of a tile waits
     // for was asked for in front of the stores of the tile before, so it need not wait for them; the second period, 1.5 us
@@ -553,7 +554,7 @@ __device__ __forceinline__ void persist_body(
             for (int r = (slot * NTWO + RS - 1) / RS; r < ((slot + 1) * NTWO + RS - 1) / RS && r < NTWO; ++r)
                 read_one(rd_a, rd_b, rd_s, mf_buf ^ 1, two_sets(r));
             if (A_ONE > 0 && slot % FN == FN - 1 && slot / FN < A_ONE) read_one(rd_a, rd_b, rd_s, mf_buf ^ 1, slot / FN);
-            if (ld < ld_end && slot == 1 + (ld_begin == 0 ? ld * EARLY_STEP : (ld - ld_begin) * NSLOT / (ld_end - ld_begin))) {
+            if (ld < ld_end && slot == 1 + (ld - ld_begin) * NSLOT / (ld_end - ld_begin)) {
                 fetch_one(ld, ld_b, ld_a);
                 ++ld;
             }

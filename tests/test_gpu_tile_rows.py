@@ -68,7 +68,7 @@ def test_fp8_heights_against_the_oracle_and_each_other(H, F, counts):
     assert np.linalg.norm(y - c["ref"].y) <= 5e-3 * np.linalg.norm(c["ref"].y)
 
 
-# few rows per expert (loads a period ahead) and, on average, more than 640 (the loads of both operands in step)
+# few rows per expert, and on average more than 640
 MANY = [700, 1, 1300, 257, 0, 2000]
 
 

@@ -1,5 +1,5 @@
-"""The weights' transposes, bit for bit: in tiles of 128 x 128, and, with results of more than 140 MiB, of 256 rows x 64 columns,
-where rows do not divide into tiles (rows and columns are multiples of 128: columns always do)."""
+"""The weights' transposes, bit for bit: in tiles of 128 x 128, and, with results of more than 140 MiB, of 256 rows x 64 columns, also
+where the rows do not divide into tiles.  (The columns always do: the entry point takes multiples of 128.)"""
 import pytest
 import torch
 
